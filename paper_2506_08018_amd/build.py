@@ -10,20 +10,23 @@ OBJ_DIR = os.path.join(HERE, "_build")
 
 COMMON = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# per-source extra flags: the quantizer's arithmetic is specified operation by operation
-SOURCES = {
-    "kvmix_quant.hip": ["-ffp-contract=off"],
-    # tile claims are single-lane LDS atomics whose result is taken late; the wave-reduction rewrite of
-    # uniform atomics would put a wait right behind them
-    "kvmix_attn.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
-    "kvmix_mixed.hip": ["-ffp-contract=off"],
-    "kvmix_api.hip": [],
+# tile claims are single-lane LDS atomics whose result is taken late; the wave-reduction rewrite of
+# uniform atomics would put a wait right behind them
+ATTN = ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
+# object -> (source, extra flags): the quantizer's arithmetic is specified operation by operation; the attention kernel exists
+# with 8 and with 12 waves per workgroup
+OBJECTS = {
+    "kvmix_quant.o": ("kvmix_quant.hip", ["-ffp-contract=off"]),
+    "kvmix_attn8.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=8"]),
+    "kvmix_attn12.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=12"]),
+    "kvmix_mixed.o": ("kvmix_mixed.hip", ["-ffp-contract=off"]),
+    "kvmix_api.o": ("kvmix_api.hip", []),
 }
 
 
 def _compile(item):
-    src, extra = item
-    obj = os.path.join(OBJ_DIR, src.replace(".hip", ".o"))
+    name, (src, extra) = item
+    obj = os.path.join(OBJ_DIR, name)
     cmd = COMMON + extra + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
@@ -34,8 +37,8 @@ def _compile(item):
 
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        results = list(ex.map(_compile, SOURCES.items()))
+    with ThreadPoolExecutor(max_workers=len(OBJECTS)) as ex:
+        results = list(ex.map(_compile, OBJECTS.items()))
     if verbose:
         for obj, err in results:
             if err.strip():

@@ -246,7 +246,9 @@ namespace {
 // Everything an attention launch needs, filled by plan_attention after all host-side checks have passed.
 // `mixed`: the fronts of Keys and Values differ; the tokens between them go to a launch of their own (m) that
 // leaves one more partial for the main launch's merge.
-struct AttnPlan { AttnArgs a; int kb, vb, G, units; bool mixed; MixedArgs m; };
+struct AttnPlan { AttnArgs a; int kb, vb, G, units, waves; bool mixed; MixedArgs m; };
+
+constexpr int kWindowTileCost = 3;   // packed tiles that take a wave as long as one window tile
 
 size_t split_workspace_bytes(int units, int n_parts, int G) {
   return counters_bytes(units * (G > 8 ? G / 8 : 1)) + (size_t)units * n_parts * G * (kD + 2) * sizeof(float);
@@ -272,6 +274,19 @@ Fronts fronts_of(const kvmix_layer_cache* c, int n_w) {
   f.w0_eff = f.n_w_eff > 0 ? slot_of(c, t_a) : 0;
   f.mixed = true;
   return f;
+}
+
+// Waves per workgroup of the attention kernel. 12 waves fill a compute unit with one workgroup, 8 leave room for two.
+// Launches that need more workgroups than there are compute units run 8: twice the workgroups are resident, so that one's start and
+// merge overlap another's stream (512 units of 128 tiles: 55.0 us against 57.8; 600 of 36: 23.9 against 27.2; 2048 of 20: 41.2
+// against 53.5). With at most one workgroup per compute unit the 4 more waves pay when each has many tiles to stream (256
+// units of 128 tiles: 22.2 us against 23.9; 32 tiles: 14.3 against 14.9), and cost in start and merge when there are few
+// (16 tiles: 12.5 us against 12.2; 9 tiles: 7.0 against 6.9).
+// 8 heads with 3- or 4-bit Values do not fit the 128 registers of the 8-wave form (spilling: 93 us where 12 waves take 62).
+int attn_waves(long long workgroups, int n_tiles, int n_splits, int G, int v_bits) {
+  if (G >= 8 && (v_bits == 3 || v_bits == 4)) return 12;
+  const int cus = num_cus();
+  return workgroups > (cus > 0 ? cus : 256) || n_tiles <= 20 * n_splits ? 8 : 12;
 }
 
 // Validates an attention call against the cache state `c` (window count n_w) and fills the launch descriptor;
@@ -322,19 +337,29 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     a.counters = reinterpret_cast<uint32_t*>(workspace);
     a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + counters_bytes(out_units(sh)));
   }
+  // The counters' 256 bytes (at least) are shared out evenly: splits that arrive together then meet on fewer cache lines
+  // (8 units x 32 splits, whose 256 arrivals queued up on one line for 1.3 us on average: see kvmix_attn.hip)
+  a.counter_stride = 1;
+  while (a.counter_stride * 2 * out_units(sh) <= 64) a.counter_stride *= 2;
   a.q = q; a.out = out;
   a.packed = c->packed;
   a.k_win = c->k_win; a.v_win = c->v_win;
   a.k_new = k_new; a.v_new = v_new; a.k_win_w = c->k_win; a.v_win_w = c->v_win; a.new_slot = new_slot;
-  a.tiles_cap = c->T_cap / kTile; a.W_cap = c->W_cap; a.n_tiles = fr.packed_tiles; a.n_w = fr.n_w_eff; a.w0 = fr.w0_eff;
-  a.Hq = sh->Hq; a.Hkv = sh->Hkv; a.n_splits = n_splits; a.n_parts = n_parts;
-  a.items_q = n_items / n_splits; a.items_r = n_items % n_splits;
+  a.tiles_cap = c->T_cap / kTile; a.W_cap = c->W_cap; a.n_w = fr.n_w_eff;
+  a.ring_tiles = c->W_cap / kTile; a.w0_tile = fr.w0_eff / kTile;
+  a.n_splits = n_splits; a.n_parts = n_parts;
+  const int live = (fr.n_w_eff + kTile - 1) / kTile;
+  a.win_each = live / n_splits; a.win_extra = live % n_splits;
+  a.win_tiles = kWindowTileCost < fr.packed_tiles / n_splits ? kWindowTileCost : fr.packed_tiles / n_splits;
+  a.items_q = (fr.packed_tiles + a.win_extra * a.win_tiles) / n_splits;
+  a.items_r = (fr.packed_tiles + a.win_extra * a.win_tiles) % n_splits;
   const float scale = softmax_scale > 0.0f ? softmax_scale : 1.0f / std::sqrt((float)kD);
   a.scale_log2 = scale * 1.4426950408889634f;
   plan->a = a;
   plan->kb = cfg->k_bits == 16 ? 2 : cfg->k_bits;
   plan->vb = cfg->v_bits == 16 ? 2 : cfg->v_bits;
   plan->G = G; plan->units = units;
+  plan->waves = attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, G, plan->vb);
   plan->mixed = fr.mixed;
   if (fr.mixed) {
     // with the append inside the launch the new token must be a window token of the main launch
@@ -358,7 +383,8 @@ int launch_plan(const AttnPlan& p, void* stream) {
     const hipError_t e = launch_mixed_fronts(p.m, p.units, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e);
   }
-  const hipError_t e = launch_decode_attn(p.a, p.kb, p.vb, p.G, p.units, (hipStream_t)stream);
+  const hipError_t e = p.waves == 8 ? launch_decode_attn<8>(p.a, p.kb, p.vb, p.G, p.units, (hipStream_t)stream)
+                                    : launch_decode_attn<12>(p.a, p.kb, p.vb, p.G, p.units, (hipStream_t)stream);
   return e == hipSuccess ? KVMIX_OK : hip_fail(e);
 }
 

@@ -30,9 +30,9 @@ namespace kvmix {
 
 namespace {
 
-// waves per workgroup: 3 per SIMD where the LDS exchange areas fit (register budget 512 / 3 per lane)
-constexpr int waves_for(int G) { return 12; }
-constexpr int kDepth = 1;            // tiles a wave requests ahead; 2 and 3 measured no faster (the loop runs at the memory system's rate)
+// Waves per workgroup; this file is compiled once for each of the two forms (the launch picks one, see attn_waves in kvmix_api.hip).
+// 12 waves, one workgroup per CU: 168 registers per lane. 8 waves: 128 registers, two workgroups per CU.
+constexpr int kNW = KVMIX_WAVES;
 constexpr int kMergeBatch = 32;          // splits whose partials the merging workgroup requests together (one round trip)
 // Reference of the running softmax (log2 units): numerators 2^(score - reference) are kept at or below 2^kRefCap;
 // when a score would exceed that, the reference is raised to (that score - kRefCap + 4), which leaves room for
@@ -161,6 +161,21 @@ __device__ __forceinline__ u32x2_t buf_load8(rsrc_t r, uint32_t voff, uint32_t s
   return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, kStreaming));
 }
 
+// 16 bytes per lane from memory into LDS: lane l's go to dst + 16 l (dst: wave-uniform). Counted like a load, waited for
+// explicitly before the LDS is read.
+__device__ __forceinline__ void buf_load_to_lds16(rsrc_t r, uint32_t voff, uint32_t soff, void* dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)voff, (int)soff, 0, 0);
+}
+// Transposing read: of a group of 16 lanes, lane i passes the address of 4 halves of row i / 4 (columns 4 (i % 4) .. +3) and gets column i
+// of the four rows. Two of them, four rows (1 KiB) apart: 8 consecutive rows of the lane's column.
+__device__ __forceinline__ half8_t read_transposed(const char* lds, int off) {
+  typedef short short4_t __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) short4_t* lds4_t;
+  const short4_t a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(lds + off));
+  const short4_t b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(lds + off + 4 * kD * 2));
+  return __builtin_bit_cast(half8_t, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // The lane's share of one packed tile as loaded (Raw) and prepared for unpacking (Codes).
 template <int BITS> struct Raw;
 template <> struct Raw<1> {     // the bit plane alone: 8 bytes per lane
@@ -218,8 +233,9 @@ template <int KB, int VB> struct Stage {
   u32x4_t meta;
   Raw<KB> kc; Raw<VB> vc;
   // rec: buffer resource over the unit's records; t: tile index inside the unit (wave-uniform)
-  __device__ __forceinline__ void load(rsrc_t rec, int t, int lane) {
-    const uint32_t l16 = 16u * lane, l8 = 8u * lane;
+  // l16: 16 * lane
+  __device__ __forceinline__ void load(rsrc_t rec, int t, uint32_t l16) {
+    const uint32_t l8 = l16 >> 1;
     const uint32_t soff = (uint32_t)t * (uint32_t)(record_words(KB, VB) * 4);
     meta = buf_load16(rec, l16, soff);
     kc.load(rec, soff + (uint32_t)(kMetaWords * 4), l16, l8);
@@ -262,184 +278,208 @@ __device__ __forceinline__ half_t split_part(float x, bool lo_part) {
 __device__ __forceinline__ float lo_half(uint32_t v) { return (float)__builtin_bit_cast(half_t, (uint16_t)(v & 0xffffu)); }
 __device__ __forceinline__ float hi_half(uint32_t v) { return (float)__builtin_bit_cast(half_t, (uint16_t)(v >> 16)); }
 
-// Wave-private LDS exchange area. Operand rows exist for the 2*G used MFMA columns only (row 2h holds the hi
-// parts of head h, row 2h+1 its lo parts: neighbours, so that one two-address LDS write stores both); the lanes
-// of unused columns all read an extra zero row.
-// Row pitches (272 B, 80 B) put the rows read by one 16-byte operand load into distinct banks.
+// Wave-private LDS exchange area.
+// A matrix operand (16 columns x 128 reduction positions, or x 32 for one channel block of the Values) is kept in the order in
+// which a wave reads it: piece P = 4 * ks + kq (8 reduction positions) holds 16 bytes per operand row, rows 0 .. G-1 the hi parts of
+// the heads, rows G .. 2G-1 the lo parts (an immediate offset apart, so that one two-address LDS write stores both). The head's place is
+// XORed with P % 4 from 4 heads on: the 4 bytes per lane of a write then fall into distinct banks, and so do the 16 bytes
+// per lane of a read (measured: 4.5 cycles per read of 1 KiB, 8.4 with operand rows 272 bytes apart; with 4 or 8 heads the
+// exchange area was what bound the packed loop). Columns past the used ones repeat those of the heads h % G, and nothing they
+// compute is stored.
+// The Key side of a tile is done with its part before the Value side writes its own, so the two share memory (the
+// wave's LDS operations run in order; a fence between the steps pins the compiler): 16 waves per CU fit.
+// With 1 or 2 heads the few rows are kept whole, 320 bytes apart: the lanes of one row read the same 16 bytes, and a write is
+// contiguous.
+template <int G> struct Operand {
+  static constexpr bool kPieces = G >= 4;
+  static constexpr int kPiece = kPieces ? 32 * G : 16;        // bytes from a row's 8 reduction positions to its next 8
+  static constexpr int kRow = kPieces ? 16 : 320;             // bytes from a head to the next
+  static constexpr int kStep = 4 * kPiece;                    // bytes per ks (Keys) or channel block (Values)
+  static constexpr int kLo = kRow * G;                        // from a head's hi part to its lo part
+  static constexpr int kBytes = kPieces ? 4 * kStep : 2 * G * kRow;
+  // byte offset of the 4 bytes (reduction positions 2l, 2l+1 of the whole operand) that lane l writes for head hh
+  static __device__ __forceinline__ int write_at(int l, int hh) { return (l >> 2) * kPiece + 4 * (l & 3) + kRow * (hh ^ (kPieces ? (l >> 2) & 3 : 0)); }
+  // byte offset of the 16 bytes that a lane (column of head h, part) reads as k-quarter kq of step 0
+  static __device__ __forceinline__ int read_at(int kq, int h, bool lo) { return kq * kPiece + kRow * (h ^ (kPieces ? kq : 0)) + (lo ? kLo : 0); }
+};
+// Groups of 8 heads: the 16 columns are all in use, and every lane folds the scales into its own operand instead (the
+// scales of the tile go through LDS, not the products: 2 bytes per position instead of 32): the two-address writes of the
+// products took half of the LDS time, which bound the loop.
+template <int G> constexpr bool kOwnOperand = G == 8;
 template <int G> struct __attribute__((aligned(16))) WaveLds {
-  static constexpr int kRows = 2 * G;                 // index of the zero row (present when columns are unused)
-  static constexpr int kZeroRow = kRows < 16 ? 1 : 0;
-  uint16_t bk[kRows + kZeroRow][kD + 8];   // scale-folded query [row][channel]
-  // zero-points of the tile: the Key ones [channel] while the Key side is worked on, then the Value ones
-  // [channel block][token] (the same 256 bytes: the Key side is done with them before the Value ones are written)
-  union { uint16_t zk[kD]; uint16_t zv[4][kTile]; };
-  // scores of the tile [row][token] (rows as in bk). Pitch 144 B: the rows are written 16 bytes per lane by
-  // the 16 columns at once, and with a pitch of 128 B all rows would start in the same banks (measured: the two
-  // stores of a tile took as long as all its other LDS traffic together)
-  float s[2 * G][kTile + 4];
-  // scale-folded softmax numerators [channel block][row][token]; the four blocks, written together 4 bytes per
-  // lane, start 64 bytes apart modulo the 256 bytes of one pass over the banks
-  struct BvBlock { uint16_t r[kRows + kZeroRow][kTile + 8]; uint16_t pad[((kRows + kZeroRow) * (kTile + 8) * 2 % 256 == 64) ? 0 : (64 + 256 - (kRows + kZeroRow) * (kTile + 8) * 2 % 256) % 256 / 2]; };
-  BvBlock bv[4];
-  uint16_t pq[kRows + kZeroRow][kTile + 8];   // softmax numerators as two fp16 terms [row][token] (rows as in bk)
+  static constexpr int kOpBytes = kOwnOperand<G> ? kD * 2 : Operand<G>::kBytes;
+  struct Key {
+    char op[kOpBytes];            // scale-folded query (own operand: the Key scales [channel])
+    uint16_t zk[kD];              // Key zero-points of the tile [channel]
+  };
+  struct Value {
+    char op[kOpBytes];               // scale-folded numerators (own operand: the Value scales [block][token])
+    // scores of the tile [row][token] (rows: head h hi 2h, lo 2h + 1). Pitch 144 B: the rows are written 16 bytes per lane by
+    // the 16 columns at once, and with a pitch of 128 B all rows would start in the same banks (measured: the two
+    // stores of a tile took as long as all its other LDS traffic)
+    float s[2 * G][kTile + 4];
+    char pq[Operand<G>::kStep];      // softmax numerators as two fp16 terms, an operand of 32 positions
+    uint16_t zv[4][kTile];           // Value zero-points [channel block][token]
+  };
+  union { Key k; Value v; };
 };
 
-template <int G> struct MergeLds {        // per-wave reference maximum and sum of numerators of every head
-  float m[waves_for(G)][G];
-  float l[waves_for(G)][G];
+template <int G, int NW> struct MergeLds {        // per-wave reference maximum and sum of numerators of every head
+  float m[NW][G];
+  float l[NW][G];
 };
 
-template <int KB, int VB, int G>
-__global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnArgs a) {
-  constexpr int kWaves = waves_for(G);
+template <int KB, int VB, int G, int NW>
+__global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(AttnArgs a) {
+  constexpr int kWaves = NW;
   constexpr int kThreads = kWaves * kWave;
   // per wave: the exchange area of the packed tiles; before that, the staging area in which a window tile's
   // Value rows (token-major in memory) are turned into matrix-core operands (8 consecutive tokens per lane)
-  constexpr int kTPitch = kD + 8;   // fp16 elements per staged row (272 B: 16-byte aligned rows)
   // and, once the wave has worked through its tiles, its result (a wave's memory is its own: a wave that is
   // done never waits for the others)
-  union WaveArea { WaveLds<G> x; uint16_t t[kTile][kTPitch]; float o[G][kD + 16]; };   // result rows 64 bytes apart modulo a pass over the banks
+  union __attribute__((aligned(256))) WaveArea { WaveLds<G> x; uint16_t t[kTile][kD]; float o[G][kD + 16]; };   // result rows 64 bytes apart modulo a pass over the banks
   __shared__ WaveArea s_wave[kWaves];
-  __shared__ MergeLds<G> R;
+  __shared__ MergeLds<G, NW> R;
   __shared__ int s_next;   // next unclaimed packed tile of this workgroup
   __shared__ int s_done;   // waves that have delivered their result
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // said to be uniform: what depends on it alone lives in scalar registers
   const int col = lane & 15, kq = lane >> 4;         // MFMA column / row index, k-quarter
-  const int h = col & 7;
+  const int h = col & (G - 1);                       // head of the column (columns past the used ones repeat them)
   const bool lo_part = col >= 8;
-  const bool col_valid = h < G;
+  const bool col_valid = (col & 7) < G;              // the column's results are stored
   const int sp = blockIdx.x, u = blockIdx.y;
   // Query groups of more than 8 heads run as blocks of 8 heads in workgroups of their own (grid z): the blocks of
   // a unit read the same records and window rows at about the same time, so a tile comes from HBM once and from
   // the caches after that. uo numbers the (unit, head block) pairs: rows uo*8 .. uo*8+7 of q and out.
   const int uo = u * (int)gridDim.z + (int)blockIdx.z;
   WaveLds<G>& L = s_wave[wave].x;
-  uint16_t (&T)[kTile][kTPitch] = s_wave[wave].t;
-  const int row = col_valid ? 2 * h + (lo_part ? 1 : 0) : WaveLds<G>::kRows;   // operand row of this lane's column
+  uint16_t (&T)[kTile][kD] = s_wave[wave].t;
+  const int row = 2 * h + (lo_part ? 1 : 0);         // score row of this lane's column
+  const int op_read = Operand<G>::read_at(kq, h, lo_part);
 
-  // Work items of this split: window tiles first, then packed tiles. Split sp takes items_q items, the first
-  // items_r splits one more (quotient and remainder come from the host: the start of a launch is latency-bound
-  // and integer division takes hundreds of instructions here).
-  const int n_wt = a.W_cap >> 5;
-  const int item_begin = sp * a.items_q + (sp < a.items_r ? sp : a.items_r);
-  const int item_end = item_begin + a.items_q + (sp < a.items_r ? 1 : 0);
-  const int win_begin = item_begin < n_wt ? item_begin : n_wt;
-  const int win_end = item_end < n_wt ? item_end : n_wt;
-  const int p_begin = (item_begin > n_wt ? item_begin : n_wt) - n_wt;
-  const int p_end = (item_end > n_wt ? item_end : n_wt) - n_wt;
+  // Work of this split: of the window's live tiles (numbered by age) those with index sp, sp + n_splits, ..., so
+  // that every split carries its share of them, and a contiguous range of packed tiles. The first a.win_extra splits have one window tile more than the
+  // others and a.win_tiles packed tiles less. (Quotient and remainder come from the host: the start of a launch is
+  // latency-bound and integer division takes hundreds of instructions here.)
+  const int extra = sp < a.win_extra ? sp : a.win_extra;
+  const int p_begin = sp * a.items_q + (sp < a.items_r ? sp : a.items_r) - extra * a.win_tiles;
+  const int p_end = p_begin + a.items_q + (sp < a.items_r ? 1 : 0) - (sp < a.win_extra ? a.win_tiles : 0);
+  const int n_win = a.win_each + (sp < a.win_extra ? 1 : 0);
 
-  // ---- the query and the wave's first window tile are requested before anything else is done.
+  // ---- the query and the wave's first tile are requested before anything else is done.
   // Packed tiles are claimed from a workgroup counter; the first claims are static (wave order).
   const uint16_t* qbase = a.q + (size_t)uo * (G * kD);   // heads of unit u = (b, j) are rows (b*Hkv + j)*G .. +G-1 of q and out
-  half8_t qB[4];       // plain q as B operand: hi columns hold head h, everything else zero
+  half8_t qB[4];       // plain q as B operand: the column's head (hi and lo columns alike, zero in columns not in use)
   uint32_t qraw[G];    // q of channels (2*lane, 2*lane+1) of every head
-  {
-    const half8_t zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  // loaded by the hi columns in use only (a load's cost at the start of a launch is its active lanes), copied to the lo columns later
+#pragma unroll
+  for (int ks = 0; ks < 4; ks++) {
+    qB[ks] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
+    if (col < G) qB[ks] = *reinterpret_cast<const half8_t*>(qbase + col * kD + 32 * ks + 8 * kq);
+  }
+  auto copy_q_to_lo = [&]() {
 #pragma unroll
     for (int ks = 0; ks < 4; ks++) {
-      half8_t v = zero8;
-      if (col_valid && !lo_part) v = *reinterpret_cast<const half8_t*>(qbase + (size_t)h * kD + 32 * ks + 8 * kq);
-      qB[ks] = v;
-    }
+      u32x4_t v = __builtin_bit_cast(u32x4_t, qB[ks]);
 #pragma unroll
-    for (int hh = 0; hh < G; hh++) qraw[hh] = reinterpret_cast<const uint32_t*>(qbase + (size_t)hh * kD)[lane];
-  }
-
-  // Fused append: the newest token of the unit is not in the window arrays yet. The wave that takes the window
-  // tile of its ring slot reads that one row from k_new / v_new instead of the ring, treats it like any other
-  // row of the tile (the host counts it in n_w) and stores it into the ring for the steps to come.
-  const int new_tile = a.new_slot >= 0 ? (a.new_slot >> 5) : -1;
-  const int new_tau = a.new_slot & 31;
+      for (int i = 0; i < 4; i++) { const int w = (int)v[i]; v[i] = (uint32_t)__builtin_amdgcn_update_dpp(w, w, 0x128, 0xf, 0xc, false); }   // row_ror:8 into lanes 8..15
+      qB[ks] = as_half8(v);
+    }
+  };
+#pragma unroll
+  for (int hh = 0; hh < G; hh++) qraw[hh] = reinterpret_cast<const uint32_t*>(qbase + hh * kD)[lane];
 
   constexpr uint32_t kRecBytes = (uint32_t)(record_words(KB, VB) * 4);
   const rsrc_t up = make_rsrc(reinterpret_cast<const char*>(a.packed) + (size_t)u * a.tiles_cap * kRecBytes, (uint32_t)a.tiles_cap * kRecBytes);
-  const int n_win = win_end - win_begin;
   const int n_early = n_win < kWaves ? kWaves - n_win : 0;      // waves n_win .. kWaves-1 start on packed tiles
   const bool has_packed = p_end > p_begin;
-  const bool early = has_packed && wave >= n_win;
-  Stage<KB, VB> st[kDepth];
-  int it[kDepth];
+  const bool early = wave >= n_win;
+  // (written before the first load into LDS is issued: the compiler lets an LDS write wait for those)
+  if (tid == 0) { s_next = p_begin + n_early; s_done = 0; }
+  const rsrc_t vring = make_rsrc(a.v_win + (size_t)u * a.W_cap * kD, (uint32_t)a.W_cap * (kD * 2));
+  Stage<KB, VB> st;
+  int it = p_end;
+  uint32_t lane16 = 16u * lane;
+  asm volatile("" : "+v"(lane16));     // kept in a register of its own: computed again it would land in one that a pending load fills, and wait
 
-  // window tile wi of the ring: the Key rows as MFMA A operands (rows = tokens), the Value rows as loaded:
-  // 16-byte piece lane + 64*j of the tile's 8 KiB, i.e. token 4*j + kq, channels 8*col .. 8*col+7
-  struct WinTile { half8_t Ak[2][4]; u32x4_t Vr[8]; };
-  auto win_first = [&](int wi) { const int r = wi * kTile - a.w0; return r < 0 ? r + a.W_cap : r; };   // ring rank of the tile's first slot
-  auto win_load = [&](int wi, WinTile& w) {
-    const int slot0 = wi * kTile;
+  // Window tile r (by age) of the unit: the Key rows as MFMA A operands (rows = tokens), the Value rows straight into the
+  // wave's staging area (loads that write LDS: no registers are held while they are under way, which lets a wave fit
+  // into 128 registers). The Value rows are requested when the Key rows have arrived: requested together they delay the
+  // first packed tiles (16 layers of 256 units: 364 us, 360.5 us this way).
+  // Fused append: the newest token of the unit is not in the window arrays yet. The wave that takes its tile reads
+  // that one row from k_new / v_new instead of the ring, treats it like any other row of the tile (the host
+  // counts it in n_w) and stores it into the ring for the steps to come.
+  const int new_tau = a.new_slot & 31;
+  auto win_slot = [&](int r) { int wi = a.w0_tile + r; wi = wi >= a.ring_tiles ? wi - a.ring_tiles : wi; return wi * kTile; };   // first slot of the tile
+  auto win_new = [&](int slot0) { return a.new_slot >= 0 && slot0 == (a.new_slot & ~31); };     // wave-uniform
+  struct WinKeys { half8_t r[2][4]; };
+  auto win_load_k = [&](int r, int lane, WinKeys& w) {
+    const int col = lane & 15, kq = lane >> 4;
+    const int slot0 = win_slot(r);
     const uint16_t* kw = a.k_win + ((size_t)u * a.W_cap + slot0) * kD;
     const uint16_t* kn = a.k_new + (size_t)u * kD;
-    const bool has_new = wi == new_tile;      // wave-uniform
+    const bool has_new = win_new(slot0);
 #pragma unroll
     for (int m = 0; m < 2; m++) {
       const int tau = 8 * (col >> 2) + 4 * m + (col & 3);   // row `col` of M-tile m
       // a slot past the live tokens is not read: its lanes take the tile's first row instead (live, and already on its
       // way: a cache hit), whose products the softmax mask discards; no byte of a dead slot reaches the arithmetic
-      const int tau_r = win_first(wi) + tau < a.n_w ? tau : 0;
+      const int tau_r = r * kTile + tau < a.n_w ? tau : 0;
       const uint16_t* rowp = (has_new && tau == new_tau) ? kn : kw + (size_t)tau_r * kD;
 #pragma unroll
-      for (int ks = 0; ks < 4; ks++) w.Ak[m][ks] = *reinterpret_cast<const half8_t*>(rowp + 32 * ks + 8 * kq);
+      for (int ks = 0; ks < 4; ks++) w.r[m][ks] = *reinterpret_cast<const half8_t*>(rowp + 32 * ks + 8 * kq);
     }
   };
-  // The Value rows are requested only when the Key rows have been consumed: fewer registers in flight (no
-  // spills in any variant) and a smaller first burst, so that the first packed tiles arrive earlier
-  // (measured 0.3-0.4 us per launch against requesting both at the start).
-  auto win_load_v = [&](int wi, WinTile& w) {
-    const uint16_t* vw = a.v_win + ((size_t)u * a.W_cap + wi * kTile) * kD;
-    const uint16_t* vn = a.v_new + (size_t)u * kD;
-    const bool has_new = wi == new_tile;
+  // Value rows 4j .. 4j+3 per instruction, 16 bytes per lane in lane order: chunk c (8 channels) of row t goes to chunk
+  // c ^ swizzle(t) of its row, so that the transposing reads below find their 8 rows x 32 bytes in distinct banks.
+  auto swizzle = [](int t) { return 2 * ((t & 3) + 4 * ((t >> 3) & 1)); };
+  auto win_load_v = [&](int r, int lane) {
+    const int col = lane & 15, kq = lane >> 4;
+    const int slot0 = win_slot(r);
+    const int skip = win_new(slot0) ? new_tau : -1;             // not in the ring yet
 #pragma unroll
     for (int j = 0; j < 8; j++) {
-      const int tv = win_first(wi) + 4 * j + kq < a.n_w ? 4 * j + kq : 0;      // dead slots: the first row again (weight zero)
-      const uint16_t* rowp = (has_new && 4 * j + kq == new_tau) ? vn : vw + (size_t)tv * kD;
-      w.Vr[j] = *reinterpret_cast<const u32x4_t*>(rowp + 8 * col);
+      const int tau = 4 * j + kq;
+      const int tau_r = (r * kTile + tau < a.n_w && tau != skip) ? tau : 0;      // dead slots: the first row again (weight zero)
+      buf_load_to_lds16(vring, 256u * tau_r + 16u * (col ^ (2 * kq) ^ ((j & 2) ? 8 : 0)), 256u * slot0, &T[4 * j][0]);
     }
   };
-  // the append itself: the lanes that hold pieces of the new row store them into its ring slot
-  auto store_new_k = [&](int wi, const WinTile& w) {
-    if (wi != new_tile) return;
-    uint16_t* dst = a.k_win_w + ((size_t)u * a.W_cap + a.new_slot) * kD;
-#pragma unroll
-    for (int m = 0; m < 2; m++) {
-      const int tau = 8 * (col >> 2) + 4 * m + (col & 3);
-      if (tau == new_tau) {
-#pragma unroll
-        for (int ks = 0; ks < 4; ks++) *reinterpret_cast<half8_t*>(dst + 32 * ks + 8 * kq) = w.Ak[m][ks];
-      }
-    }
+  // the append itself, one row of each side, 16 lanes each: requested with the tile, then stored into the ring and (the
+  // Value row) into the staging area
+  auto append_load = [&](bool has_new) {
+    u32x4_t x = {0, 0, 0, 0};
+    if (has_new && lane < 32) x = *reinterpret_cast<const u32x4_t*>((lane >= 16 ? a.v_new : a.k_new) + (size_t)u * kD + 8 * col);
+    return x;
   };
-  auto store_new_v = [&](int wi, const WinTile& w) {
-    if (wi != new_tile) return;
-    uint16_t* dst = a.v_win_w + ((size_t)u * a.W_cap + a.new_slot) * kD;
-#pragma unroll
-    for (int j = 0; j < 8; j++)
-      if (4 * j + kq == new_tau) *reinterpret_cast<u32x4_t*>(dst + 8 * col) = w.Vr[j];
+  auto append_stage = [&](const u32x4_t& x) {
+    if (lane >= 16 && lane < 32) *reinterpret_cast<u32x4_t*>(&T[new_tau][8 * (col ^ swizzle(new_tau))]) = x;
   };
-  WinTile wt;
-  int wi = win_begin + wave;
-  // tiles wholly outside the n_w valid tokens are skipped (w0 and tiles are 32-aligned)
-  while (wi < win_end && win_first(wi) >= a.n_w) wi += kWaves;
-  if (wi < win_end) win_load(wi, wt);
-
-  if (tid == 0) { s_next = p_begin + kDepth * n_early; s_done = 0; }
+  auto append_store = [&](const u32x4_t& x) {
+    if (lane < 32) *reinterpret_cast<u32x4_t*>((lane >= 16 ? a.v_win_w : a.k_win_w) + ((size_t)u * a.W_cap + a.new_slot) * kD + 8 * col) = x;
+  };
   // The only workgroup barrier before the results are merged: the counters are set. It must not wait for the
   // loads just requested (a full __syncthreads would): LDS serves a wave's operations in order, so waiting for
-  // the wave's LDS operations before the barrier is all that the two counter writes need.
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");   // no memory access of the code below moves above the barrier
+  // the wave's LDS operations before the barrier is all that the two counter writes need. Both kinds of wave pass a barrier
+  // of their own code path: what a wave has requested before it stays in registers of that path alone.
+  auto start_barrier = [&]() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");   // no memory access of the code below moves above the barrier
+  };
 
   // q of the lane's two channels, prescaled so that code products of all four channel blocks come out in the
   // same unit: the field of block ks sits at bit field_pos(ks), the query is scaled by 2^(field_pos(0) - field_pos(ks))
   // (exact in fp16 for |q| >= 2^-8; smaller values lose bits far below anything the scores resolve)
   constexpr int kPos0 = field_pos<KB>(0);
+  const half_t pre = (half_t)__builtin_ldexpf(1.0f, kPos0 - field_pos<KB>(lane >> 4));
   half2_t qh[G];
-  {
-    const half_t pre = (half_t)__builtin_ldexpf(1.0f, kPos0 - field_pos<KB>(lane >> 4));
 #pragma unroll
-    for (int hh = 0; hh < G; hh++) qh[hh] = as_half2(qraw[hh]) * half2_t{pre, pre};
-  }
+  for (int hh = 0; hh < G; hh++) qh[hh] = as_half2(qraw[hh]) * half2_t{pre, pre};
+  // zero outside the lo columns
+  const uint32_t lo_mask = lo_part ? 0xFFFFFFFFu : 0u;
+  auto lo_only = [&](half8_t v) { return as_half8(__builtin_bit_cast(u32x4_t, v) & lo_mask); };
 
   const half8_t zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
   const half8_t ones8 = {1, 1, 1, 1, 1, 1, 1, 1};
@@ -486,91 +526,86 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
   auto grab_take = [](int t) -> int { return __builtin_amdgcn_readfirstlane(t); };
   auto grab = [&]() -> int { return grab_take(grab_issue()); };
 
-  // ---- fp16 window tiles (few): taken round-robin by the waves before the packed stream.
-  // A wave that started on packed tiles has no window tile; the nesting keeps its tile registers
-  // out of the live ranges in here.
-  if (!early) {
-  while (wi < win_end) {
-    const int first = win_first(wi);
-    const half8_t (&Ak)[2][4] = wt.Ak;
-    float4_t S[2] = {float4_t{0, 0, 0, 0}, float4_t{0, 0, 0, 0}};
-#pragma unroll
-    for (int m = 0; m < 2; m++)
-#pragma unroll
-      for (int ks = 0; ks < 4; ks++) S[m] = mfma16(Ak[m][ks], qB[ks], S[m]);
-    store_new_k(wi, wt);
-    win_load_v(wi, wt);
-    // Value rows into the staging area as loaded (their registers are free again before the softmax). Rows
-    // 16..31 swap neighbouring 32-byte blocks, so that the lanes of different kq read from different banks.
-#pragma unroll
-    for (int j = 0; j < 8; j++) *reinterpret_cast<u32x4_t*>(&T[4 * j + kq][8 * (col ^ (j >= 4 ? 2 : 0))]) = wt.Vr[j];
-    store_new_v(wi, wt);
-    float x[8], p[8];
-#pragma unroll
-    for (int m = 0; m < 2; m++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) x[4 * m + r] = (first + 8 * kq + 4 * m + r) < a.n_w ? S[m][r] : -INFINITY;
-#pragma unroll
-    for (int e = 0; e < 8; e++) x[e] = x[e] + ror8(x[e]);   // hi column + lo column (lo is zero here)
-    raise_reference(max8(x) * c_plain);
-#pragma unroll
-    for (int e = 0; e < 8; e++) p[e] = fast_exp2(x[e] * c_plain - mref);
-    half8_t PB;
-#pragma unroll
-    for (int e = 0; e < 8; e++) PB[e] = split_part(col_valid ? p[e] : 0.0f, lo_part);
-    accZ = mfma16(col >= 4 ? ones8 : zero8, PB, accZ);   // rows 4..15 accumulate the sum of numerators
-    // Value rows back from the staging area, channel by channel
-    wave_lds_fence();
-#pragma unroll
-    for (int m = 0; m < 8; m++) {
-      half8_t Avm;
-#pragma unroll
-      for (int e = 0; e < 8; e++) Avm[e] = __builtin_bit_cast(half_t, T[8 * kq + e][16 * (m ^ (kq >> 1)) + col]);
-      float4_t t = mfma16(Avm, PB, float4_t{0, 0, 0, 0});
-      if constexpr (VB == 3) {   // the final 7/3 step factor of channels 10 / 21 applies to codes only
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-          const int dd = 16 * (m & 1) + 4 * kq + r;
-          if (dd == 10 || dd == 21) t[r] *= (3.0f / 7.0f);
-        }
-      }
-      acc[m] += t * __builtin_ldexpf(1.0f, field_pos<VB>(m & 3) - 24);
-    }
-    wave_lds_fence();   // the staging area is free again
-    wi += kWaves;
-    while (wi < win_end && win_first(wi) >= a.n_w) wi += kWaves;
-    if (wi < win_end) win_load(wi, wt);
-  }
-  if (has_packed) {   // claim the first packed tiles now
-#pragma unroll
-    for (int s = 0; s < kDepth; s++) {
-      it[s] = grab();
-      st[s].load(up, it[s] < p_end ? it[s] : p_end - 1, lane);
-    }
-  }
-  }
-  // The waves without a window tile take their first packed tiles by wave order (the counter starts behind
-  // them). They request them only here, not at the kernel's start: tile registers that stay live across the
-  // window code above push the kernel over its register budget, and the spill that follows waits for every
-  // outstanding load; requested here they cost nothing measurable (the start of a launch is bound by the
-  // request rate of the window and query loads anyway).
+  // ---- fp16 window tiles: taken round-robin by the waves before the packed stream.
   // Past the end a wave re-reads the last tile (cache hit) and skips its work: the load stream and the
   // loop body stay uniform, which keeps the outstanding-load accounting exact.
-  if (early) {
+  if (!early) {
+    int r = sp + wave * a.n_splits;                      // < the number of live tiles, since wave < n_win
+    const int r_step = kWaves * a.n_splits;
+    int left = (n_win - wave + kWaves - 1) / kWaves;     // tiles of this wave
+    for (int begin = 1; left > 0; left--, r += r_step) {
+      asm volatile("" : "+s"(begin));     // (keeps the first pass from being compiled a second time: the code is read cold at the start of a launch)
+      const int first = r * kTile;
+      // the lane number as a value of this iteration: addresses derived from it are not kept in registers around the loop
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      WinKeys wk;
+      const bool has_new = win_new(win_slot(r));
+      win_load_k(r, ln, wk);
+      const u32x4_t appended = append_load(has_new);
+      __builtin_amdgcn_sched_barrier(0);      // (matrix instructions moved up here would wait for their rows in front of the barrier)
+      if (begin) start_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      if (begin) copy_q_to_lo();
+      begin = 0;
+      float4_t S[2] = {float4_t{0, 0, 0, 0}, float4_t{0, 0, 0, 0}};
 #pragma unroll
-    for (int s = 0; s < kDepth; s++) {
-      it[s] = p_begin + s * n_early + (wave - n_win);
-      st[s].load(up, it[s] < p_end ? it[s] : p_end - 1, lane);
+      for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++) S[m] = mfma16(wk.r[m][ks], qB[ks], S[m]);
+      win_load_v(r, ln);
+      float x[8], p[8];
+#pragma unroll
+      for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; r4++) x[4 * m + r4] = (first + 8 * kq + 4 * m + r4) < a.n_w ? S[m][r4] : -INFINITY;
+      raise_reference(max8(x) * c_plain);
+#pragma unroll
+      for (int e = 0; e < 8; e++) p[e] = fast_exp2(x[e] * c_plain - mref);
+      half8_t PB;
+#pragma unroll
+      for (int e = 0; e < 8; e++) PB[e] = split_part(p[e], lo_part);
+      accZ = mfma16(col >= 4 ? ones8 : zero8, PB, accZ);   // rows 4..15 accumulate the sum of numerators
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the Value rows are in the staging area
+      if (has_new) append_stage(appended);
+      wave_lds_fence();
+      // lane's part of the transposing reads: rows 8*kq + col/4 (+ 4), channels 4 * (col % 4) .. +3 of a block of 16
+      const int c = ln & 15, k4 = ln >> 4;
+      const int t_off = (8 * k4 + (c >> 2)) * (kD * 2) + ((((c & 3) >> 1) ^ (2 * (c >> 2) + 8 * (k4 & 1))) << 4) + 8 * (c & 1);
+#pragma unroll
+      for (int m = 0; m < 8; m++) {
+        const half8_t Avm = read_transposed(reinterpret_cast<const char*>(&T[0][0]), t_off ^ (m << 5));
+        float4_t t = mfma16(Avm, PB, float4_t{0, 0, 0, 0});
+        if constexpr (VB == 3) {   // the final 7/3 step factor of channels 10 / 21 applies to codes only
+#pragma unroll
+          for (int r4 = 0; r4 < 4; r4++) {
+            const int dd = 16 * (m & 1) + 4 * kq + r4;
+            if (dd == 10 || dd == 21) t[r4] *= (3.0f / 7.0f);
+          }
+        }
+        acc[m] += t * __builtin_ldexpf(1.0f, field_pos<VB>(m & 3) - 24);
+        if (m & 1) __builtin_amdgcn_sched_barrier(0);      // (reads of all eight blocks hoisted together do not fit the registers)
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the staging area has been read: it is free again
+      if (has_new) append_store(appended);                 // (after the reads: those would wait for a store in front of them)
+    }
+    if (has_packed) {   // claim the first packed tile now
+      it = grab();
+      st.load(up, it < p_end ? it : p_end - 1, lane16);
     }
   }
-
-  // zero the wave's exchange area (it shared its memory with the staging area): the rows of unused
-  // operand columns stay zero from here on
-  {
-    u32x4_t* z = reinterpret_cast<u32x4_t*>(&L);
-    for (int i = lane; i < (int)(sizeof(WaveLds<G>) / 16); i += kWave) z[i] = u32x4_t{0, 0, 0, 0};
+  // (a condition of its own: as the else of the one above it would be laid out in front of it, and the loads above would then wait
+  // for the query, behind which the registers they share with the tile become free)
+  int early_s = __builtin_amdgcn_readfirstlane(early ? 1 : 0);
+  asm volatile("" : "+s"(early_s));
+  if (early_s) {
+    it = p_begin + (wave - n_win);
+    if (has_packed) st.load(up, it < p_end ? it : p_end - 1, lane16);
+    __builtin_amdgcn_sched_barrier(0);
+    start_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (G > 2) copy_q_to_lo();      // (smaller groups use it for window tiles only)
   }
-  wave_lds_fence();
 
   // ---- small query groups (G <= 2): the matrix core's columns are nearly empty, so the per-tile extras
   // (Key zero-point term, Value zero-point term, sum of numerators) are cheaper on the vector unit:
@@ -590,6 +625,8 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
   }
   const float inv_c_code = 1.0f / c_code;
 
+  auto op_write = [&](int hh) { return Operand<G>::write_at(lane, hh); };
+
   auto process_small = [&](const Stage<KB, VB>& st) {
     // -- Key side. Lane owns channels 2*lane, 2*lane+1: scale-folded query to LDS, zero-point term by dot product
     float zt[G];
@@ -600,8 +637,8 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
       for (int hh = 0; hh < G; hh++) {
         uint32_t hi, lo;
         mul_split(qh[hh], s2, hi, lo);
-        reinterpret_cast<uint32_t*>(&L.bk[2 * hh][0])[lane] = hi;
-        reinterpret_cast<uint32_t*>(&L.bk[2 * hh + 1][0])[lane] = lo;
+        *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh)]) = hi;
+        *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh) + Operand<G>::kLo]) = lo;
         const float zp = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, qraw[hh]), __builtin_bit_cast(half2_t, kz_pair), 0.0f, false);
         zt[hh] = wave_sum(zp) * c_plain;
       }
@@ -611,7 +648,7 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
       const Codes<KB> kc(st.kc);
       half8_t Bk[4];
 #pragma unroll
-      for (int ks = 0; ks < 4; ks++) Bk[ks] = *reinterpret_cast<const half8_t*>(&L.bk[row][32 * ks + 8 * kq]);
+      for (int ks = 0; ks < 4; ks++) Bk[ks] = *reinterpret_cast<const half8_t*>(&L.k.op[op_read + ks * Operand<G>::kStep]);
       float4_t S[2] = {float4_t{0, 0, 0, 0}, float4_t{0, 0, 0, 0}};
 #pragma unroll
       for (int m = 0; m < 2; m++)
@@ -624,22 +661,22 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
         if (kq == 2) S[1][1] *= (7.0f / 3.0f);
       }
       if (col_valid) {
-        *reinterpret_cast<float4_t*>(&L.s[row][8 * kq]) = S[0];
-        *reinterpret_cast<float4_t*>(&L.s[row][8 * kq + 4]) = S[1];
+        *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq]) = S[0];
+        *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq + 4]) = S[1];
       }
     }
     wave_lds_fence();
     // -- Value side. Lane (tp, g) owns tokens (2*tp, 2*tp+1) of channel block g.
     {
-      const int tp = lane & 15, g = lane >> 4;
+      const int tp = lane & 15;
       const float s0 = lo_half(st.meta[2]), s1 = hi_half(st.meta[2]);
       const float z0 = lo_half(st.meta[3]), z1 = hi_half(st.meta[3]);
       float sum0[G], sum1[G];
       bool over = false;
 #pragma unroll
       for (int hh = 0; hh < G; hh++) {
-        const float2_t sh = *reinterpret_cast<const float2_t*>(&L.s[2 * hh][2 * tp]);
-        const float2_t sl = *reinterpret_cast<const float2_t*>(&L.s[2 * hh + 1][2 * tp]);
+        const float2_t sh = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh][2 * tp]);
+        const float2_t sl = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh + 1][2 * tp]);
         sum0[hh] = sh[0] + sl[0];
         sum1[hh] = sh[1] + sl[1];
         // score = sum * c_code + zt; it exceeds what the reference allows iff sum > (reference + cap - zt) / c_code
@@ -672,8 +709,8 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
         zacc[hh] += p0 * z0 + p1 * z1;
         uint32_t hi, lo;
         split_pair(p0 * s0, p1 * s1, hi, lo);
-        reinterpret_cast<uint32_t*>(&L.bv[g].r[2 * hh][0])[tp] = hi;
-        reinterpret_cast<uint32_t*>(&L.bv[g].r[2 * hh + 1][0])[tp] = lo;
+        *reinterpret_cast<uint32_t*>(&L.v.op[op_write(hh)]) = hi;          // lane 16 g + tp: positions 2 tp, 2 tp + 1 of block g
+        *reinterpret_cast<uint32_t*>(&L.v.op[op_write(hh) + Operand<G>::kLo]) = lo;
       }
     }
     wave_lds_fence();
@@ -681,7 +718,7 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
       const Codes<VB> vc(st.vc);
       half8_t Bv[4];
 #pragma unroll
-      for (int g = 0; g < 4; g++) Bv[g] = *reinterpret_cast<const half8_t*>(&L.bv[g].r[row][8 * kq]);
+      for (int g = 0; g < 4; g++) Bv[g] = *reinterpret_cast<const half8_t*>(&L.v.op[op_read + g * Operand<G>::kStep]);
 #pragma unroll
       for (int m = 0; m < 8; m++) {
         acc[m] = mfma16(vc.lo(m), Bv[m >> 1], acc[m]);
@@ -694,14 +731,19 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
     // -- Key side. Cooperative operand preparation: lane owns channels 2*lane, 2*lane+1.
     {
       const half2_t s2 = as_half2(st.meta[0]);
+      if constexpr (kOwnOperand<G>) {
+        // the scale carries the field position's power of two here (exact, or off by 2^-19 of the scale's unit at most)
+        reinterpret_cast<uint32_t*>(L.k.op)[lane] = as_u32(s2 * half2_t{pre, pre});
+      } else {
 #pragma unroll
-      for (int hh = 0; hh < G; hh++) {
-        uint32_t hi, lo;
-        mul_split(qh[hh], s2, hi, lo);
-        reinterpret_cast<uint32_t*>(&L.bk[2 * hh][0])[lane] = hi;
-        reinterpret_cast<uint32_t*>(&L.bk[2 * hh + 1][0])[lane] = lo;
+        for (int hh = 0; hh < G; hh++) {
+          uint32_t hi, lo;
+          mul_split(qh[hh], s2, hi, lo);
+          *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh)]) = hi;
+          *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh) + Operand<G>::kLo]) = lo;
+        }
       }
-      reinterpret_cast<uint32_t*>(&L.zk[0])[lane] = st.meta[1];
+      reinterpret_cast<uint32_t*>(&L.k.zk[0])[lane] = st.meta[1];
     }
     wave_lds_fence();
     float x[8], zt;
@@ -711,9 +753,14 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
       float4_t Sz = {0, 0, 0, 0};
 #pragma unroll
       for (int ks = 0; ks < 4; ks++) {
-        Bk[ks] = *reinterpret_cast<const half8_t*>(&L.bk[row][32 * ks + 8 * kq]);
-        const half8_t z8 = *reinterpret_cast<const half8_t*>(&L.zk[32 * ks + 8 * kq]);
+        const half8_t z8 = *reinterpret_cast<const half8_t*>(&L.k.zk[32 * ks + 8 * kq]);
         Sz = mfma16(z8, qB[ks], Sz);     // every A row is the zero-point vector
+        if constexpr (kOwnOperand<G>) {
+          const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.k.op[64 * ks + 16 * kq]);
+          Bk[ks] = __builtin_elementwise_fma(qB[ks], s8, -lo_only(qB[ks] * s8));
+        } else {
+          Bk[ks] = *reinterpret_cast<const half8_t*>(&L.k.op[op_read + ks * Operand<G>::kStep]);
+        }
       }
       float4_t S[2] = {float4_t{0, 0, 0, 0}, float4_t{0, 0, 0, 0}};
 #pragma unroll
@@ -726,7 +773,7 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
         if (kq == 1) S[0][2] *= (7.0f / 3.0f);
         if (kq == 2) S[1][1] *= (7.0f / 3.0f);
       }
-      zt = Sz[0] * c_plain;          // zero in lo columns (their plain-query operand is zero)
+      zt = Sz[0] * c_plain;
 #pragma unroll
       for (int m = 0; m < 2; m++)
 #pragma unroll
@@ -745,8 +792,8 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
 
     // -- Value side. Scores to LDS; lane (tp, g) then owns tokens (2*tp, 2*tp+1) of channel block g.
     if (col_valid) {
-      *reinterpret_cast<float4_t*>(&L.s[row][8 * kq]) = float4_t{x[0], x[1], x[2], x[3]};
-      *reinterpret_cast<float4_t*>(&L.s[row][8 * kq + 4]) = float4_t{x[4], x[5], x[6], x[7]};
+      *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq]) = float4_t{x[0], x[1], x[2], x[3]};
+      *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq + 4]) = float4_t{x[4], x[5], x[6], x[7]};
     }
     wave_lds_fence();
     // The four lane groups g would all compute the same numerators; instead group g finishes those of the
@@ -762,8 +809,8 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
 #pragma unroll
       for (int k = 0; k < G / 4; k++) {
         const int hh = 4 * k + g;                                  // differs between the lane groups
-        sh[k] = *reinterpret_cast<const float2_t*>(&L.s[2 * hh][2 * tp]);
-        sl[k] = *reinterpret_cast<const float2_t*>(&L.s[2 * hh + 1][2 * tp]);
+        sh[k] = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh][2 * tp]);
+        sl[k] = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh + 1][2 * tp]);
       }
 #pragma unroll
       for (int k = 0; k < G / 4; k++) {
@@ -774,20 +821,35 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
         const float p0 = fast_exp2(sh[k][0] + sl[k][0]), p1 = fast_exp2(sh[k][1] + sl[k][1]);
         const half2_t hv = {(half_t)p0, (half_t)p1};
         const half2_t lv = {(half_t)(p0 - (float)hv[0]), (half_t)(p1 - (float)hv[1])};
-        reinterpret_cast<uint32_t*>(&L.pq[2 * hh][0])[tp] = as_u32(hv);
-        reinterpret_cast<uint32_t*>(&L.pq[2 * hh + 1][0])[tp] = as_u32(lv);
+        const int at = Operand<G>::write_at(tp, hh);
+        *reinterpret_cast<uint32_t*>(&L.v.pq[at]) = as_u32(hv);
+        *reinterpret_cast<uint32_t*>(&L.v.pq[at + Operand<G>::kLo]) = as_u32(lv);
       }
-      reinterpret_cast<uint32_t*>(&L.zv[0][0])[lane] = st.meta[3];
+      reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = st.meta[3];
+      if constexpr (kOwnOperand<G>) reinterpret_cast<uint32_t*>(L.v.op)[lane] = st.meta[2];
     }
     wave_lds_fence();
-    {
-      const int tp = lane & 15, g = lane >> 4;
+    half8_t Bv[4];
+    // plain numerators: the column's own row
+    const half8_t PB = *reinterpret_cast<const half8_t*>(&L.v.pq[op_read]);
+    if constexpr (kOwnOperand<G>) {
+      // hi columns: the rounded products p * s; lo columns: what the rounding left, and the small terms' products
+      const half8_t p8 = *reinterpret_cast<const half8_t*>(&L.v.pq[Operand<G>::read_at(kq, h, false)]);
+      const half8_t px = lo_only(p8), dx = lo_only(PB);
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.v.op[64 * g + 16 * kq]);
+        Bv[g] = __builtin_elementwise_fma(dx, s8, __builtin_elementwise_fma(p8, s8, -(px * s8)));
+      }
+    } else {
+      const int tp = lane & 15;
       const half2_t s2 = as_half2(st.meta[2]);
       uint32_t pw[G], dw[G];
 #pragma unroll
       for (int hh = 0; hh < G; hh++) {
-        pw[hh] = reinterpret_cast<const uint32_t*>(&L.pq[2 * hh][0])[tp];
-        dw[hh] = reinterpret_cast<const uint32_t*>(&L.pq[2 * hh + 1][0])[tp];
+        const int at = Operand<G>::write_at(tp, hh);
+        pw[hh] = *reinterpret_cast<const uint32_t*>(&L.v.pq[at]);
+        dw[hh] = *reinterpret_cast<const uint32_t*>(&L.v.pq[at + Operand<G>::kLo]);
       }
 #pragma unroll
       for (int hh = 0; hh < G; hh++) {
@@ -795,22 +857,19 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
         // (p2 + d2) * s2: exact product of the leading term in two parts, the small term's product folded into the second
         const half2_t hv = p2 * s2;
         const half2_t lv = __builtin_elementwise_fma(d2, s2, __builtin_elementwise_fma(p2, s2, -hv));
-        reinterpret_cast<uint32_t*>(&L.bv[g].r[2 * hh][0])[tp] = as_u32(hv);
-        reinterpret_cast<uint32_t*>(&L.bv[g].r[2 * hh + 1][0])[tp] = as_u32(lv);
+        *reinterpret_cast<uint32_t*>(&L.v.op[op_write(hh)]) = as_u32(hv);
+        *reinterpret_cast<uint32_t*>(&L.v.op[op_write(hh) + Operand<G>::kLo]) = as_u32(lv);
       }
+      wave_lds_fence();
+#pragma unroll
+      for (int g = 0; g < 4; g++) Bv[g] = *reinterpret_cast<const half8_t*>(&L.v.op[op_read + g * Operand<G>::kStep]);
     }
-    wave_lds_fence();
     {
       const Codes<VB> vc(st.vc);
-      half8_t Bv[4];
-#pragma unroll
-      for (int g = 0; g < 4; g++) Bv[g] = *reinterpret_cast<const half8_t*>(&L.bv[g].r[row][8 * kq]);
-      // plain numerators: the column's own row (unused columns: the zero row)
-      const half8_t PB = *reinterpret_cast<const half8_t*>(&L.pq[row][8 * kq]);
       // zero-point term: A rows 0..3 carry the zero-points of channel blocks 0..3, rows 4..15 are ones
       // and accumulate the sum of the numerators
       half8_t z8 = ones8;
-      if (col < 4) z8 = *reinterpret_cast<const half8_t*>(&L.zv[col][8 * kq]);
+      if (col < 4) z8 = *reinterpret_cast<const half8_t*>(&L.v.zv[col][8 * kq]);
       accZ = mfma16(z8, PB, accZ);
 #pragma unroll
       for (int m = 0; m < 8; m++) {
@@ -824,15 +883,11 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
   };
 
   if (has_packed) {
-    while (it[0] < p_end) {      // a wave's items increase: it[0] is the oldest one in flight
-#pragma unroll
-      for (int s = 0; s < kDepth; s++) {
-        const int ticket = grab_issue();
-        if (it[s] < p_end) process(st[s]);   // past the end: skip the work, keep the load stream
-        const int nxt = grab_take(ticket);
-        it[s] = nxt;
-        st[s].load(up, nxt < p_end ? nxt : p_end - 1, lane);
-      }
+    while (it < p_end) {
+      const int ticket = grab_issue();
+      process(st);
+      it = grab_take(ticket);
+      st.load(up, it < p_end ? it : p_end - 1, lane16);
     }
   }
 
@@ -961,7 +1016,7 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partial stores have completed ...
   __syncthreads();                                     // ... and so have those of all waves, before the arrival is counted
   if (tid == 0) {
-    const uint32_t prev = __hip_atomic_fetch_add(&a.counters[uo], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t prev = __hip_atomic_fetch_add(&a.counters[uo * a.counter_stride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_done = (prev == (uint32_t)a.n_splits - 1u);   // reused as the "last workgroup" flag
   }
   __syncthreads();
@@ -1001,16 +1056,16 @@ __global__ __launch_bounds__(waves_for(G) * kWave) void decode_attn_kernel(AttnA
     }
     outp[idx] = __builtin_bit_cast(uint16_t, (half_t)(O / Lsum));
   }
-  if (tid == 0) __hip_atomic_store(&a.counters[uo], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) __hip_atomic_store(&a.counters[uo * a.counter_stride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <int KB, int VB>
 hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
   switch (G) {
-    case 1: decode_attn_kernel<KB, VB, 1><<<grid, waves_for(1) * kWave, 0, s>>>(a); break;
-    case 2: decode_attn_kernel<KB, VB, 2><<<grid, waves_for(2) * kWave, 0, s>>>(a); break;
-    case 4: decode_attn_kernel<KB, VB, 4><<<grid, waves_for(4) * kWave, 0, s>>>(a); break;
-    case 8: decode_attn_kernel<KB, VB, 8><<<grid, waves_for(8) * kWave, 0, s>>>(a); break;
+    case 1: decode_attn_kernel<KB, VB, 1, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
+    case 2: decode_attn_kernel<KB, VB, 2, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
+    case 4: decode_attn_kernel<KB, VB, 4, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
+    case 8: decode_attn_kernel<KB, VB, 8, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1018,7 +1073,8 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_decode_attn(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s) {
+template <>
+hipError_t launch_decode_attn<kNW>(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s) {
   const int head_blocks = G > 8 ? G / 8 : 1;
   if (G > 8) G = 8;
   const dim3 grid(a.n_splits, units, head_blocks);

@@ -132,10 +132,16 @@ struct AttnArgs {
   int new_slot;           // -1: nothing to append
   float* part;            // partials: [units][n_parts][G][kD + 2], the first n_splits of a unit written by this launch
   int n_parts;            // n_splits, plus one when an earlier launch left the partial of the tokens between two fronts
-  uint32_t* counters;     // [units] arrival counters (zero before and after every call)
-  int tiles_cap, W_cap, n_tiles, n_w, w0;
-  int Hq, Hkv, n_splits;
-  int items_q, items_r;   // (window tiles + packed tiles) divided by n_splits: quotient and remainder
+  uint32_t* counters;     // arrival counters (zero before and after every call), one per (unit, head block), counter_stride words apart
+  int counter_stride;
+  int tiles_cap, W_cap, n_w;
+  int ring_tiles, w0_tile;       // W_cap / 32; ring tile that holds the oldest window token
+  int n_splits;
+  // window tiles with live tokens: win_each per split, one more for the first win_extra splits
+  int win_each, win_extra;
+  // packed tiles: (packed tiles + win_extra * win_tiles) divided by n_splits, quotient and remainder; the splits with a
+  // window tile more than the others take win_tiles packed tiles less
+  int items_q, items_r, win_tiles;
   float scale_log2;       // softmax_scale * log2(e)
 };
 
@@ -161,6 +167,10 @@ hipError_t launch_mixed_fronts(const MixedArgs& a, int units, hipStream_t s);
 hipError_t launch_dequant(const DequantArgs& a, int units, hipStream_t s);
 hipError_t launch_append(const AppendArgs& a, hipStream_t s);
 hipError_t launch_stream_read(const void* buf, size_t bytes, int workgroups, int threads, uint32_t* sink, hipStream_t s);
+// WAVES: waves per workgroup, 8 or 12
+template <int WAVES>
 hipError_t launch_decode_attn(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s);
+template <> hipError_t launch_decode_attn<8>(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s);
+template <> hipError_t launch_decode_attn<12>(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s);
 
 }  // namespace kvmix

@@ -368,3 +368,47 @@ def test_graph_replays_match_eager(n_splits):
         st, want = rc.decode_attn(u16(qn))
         assert_attn_close(t16(out_g), want, f"graph replay {rep}", tight=True)
         assert not ws[: 4 * shape.units].any()
+
+
+@pytest.mark.parametrize("B,G,Hkv,kb,vb,tiles,W,n_w,n_splits", [
+    (33, 1, 8, 2, 2, 5, 32, 40, 0),       # 264 units: more workgroups than compute units
+    (33, 8, 8, 2, 3, 5, 32, 63, 0),       # the same with 8 heads and 3-bit Values
+    (33, 4, 8, 3, 4, 0, 64, 70, 0),       # nothing packed yet
+    (1, 4, 1, 3, 4, 38, 32, 45, 2),       # 20 tiles per split, and one more
+    (1, 4, 1, 3, 4, 39, 32, 45, 2),
+    (1, 2, 2, 2, 2, 3, 288, 300, 4),      # 10 window tiles over 4 splits, fewer packed tiles than splits
+    (1, 8, 1, 2, 2, 2, 448, 460, 1),      # 15 window tiles: two rounds of window tiles for some waves
+    (2, 4, 2, 16, 16, 0, 32, 835, 3),     # 27 window tiles, 9 per split, nothing packed ever
+])
+def test_wave_forms_and_window_shares(B, G, Hkv, kb, vb, tiles, W, n_w, n_splits):
+    """Both workgroup forms of the attention kernel and the window tiles' distribution over splits and waves, on a ring that starts at
+    slot 32 (its tiles wrap), plain and with the append inside."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case forms B={B} G={G} Hkv={Hkv} bits={kb}/{vb} tiles={tiles} n_w={n_w} splits={n_splits}", flush=True)
+    T = 32 * tiles + n_w
+    W_cap = ((n_w + 63) // 32) * 32
+    q, k, v = synth.gen_layer_numpy(970 + G, 0, B, Hkv * G, Hkv, T + 1)
+    _, _, _, rc, gc, shape, cfg = make_pair(B, Hkv * G, Hkv, T, W, kb, vb, T_cap=32 * tiles + 64, W_cap=W_cap,
+                                            q_k_v=(q, k[:, :, :T], v[:, :, :T]))
+    for side in (gc.k_win, gc.v_win):      # turn both rings by one tile
+        w = side.view(torch.int16).view(shape.units, W_cap, 128)
+        w.copy_(torch.roll(w, 32, dims=1))
+    gc.c.w0 = 32
+    st, want = rc.decode_attn(u16(q))
+    assert st == 0
+    assert_attn_close(run_attn(gc, shape, cfg, q, n_splits=n_splits), want, "plain", tight=True)
+    if rc.n_w + 1 == W + 32 and kb != 16:
+        return
+    assert rc.append(u16(k[:, :, T]), u16(v[:, :, T])) == 0
+    st, want = rc.decode_attn(u16(q))
+    qt = torch.from_numpy(q).cuda()
+    out = torch.zeros_like(qt)
+    ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
+    kv.decode_step(shape, cfg, torch.from_numpy(k[:, :, T].copy()).cuda(), torch.from_numpy(v[:, :, T].copy()).cuda(), qt, gc, out, ws, n_splits=n_splits)
+    torch.cuda.synchronize()
+    assert_attn_close(t16(out), want, "step", tight=True)
+    slot = (32 + rc.n_w - 1) % W_cap
+    for side, src in ((gc.k_win, k), (gc.v_win, v)):
+        row = side.view(torch.int16).view(B, Hkv, W_cap, 128)[:, :, slot].cpu().numpy().view(np.uint16)
+        assert np.array_equal(row, u16(src[:, :, T])), "appended row"

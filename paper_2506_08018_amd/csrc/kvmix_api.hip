@@ -284,9 +284,27 @@ Fronts fronts_of(const kvmix_layer_cache* c, int n_w) {
 // (16 tiles: 12.5 us against 12.2; 9 tiles: 7.0 against 6.9).
 // 8 heads with 3- or 4-bit Values do not fit the 128 registers of the 8-wave form (spilling: 93 us where 12 waves take 62).
 int attn_waves(long long workgroups, int n_tiles, int n_splits, int G, int v_bits) {
-  if (G >= 8 && (v_bits == 3 || v_bits == 4)) return 12;
+  if (G > 8) return 8;
+  if (G == 8 && (v_bits == 3 || v_bits == 4)) return 12;
   const int cus = num_cus();
   return workgroups > (cus > 0 ? cus : 256) || n_tiles <= 20 * n_splits ? 8 : 12;
+}
+
+// Split count of a launch in blocks of 16 heads, at least 6 tiles per split: the smallest modelled time, in units of the 0.19 us that
+// a tile takes a workgroup with a compute unit to itself. A launch takes about 21 of them besides its tiles, 26 more for merging splits and 1.2 per
+// split; workgroups that share a compute unit share its rate. Fitted to 1 x 72 heads over 8000 tokens (1, 4, 8, 16, 32 splits:
+// 49.9, 20.7, 15.1, 14.0, 16.1 us), 16 x 48 over 4000 (4, 5, 6, 8: 16.9, 16.0, 20.6, 19.6 us), 32 x 72 over 4000 (1, 2, 3, 4:
+// 27.5, 30.1, 27.0, 32.1 us) and 4 x 16 over 1000 (1, 2, 5: 10.7, 12.8, 11.3 us).
+int wide_splits(int workgroups, int n_items, int s_max) {
+  const int cus = num_cus();
+  int best_s = 1;
+  double best = 0.0;
+  for (int s = 1; s == 1 || (s <= s_max && s * 6 <= n_items); s++) {
+    const double sharing = cus > 0 ? (double)(((long long)workgroups * s + cus - 1) / cus) : 1.0;
+    const double cost = (s == 1 ? 21.0 : 47.0) + sharing * n_items / s + 1.2 * s;
+    if (s == 1 || cost < best) { best = cost; best_s = s; }
+  }
+  return best_s;
 }
 
 // Validates an attention call against the cache state `c` (window count n_w) and fills the launch descriptor;
@@ -306,7 +324,8 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   const Fronts fr = fronts_of(c, n_w);
   const int n_items = c->W_cap / kTile + fr.packed_tiles;
   if (n_splits < 0 || n_splits > max_splits(sh)) return KVMIX_ERR_BAD_SHAPE;
-  if (n_splits == 0) {
+  const bool any_splits = n_splits == 0;
+  if (any_splits) {
     // One workgroup occupies a whole compute unit (LDS), so the launch runs in rounds of `cus` workgroups. A round
     // costs a fixed part (start, merge of the waves, partial and arrival: about what 48 tiles take) plus the tiles
     // of one split; take the split count with the smallest rounds x (48 + tiles per split), at least 8 tiles each.
@@ -328,6 +347,16 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     if (unsplit <= 1.06 * best) n_splits = 1;
   }
   if (n_splits > n_items) n_splits = n_items;
+  if (any_splits && G > 8) {
+    // Groups of 16 heads and more run other workgroups than the count above assumes (blocks of 16 heads). The count above is what a
+    // workspace is refused or accepted by; one that also holds the partials of the count that suits these workgroups gets that one.
+    const int n = wide_splits(units * attn_head_blocks(G), n_items, max_splits(sh));
+    const int n_parts = n + (fr.mixed ? 1 : 0);
+    const bool fits = n_parts == 1 || (workspace && aligned16(workspace) && workspace_bytes >= split_workspace_bytes(units, n_parts, G));
+    const int old_parts = n_splits + (fr.mixed ? 1 : 0);
+    const bool old_fits = old_parts == 1 || (workspace && aligned16(workspace) && workspace_bytes >= split_workspace_bytes(units, old_parts, G));
+    if (fits && old_fits) n_splits = n;
+  }
   AttnArgs a{};
   const int n_parts = n_splits + (fr.mixed ? 1 : 0);
   if (n_parts > 1) {
@@ -341,7 +370,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   // (8 units x 32 splits, whose 256 arrivals queued up on one line for 1.3 us on average: see kvmix_attn.hip)
   a.counter_stride = 1;
   while (a.counter_stride * 2 * out_units(sh) <= 64) a.counter_stride *= 2;
-  a.q = q; a.out = out;
+  a.q = q; a.out = out; a.G = G;
   a.packed = c->packed;
   a.k_win = c->k_win; a.v_win = c->v_win;
   a.k_new = k_new; a.v_new = v_new; a.k_win_w = c->k_win; a.v_win_w = c->v_win; a.new_slot = new_slot;
@@ -371,7 +400,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     m.n_qk = c->n_q; m.n_qv = c->n_q + c->v_lead;
     m.t_begin = fr.packed_tiles * kTile; m.t_end = (int)fr.t_a;
     m.slot_begin = slot_of(c, m.t_begin);
-    m.G = G; m.G_main = G > 8 ? 8 : G;
+    m.G = G; m.G_main = G;
     m.scale_log2 = a.scale_log2;
     plan->m = m;
   }
@@ -449,12 +478,10 @@ int kvmix_decode_attn_static(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, 
   if (!aligned16(q) || !aligned16(out)) return KVMIX_ERR_ALIGN;
   if (!c) return KVMIX_ERR_NULL;
   AttnPlan plan;
-  // First pass with a workspace of "any size" at a dummy aligned address: settles the split count and runs
-  // every other check; the size that split count needs is then held against the array's fixed size.
-  int st = plan_attention(sh, cfg, q, c, c->n_w, nullptr, nullptr, -1, softmax_scale, out, reinterpret_cast<void*>(256), ~(size_t)0, n_splits, &plan);
+  // First pass with a workspace of the array's size at a dummy aligned address: settles the split count and runs every check.
+  int st = plan_attention(sh, cfg, q, c, c->n_w, nullptr, nullptr, -1, softmax_scale, out, reinterpret_cast<void*>(256), kScratchBytes, n_splits, &plan);
   if (st) return st;
   if (plan.a.n_parts > 1) {
-    if (split_workspace_bytes(plan.units, plan.a.n_parts, plan.G) > kScratchBytes) return KVMIX_ERR_WORKSPACE;
     void* ptr = nullptr;
     st = scratch_address(&ptr, (hipStream_t)stream);
     if (st) return st;

@@ -164,7 +164,7 @@ __device__ __forceinline__ u32x2_t buf_load8(rsrc_t r, uint32_t voff, uint32_t s
 // 16 bytes per lane from memory into LDS: lane l's go to dst + 16 l (dst: wave-uniform). Counted like a load, waited for
 // explicitly before the LDS is read.
 __device__ __forceinline__ void buf_load_to_lds16(rsrc_t r, uint32_t voff, uint32_t soff, void* dst) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)voff, (int)soff, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)voff, (int)soff, 0, kStreaming);
 }
 // Transposing read: of a group of 16 lanes, lane i passes the address of 4 halves of row i / 4 (columns 4 (i % 4) .. +3) and gets column i
 // of the four rows. Two of them, four rows (1 KiB) apart: 8 consecutive rows of the lane's column.
@@ -305,7 +305,9 @@ template <int G> struct Operand {
 // Groups of 8 heads: the 16 columns are all in use, and every lane folds the scales into its own operand instead (the
 // scales of the tile go through LDS, not the products: 2 bytes per position instead of 32): the two-address writes of the
 // products took half of the LDS time, which bound the loop.
-template <int G> constexpr bool kOwnOperand = G == 8;
+template <int G> constexpr bool kOwnOperand = G >= 8;
+// Groups of 16 heads and more run in blocks of 16, one head per column: see process_wide.
+template <int G> constexpr bool kWide = G == 16;
 template <int G> struct __attribute__((aligned(16))) WaveLds {
   static constexpr int kOpBytes = kOwnOperand<G> ? kD * 2 : Operand<G>::kBytes;
   struct Key {
@@ -317,8 +319,8 @@ template <int G> struct __attribute__((aligned(16))) WaveLds {
     // scores of the tile [row][token] (rows: head h hi 2h, lo 2h + 1). Pitch 144 B: the rows are written 16 bytes per lane by
     // the 16 columns at once, and with a pitch of 128 B all rows would start in the same banks (measured: the two
     // stores of a tile took as long as all its other LDS traffic)
-    float s[2 * G][kTile + 4];
-    char pq[Operand<G>::kStep];      // softmax numerators as two fp16 terms, an operand of 32 positions
+    float s[kWide<G> ? 1 : 2 * G][kTile + 4];
+    char pq[kWide<G> ? 16 : Operand<G>::kStep];      // softmax numerators as two fp16 terms, an operand of 32 positions
     uint16_t zv[4][kTile];           // Value zero-points [channel block][token]
   };
   union { Key k; Value v; };
@@ -347,13 +349,16 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // said to be uniform: what depends on it alone lives in scalar registers
   const int col = lane & 15, kq = lane >> 4;         // MFMA column / row index, k-quarter
   const int h = col & (G - 1);                       // head of the column (columns past the used ones repeat them)
-  const bool lo_part = col >= 8;
+  const bool lo_part = !kWide<G> && col >= 8;
   const bool col_valid = (col & 7) < G;              // the column's results are stored
   const int sp = blockIdx.x, u = blockIdx.y;
   // Query groups of more than 8 heads run as blocks of 8 heads in workgroups of their own (grid z): the blocks of
   // a unit read the same records and window rows at about the same time, so a tile comes from HBM once and from
   // the caches after that. uo numbers the (unit, head block) pairs: rows uo*8 .. uo*8+7 of q and out.
+  // Blocks of 16: the last one of a group may be partly empty; its idle columns repeat the group's last head.
   const int uo = u * (int)gridDim.z + (int)blockIdx.z;
+  const int head0 = kWide<G> ? (int)blockIdx.z * G : 0;              // first head of the block inside the unit's group
+  const int n_heads = kWide<G> ? (a.G - head0 < G ? a.G - head0 : G) : G;
   WaveLds<G>& L = s_wave[wave].x;
   uint16_t (&T)[kTile][kD] = s_wave[wave].t;
   const int row = 2 * h + (lo_part ? 1 : 0);         // score row of this lane's column
@@ -370,16 +375,18 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
 
   // ---- the query and the wave's first tile are requested before anything else is done.
   // Packed tiles are claimed from a workgroup counter; the first claims are static (wave order).
-  const uint16_t* qbase = a.q + (size_t)uo * (G * kD);   // heads of unit u = (b, j) are rows (b*Hkv + j)*G .. +G-1 of q and out
+  const size_t row0 = kWide<G> ? (size_t)u * a.G + head0 : (size_t)uo * G;      // first of the block's rows of q and out
+  const uint16_t* qbase = a.q + row0 * kD;   // heads of unit u = (b, j) are rows (b*Hkv + j)*G .. +G-1 of q and out
   half8_t qB[4];       // plain q as B operand: the column's head (hi and lo columns alike, zero in columns not in use)
-  uint32_t qraw[G];    // q of channels (2*lane, 2*lane+1) of every head
+  uint32_t qraw[G];    // q of channels (2*lane, 2*lane+1) of every head (not needed where the lanes make their own operands)
   // loaded by the hi columns in use only (a load's cost at the start of a launch is its active lanes), copied to the lo columns later
 #pragma unroll
   for (int ks = 0; ks < 4; ks++) {
     qB[ks] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
-    if (col < G) qB[ks] = *reinterpret_cast<const half8_t*>(qbase + col * kD + 32 * ks + 8 * kq);
+    if (col < G) qB[ks] = *reinterpret_cast<const half8_t*>(qbase + (col < n_heads ? col : n_heads - 1) * kD + 32 * ks + 8 * kq);
   }
   auto copy_q_to_lo = [&]() {
+    if constexpr (kWide<G>) return;
 #pragma unroll
     for (int ks = 0; ks < 4; ks++) {
       u32x4_t v = __builtin_bit_cast(u32x4_t, qB[ks]);
@@ -389,7 +396,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
   };
 #pragma unroll
-  for (int hh = 0; hh < G; hh++) qraw[hh] = reinterpret_cast<const uint32_t*>(qbase + hh * kD)[lane];
+  for (int hh = 0; hh < G; hh++) qraw[hh] = kOwnOperand<G> ? 0u : reinterpret_cast<const uint32_t*>(qbase + hh * kD)[lane];
 
   constexpr uint32_t kRecBytes = (uint32_t)(record_words(KB, VB) * 4);
   const rsrc_t up = make_rsrc(reinterpret_cast<const char*>(a.packed) + (size_t)u * a.tiles_cap * kRecBytes, (uint32_t)a.tiles_cap * kRecBytes);
@@ -562,10 +569,11 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       raise_reference(max8(x) * c_plain);
 #pragma unroll
       for (int e = 0; e < 8; e++) p[e] = fast_exp2(x[e] * c_plain - mref);
-      half8_t PB;
+      half8_t PB, PL;                                      // (blocks of 16: both parts in every column)
 #pragma unroll
-      for (int e = 0; e < 8; e++) PB[e] = split_part(p[e], lo_part);
+      for (int e = 0; e < 8; e++) { PB[e] = split_part(p[e], lo_part); if constexpr (kWide<G>) PL[e] = split_part(p[e], true); }
       accZ = mfma16(col >= 4 ? ones8 : zero8, PB, accZ);   // rows 4..15 accumulate the sum of numerators
+      if constexpr (kWide<G>) accZ = mfma16(col >= 4 ? ones8 : zero8, PL, accZ);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the Value rows are in the staging area
       if (has_new) append_stage(appended);
       wave_lds_fence();
@@ -576,6 +584,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       for (int m = 0; m < 8; m++) {
         const half8_t Avm = read_transposed(reinterpret_cast<const char*>(&T[0][0]), t_off ^ (m << 5));
         float4_t t = mfma16(Avm, PB, float4_t{0, 0, 0, 0});
+        if constexpr (kWide<G>) t = mfma16(Avm, PL, t);
         if constexpr (VB == 3) {   // the final 7/3 step factor of channels 10 / 21 applies to codes only
 #pragma unroll
           for (int r4 = 0; r4 < 4; r4++) {
@@ -728,6 +737,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   };
 
   auto process_large = [&](const Stage<KB, VB>& st) {
+    if constexpr (kWide<G>) return;
     // -- Key side. Cooperative operand preparation: lane owns channels 2*lane, 2*lane+1.
     {
       const half2_t s2 = as_half2(st.meta[0]);
@@ -878,8 +888,77 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
     wave_lds_fence();   // the next tile's operand writes come after these reads
   };
+  // Blocks of 16 heads (groups of 16 and more, multi-query attention): a column is a head, the hi and lo parts are two matrix instructions
+  // on the same accumulators. The scores come out with a lane holding 8 tokens of its head, which are the tokens
+  // of its operand for the Values: softmax, numerators and operands stay in the lane, only the tile's scales and minima
+  // go through LDS, and the codes are cut out once for 16 heads. Bound by instruction issue (about 200 vector and 38 matrix
+  // instructions per tile and wave); blocks of 8 took 1.8 times the cycles per head.
+  auto process_wide = [&](const Stage<KB, VB>& st) {
+    reinterpret_cast<uint32_t*>(L.k.op)[lane] = as_u32(as_half2(st.meta[0]) * half2_t{pre, pre});
+    reinterpret_cast<uint32_t*>(&L.k.zk[0])[lane] = st.meta[1];
+    wave_lds_fence();
+    float x[8];
+    {
+      const Codes<KB> kc(st.kc);
+      float4_t S[2] = {float4_t{0, 0, 0, 0}, float4_t{0, 0, 0, 0}}, Sz = {0, 0, 0, 0};
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) {
+        const half8_t z8 = *reinterpret_cast<const half8_t*>(&L.k.zk[32 * ks + 8 * kq]);
+        const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.k.op[64 * ks + 16 * kq]);
+        Sz = mfma16(z8, qB[ks], Sz);       // every A row is the zero-point vector
+        const half8_t hi = qB[ks] * s8, lo = __builtin_elementwise_fma(qB[ks], s8, -hi);
+#pragma unroll
+        for (int m = 0; m < 2; m++) {
+          const half8_t c = kc.lo(ks + 4 * m);
+          S[m] = mfma16(c, hi, S[m]);
+          S[m] = mfma16(c, lo, S[m]);
+        }
+      }
+      if constexpr (KB == 3) {   // tokens 10 and 21 of the group step by s*7/3
+        if (kq == 1) S[0][2] *= (7.0f / 3.0f);
+        if (kq == 2) S[1][1] *= (7.0f / 3.0f);
+      }
+      const float zt = Sz[0] * c_plain;
+#pragma unroll
+      for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) x[4 * m + r] = S[m][r];
+      raise_reference(max8(x) * c_code + zt);
+      const float off = zt - mref;
+#pragma unroll
+      for (int e = 0; e < 8; e++) x[e] = fast_exp2(x[e] * c_code + off);       // the numerators of tokens 8*kq + e
+    }
+    reinterpret_cast<uint32_t*>(L.v.op)[lane] = st.meta[2];
+    reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = st.meta[3];
+    wave_lds_fence();
+    half8_t P, R8;       // numerators as two fp16 terms: rounded to nearest, and the rest
+#pragma unroll
+    for (int e = 0; e < 8; e++) { P[e] = (half_t)x[e]; R8[e] = (half_t)(x[e] - (float)P[e]); }
+    // zero-point term: A rows 0..3 carry the zero-points of channel blocks 0..3, rows 4..15 are ones
+    // and accumulate the sum of the numerators
+    half8_t z8 = ones8;
+    if (col < 4) z8 = *reinterpret_cast<const half8_t*>(&L.v.zv[col][8 * kq]);
+    accZ = mfma16(z8, P, accZ);
+    accZ = mfma16(z8, R8, accZ);
+    const Codes<VB> vc(st.vc);
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+      const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.v.op[64 * g + 16 * kq]);
+      const half8_t hi = P * s8;
+      const half8_t lo = __builtin_elementwise_fma(R8, s8, __builtin_elementwise_fma(P, s8, -hi));
+#pragma unroll
+      for (int m = 2 * g; m < 2 * g + 2; m++) {
+        const half8_t c = vc.lo(m);
+        acc[m] = mfma16(c, hi, acc[m]);
+        acc[m] = mfma16(c, lo, acc[m]);
+      }
+    }
+    wave_lds_fence();   // the next tile's scales come after these reads
+  };
   auto process = [&](const Stage<KB, VB>& st) {
-    if constexpr (kSmall) process_small(st); else process_large(st);
+    if constexpr (kWide<G>) process_wide(st);
+    else if constexpr (kSmall) process_small(st);
+    else process_large(st);
   };
 
   if (has_packed) {
@@ -916,7 +995,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
 #pragma unroll
     for (int g = 0; g < 4; g++) zsum[g] = __shfl(accZ[g], col);
     lsum = __shfl(accZ[0], 16 + col);
-    lsum += ror8(lsum);
+    if constexpr (!kWide<G>) lsum += ror8(lsum);
   }
 #pragma unroll
   for (int m = 0; m < 8; m++) {
@@ -930,7 +1009,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         if (dd == 10 || dd == 21) v *= (7.0f / 3.0f);
       }
       v += zsum[m >> 1];
-      o4[r] = v + ror8(v);
+      o4[r] = kWide<G> ? v : v + ror8(v);
     }
     if (col < G) *reinterpret_cast<float4_t*>(&s_wave[wave].o[col][16 * m + 4 * kq]) = o4;   // channels 16m + 4kq .. +3
   }
@@ -951,7 +1030,12 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       O += s_wave[w].o[hh][d] * f;
     }
   };
-  uint16_t* outp = a.out + (size_t)uo * (G * kD);
+  uint16_t* outp = a.out + row0 * kD;
+  // partial of split s, head hh of the block (blocks of 16: [unit][split][head of the group])
+  const size_t part0 = kWide<G> ? (size_t)u * a.n_parts * a.G + head0 : (size_t)uo * a.n_parts * G;
+  const int part_step = kWide<G> ? a.G : G;
+  auto part_at = [&](int s, int hh) { return a.part + (part0 + (size_t)s * part_step + hh) * (kD + 2); };
+  const int n_out = n_heads * kD;
 
   if (a.n_parts == 1) {
     if constexpr (G <= 2) {
@@ -989,7 +1073,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       }
     } else {
       __syncthreads();
-      for (int idx = tid; idx < G * kD; idx += kThreads) {
+      for (int idx = tid; idx < n_out; idx += kThreads) {
         float M, Lsum, O;
         combine(idx, M, Lsum, O);
         outp[idx] = __builtin_bit_cast(uint16_t, (half_t)(O / Lsum));
@@ -999,12 +1083,12 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   }
 
   __syncthreads();
-  for (int idx = tid; idx < G * kD; idx += kThreads) {
+  for (int idx = tid; idx < n_out; idx += kThreads) {
     float M, Lsum, O;
     combine(idx, M, Lsum, O);
     // agent-scope stores: written through to the level all XCDs share (no cache-wide flush needed)
     const int hh = idx / kD, d = idx % kD;
-    float* pp = a.part + (((size_t)uo * a.n_parts + sp) * G + hh) * (kD + 2);
+    float* pp = part_at(sp, hh);
     if (d == 0) { st_agent(pp, M); st_agent(pp + 1, Lsum); }
     st_agent(pp + 2 + d, O);
   }
@@ -1021,10 +1105,10 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   }
   __syncthreads();
   if (!s_done) return;
-  for (int idx = tid; idx < G * kD; idx += kThreads) {
+  for (int idx = tid; idx < n_out; idx += kThreads) {
     const int hh = __builtin_amdgcn_readfirstlane(idx / kD), d = idx % kD;   // a wave's 64 outputs share the head
-    const float* base = a.part + ((size_t)uo * a.n_parts * G + hh) * (kD + 2);
-    const size_t stride = (size_t)G * (kD + 2);
+    const float* base = part_at(0, hh);
+    const size_t stride = (size_t)part_step * (kD + 2);
     // one pass, kMergeBatch partials per round trip: lane k requests reference and sum of the batch's k-th
     // partial, every lane its channel of each of them, all before the first use; the weights 2^(m_k - M) are
     // computed once per wave (lane k holds the k-th) and handed out as scalars
@@ -1066,6 +1150,9 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
     case 2: decode_attn_kernel<KB, VB, 2, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
     case 4: decode_attn_kernel<KB, VB, 4, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
     case 8: decode_attn_kernel<KB, VB, 8, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
+#if KVMIX_WAVES == 8
+    case 16: decode_attn_kernel<KB, VB, 16, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
+#endif
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1075,8 +1162,8 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
 
 template <>
 hipError_t launch_decode_attn<kNW>(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s) {
-  const int head_blocks = G > 8 ? G / 8 : 1;
-  if (G > 8) G = 8;
+  const int head_blocks = attn_head_blocks(G);
+  if (G > 8) G = 16;
   const dim3 grid(a.n_splits, units, head_blocks);
   switch (k_bits * 10 + v_bits) {
     case 11: return launch_g<1, 1>(a, G, grid, s);

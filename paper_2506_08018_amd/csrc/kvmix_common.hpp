@@ -134,6 +134,7 @@ struct AttnArgs {
   int n_parts;            // n_splits, plus one when an earlier launch left the partial of the tokens between two fronts
   uint32_t* counters;     // arrival counters (zero before and after every call), one per (unit, head block), counter_stride words apart
   int counter_stride;
+  int G;                  // query heads per kv head
   int tiles_cap, W_cap, n_w;
   int ring_tiles, w0_tile;       // W_cap / 32; ring tile that holds the oldest window token
   int n_splits;
@@ -155,7 +156,7 @@ struct MixedArgs {
   int n_qk, n_qv;          // the two fronts
   int t_begin, t_end;      // t_begin is a multiple of 32
   int slot_begin;          // ring slot of token t_begin
-  int G, G_main;           // query heads per kv head; heads per (unit, block) pair of the main kernel's partials (min(G, 8))
+  int G, G_main;           // query heads per kv head; heads per row of the main kernel's partials
   float scale_log2;
 };
 
@@ -167,7 +168,9 @@ hipError_t launch_mixed_fronts(const MixedArgs& a, int units, hipStream_t s);
 hipError_t launch_dequant(const DequantArgs& a, int units, hipStream_t s);
 hipError_t launch_append(const AppendArgs& a, hipStream_t s);
 hipError_t launch_stream_read(const void* buf, size_t bytes, int workgroups, int threads, uint32_t* sink, hipStream_t s);
-// WAVES: waves per workgroup, 8 or 12
+// Workgroups that share the heads of one unit: groups of 16 heads and more run in blocks of 16.
+constexpr int attn_head_blocks(int G) { return G > 8 ? (G + 15) / 16 : 1; }
+// WAVES: waves per workgroup, 8 or 12 (groups of 16 heads and more: 8)
 template <int WAVES>
 hipError_t launch_decode_attn(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s);
 template <> hipError_t launch_decode_attn<8>(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s);

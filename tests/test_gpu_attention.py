@@ -412,3 +412,26 @@ def test_wave_forms_and_window_shares(B, G, Hkv, kb, vb, tiles, W, n_w, n_splits
     for side, src in ((gc.k_win, k), (gc.v_win, v)):
         row = side.view(torch.int16).view(B, Hkv, W_cap, 128)[:, :, slot].cpu().numpy().view(np.uint16)
         assert np.array_equal(row, u16(src[:, :, T])), "appended row"
+
+
+@pytest.mark.parametrize("G,Hkv,kb,vb,tiles,n_w,n_splits", [
+    (16, 2, 2, 2, 9, 33, 1), (24, 1, 1, 3, 7, 40, 2), (40, 1, 4, 4, 3, 32, 0), (16, 1, 16, 16, 0, 75, 2), (512, 1, 3, 1, 2, 40, 0),
+])
+def test_blocks_of_sixteen_heads(G, Hkv, kb, vb, tiles, n_w, n_splits):
+    """Groups that fill blocks of 16 heads, end inside one, or need many; with a workspace and, where the call asks for or gets
+    one split, without."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case sixteen G={G} bits={kb}/{vb} tiles={tiles} splits={n_splits}", flush=True)
+    q, k, v, rc, gc, shape, cfg = make_pair(2, G * Hkv, Hkv, 32 * tiles + n_w, 32, kb, vb, seed=1040 + G)
+    st, want = rc.decode_attn(u16(q))
+    assert st == 0
+    assert_attn_close(run_attn(gc, shape, cfg, q, n_splits=n_splits), want, f"G={G}", tight=True)
+    qt = torch.from_numpy(q).cuda()
+    out = torch.zeros_like(qt)
+    kv.decode_attn(shape, cfg, qt, gc, out, None, n_splits=1)
+    torch.cuda.synchronize()
+    assert_attn_close(t16(out), want, f"G={G} no workspace", tight=True)
+    kv.decode_attn_static(shape, cfg, qt, gc, out, n_splits=n_splits)
+    torch.cuda.synchronize()
+    assert_attn_close(t16(out), want, f"G={G} static", tight=True)

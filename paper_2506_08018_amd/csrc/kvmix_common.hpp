@@ -103,6 +103,10 @@ struct QuantArgs {
   int tiles_cap;   // tiles per unit in the packed cache
   int tile0;       // first destination tile
   int Hkv;
+  // Input rows that stay in the window (an appending launch only): workgroups from n_tiles on copy input rows copy_row .. copy_row +
+  // n_copy - 1 to the ring slots (copy_slot + i) % W_cap, 32 rows each; none of them is a slot that the launch's tiles read
+  int n_tiles, n_copy, copy_row, copy_slot;
+  uint16_t* k_ring_w; uint16_t* v_ring_w;
   // Ageing with separate fronts (every row comes from the ring, row r of the launch is token 32*tile0 + r): the Key
   // side is written for the destination tiles [k_tile_a, k_tile_b) only, the Value side for the tokens
   // [v_tok_a, v_tok_b) only; everything else in the records is left as it is.
@@ -160,7 +164,8 @@ struct MixedArgs {
   float scale_log2;
 };
 
-hipError_t launch_quantize_pack(const QuantArgs& a, int k_bits, int v_bits,
+// over n_tiles tiles (and the window rows that a.n_copy names)
+hipError_t launch_quantize_pack(QuantArgs a, int k_bits, int v_bits,
                                 int n_tiles, int units, hipStream_t s);
 hipError_t launch_quantize_fronts(const QuantArgs& a, int k_bits, int v_bits,
                                   int n_tiles, int units, hipStream_t s);

@@ -164,11 +164,27 @@ __device__ __forceinline__ const uint16_t* ring_row(const uint16_t* ring, const 
 // only; the Value wave writes the codes and metadata of the tokens [v_tok_a, v_tok_b) only, merging them into
 // words that it shares with other tokens.
 template <int KB, int VB, bool PARTIAL>
-__global__ __launch_bounds__(128) void quantize_pack_kernel(QuantArgs a) {
+__global__ __launch_bounds__(128, 5) void quantize_pack_kernel(QuantArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int kq = lane >> 4, j = (lane >> 2) & 3, q = lane & 3;
   const int tile_in = blockIdx.x, jh = blockIdx.y, b = blockIdx.z;   // no integer division at the start of a short kernel
   const int u = b * a.Hkv + jh;
+  if constexpr (!PARTIAL) {
+    if (tile_in >= a.n_tiles) {       // window rows: one side per wave, 16 bytes per lane
+      const uint16_t* in = wave ? a.v + b * a.v_unit_b + jh * a.v_unit_h : a.k + b * a.k_unit_b + jh * a.k_unit_h;
+      uint16_t* ring = (wave ? a.v_ring_w : a.k_ring_w) + (size_t)u * a.W_cap * kD;
+      const int64_t tok = wave ? a.v_tok : a.k_tok;
+      const int i0 = (tile_in - a.n_tiles) * kTile + (lane >> 4), c = 8 * (lane & 15);
+      u32x4_t x[8];
+#pragma unroll
+      for (int n = 0; n < 8; n++)
+        if (i0 + 4 * n < a.n_copy) x[n] = *reinterpret_cast<const u32x4_t*>(in + (int64_t)(a.copy_row + i0 + 4 * n) * tok + c);
+#pragma unroll
+      for (int n = 0; n < 8; n++)
+        if (i0 + 4 * n < a.n_copy) *reinterpret_cast<u32x4_t*>(ring + (size_t)((a.copy_slot + i0 + 4 * n) % a.W_cap) * kD + c) = x[n];
+      return;
+    }
+  }
   if constexpr (PARTIAL) {
     const int tile_abs = a.tile0 + tile_in;
     if (wave == 0 && (tile_abs < a.k_tile_a || tile_abs >= a.k_tile_b)) return;   // wave-uniform; the waves never synchronize
@@ -414,7 +430,7 @@ hipError_t launch_qp(const QuantArgs& a, dim3 grid, hipStream_t s) {
 template <bool PARTIAL>
 hipError_t launch_bits(const QuantArgs& a, int k_bits, int v_bits, int n_tiles, int units, hipStream_t s) {
   if (n_tiles == 0 || units == 0) return hipSuccess;
-  const dim3 grid(n_tiles, a.Hkv, units / a.Hkv);
+  const dim3 grid(n_tiles + (PARTIAL ? 0 : (a.n_copy + kTile - 1) / kTile), a.Hkv, units / a.Hkv);
   switch (k_bits * 10 + v_bits) {
     case 11: return launch_qp<1, 1, PARTIAL>(a, grid, s);
     case 12: return launch_qp<1, 2, PARTIAL>(a, grid, s);
@@ -438,7 +454,8 @@ hipError_t launch_bits(const QuantArgs& a, int k_bits, int v_bits, int n_tiles, 
 
 }  // namespace
 
-hipError_t launch_quantize_pack(const QuantArgs& a, int k_bits, int v_bits, int n_tiles, int units, hipStream_t s) {
+hipError_t launch_quantize_pack(QuantArgs a, int k_bits, int v_bits, int n_tiles, int units, hipStream_t s) {
+  a.n_tiles = n_tiles;
   return launch_bits<false>(a, k_bits, v_bits, n_tiles, units, s);
 }
 

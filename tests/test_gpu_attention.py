@@ -435,3 +435,37 @@ def test_blocks_of_sixteen_heads(G, Hkv, kb, vb, tiles, n_w, n_splits):
     kv.decode_attn_static(shape, cfg, qt, gc, out, n_splits=n_splits)
     torch.cuda.synchronize()
     assert_attn_close(t16(out), want, f"G={G} static", tight=True)
+
+
+@pytest.mark.parametrize("W,W_cap,T0", [(32, 64, 0), (32, 64, 63), (32, 96, 37), (32, 128, 63), (64, 192, 64 + 31), (0, 32, 0), (0, 64, 31)])
+def test_chunk_copy_inside_the_quantizer_launch(W, W_cap, T0):
+    """Rows that stay in the window ride in the quantizer's launch where no row lands in a slot that is still to be read, and are
+    copied after it where one does: chunks around both cases, rings of different room, from empty and part-filled windows."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case chunk copy W={W} W_cap={W_cap} T0={T0}", flush=True)
+    B, Hkv, kb, vb = 2, 3, 3, 2
+    chunks = [100, 33, 1, 64, 31, 5, 130, 29, 3, 32, 2]
+    total = T0 + sum(chunks)
+    q, k, v = synth.gen_layer_numpy(1100 + T0, 0, B, Hkv, Hkv, total)
+    _, _, _, rc, gc, shape, cfg = make_pair(B, Hkv, Hkv, max(T0, 1), W, kb, vb, T_cap=(total + 63) // 32 * 32, W_cap=W_cap,
+                                            q_k_v=(q, k[:, :, :max(T0, 1)], v[:, :, :max(T0, 1)])) if T0 else (
+        None, None, None, *_empty_pair(B, Hkv, W, kb, vb, (total + 63) // 32 * 32, W_cap))
+    kt, vt = torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda()
+    t = T0
+    for n in chunks:
+        for i in range(n):
+            assert rc.append(u16(k[:, :, t + i]), u16(v[:, :, t + i])) == 0
+        kv.append_tokens(shape, cfg, kt[:, :, t:t + n], vt[:, :, t:t + n], gc)
+        t += n
+        assert (gc.n_q, gc.n_w, gc.w0) == (rc.n_q, rc.n_w, rc.w0)
+        torch.cuda.synchronize()
+        assert_cache_equal(rc, gc)
+        assert_windows_equal(rc, gc)
+
+
+def _empty_pair(B, Hkv, W, kb, vb, T_cap, W_cap):
+    import paper_2506_08018_amd as kv
+    from oracle.kvmix_ref import RefCache
+    shape, cfg = kv.Shape(B, Hkv, Hkv), kv.LayerCfg(kb, vb, W)
+    return RefCache(B, Hkv, Hkv, kb, vb, W, T_cap, W_cap), kv.LayerCache(shape, cfg, T_cap, W_cap), shape, cfg

@@ -91,12 +91,18 @@ def _check(status, where):
         raise KVMixError(status, where)
 
 
+_raw_stream = None      # torch's lookup of the current stream's handle, without a Stream object around it
+
+
 def _stream(stream=None):
     """hipStream_t of torch's current stream, or of the given torch stream / raw handle."""
     if stream is None:
+        global _raw_stream
         import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream if isinstance(stream, int) else stream.cuda_stream)
+        if _raw_stream is None:
+            _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda dev: torch.cuda.current_stream(dev).cuda_stream)
+        return _raw_stream(torch.cuda.current_device())
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def cache_bytes(shape, cfg, T_cap, W_cap):
@@ -172,9 +178,10 @@ def append(shape, cfg, k_new, v_new, cache):
 
 def append_tokens(shape, cfg, k_new, v_new, cache):
     """k_new, v_new: fp16 CUDA tensors [B][Hkv][n][128] (last dim contiguous, any strides otherwise)."""
-    assert k_new.element_size() == 2 and k_new.stride(3) == 1 and v_new.stride() == k_new.stride() and v_new.shape == k_new.shape
-    st = lib().kvmix_append_tokens(C.byref(shape), C.byref(cfg), k_new.data_ptr(), v_new.data_ptr(), k_new.stride(2),
-                                   k_new.stride(1), k_new.stride(0), k_new.shape[2], C.byref(cache.c), _stream())
+    strides, size = k_new.stride(), k_new.shape
+    assert k_new.element_size() == 2 and strides[3] == 1 and v_new.stride() == strides and v_new.shape == size
+    st = lib().kvmix_append_tokens(C.byref(shape), C.byref(cfg), k_new.data_ptr(), v_new.data_ptr(), strides[2],
+                                   strides[1], strides[0], size[2], C.byref(cache.c), _stream())
     _check(st, "kvmix_append_tokens")
 
 

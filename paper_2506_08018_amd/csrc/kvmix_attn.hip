@@ -410,7 +410,6 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   const bool early = wave >= n_win;
   // (written before the first load into LDS is issued: the compiler lets an LDS write wait for those)
   if (tid == 0) { s_next = p_begin + n_early; s_done = 0; }
-  const rsrc_t vring = make_rsrc(a.v_win + (size_t)u * a.W_cap * kD, (uint32_t)a.W_cap * (kD * 2));
   Stage<KB, VB> st;
   int it = p_end;
   uint32_t lane16 = 16u * lane;
@@ -451,11 +450,13 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     const int col = lane & 15, kq = lane >> 4;
     const int slot0 = win_slot(r);
     const int skip = win_new(slot0) ? new_tau : -1;             // not in the ring yet
+    // (a resource over the tile: a ring may be larger than 32-bit offsets reach)
+    const rsrc_t rows = make_rsrc(a.v_win + ((size_t)u * a.W_cap + slot0) * kD, kTile * kD * 2);
 #pragma unroll
     for (int j = 0; j < 8; j++) {
       const int tau = 4 * j + kq;
       const int tau_r = (r * kTile + tau < a.n_w && tau != skip) ? tau : 0;      // dead slots: the first row again (weight zero)
-      buf_load_to_lds16(vring, 256u * tau_r + 16u * (col ^ (2 * kq) ^ ((j & 2) ? 8 : 0)), 256u * slot0, &T[4 * j][0]);
+      buf_load_to_lds16(rows, 256u * tau_r + 16u * (col ^ (2 * kq) ^ ((j & 2) ? 8 : 0)), 0, &T[4 * j][0]);
     }
   };
   // the append itself, one row of each side, 16 lanes each: requested with the tile, then stored into the ring and (the

@@ -436,9 +436,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     for (int m = 0; m < 2; m++) {
       const int tau = 8 * (col >> 2) + 4 * m + (col & 3);   // row `col` of M-tile m
       // a slot past the live tokens is not read: its lanes take the tile's first row instead (live, and already on its
-      // way: a cache hit), whose products the softmax mask discards; no byte of a dead slot reaches the arithmetic
+      // way: a cache hit; k_new where the new token is that row), whose products the softmax mask discards
       const int tau_r = r * kTile + tau < a.n_w ? tau : 0;
-      const uint16_t* rowp = (has_new && tau == new_tau) ? kn : kw + (size_t)tau_r * kD;
+      const uint16_t* rowp = (has_new && tau_r == new_tau) ? kn : kw + (size_t)tau_r * kD;
 #pragma unroll
       for (int ks = 0; ks < 4; ks++) w.r[m][ks] = *reinterpret_cast<const half8_t*>(rowp + 32 * ks + 8 * kq);
     }
@@ -449,15 +449,15 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   auto win_load_v = [&](int r, int lane) {
     const int col = lane & 15, kq = lane >> 4;
     const int slot0 = win_slot(r);
-    const int skip = win_new(slot0) ? new_tau : -1;             // not in the ring yet
-    // (a resource over the tile: a ring may be larger than 32-bit offsets reach)
-    const rsrc_t rows = make_rsrc(a.v_win + ((size_t)u * a.W_cap + slot0) * kD, kTile * kD * 2);
+    // The resource spans the tile's rows that are live and in the ring (a new token is the last live row of its tile and not in
+    // the ring yet). Rows beyond it are not read: their lanes write zeros, which meet a weight of zero (a dead slot may hold infinities
+    // and NaN). A resource over the tile: a ring may be larger than 32-bit offsets reach.
+    const int live = a.n_w - r * kTile;
+    const int n_rows = win_new(slot0) ? new_tau : live < kTile ? live : kTile;
+    const rsrc_t rows = make_rsrc(a.v_win + ((size_t)u * a.W_cap + slot0) * kD, (uint32_t)n_rows * (kD * 2));
 #pragma unroll
-    for (int j = 0; j < 8; j++) {
-      const int tau = 4 * j + kq;
-      const int tau_r = (r * kTile + tau < a.n_w && tau != skip) ? tau : 0;      // dead slots: the first row again (weight zero)
-      buf_load_to_lds16(rows, 256u * tau_r + 16u * (col ^ (2 * kq) ^ ((j & 2) ? 8 : 0)), 0, &T[4 * j][0]);
-    }
+    for (int j = 0; j < 8; j++)
+      buf_load_to_lds16(rows, 256u * (4 * j + kq) + 16u * (col ^ (2 * kq) ^ ((j & 2) ? 8 : 0)), 0, &T[4 * j][0]);
   };
   // the append itself, one row of each side, 16 lanes each: requested with the tile, then stored into the ring and (the
   // Value row) into the staging area

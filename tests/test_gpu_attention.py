@@ -469,3 +469,35 @@ def _empty_pair(B, Hkv, W, kb, vb, T_cap, W_cap):
     from oracle.kvmix_ref import RefCache
     shape, cfg = kv.Shape(B, Hkv, Hkv), kv.LayerCfg(kb, vb, W)
     return RefCache(B, Hkv, Hkv, kb, vb, W, T_cap, W_cap), kv.LayerCache(shape, cfg, T_cap, W_cap), shape, cfg
+
+
+@pytest.mark.parametrize("G,Hkv,kb,vb,tiles,W,n_splits", [
+    (1, 2, 2, 2, 9, 64, 1), (2, 2, 3, 2, 9, 32, 2), (4, 2, 3, 4, 26, 64, 1), (8, 1, 2, 2, 5, 32, 1), (8, 1, 2, 3, 9, 32, 2),
+    (16, 1, 2, 2, 9, 32, 0), (40, 1, 3, 4, 4, 64, 1), (4, 2, 2, 2, 3, 0, 1), (1, 2, 16, 16, 0, 64, 1), (8, 2, 16, 16, 0, 416, 2),
+])
+def test_step_that_opens_a_window_tile(G, Hkv, kb, vb, tiles, W, n_splits):
+    """A fused step whose token is the first of its window tile, on rings whose slots outside the live tokens hold infinities and NaN:
+    no row of the new tile is in the ring yet. Then two more steps into the same tile."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case opens a tile G={G} bits={kb}/{vb} tiles={tiles} W={W} splits={n_splits}", flush=True)
+    B, T, W_cap, steps = 2, 32 * tiles + W, W + 64, 3
+    q, k, v = synth.gen_layer_numpy(1200 + G, 0, B, Hkv * G, Hkv, T + steps)
+    _, _, _, rc, gc, shape, cfg = make_pair(B, Hkv * G, Hkv, T, W, kb, vb, W_cap=W_cap, q_k_v=(q, k[:, :, :T], v[:, :, :T]))
+    assert (gc.n_w, gc.n_q) == (W, 32 * tiles)
+    ring_k, ring_v = (t.view(torch.float16).view(shape.units, W_cap, 128) for t in (gc.k_win, gc.v_win))
+    ring_k[:, W:] = float("nan")
+    ring_v[:, W:] = float("inf")
+    ring_v[:, W + 1::2] = float("nan")
+    qt = torch.from_numpy(q).cuda()
+    out = torch.zeros_like(qt)
+    ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
+    for s in range(steps):
+        kn, vn = k[:, :, T + s].copy(), v[:, :, T + s].copy()
+        assert rc.append(u16(kn), u16(vn)) == 0
+        st, want = rc.decode_attn(u16(q))
+        assert st == 0
+        kv.decode_step(shape, cfg, torch.from_numpy(kn).cuda(), torch.from_numpy(vn).cuda(), qt, gc, out, ws, n_splits=n_splits)
+        torch.cuda.synchronize()
+        assert_attn_close(t16(out), want, f"step {s}", tight=True)
+        assert_windows_equal(rc, gc)

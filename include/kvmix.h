@@ -171,7 +171,9 @@ int kvmix_cache_bytes(const kvmix_shape* shape, const kvmix_layer_cfg* cfg, int 
 
 /* Workspace needed by kvmix_decode_attn for any context up to T_max packed tokens (split
  * partials + arrival counters, and the partial of the tokens between the two fronts when v_lead != 0). The
- * workspace must be zero-filled once before first use; every call leaves the counters zero again. */
+ * workspace must be zero-filled once before first use; every call leaves the counters zero again. How many counters
+ * there are depends on the shape: a workspace that has served one shape is zero-filled again before it serves
+ * another (with more units its counters would lie where the first shape left partials). */
 int kvmix_workspace_bytes(const kvmix_shape* shape, int T_max, size_t* bytes);
 
 /* Part 1 (Sec. 3.2.2 steps 1-4, Sec. 3.4 item 1). Quantize n_tokens (multiple of 32) fp16
@@ -214,10 +216,10 @@ int kvmix_decode_attn(const kvmix_shape* shape, const kvmix_layer_cfg* cfg, cons
 
 /* kvmix_decode_attn for callers that cannot allocate or hand over a workspace (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): same arguments and result, but the split partials and
- * arrival counters live in a fixed array of KVMIX_STATIC_SCRATCH_BYTES that is part of the library's device
- * image (each GPU the library runs on holds its own copy until the process ends). The call allocates nothing.
- * It returns KVMIX_ERR_WORKSPACE when the (explicit or library-chosen) split count needs more than the array
- * holds: units * n_splits * G * 520 bytes + 4 bytes per unit rounded up to 256. The first call on a device looks
+ * arrival counters live in a fixed array that is part of the library's device image (each GPU the library runs on
+ * holds its own copy until the process ends). The call allocates nothing, and calls of different shapes may follow
+ * each other. It returns KVMIX_ERR_WORKSPACE when the (explicit or library-chosen) split count needs more than
+ * KVMIX_STATIC_SCRATCH_BYTES: units * n_splits * G * 520 bytes + 4 bytes per unit rounded up to 256. The first call on a device looks
  * up the array's address and clears its counters on `stream`; make that call with the device current and outside
  * any graph capture. All calls on one GPU share the array: calls that overlap in time on one GPU (different
  * streams) race; calls on one stream, or otherwise ordered, are safe. */

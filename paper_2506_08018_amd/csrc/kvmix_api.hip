@@ -427,9 +427,14 @@ int launch_plan(const AttnPlan& p, void* stream) {
   return e == hipSuccess ? KVMIX_OK : hip_fail(e);
 }
 
-// ---- split workspace of kvmix_decode_attn_static: a fixed array in device memory, one copy per GPU
+// ---- split workspace of kvmix_decode_attn_static: a fixed array in device memory, one copy per GPU. Its arrival counters have a
+// place of their own, the same for every shape: calls of different shapes follow each other without the array being cleared, and a counter
+// must never lie where another shape leaves partials. A split call has at least two partials of 520 bytes per head, so that what
+// fits kScratchBytes has no more than this many counters (at most one per head).
 constexpr size_t kScratchBytes = KVMIX_STATIC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kScratchCounterBytes = 16384;
+static_assert(kScratchCounterBytes / sizeof(uint32_t) >= kScratchBytes / (2 * (kD + 2) * sizeof(float)), "counters of every shape that fits");
+static __device__ __align__(256) unsigned char scratch[kScratchCounterBytes + kScratchBytes];
 // In host code the array's name is only a handle; its address on a device comes from hipGetSymbolAddress,
 // asked once per device with that device current. Each GPU holds its own copy at its own address.
 std::mutex g_scratch_mutex;
@@ -440,9 +445,9 @@ __global__ void clear_words_kernel(uint32_t* p, int n) {
   if (i < n) p[i] = 0u;
 }
 
-// Address of the current device's copy of `scratch`. The first call on a device also clears the array (the
-// arrival counters sit at its start) on `stream`, ahead of the first launch that uses it; afterwards every
-// attention launch leaves the counters zero again.
+// Address of the current device's copy of `scratch`. The first call on a device also clears the arrival counters
+// at its start on `stream`, ahead of the first launch that uses them; afterwards every attention launch leaves them
+// zero again.
 int scratch_address(void** ptr, hipStream_t stream) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -454,7 +459,7 @@ int scratch_address(void** ptr, hipStream_t stream) {
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return hip_fail(e);
     if (!p) return hip_fail(hipErrorInvalidSymbol);
-    constexpr int kWords = (int)(kScratchBytes / 4);       // the whole array: the counters sit at its start, however many
+    constexpr int kWords = (int)(kScratchCounterBytes / 4);
     clear_words_kernel<<<kWords / 256, 256, 0, stream>>>(reinterpret_cast<uint32_t*>(p), kWords);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e);
@@ -496,7 +501,7 @@ int kvmix_decode_attn_static(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, 
     st = scratch_address(&ptr, (hipStream_t)stream);
     if (st) return st;
     plan.a.counters = reinterpret_cast<uint32_t*>(ptr);
-    plan.a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ptr) + counters_bytes(plan.units * (plan.G > 8 ? plan.G / 8 : 1)));
+    plan.a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ptr) + kScratchCounterBytes);
     plan.m.part = plan.a.part;
   } else {
     plan.a.counters = nullptr; plan.a.part = nullptr;

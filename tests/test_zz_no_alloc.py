@@ -48,3 +48,17 @@ def test_static_scratch_rejects_oversized_requests():
         kv.decode_attn_static(shape, cfg, q, gc, out, n_splits=8)
     assert e.value.status == -6
     assert not out.any()
+
+
+def test_static_scratch_across_shapes():
+    """Calls of different shapes in turn: the arrival counters of a shape with many units do not lie where a shape with few of
+    them leaves its partials."""
+    # (units, G, splits): 4 units with partials, 128 units, 4 again, blocks of heads on 27 units, 300 units, 2 units
+    for (B, Hkv, G, T, ns) in [(2, 2, 4, 32 * 20 + 5, 8), (16, 8, 1, 32 * 9 + 5, 2), (2, 2, 4, 32 * 20 + 5, 8), (27, 1, 48, 32 * 6 + 3, 2),
+                               (75, 4, 2, 32 * 4 + 40, 3), (1, 2, 1, 32 * 30, 16)]:
+        print(f"case static scratch across shapes units={B * Hkv} G={G} splits={ns}", flush=True)
+        q, k, v, rc, gc, shape, cfg = make_pair(B, Hkv * G, Hkv, T, 32, 2, 2, seed=990 + B)
+        st, want = rc.decode_attn(u16(q))
+        assert st == 0
+        for call in range(2):
+            assert_attn_close(run_static(gc, shape, cfg, q, ns), want, f"units={B * Hkv} G={G} splits={ns} call {call}", tight=True)

@@ -104,6 +104,13 @@ def assert_attn_close(got_bits, want_bits, what="", tight=False, tight_abs=None)
     return err.max(), rel.max()
 
 
+def counters_of(ws, shape):
+    """The bytes at the start of an attention workspace that hold the arrival counters: 4 per (unit, 8 query heads) in whole 256s. A
+    launch with few of them spreads them over all of these bytes."""
+    n = 4 * shape.units * max(1, shape.Hq // shape.Hkv // 8)
+    return ws[: (n + 255) // 256 * 256]
+
+
 def run_attn(gc, shape, cfg, q, n_splits=0, softmax_scale=0.0):
     import torch
     import paper_2506_08018_amd as kv
@@ -112,5 +119,5 @@ def run_attn(gc, shape, cfg, q, n_splits=0, softmax_scale=0.0):
     ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
     kv.decode_attn(shape, cfg, qt, gc, out, ws, softmax_scale=softmax_scale, n_splits=n_splits)
     torch.cuda.synchronize()
-    assert not ws[: 4 * shape.units * max(1, shape.Hq // shape.Hkv // 8)].any(), "arrival counters not reset"
+    assert not counters_of(ws, shape).any(), "arrival counters not reset"
     return t16(out)

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import kvmix_synth as synth
-from gpu_common import assert_attn_close, assert_cache_equal, assert_windows_equal, bits_of, make_pair, run_attn, t16, u16
+from gpu_common import assert_attn_close, assert_cache_equal, assert_windows_equal, bits_of, counters_of, make_pair, run_attn, t16, u16
 
 pytestmark = pytest.mark.gpu
 
@@ -227,7 +227,7 @@ def test_decode_step_equals_append_then_attention(kb, vb, G, n_splits):
         torch.cuda.synchronize()
         assert (gc.n_q, gc.n_w, gc.w0) == (rc.n_q, rc.n_w, rc.w0)
         assert_attn_close(t16(out), want, f"decode_step {s} (n_q {gc.n_q}, n_w {gc.n_w})", tight=True)
-    assert not ws[: 4 * shape.units].any()
+    assert not counters_of(ws, shape).any()
     if kb != 16:
         assert_cache_equal(rc, gc)
     assert_windows_equal(rc, gc)
@@ -259,7 +259,7 @@ def test_multi_query_and_large_groups(Hq, Hkv, kb, vb, n_splits):
         kv.decode_step(shape, cfg, torch.from_numpy(kn[:, :, s].copy()).cuda(), torch.from_numpy(vn[:, :, s].copy()).cuda(), qt, gc, out, ws, n_splits=n_splits)
         torch.cuda.synchronize()
         assert_attn_close(t16(out), want, f"Hq={Hq} Hkv={Hkv} step {s}", tight=True)
-    assert not ws[: 4 * shape.units * max(1, Hq // Hkv // 8)].any()
+    assert not counters_of(ws, shape).any()
 
 
 def test_decode_steps_with_window_length_zero():
@@ -367,7 +367,7 @@ def test_graph_replays_match_eager(n_splits):
         assert_attn_close(t16(out_g), t16(out_e), f"graph replay {rep} vs eager", tight=True)
         st, want = rc.decode_attn(u16(qn))
         assert_attn_close(t16(out_g), want, f"graph replay {rep}", tight=True)
-        assert not ws[: 4 * shape.units].any()
+        assert not counters_of(ws, shape).any()
 
 
 @pytest.mark.parametrize("B,G,Hkv,kb,vb,tiles,W,n_w,n_splits", [

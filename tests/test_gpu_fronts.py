@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import kvmix_synth as synth
-from gpu_common import assert_attn_close, assert_windows_equal, bits_of, t16, u16
+from gpu_common import assert_attn_close, assert_windows_equal, bits_of, counters_of, t16, u16
 from oracle import kvmix_ref as ref
 from oracle.kvmix_ref import RefCache
 
@@ -46,7 +46,7 @@ def attn_both(rc, gc, shape, cfg, q, n_splits=0, static=False, what=""):
         ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
         kv.decode_attn(shape, cfg, qt, gc, out, ws, n_splits=n_splits)
         torch.cuda.synchronize()
-        assert not ws[: 4 * shape.units * max(1, shape.Hq // shape.Hkv // 8)].any(), "arrival counters not reset"
+        assert not counters_of(ws, shape).any(), "arrival counters not reset"
     torch.cuda.synchronize()
     assert_attn_close(t16(out), want, what, tight=True)
 
@@ -177,7 +177,7 @@ def test_decode_loop_under_the_count_formula(kb, vb, G, r_k, r_v):
         assert_same_state(rc, gc, f"after step {s}")
     assert_windows_equal(rc, gc)
     assert seen_unfused > 0          # steps on which the new token shared its tile with the younger front
-    assert not ws[: 4 * shape.units].any()
+    assert not counters_of(ws, shape).any()
 
 
 def test_fronts_error_returns():

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import kvmix_synth as synth
-from gpu_common import assert_attn_close, bits_of, t16, u16
+from gpu_common import assert_attn_close, bits_of, counters_of, t16, u16
 
 pytestmark = pytest.mark.gpu
 
@@ -34,7 +34,7 @@ def test_full_size_sampled_units(name, n_sample):
         out = torch.zeros_like(q)
         kv.decode_attn(shape, cfg, q, gc, out, ws)
         torch.cuda.synchronize()
-        assert not ws[: 4 * shape.units].any()
+        assert not counters_of(ws, shape).any()
         units = rng.choice(B * Hkv, min(n_sample, B * Hkv), replace=False)
         tiles = n_q // 32
         records = gc.packed.view(torch.int32).view(B * Hkv, tiles, -1)
@@ -101,7 +101,7 @@ def test_full_size_fused_steps(name, kb, vb, layer, steps):
             assert_attn_close(t16(out[b, j * G:(j + 1) * G]).reshape(1, G, 128), want, f"{name} fused step {s} unit {(b, j)}", tight=True,
                               tight_abs=2.5e-4)
     assert gc.n_q == n_q0 + 32     # the flush happened inside the run
-    assert not ws[: 4 * shape.units].any()
+    assert not counters_of(ws, shape).any()
     tiles = (T + synth.GEN_ROOM) // 32
     records = gc.packed.view(torch.int32).view(B * Hkv, tiles, -1)
     for (b, j, ku, vu, rc), u in zip(refs, units):                                   # the flushed tile, bit for bit

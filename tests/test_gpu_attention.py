@@ -379,6 +379,9 @@ def test_graph_replays_match_eager(n_splits):
     (1, 2, 2, 2, 2, 3, 288, 300, 4),      # 10 window tiles over 4 splits, fewer packed tiles than splits
     (1, 8, 1, 2, 2, 2, 448, 460, 1),      # 15 window tiles: two rounds of window tiles for some waves
     (2, 4, 2, 16, 16, 0, 32, 835, 3),     # 27 window tiles, 9 per split, nothing packed ever
+    (1, 4, 1, 16, 16, 0, 32, 1207, 1),    # 38 window tiles for 12 waves: up to four rounds
+    (1, 1, 2, 2, 2, 9, 448, 460, 1),      # 15 window tiles for 12 waves, packed tiles after them
+    (1, 8, 1, 3, 4, 9, 448, 460, 1),
 ])
 def test_wave_forms_and_window_shares(B, G, Hkv, kb, vb, tiles, W, n_w, n_splits):
     """Both workgroup forms of the attention kernel and the window tiles' distribution over splits and waves, on a ring that starts at
@@ -501,3 +504,44 @@ def test_step_that_opens_a_window_tile(G, Hkv, kb, vb, tiles, W, n_splits):
         torch.cuda.synchronize()
         assert_attn_close(t16(out), want, f"step {s}", tight=True)
         assert_windows_equal(rc, gc)
+
+
+@pytest.mark.parametrize("B,Hkv,G,tiles,refused_below,split_from", [
+    (25, 4, 16, 61, 1, 5),       # 100 units: unsplit by the count that a workspace is held against, 5 splits where there is room
+    (1, 1, 72, 37, 5, 6),        # 5 splits by the one, 6 by the other
+    (1, 1, 72, 35, 4, 1),        # 4 splits by the one, none by the other
+])
+def test_workspaces_of_blocks_of_sixteen_heads(B, Hkv, G, tiles, refused_below, split_from):
+    """Split count left to the library, groups of 16 heads and more: a workspace is refused or accepted by one count (partials for
+    `refused_below` splits) and used for another one (`split_from`) only where it holds that one's partials as well."""
+    import torch
+    import paper_2506_08018_amd as kv
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the expected counts are those of 256 compute units")
+    print(f"case wide workspaces units={B * Hkv} G={G} tiles={tiles}", flush=True)
+    q, k, v, rc, gc, shape, cfg = make_pair(B, Hkv * G, Hkv, 32 * tiles + 40, 32, 2, 2, seed=1300 + tiles)
+    assert (gc.n_q, gc.n_w, gc.W_cap) == (32 * tiles, 40, 96)
+    st, want = rc.decode_attn(u16(q))
+    assert st == 0
+    qt = torch.from_numpy(q).cuda()
+    head = counters_of(torch.zeros(1 << 16, dtype=torch.uint8), shape).numel()
+    need = lambda parts: head + shape.units * parts * G * 130 * 4
+    for parts in range(0, max(refused_below, split_from) + 2):
+        for short in (0, 4):
+            size = max(0, need(parts) - short) if parts else 0
+            ws = torch.zeros(size, dtype=torch.uint8, device="cuda") if size else None
+            out = torch.zeros_like(qt)
+            holds = 0 if not parts else parts - (short > 0)
+            if refused_below > 1 and holds < refused_below:
+                with pytest.raises(kv.KVMixError) as e:
+                    kv.decode_attn(shape, cfg, qt, gc, out, ws)
+                assert e.value.status == (-6 if size else -1)
+                continue
+            kv.decode_attn(shape, cfg, qt, gc, out, ws)
+            torch.cuda.synchronize()
+            assert_attn_close(t16(out), want, f"workspace of {holds} partials", tight=True)
+            if size:
+                assert not counters_of(ws, shape).any()
+                used = split_from if holds >= split_from else refused_below       # splits whose partials are found in the workspace
+                written = ws[head:].view(torch.int32)[: holds * shape.units * G * 130].view(-1, 130).any(dim=1)
+                assert int(written.sum()) == (shape.units * used * G if used > 1 else 0), f"workspace of {holds} partials"

@@ -110,7 +110,7 @@ STATES = [      # (tokens, [(keep_k, keep_v) flushes in order]): what the fronts
 ]
 
 
-@pytest.mark.parametrize("G", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("G", [1, 2, 4, 8, 16, 24, 72])      # 24, 72: the last block of 16 heads is half full
 @pytest.mark.parametrize("state", range(len(STATES)))
 def test_attention_with_fronts_apart(G, state):
     import torch

@@ -286,8 +286,11 @@ __device__ __forceinline__ float hi_half(uint32_t v) { return (float)__builtin_b
 // the heads, rows G .. 2G-1 the lo parts (an immediate offset apart, so that one two-address LDS write stores both). The head's place is
 // XORed with P % 4 from 4 heads on: the 4 bytes per lane of a write then fall into distinct banks, and so do the 16 bytes
 // per lane of a read (measured: 4.5 cycles per read of 1 KiB, 8.4 with operand rows 272 bytes apart; with 4 or 8 heads the
-// exchange area was what bound the packed loop). Columns past the used ones repeat those of the heads h % G, and nothing they
-// compute is stored.
+// exchange area was what bound the packed loop).
+// Up to 4 heads leave columns idle; nothing they compute is stored. Their lanes read 16 bytes of zeros that every step has at the same
+// offset from its start: with the heads' operands repeated in them instead the matrix core takes more power and the clock goes down in
+// a run of launches (4 heads: 2.13 GHz, 2.23 with zeros; 1 head: 2.21, 2.28). 8 layers of 128 units x 8200 tokens, 4 heads: 208.5 us repeated,
+// 204.3 with zeros; 16 layers of 256 units x 4100 tokens, 1 head: 354.2, 351.9.
 // The Key side of a tile is done with its part before the Value side writes its own, so the two share memory (the
 // wave's LDS operations run in order; a fence between the steps pins the compiler): 16 waves per CU fit.
 // With 1 or 2 heads the few rows are kept whole, 320 bytes apart: the lanes of one row read the same 16 bytes, and a write is
@@ -296,11 +299,13 @@ template <int G> struct Operand {
   static constexpr bool kPieces = G >= 4;
   static constexpr int kPiece = kPieces ? 32 * G : 16;        // bytes from a row's 8 reduction positions to its next 8
   static constexpr int kRow = kPieces ? 16 : 320;             // bytes from a head to the next
-  static constexpr int kStep = 4 * kPiece;                    // bytes per ks (Keys) or channel block (Values)
+  static constexpr bool kIdle = G <= 4;                       // there are columns not in use
+  static constexpr int kStep = 4 * kPiece + (kPieces && kIdle ? 16 : 0);      // bytes per ks (Keys) or channel block (Values)
   static constexpr int kLo = kRow * G;                        // from a head's hi part to its lo part
-  static constexpr int kBytes = kPieces ? 4 * kStep : 2 * G * kRow;
+  static constexpr int kZeroAt = kPieces ? 4 * kPiece : 2 * G * kRow;         // the zeros of step 0: behind its pieces, or behind the rows
+  static constexpr int kBytes = kPieces ? 4 * kStep : 2 * G * kRow + 3 * kStep + 16;
   // byte offset of the 4 bytes (reduction positions 2l, 2l+1 of the whole operand) that lane l writes for head hh
-  static __device__ __forceinline__ int write_at(int l, int hh) { return (l >> 2) * kPiece + 4 * (l & 3) + kRow * (hh ^ (kPieces ? (l >> 2) & 3 : 0)); }
+  static __device__ __forceinline__ int write_at(int l, int hh) { return (l >> 4) * kStep + ((l >> 2) & 3) * kPiece + 4 * (l & 3) + kRow * (hh ^ (kPieces ? (l >> 2) & 3 : 0)); }
   // byte offset of the 16 bytes that a lane (column of head h, part) reads as k-quarter kq of step 0
   static __device__ __forceinline__ int read_at(int kq, int h, bool lo) { return kq * kPiece + kRow * (h ^ (kPieces ? kq : 0)) + (lo ? kLo : 0); }
 };
@@ -364,7 +369,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   WaveLds<G>& L = s_wave[wave].x;
   uint16_t (&T)[kTile][kD] = s_wave[wave].t;
   const int row = 2 * h + (lo_part ? 1 : 0);         // score row of this lane's column
-  const int op_read = Operand<G>::read_at(kq, h, lo_part);
+  const int op_read = Operand<G>::kIdle && !col_valid ? Operand<G>::kZeroAt : Operand<G>::read_at(kq, h, lo_part);
 
   // Work of this split: of the window's live tiles (numbered by age) those with index sp, sp + n_splits, ..., so
   // that every split carries its share of them, and a contiguous range of packed tiles. The first a.win_extra splits have one window tile more than the
@@ -630,7 +635,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     __builtin_amdgcn_sched_barrier(0);
     start_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (G > 2) copy_q_to_lo();      // (smaller groups use it for window tiles only)
+    if constexpr (kOwnOperand<G>) copy_q_to_lo();      // (smaller groups use the lo columns for window tiles only)
   }
 
   // ---- small query groups (G <= 2): the matrix core's columns are nearly empty, so the per-tile extras
@@ -979,6 +984,14 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   };
 
   if (has_packed) {
+    // the zeros of the idle columns (the wave's area held window rows up to here; nothing else is written to these places)
+    if constexpr (Operand<G>::kIdle) {
+      if (lane < 4) *reinterpret_cast<u32x4_t*>(&L.k.op[Operand<G>::kZeroAt + lane * Operand<G>::kStep]) = u32x4_t{0, 0, 0, 0};
+      if constexpr (Operand<G>::kPieces) {
+        if (lane == 4) *reinterpret_cast<u32x4_t*>(&L.v.pq[Operand<G>::kZeroAt]) = u32x4_t{0, 0, 0, 0};
+      }
+      wave_lds_fence();
+    }
     while (it < p_end) {
       const int ticket = grab_issue();
       process(st);

@@ -78,7 +78,7 @@ int check_cache(const kvmix_layer_cfg* cfg, const kvmix_layer_cache* c, bool nee
   return KVMIX_OK;
 }
 
-// (unit, block of at most 8 query heads) pairs: each is one workgroup per split
+// (unit, block of at most 8 query heads) pairs: each is one workgroup per split (blocks of 16 heads: at least half as many)
 int out_units(const kvmix_shape* sh) {
   const int G = sh->Hq / sh->Hkv;
   return sh->B * sh->Hkv * (G > 8 ? G / 8 : 1);
@@ -256,7 +256,7 @@ namespace {
 // Everything an attention launch needs, filled by plan_attention after all host-side checks have passed.
 // `mixed`: the fronts of Keys and Values differ; the tokens between them go to a launch of their own (m) that
 // leaves one more partial for the main launch's merge.
-struct AttnPlan { AttnArgs a; int kb, vb, G, units, waves; bool mixed; MixedArgs m; };
+struct AttnPlan { AttnArgs a; int kb, vb, G, block, units, waves; bool mixed; MixedArgs m; };
 
 constexpr int kWindowTileCost = 3;   // packed tiles that take a wave as long as one window tile
 
@@ -293,26 +293,40 @@ Fronts fronts_of(const kvmix_layer_cache* c, int n_w) {
 // units of 128 tiles: 22.2 us against 23.9; 32 tiles: 14.3 against 14.9), and cost in start and merge when there are few
 // (16 tiles: 12.5 us against 12.2; 9 tiles: 7.0 against 6.9).
 // 8 heads with 3- or 4-bit Values do not fit the 128 registers of the 8-wave form (spilling: 93 us where 12 waves take 62).
-int attn_waves(long long workgroups, int n_tiles, int n_splits, int G, int v_bits) {
-  if (G > 8) return 8;
-  if (G == 8 && (v_bits == 3 || v_bits == 4)) return 12;
+int attn_waves(long long workgroups, int n_tiles, int n_splits, int block, int v_bits) {
+  if (block > 8) return 8;
+  if (block == 8 && (v_bits == 3 || v_bits == 4)) return 12;
   const int cus = num_cus();
   return workgroups > (cus > 0 ? cus : 256) || n_tiles <= 20 * n_splits ? 8 : 12;
 }
 
-// Split count of a launch in blocks of 16 heads, at least 6 tiles per split: the smallest modelled time, in units of the 0.19 us that
-// a tile takes a workgroup with a compute unit to itself. A launch takes about 21 of them besides its tiles, 26 more for merging splits and 1.2 per
-// split; workgroups that share a compute unit share its rate. Fitted to 1 x 72 heads over 8000 tokens (1, 4, 8, 16, 32 splits:
-// 49.9, 20.7, 15.1, 14.0, 16.1 us), 16 x 48 over 4000 (4, 5, 6, 8: 16.9, 16.0, 20.6, 19.6 us), 32 x 72 over 4000 (1, 2, 3, 4:
-// 27.5, 30.1, 27.0, 32.1 us) and 4 x 16 over 1000 (1, 2, 5: 10.7, 12.8, 11.3 us).
-int wide_splits(int workgroups, int n_items, int s_max) {
-  const int cus = num_cus();
+// Groups of 16 heads and more run in blocks of 16 or of 8 heads. A block of 16 takes less work per head, a block of 8 has the shorter
+// chain per tile and half the outputs to combine and to merge. Modelled times of a launch, in units of the 0.19 us that a 2/2-bit tile takes a
+// workgroup of 16 heads with a compute unit to itself; fixed parts and merging splits besides the tiles. Blocks of 16: workgroups that share
+// a compute unit share its rate, and the second one starts late. A tile of 3/4 bit counts as 1.3 (8 x 48 heads over 8000 tokens: 17.5 us in
+// blocks of 8, 17.1 in blocks of 16; 2/2 bit 16.2, 16.4), a window tile as 2.4 (full precision, 32 x 48 over 2000: 26.1, 22.9; 8 x 72:
+// 15.0, 14.4; 8 x 48: 12.2, 14.6). Fitted to 1 x 72 heads over 8000 tokens (1, 4, 8, 16, 32 splits:
+// 51.8, 21.3, 15.7, 14.3, 16.4 us in blocks of 16; 40.6, 16.7, 12.9, 11.2, 15.2 in blocks of 8), 16 x 48 over 4000 (2, 4, 6, 8: 22.4, 16.9,
+// 20.6, 19.4), 32 x 48 over 2000 (1, 2, 4: 16.7, 16.3, 19.0; 14.6 in blocks of 8, unsplit), 1 x 16 over 64, 480 and 992 (unsplit: 5.8, 7.8,
+// 10.4; 4.8, 7.2, 9.7).
+double tile_work(int packed_tiles, int window_tiles, int k_bits, int v_bits) {
+  return packed_tiles * (1.0 + 0.1 * (k_bits + v_bits - 4)) + 2.4 * window_tiles;
+}
+double cost_of_16(double sharing, double work, int s) {
+  return s == 1 ? 24.0 + 0.98 * sharing * work : 47.0 + 12.0 * (sharing - 1.0) + sharing * work / s + 1.2 * s;
+}
+double cost_of_8(double work, int s) {      // one workgroup per compute unit
+  return s == 1 ? 24.5 + 0.755 * work : 40.0 + 0.725 * work / s + 0.62 * s;
+}
+double sharing_of(int workgroups, int s, int cus) { return (double)(((long long)workgroups * s + cus - 1) / cus); }
+// Split count of a launch in blocks of 16 heads, at least 6 tiles per split: the smallest modelled time, all tiles alike (weighted, 32 x 72
+// heads over 2000 full-precision tokens get 3 splits and take 27.6 us instead of 26.7)
+int wide_splits(int workgroups, int n_items, int s_max, int cus) {
   int best_s = 1;
   double best = 0.0;
   for (int s = 1; s == 1 || (s <= s_max && s * 6 <= n_items); s++) {
-    const double sharing = cus > 0 ? (double)(((long long)workgroups * s + cus - 1) / cus) : 1.0;
-    const double cost = (s == 1 ? 21.0 : 47.0) + sharing * n_items / s + 1.2 * s;
-    if (s == 1 || cost < best) { best = cost; best_s = s; }
+    const double c = cost_of_16(sharing_of(workgroups, s, cus), n_items, s);
+    if (s == 1 || c < best) { best = c; best_s = s; }
   }
   return best_s;
 }
@@ -336,9 +350,10 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   if (n_splits < 0 || n_splits > max_splits(sh)) return KVMIX_ERR_BAD_SHAPE;
   const bool any_splits = n_splits == 0;
   if (any_splits) {
-    // One workgroup occupies a whole compute unit (LDS), so the launch runs in rounds of `cus` workgroups. A round
-    // costs a fixed part (start, merge of the waves, partial and arrival: about what 48 tiles take) plus the tiles
-    // of one split; take the split count with the smallest rounds x (48 + tiles per split), at least 8 tiles each.
+    // The launch is taken to run in rounds of `cus` workgroups. A round costs a fixed part (start, merge of the waves,
+    // partial and arrival: about what 48 tiles take) plus the tiles of one split; take the split count with the
+    // smallest rounds x (48 + tiles per split), at least 8 tiles each. (Twice as many workgroups of 8 waves fit the card; the count is
+    // also what a workspace is refused or accepted by, and 128 units of 256 tiles take 24.4 us with 4 splits of 8 waves, 23.8 with 2 of 12.)
     const int cus = num_cus();
     if (cus == 0) return hip_fail(hipErrorInvalidDevice);
     const int ou = out_units(sh);
@@ -357,15 +372,24 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     if (unsplit <= 1.06 * best) n_splits = 1;
   }
   if (n_splits > n_items) n_splits = n_items;
-  if (any_splits && G > 8) {
-    // Groups of 16 heads and more run other workgroups than the count above assumes (blocks of 16 heads). The count above is what a
-    // workspace is refused or accepted by; one that also holds the partials of the count that suits these workgroups gets that one.
-    const int n = wide_splits(units * attn_head_blocks(G), n_items, max_splits(sh));
-    const int n_parts = n + (fr.mixed ? 1 : 0);
-    const bool fits = n_parts == 1 || (workspace && aligned16(workspace) && workspace_bytes >= split_workspace_bytes(units, n_parts, G));
-    const int old_parts = n_splits + (fr.mixed ? 1 : 0);
-    const bool old_fits = old_parts == 1 || (workspace && aligned16(workspace) && workspace_bytes >= split_workspace_bytes(units, old_parts, G));
-    if (fits && old_fits) n_splits = n;
+  int block = G;
+  if (G > 8) {
+    // Blocks of 8 heads where a launch of them has at most one workgroup per compute unit (see above: the faster ones at equal split
+    // counts), blocks of 16 otherwise.
+    const int cus = num_cus();
+    block = cus > 0 && (long long)out_units(sh) * n_splits <= cus ? 8 : 16;
+    if (any_splits) {
+      // The count above is that of blocks of 8, and it is what a workspace is refused or accepted by. A workspace that also holds the
+      // partials of the count that suits blocks of 16 gets those where they are modelled to be faster, or within 2 % (4 x 48 heads over
+      // 32 000 tokens, modelled alike: 23.3 us in blocks of 8, 21.9 in blocks of 16).
+      const double work = tile_work(fr.packed_tiles, (fr.n_w_eff + kTile - 1) / kTile, cfg->k_bits, cfg->v_bits);
+      const int wide = units * ((G + 15) / 16), n = wide_splits(wide, n_items, max_splits(sh), cus);
+      auto fits = [&](int splits) {
+        const int parts = splits + (fr.mixed ? 1 : 0);
+        return parts == 1 || (workspace && aligned16(workspace) && workspace_bytes >= split_workspace_bytes(units, parts, G));
+      };
+      if (fits(n) && fits(n_splits) && (block == 16 || cost_of_16(sharing_of(wide, n, cus), work, n) < 1.02 * cost_of_8(work, n_splits))) { n_splits = n; block = 16; }
+    }
   }
   AttnArgs a{};
   const int n_parts = n_splits + (fr.mixed ? 1 : 0);
@@ -377,7 +401,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + counters_bytes(out_units(sh)));
   }
   // The counters' 256 bytes (at least) are shared out evenly: splits that arrive together then meet on fewer cache lines
-  // (8 units x 32 splits, whose 256 arrivals queued up on one line for 1.3 us on average: see kvmix_attn.hip)
+  // (8 units x 32 splits, whose 256 arrivals queued up on one line for 1.3 us on average)
   a.counter_stride = 1;
   while (a.counter_stride * 2 * out_units(sh) <= 64) a.counter_stride *= 2;
   a.q = q; a.out = out; a.G = G;
@@ -398,7 +422,8 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   plan->kb = cfg->k_bits == 16 ? 2 : cfg->k_bits;
   plan->vb = cfg->v_bits == 16 ? 2 : cfg->v_bits;
   plan->G = G; plan->units = units;
-  plan->waves = attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, G, plan->vb);
+  plan->block = block;
+  plan->waves = attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, plan->block, plan->vb);
   plan->mixed = fr.mixed;
   if (fr.mixed) {
     // with the append inside the launch the new token must be a window token of the main launch
@@ -410,7 +435,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     m.n_qk = c->n_q; m.n_qv = c->n_q + c->v_lead;
     m.t_begin = fr.packed_tiles * kTile; m.t_end = (int)fr.t_a;
     m.slot_begin = slot_of(c, m.t_begin);
-    m.G = G; m.G_main = G;
+    m.G = G; m.G_main = block == 16 ? G : block;
     m.scale_log2 = a.scale_log2;
     plan->m = m;
   }
@@ -422,8 +447,8 @@ int launch_plan(const AttnPlan& p, void* stream) {
     const hipError_t e = launch_mixed_fronts(p.m, p.units, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e);
   }
-  const hipError_t e = p.waves == 8 ? launch_decode_attn<8>(p.a, p.kb, p.vb, p.G, p.units, (hipStream_t)stream)
-                                    : launch_decode_attn<12>(p.a, p.kb, p.vb, p.G, p.units, (hipStream_t)stream);
+  const hipError_t e = p.waves == 8 ? launch_decode_attn<8>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream)
+                                    : launch_decode_attn<12>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream);
   return e == hipSuccess ? KVMIX_OK : hip_fail(e);
 }
 

@@ -11,7 +11,7 @@
 // exact, and MFMA honours subnormal inputs (3-bit codes are a 2-bit plane plus a 1-bit plane). The scale factors ride in the B operand, split
 // into an fp16 (hi, lo) pair held in two MFMA columns so that the products stay exact to
 // ~22 bits; the up-to-8 query heads of the group use columns 0..7 (hi) and 8..15 (lo). Groups of 16 heads and more run in
-// blocks of 16, a head per column, with hi and lo as two instructions on the same accumulators.
+// blocks of 8, or in blocks of 16: a head per column, with hi and lo as two instructions on the same accumulators.
 // The fp16 window runs on MFMAs with plain fp16 operands; so do the zero-point sums for groups of
 // 4 query heads and more, while groups of 1 or 2 heads take them (and the softmax denominator) on the
 // vector unit, where they are cheaper than matrix instructions with mostly empty columns.
@@ -313,7 +313,7 @@ template <int G> struct Operand {
 // scales of the tile go through LDS, not the products: 2 bytes per position instead of 32): the two-address writes of the
 // products took half of the LDS time, which bound the loop.
 template <int G> constexpr bool kOwnOperand = G >= 8;
-// Groups of 16 heads and more run in blocks of 16, one head per column: see process_wide.
+// Blocks of 16 heads, one head per column: see process_wide.
 template <int G> constexpr bool kWide = G == 16;
 template <int G> struct __attribute__((aligned(16))) WaveLds {
   static constexpr int kOpBytes = kOwnOperand<G> ? kD * 2 : Operand<G>::kBytes;
@@ -359,9 +359,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   const bool lo_part = !kWide<G> && col >= 8;
   const bool col_valid = (col & 7) < G;              // the column's results are stored
   const int sp = blockIdx.x, u = blockIdx.y;
-  // Query groups of more than 8 heads run as blocks of 8 heads in workgroups of their own (grid z): the blocks of
-  // a unit read the same records and window rows at about the same time, so a tile comes from HBM once and from
-  // the caches after that. uo numbers the (unit, head block) pairs: rows uo*8 .. uo*8+7 of q and out.
+  // Query groups of more than 8 heads run as blocks of 8 or 16 heads in workgroups of their own (grid z): the blocks
+  // of a unit read the same records and window rows at about the same time, so a tile comes from HBM once and from
+  // the caches after that. uo numbers the (unit, head block) pairs; blocks of 8: rows uo*8 .. uo*8+7 of q and out.
   // Blocks of 16: the last one of a group may be partly empty; its idle columns repeat the group's last head.
   const int uo = u * (int)gridDim.z + (int)blockIdx.z;
   const int head0 = kWide<G> ? (int)blockIdx.z * G : 0;              // first head of the block inside the unit's group
@@ -1061,7 +1061,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
   };
   uint16_t* outp = a.out + row0 * kD;
-  // partial of split s, head hh of the block (blocks of 16: [unit][split][head of the group])
+  // partial of split s, head hh of the block: [unit][block][split][head of the block] (blocks of 16: [unit][split][head of the group])
   const size_t part0 = kWide<G> ? (size_t)u * a.n_parts * a.G + head0 : (size_t)uo * a.n_parts * G;
   const int part_step = kWide<G> ? a.G : G;
   auto part_at = [&](int s, int hh) { return a.part + (part0 + (size_t)s * part_step + hh) * (kD + 2); };
@@ -1191,27 +1191,25 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
 }  // namespace
 
 template <>
-hipError_t launch_decode_attn<kNW>(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s) {
-  const int head_blocks = attn_head_blocks(G);
-  if (G > 8) G = 16;
-  const dim3 grid(a.n_splits, units, head_blocks);
+hipError_t launch_decode_attn<kNW>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s) {
+  const dim3 grid(a.n_splits, units, (a.G + block - 1) / block);
   switch (k_bits * 10 + v_bits) {
-    case 11: return launch_g<1, 1>(a, G, grid, s);
-    case 12: return launch_g<1, 2>(a, G, grid, s);
-    case 13: return launch_g<1, 3>(a, G, grid, s);
-    case 14: return launch_g<1, 4>(a, G, grid, s);
-    case 21: return launch_g<2, 1>(a, G, grid, s);
-    case 31: return launch_g<3, 1>(a, G, grid, s);
-    case 41: return launch_g<4, 1>(a, G, grid, s);
-    case 22: return launch_g<2, 2>(a, G, grid, s);
-    case 23: return launch_g<2, 3>(a, G, grid, s);
-    case 24: return launch_g<2, 4>(a, G, grid, s);
-    case 32: return launch_g<3, 2>(a, G, grid, s);
-    case 33: return launch_g<3, 3>(a, G, grid, s);
-    case 34: return launch_g<3, 4>(a, G, grid, s);
-    case 42: return launch_g<4, 2>(a, G, grid, s);
-    case 43: return launch_g<4, 3>(a, G, grid, s);
-    case 44: return launch_g<4, 4>(a, G, grid, s);
+    case 11: return launch_g<1, 1>(a, block, grid, s);
+    case 12: return launch_g<1, 2>(a, block, grid, s);
+    case 13: return launch_g<1, 3>(a, block, grid, s);
+    case 14: return launch_g<1, 4>(a, block, grid, s);
+    case 21: return launch_g<2, 1>(a, block, grid, s);
+    case 31: return launch_g<3, 1>(a, block, grid, s);
+    case 41: return launch_g<4, 1>(a, block, grid, s);
+    case 22: return launch_g<2, 2>(a, block, grid, s);
+    case 23: return launch_g<2, 3>(a, block, grid, s);
+    case 24: return launch_g<2, 4>(a, block, grid, s);
+    case 32: return launch_g<3, 2>(a, block, grid, s);
+    case 33: return launch_g<3, 3>(a, block, grid, s);
+    case 34: return launch_g<3, 4>(a, block, grid, s);
+    case 42: return launch_g<4, 2>(a, block, grid, s);
+    case 43: return launch_g<4, 3>(a, block, grid, s);
+    case 44: return launch_g<4, 4>(a, block, grid, s);
   }
   return hipErrorInvalidValue;
 }

@@ -160,7 +160,7 @@ struct MixedArgs {
   int n_qk, n_qv;          // the two fronts
   int t_begin, t_end;      // t_begin is a multiple of 32
   int slot_begin;          // ring slot of token t_begin
-  int G, G_main;           // query heads per kv head; heads per row of the main kernel's partials
+  int G, G_main;           // query heads per kv head; heads that the main kernel's partials lie together for (G, or its block of 8)
   float scale_log2;
 };
 
@@ -173,12 +173,11 @@ hipError_t launch_mixed_fronts(const MixedArgs& a, int units, hipStream_t s);
 hipError_t launch_dequant(const DequantArgs& a, int units, hipStream_t s);
 hipError_t launch_append(const AppendArgs& a, hipStream_t s);
 hipError_t launch_stream_read(const void* buf, size_t bytes, int workgroups, int threads, uint32_t* sink, hipStream_t s);
-// Workgroups that share the heads of one unit: groups of 16 heads and more run in blocks of 16.
-constexpr int attn_head_blocks(int G) { return G > 8 ? (G + 15) / 16 : 1; }
-// WAVES: waves per workgroup, 8 or 12 (groups of 16 heads and more: 8)
+// WAVES: waves per workgroup, 8 or 12 (blocks of 16 heads: 8). block: query heads per workgroup (1, 2, 4, 8 or 16); a unit's group of
+// a.G heads takes (a.G + block - 1) / block workgroups per split.
 template <int WAVES>
-hipError_t launch_decode_attn(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s);
-template <> hipError_t launch_decode_attn<8>(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s);
-template <> hipError_t launch_decode_attn<12>(const AttnArgs& a, int k_bits, int v_bits, int G, int units, hipStream_t s);
+hipError_t launch_decode_attn(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
+template <> hipError_t launch_decode_attn<8>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
+template <> hipError_t launch_decode_attn<12>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
 
 }  // namespace kvmix

@@ -440,6 +440,42 @@ def test_blocks_of_sixteen_heads(G, Hkv, kb, vb, tiles, n_w, n_splits):
     assert_attn_close(t16(out), want, f"G={G} static", tight=True)
 
 
+@pytest.mark.parametrize("units,G,kb,vb,tiles,n_w,n_splits", [
+    (130, 16, 2, 2, 9, 33, 1), (65, 16, 3, 4, 12, 40, 2), (86, 24, 1, 3, 7, 40, 1), (26, 40, 4, 4, 5, 32, 2), (29, 72, 2, 2, 7, 63, 0),
+    (33, 16, 16, 16, 0, 75, 4), (5, 512, 3, 1, 2, 40, 0), (15, 72, 2, 4, 30, 45, 2),
+])
+def test_launches_in_blocks_of_sixteen_heads(units, G, kb, vb, tiles, n_w, n_splits):
+    """Groups of 16 heads and more where blocks of 8 would be more workgroups than there are compute units (256): blocks of 16, full and
+    partly filled, plain, static, and with the append inside, on rings with infinities and NaN in the dead slots."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case launch in sixteens units={units} G={G} bits={kb}/{vb} tiles={tiles} splits={n_splits}", flush=True)
+    assert units * (G // 8) * max(1, n_splits) > 256
+    T, W_cap = 32 * tiles + n_w, (n_w + 63) // 32 * 32
+    q, k, v = synth.gen_layer_numpy(1400 + G, 0, units, G, 1, T + 1)
+    _, _, _, rc, gc, shape, cfg = make_pair(units, G, 1, T, 32, kb, vb, T_cap=32 * tiles + 64, W_cap=W_cap, q_k_v=(q, k[:, :, :T], v[:, :, :T]))
+    for side, junk in ((gc.k_win, float("nan")), (gc.v_win, float("inf"))):
+        side.view(torch.float16).view(units, W_cap, 128)[:, n_w:] = junk
+    st, want = rc.decode_attn(u16(q))
+    assert st == 0
+    assert_attn_close(run_attn(gc, shape, cfg, q, n_splits=n_splits), want, "plain", tight=True)
+    qt = torch.from_numpy(q).cuda()
+    out = torch.zeros_like(qt)
+    if units * max(1, n_splits) * G * 520 < 4 << 20:
+        kv.decode_attn_static(shape, cfg, qt, gc, out, n_splits=n_splits)
+        torch.cuda.synchronize()
+        assert_attn_close(t16(out), want, "static", tight=True)
+    if kb != 16 and rc.n_w + 1 == 64:
+        return
+    ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
+    assert rc.append(u16(k[:, :, T]), u16(v[:, :, T])) == 0
+    st, want = rc.decode_attn(u16(q))
+    kv.decode_step(shape, cfg, torch.from_numpy(k[:, :, T].copy()).cuda(), torch.from_numpy(v[:, :, T].copy()).cuda(), qt, gc, out, ws, n_splits=n_splits)
+    torch.cuda.synchronize()
+    assert_attn_close(t16(out), want, "step", tight=True)
+    assert not counters_of(ws, shape).any()
+
+
 @pytest.mark.parametrize("W,W_cap,T0", [(32, 64, 0), (32, 64, 63), (32, 96, 37), (32, 128, 63), (64, 192, 64 + 31), (0, 32, 0), (0, 64, 31)])
 def test_chunk_copy_inside_the_quantizer_launch(W, W_cap, T0):
     """Rows that stay in the window ride in the quantizer's launch where no row lands in a slot that is still to be read, and are
@@ -476,7 +512,7 @@ def _empty_pair(B, Hkv, W, kb, vb, T_cap, W_cap):
 
 @pytest.mark.parametrize("G,Hkv,kb,vb,tiles,W,n_splits", [
     (1, 2, 2, 2, 9, 64, 1), (2, 2, 3, 2, 9, 32, 2), (4, 2, 3, 4, 26, 64, 1), (8, 1, 2, 2, 5, 32, 1), (8, 1, 2, 3, 9, 32, 2),
-    (16, 1, 2, 2, 9, 32, 0), (40, 1, 3, 4, 4, 64, 1), (4, 2, 2, 2, 3, 0, 1), (1, 2, 16, 16, 0, 64, 1), (8, 2, 16, 16, 0, 416, 2),
+    (16, 1, 2, 2, 9, 32, 0), (40, 1, 3, 4, 4, 64, 1), (512, 1, 2, 2, 9, 32, 3), (4, 2, 2, 2, 3, 0, 1), (1, 2, 16, 16, 0, 64, 1), (8, 2, 16, 16, 0, 416, 2),
 ])
 def test_step_that_opens_a_window_tile(G, Hkv, kb, vb, tiles, W, n_splits):
     """A fused step whose token is the first of its window tile, on rings whose slots outside the live tokens hold infinities and NaN:
@@ -507,13 +543,14 @@ def test_step_that_opens_a_window_tile(G, Hkv, kb, vb, tiles, W, n_splits):
 
 
 @pytest.mark.parametrize("B,Hkv,G,tiles,refused_below,split_from", [
-    (25, 4, 16, 61, 1, 5),       # 100 units: unsplit by the count that a workspace is held against, 5 splits where there is room
-    (1, 1, 72, 37, 5, 6),        # 5 splits by the one, 6 by the other
-    (1, 1, 72, 35, 4, 1),        # 4 splits by the one, none by the other
+    (25, 2, 24, 110, 1, 2),      # unsplit by the count that a workspace is held against, 2 splits (blocks of 16 heads) where there is room
+    (1, 1, 72, 37, 5, 5),        # 5 splits, blocks of 8 heads
+    (1, 1, 72, 14, 2, 1),        # 2 splits by the one, none by the other
 ])
 def test_workspaces_of_blocks_of_sixteen_heads(B, Hkv, G, tiles, refused_below, split_from):
-    """Split count left to the library, groups of 16 heads and more: a workspace is refused or accepted by one count (partials for
-    `refused_below` splits) and used for another one (`split_from`) only where it holds that one's partials as well."""
+    """Split count left to the library, groups of 16 heads and more: a workspace is refused or accepted by the count of blocks of 8 heads
+    (partials for `refused_below` splits), and blocks of 16 and their count (`split_from`) are taken only where it holds their
+    partials as well."""
     import torch
     import paper_2506_08018_amd as kv
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:

@@ -133,6 +133,26 @@ def test_attention_with_fronts_apart(G, state):
         attn_both(rc, gc, shape, cfg, q, n_splits, static, f"G={G} state={state} splits={n_splits} static={static}")
 
 
+@pytest.mark.parametrize("units,G,kb,vb,state,n_splits", [(86, 24, 2, 2, 0, 1), (29, 72, 3, 4, 1, 2), (129, 16, 4, 2, 4, 1), (5, 512, 2, 3, 2, 1)])
+def test_attention_with_fronts_apart_in_blocks_of_sixteen_heads(units, G, kb, vb, state, n_splits):
+    """More blocks of 8 heads than there are compute units (256), so that the main launch runs blocks of 16 and its merge reads the partial of
+    the tokens between the fronts from another place."""
+    import torch
+    import paper_2506_08018_amd as kv
+    T, flushes = STATES[state]
+    print(f"case fronts in sixteens units={units} G={G} state={state} splits={n_splits}", flush=True)
+    assert units * (G // 8) * n_splits > 256
+    q, k, v = synth.gen_layer_numpy(860 + state, G, units, G, 1, T)
+    rc, gc, shape, cfg = make_ring_pair(units, G, 1, kb, vb, 256, 256)
+    for t in range(T):
+        assert rc.append(u16(k[:, :, t]), u16(v[:, :, t])) == 0
+    kv.append_tokens(shape, cfg, torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda(), gc)
+    for keep_k, keep_v in flushes:
+        assert rc.flush(keep_k, keep_v) == 0
+        kv.flush(shape, cfg, gc, keep_k, keep_v)
+    attn_both(rc, gc, shape, cfg, q, n_splits, False, f"units={units} G={G} state={state}")
+
+
 @pytest.mark.parametrize("kb,vb,G,r_k,r_v", [(3, 2, 1, 0.2, 0.1), (2, 4, 4, 0.1, 0.2), (2, 2, 2, 0.1, 0.1), (3, 4, 8, 0.2, 0.2)])
 def test_decode_loop_under_the_count_formula(kb, vb, G, r_k, r_v):
     """A 200-token prompt, then decode steps. Each step: the new token is appended and attended to (fused step),

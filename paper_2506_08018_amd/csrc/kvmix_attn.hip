@@ -1179,7 +1179,10 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
     case 1: decode_attn_kernel<KB, VB, 1, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
     case 2: decode_attn_kernel<KB, VB, 2, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
     case 4: decode_attn_kernel<KB, VB, 4, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
-    case 8: decode_attn_kernel<KB, VB, 8, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
+    case 8:
+      // (8 heads with 3- or 4-bit Values always run 12 waves: attn_waves)
+      if constexpr (kNW == 12 || VB < 3) { decode_attn_kernel<KB, VB, 8, kNW><<<grid, kNW * kWave, 0, s>>>(a); break; }
+      else return hipErrorInvalidValue;
 #if KVMIX_WAVES == 8
     case 16: decode_attn_kernel<KB, VB, 16, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
 #endif

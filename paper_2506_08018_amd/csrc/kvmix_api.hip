@@ -288,10 +288,10 @@ Fronts fronts_of(const kvmix_layer_cache* c, int n_w) {
 
 // Waves per workgroup of the attention kernel. 12 waves fill a compute unit with one workgroup, 8 leave room for two.
 // Launches that need more workgroups than there are compute units run 8: twice the workgroups are resident, so that one's start and
-// merge overlap another's stream (512 units of 128 tiles: 55.0 us against 57.8; 600 of 36: 23.9 against 27.2; 2048 of 20: 41.2
-// against 53.5). With at most one workgroup per compute unit the 4 more waves pay when each has many tiles to stream (256
-// units of 128 tiles: 22.2 us against 23.9; 32 tiles: 14.3 against 14.9), and cost in start and merge when there are few
-// (16 tiles: 12.5 us against 12.2; 9 tiles: 7.0 against 6.9).
+// merge overlap another's stream (512 units of 128 tiles, 8 heads: 53.2 us against 54.1; 1 head, 600 units of 36: 23.3 against 25.9;
+// 2048 of 20: 38.9 against 50.6). With at most one workgroup per compute unit the 4 more waves pay when each has many tiles to stream (1 head,
+// 256 units of 128 tiles: 20.5 us against 23.2; 32 tiles: 10.3 against 10.6), and cost in start and merge when there are few
+// (9 tiles: 7.7 us against 7.5); from 16 to 24 tiles the two are within 2 % (16: 8.5 and 8.5).
 // 8 heads with 3- or 4-bit Values do not fit the 128 registers of the 8-wave form (spilling: 93 us where 12 waves take 62).
 int attn_waves(long long workgroups, int n_tiles, int n_splits, int block, int v_bits) {
   if (block > 8) return 8;

@@ -910,11 +910,12 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
     wave_lds_fence();   // the next tile's operand writes come after these reads
   };
-  // Blocks of 16 heads (groups of 16 and more, multi-query attention): a column is a head, the hi and lo parts are two matrix instructions
+  // Blocks of 16 heads (of groups of 16 and more, multi-query attention): a column is a head, the hi and lo parts are two matrix instructions
   // on the same accumulators. The scores come out with a lane holding 8 tokens of its head, which are the tokens
   // of its operand for the Values: softmax, numerators and operands stay in the lane, only the tile's scales and minima
-  // go through LDS, and the codes are cut out once for 16 heads. Bound by instruction issue (about 200 vector and 38 matrix
-  // instructions per tile and wave; blocks of 8 took 1.8 times the cycles per head): 72 heads x 32 sequences of 4096 tokens, 49 -> 28 us.
+  // go through LDS, and the codes are cut out once for 16 heads. Bound by instruction issue: about 260 vector and 38 matrix
+  // instructions per tile and wave; at 72 heads x 32 sequences of 4096 tokens vector and matrix units are busy 79 % of the SIMD clocks
+  // (58 + 21 %, a vector instruction 4.1 clocks, at 1.87 GHz). 27 us there; blocks of 8 took 49.
   auto process_wide = [&](const Stage<KB, VB>& st) {
     reinterpret_cast<uint32_t*>(L.k.op)[lane] = st.meta[0];
     reinterpret_cast<uint32_t*>(&L.k.zk[0])[lane] = st.meta[1];

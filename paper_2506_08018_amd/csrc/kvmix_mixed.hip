@@ -350,8 +350,8 @@ __global__ __launch_bounds__(kMixWaves * kWave) void mixed_fronts_kernel(MixedAr
   };
   if (values_packed) run(std::true_type{}); else run(std::false_type{});
   __syncthreads();
-  // the partial of head hg (within the unit's group) goes where the main kernel's merge looks for it: that kernel
-  // numbers (unit, block of G_main heads) pairs
+  // the partial of head hg (within the unit's group) goes where the main kernel's merge looks for it: blocks of 8 heads keep their partials
+  // together (G_main = 8), otherwise the heads of the whole group lie side by side (G_main = G)
   for (int idx = tid; idx < GH * kD; idx += kMixWaves * kWave) {
     const int hh = idx / kD, d = idx % kD;
     float M = -INFINITY;

@@ -186,7 +186,7 @@ def append_tokens(shape, cfg, k_new, v_new, cache):
 
 
 def decode_attn(shape, cfg, q, cache, out, workspace=None, softmax_scale=0.0, n_splits=0, stream=None):
-    """q, out: fp16 CUDA tensors [B][Hq][128], contiguous. workspace: uint8 CUDA tensor (zeroed once) or None.
+    """q, out: fp16 CUDA tensors [B][Hq][128], contiguous. workspace: uint8 CUDA tensor (zeroed once, and again for another shape) or None.
     stream: torch stream or raw hipStream_t handle (default: torch's current stream)."""
     assert q.is_contiguous() and out.is_contiguous()
     wp, wn = (workspace.data_ptr(), workspace.numel() * workspace.element_size()) if workspace is not None else (None, 0)

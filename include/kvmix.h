@@ -229,11 +229,11 @@ int kvmix_decode_attn_static(const kvmix_shape* shape, const kvmix_layer_cfg* cf
                              int n_splits, void* stream);
 
 /* kvmix_append for n_tokens consecutive new tokens per sequence (chunked prefill, speculative decoding): the same
- * counters, tile records and live window tokens as n_tokens calls of kvmix_append in a row, in at most two
- * launches: one quantize-and-pack launch over all tiles that fall due (their tokens are read from the ring or
+ * counters, tile records and live window tokens as n_tokens calls of kvmix_append in a row, in one
+ * launch: quantize-and-pack over all tiles that fall due (their tokens are read from the ring or
  * straight from k_new / v_new: Sec. 3.4 item 1, new states are quantized and joined to the cache without a pass of
- * their own through memory), then one copy of the new tokens that stay in the window (part of the same launch where none of
- * them lands in a ring slot that the launch still reads). Element (b, j, i, d)
+ * their own through memory), which also copies the new tokens that stay in the window (into a slot that the launch reads: by the
+ * workgroup that has read it); the copy alone where nothing falls due. Element (b, j, i, d)
  * of k_new / v_new is at b*batch_stride + j*head_stride + i*token_stride + d (strides in elements, multiples of 8,
  * token_stride >= 128; pointers 16-byte aligned). Capacity (T_cap, W_cap) is checked for the whole call before
  * anything is launched. Ring slots outside the n_w live tokens are unspecified afterwards. */

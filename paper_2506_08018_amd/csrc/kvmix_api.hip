@@ -200,24 +200,26 @@ int kvmix_append_tokens(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const
   // The old window tokens followed by the new ones form one sequence of m rows; its first 32 F rows leave for the
   // packed part (F tiles, from the ring or straight from the input: a token that is flushed within this call never
   // passes through the ring), the rest is the new window. The quantizer's launch over the F tiles also copies the
-  // surviving new rows into their ring slots, unless a new row lands in the slot of an old one that the quantizer still
-  // has to read: then the copy is a launch of its own, after it. (A prompt of 32 700 tokens for 8 units: 42.0 us in two launches,
-  // 38.8 in one.)
+  // surviving new rows into their ring slots: those that land in the slot of an old row by the workgroup that reads this old row.
+  // (A prompt of 32 700 tokens for 8 units: 42.0 us in two launches, 38.8 in one.)
   const long long m = (long long)c->n_w + n_tokens;
   const int F = ageing && m >= cfg->window + kTile ? (int)((m - cfg->window) / kTile) : 0;
   const long long first_kept = (long long)F * kTile;                       // first row of the sequence that stays in the window
   const int i0 = first_kept > c->n_w ? (int)(first_kept - c->n_w) : 0;      // first new token that stays
-  const int n_copy = n_tokens - i0, copy_slot = (int)((c->w0 + c->n_w + (long long)i0) % W);
-  bool copied = n_copy == 0;
+  const int n_copy = n_tokens - i0;                                         // at most W: what stays fits the ring
+  const int copy_at = (int)((c->n_w + (long long)i0) % W);                  // where it goes, counted from slot w0
   if (F > 0) {
     QuantArgs a{};
-    // ring slots relative to w0: the tiles read [0, n_read), the copy writes [at, at + n_copy) around the ring
-    const long long n_read = first_kept < c->n_w ? first_kept : c->n_w, at = (c->n_w + (long long)i0) % W;
-    if (n_copy > 0 && n_copy <= W && (n_read == 0 || (at >= n_read && at + n_copy <= W))) {
-      a.n_copy = n_copy; a.copy_row = i0; a.copy_slot = copy_slot;
-      a.k_ring_w = c->k_win; a.v_ring_w = c->v_win;
-      copied = true;
-    }
+    a.n_copy = n_copy; a.copy_row = i0; a.copy_at = copy_at;
+    a.k_ring_w = c->k_win; a.v_ring_w = c->v_win;
+    // slots [0, n_read) are read by tiles; the rows go to [copy_at, end) and, around the ring, [0, end - W)
+    const int n_read = (int)(first_kept < c->n_w ? first_kept : c->n_w), end = copy_at + n_copy;
+    a.n_read = copy_at < n_read || end > W ? n_read : 0;
+    // slots outside [0, n_read): from copy_at on (or from n_read on, where the rows begin inside it or go around)
+    int first = copy_at, last = end < W ? end : W;
+    if (end - W > n_read || first < n_read) first = n_read;
+    a.copy_tile0 = first / kTile;
+    a.copy_tiles = n_copy > 0 && last > first ? (last + kTile - 1) / kTile - a.copy_tile0 : 0;
     a.k = k_new; a.v = v_new;
     a.k_tok = token_stride; a.k_unit_b = batch_stride; a.k_unit_h = head_stride;
     a.v_tok = token_stride; a.v_unit_b = batch_stride; a.v_unit_h = head_stride;
@@ -227,13 +229,12 @@ int kvmix_append_tokens(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const
     a.Hkv = sh->Hkv;
     const hipError_t e = launch_quantize_pack(a, cfg->k_bits, cfg->v_bits, F, units, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e);
-  }
-  if (!copied) {
+  } else {
     AppendArgs ap{};
-    ap.k_new = k_new + (int64_t)i0 * token_stride; ap.v_new = v_new + (int64_t)i0 * token_stride;
+    ap.k_new = k_new; ap.v_new = v_new;
     ap.tok = token_stride; ap.head = head_stride; ap.batch = batch_stride;
     ap.k_win = c->k_win; ap.v_win = c->v_win;
-    ap.W_cap = W; ap.slot = copy_slot; ap.n = n_copy; ap.units = units; ap.Hkv = sh->Hkv;
+    ap.W_cap = W; ap.slot = (c->w0 + copy_at) % W; ap.n = n_copy; ap.units = units; ap.Hkv = sh->Hkv;
     const hipError_t e = launch_append(ap, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e);
   }

@@ -103,9 +103,11 @@ struct QuantArgs {
   int tiles_cap;   // tiles per unit in the packed cache
   int tile0;       // first destination tile
   int Hkv;
-  // Input rows that stay in the window (an appending launch only): workgroups from n_tiles on copy input rows copy_row .. copy_row +
-  // n_copy - 1 to the ring slots (copy_slot + i) % W_cap, 32 rows each; none of them is a slot that the launch's tiles read
-  int n_tiles, n_copy, copy_row, copy_slot;
+  // Input rows that stay in the window (an appending launch only): row copy_row + i, i = 0 .. n_copy - 1, goes to the ring slot that lies
+  // copy_at + i slots behind ring_w0, around the ring. The slots [0, n_read) behind ring_w0 are also read by tiles of the launch: the
+  // workgroup of the tile in question fills those, once it has its rows. The others are filled by copy_tiles workgroups from n_tiles on, 32 slots
+  // each, from slot 32 copy_tile0 on.
+  int n_tiles, n_copy, copy_row, copy_at, n_read, copy_tile0, copy_tiles;
   uint16_t* k_ring_w; uint16_t* v_ring_w;
   // Ageing with separate fronts (every row comes from the ring, row r of the launch is token 32*tile0 + r): the Key
   // side is written for the destination tiles [k_tile_a, k_tile_b) only, the Value side for the tokens

@@ -24,15 +24,30 @@ __device__ __forceinline__ int qmax_of(int i) {
   return (1 << BITS) - 1;
 }
 
-// value of lane (l ^ 1) / (l ^ 2) of each quad
-__device__ __forceinline__ uint32_t quad_x1(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false); }
-__device__ __forceinline__ uint32_t quad_x2(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false); }
+// value of lane (l ^ 1) / (l ^ 2) of each quad (every source lane exists: the last argument lets the move fold into the OR that uses it)
+__device__ __forceinline__ uint32_t quad_x1(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true); }
+__device__ __forceinline__ uint32_t quad_x2(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true); }
+// value of lane (l ^ 4): of a row of 16, by a mirror of its halves of 8 (l ^ 7), then of quads (l ^ 3)
+__device__ __forceinline__ uint32_t lane_x4(uint32_t v) {
+  const int m = __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xf, 0xf, true);
+}
 
 // Codes travel as "biased codes": the bit pattern of the float 1.5 * 2^23 + code, i.e. kBias + code. Adding
 // 1.5 * 2^23 to a value in [0, 2^22) rounds it to an integer (ties to even) in one operation and leaves that
 // integer in the low mantissa bits; the low 16 bits of kBias are zero.
 constexpr float kMagic = 12582912.0f;
 constexpr uint32_t kBias = 0x4B400000u;
+
+// range / q_max, correctly rounded: a product with the rounded reciprocal, its exact remainder and one correction. Equal to the IEEE
+// quotient for 3, 7 and 15 at every fp32 significand (tried one by one); a range of fp16 numbers is far from the ends of the exponent range.
+template <int BITS>
+__device__ __forceinline__ float over_qmax(float range) {
+  if constexpr (BITS == 1) return range;
+  constexpr float kQ = (float)((1 << BITS) - 1), kInv = 1.0f / kQ;
+  const float q = range * kInv;
+  return __builtin_fmaf(__builtin_fmaf(-kQ, q, range), kInv, q);
+}
 
 // Scale, minimum and bracketing reciprocal steps of one group from its extremes (fp32 images of fp16 values).
 struct GroupParams { float mn, s, inv_lo, inv_hi, inv2_lo, inv2_hi; bool slow; uint16_t scale_h, zero_h; };
@@ -42,7 +57,8 @@ __device__ __forceinline__ GroupParams group_params(float mn, float mx) {
   if (mn == 0.0f) mn = 0.0f;                      // -0 -> +0
   float range = mx - mn;
   if (range == 0.0f) range = 0.0f;                // a zero-range group stores scale +0 whatever the signs of its zeros
-  const float s32 = range / (float)((1 << BITS) - 1);
+  const bool infinite = range == __builtin_inff();       // (outside what the entry points promise anything for: scale infinity, codes 0)
+  const float s32 = infinite ? range : over_qmax<BITS>(range);
   // round-to-nearest-even; a 1-bit step (the range itself) beyond the fp16 range is stored as the largest fp16 number
   const half_t sh = (half_t)(BITS == 1 ? fminf(s32, 65504.0f) : s32);
   g.mn = mn;
@@ -59,34 +75,148 @@ __device__ __forceinline__ GroupParams group_params(float mn, float mx) {
   g.inv2_hi = g.inv_hi * (3.0f / 7.0f);
   // Only when the stored scale is a rounded image of range / q_max to fp16's full precision is every quotient
   // at most q_max * (1 + 2^-11) and the upper clip idle. A subnormal scale (rounded with a larger relative error)
-  // or a saturated 1-bit scale sends the whole group down the exact path, which clips.
-  g.slow = (g.s != 0.0f && g.s < 0x1p-14f) || (BITS == 1 && g.s >= 65504.0f);
+  // or a saturated 1-bit scale sends the whole group down the path that clips.
+  g.slow = (g.s != 0.0f && g.s < 0x1p-14f) || (BITS == 1 && g.s >= 65504.0f) || infinite;
   return g;
+}
+
+// Extremes of 32 fp16 numbers per half, 16 pairs from one source and 16 from another or 32 of one: three operands at a time. The
+// instructions hand a NaN on, unlike the ones that take two operands: nan says that there is one (the group then goes the slow way, with the
+// extremes of the others).
+__device__ __forceinline__ uint32_t min3(uint32_t a, uint32_t b, uint32_t c) { uint32_t r; asm("v_pk_minimum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
+__device__ __forceinline__ uint32_t max3(uint32_t a, uint32_t b, uint32_t c) { uint32_t r; asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
+template <int N>
+__device__ __forceinline__ void extremes(const uint32_t (&x)[N], half2_t& mn, half2_t& mx, bool& nan) {
+  uint32_t lo = min3(x[0], x[1], x[2]), hi = max3(x[0], x[1], x[2]);
+#pragma unroll
+  for (int i = 3; i < N; i += 2) {
+    lo = min3(lo, x[i], x[i + 1 < N ? i + 1 : i]);
+    hi = max3(hi, x[i], x[i + 1 < N ? i + 1 : i]);
+  }
+  mn = __builtin_bit_cast(half2_t, lo);
+  mx = __builtin_bit_cast(half2_t, hi);
+  nan = !(mx[0] == mx[0] && mx[1] == mx[1]);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(nan) != 0, 0)) {
+    mn = mx = __builtin_bit_cast(half2_t, x[0]);
+#pragma unroll
+    for (int i = 1; i < N; i++) {
+      mn = __builtin_elementwise_min(mn, __builtin_bit_cast(half2_t, x[i]));
+      mx = __builtin_elementwise_max(mx, __builtin_bit_cast(half2_t, x[i]));
+    }
+  }
 }
 
 // code = clamp(rint((x - mn) / s_i)) with the IEEE quotient rounded to fp32 first. The quotient q lies strictly
 // between (x - mn) * inv_lo and (x - mn) * inv_hi, and so does its fp32 image; rounding to an integer is
 // monotone, so when both products round to the same integer (each with the single rounding of a fused
-// multiply-add onto kMagic), that integer is the code. quantize_fast reports the other cases - the quotient
-// within 2^-18 relative of k + 1/2, rare - and the caller redoes a small batch of elements with
-// quantize_exact when any of them was one. x >= mn always, and only the exact path needs the upper clip.
-// d: x - mn in fp32; i: index of the element inside its group. Both return biased codes.
+// multiply-add onto kMagic), that integer is the code. x >= mn always, and the upper clip is idle but for the groups marked slow.
+// The other cases, the quotient within 2^-18 relative of k + 1/2, are in practice exact ties (fp16 inputs over an fp16 step: one
+// element in 4000, so that one batch of 1024 in five has one): resolve_tie recognises those by the exact remainder d - (k + 1/2) s,
+// which a fused multiply-add gives without rounding, and takes the even one of k and k + 1. What is left, next to never, is compared with
+// the two ends of the range of quotients that fp32 rounds to k + 1/2 (settle). No division: when every tie went through one, the
+// divisions took a quarter of the time of a tile.
+// d: x - mn in fp32; i: index of the element inside its group. All return biased codes.
+template <int BITS> constexpr bool two_bit(int i) { return BITS == 3 && (i == 10 || i == 21); }
 template <int BITS>
-__device__ __forceinline__ uint32_t quantize_fast(float d, const GroupParams& g, int i, bool& near) {
-  const bool two_bit = BITS == 3 && (i == 10 || i == 21);
-  const float lo = __builtin_fmaf(d, two_bit ? g.inv2_lo : g.inv_lo, kMagic);
-  const float hi = __builtin_fmaf(d, two_bit ? g.inv2_hi : g.inv_hi, kMagic);
-  near |= lo != hi;
-  return __builtin_bit_cast(uint32_t, lo);
+__device__ __forceinline__ uint32_t code_below(float d, const GroupParams& g, int i) {
+  return __builtin_bit_cast(uint32_t, __builtin_fmaf(d, two_bit<BITS>(i) ? g.inv2_lo : g.inv_lo, kMagic));
 }
 template <int BITS>
-__device__ __forceinline__ uint32_t quantize_exact(float d, const GroupParams& g, int i) {
-  if (g.s == 0.0f) return kBias;
-  const float r = __builtin_rintf(d / step_of<BITS>(g.s, i));
-  return kBias + (uint32_t)fminf(fmaxf(r, 0.0f), (float)qmax_of<BITS>(i));
+__device__ __forceinline__ uint32_t code_above(float d, const GroupParams& g, int i) {
+  return __builtin_bit_cast(uint32_t, __builtin_fmaf(d, two_bit<BITS>(i) ? g.inv2_hi : g.inv_hi, kMagic));
 }
-// x - mn in fp32 for an fp16 x: one fused operation (x * 1 - mn), rounded once like the subtraction
-__device__ __forceinline__ float diff(half_t x, float mn) { return __builtin_fmaf((float)x, 1.0f, -mn); }
+// An element of which the lanes in `near` are next to k + 1/2 (lo the code below): bit `at` of open is set where it is no exact tie.
+// (The step of a 2-bit element of a 3-bit group is itself rounded: its remainder does not tell.)
+template <int BITS>
+__device__ __forceinline__ uint32_t resolve_tie(uint32_t lo, float d, const GroupParams& g, int i, int at, bool near, uint32_t& open) {
+  const float rest = __builtin_fmaf((__builtin_bit_cast(float, lo) - kMagic) + 0.5f, -g.s, d);
+  open |= near & (two_bit<BITS>(i) | (rest != 0.0f)) ? 1u << at : 0u;
+  return lo + (near ? lo & 1u : 0u);
+}
+// x - mn in fp32 of the low / high half of a pair of fp16 numbers: x * 1 - mn, rounded once like the subtraction, with the conversion in
+// the same instruction
+template <int HALF>
+__device__ __forceinline__ float diff(uint32_t pair, float mn) {
+  float d;
+  if constexpr (HALF == 0) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,0]" : "=v"(d) : "v"(pair), "v"(mn));
+  else asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(pair), "v"(mn));
+  return d;
+}
+// fp32 rounds a quotient to h = k + 1/2 when it is at most half a unit in the last place of h away (half that below h = 1/2, where the
+// spacing changes); the ends times the step have at most 49 bits, so that the comparisons in 64 bits are exact.
+__device__ __forceinline__ uint32_t settle(float d, float inv_lo, float step) {
+  const uint32_t lo = __builtin_bit_cast(uint32_t, __builtin_fmaf(d, inv_lo, kMagic));
+  const float h = (__builtin_bit_cast(float, lo) - kMagic) + 0.5f;
+  const double half = (double)__builtin_bit_cast(float, __builtin_bit_cast(uint32_t, h) & 0x7f800000u) * 0x1p-24;
+  const double s = (double)step;
+  uint32_t code = lo + (lo & 1u);
+  if ((double)d > s * ((double)h + half)) code = lo + 1u;
+  if ((double)d < s * ((double)h - (h == 0.5f ? 0.5 * half : half))) code = lo;
+  return code;
+}
+// A lane's batch of 16 elements: code[at], of element first + at of the group g0 (Values), whose fp16 number is half at % 2 of pair[at / 2],
+// or of element first + at % 8 of g0 or g1 (Keys), half at / 8 of pair[at % 8]. open: the elements to compare with the ends of the range; one
+// per lane and round, next to never.
+template <int BITS, bool KEYS>
+__device__ __forceinline__ void settle_open(uint32_t (&code)[16], const uint32_t (&pair)[8], const GroupParams& g0, const GroupParams& g1, int first, uint32_t open) {
+  const float mn0 = g0.mn, mn1 = g1.mn, s0 = g0.s, s1 = g1.s, inv0 = g0.inv_lo, inv1 = g1.inv_lo, inv2_0 = g0.inv2_lo, inv2_1 = g1.inv2_lo;
+#pragma unroll 1
+  while (__builtin_amdgcn_ballot_w64(open != 0) != 0) {
+    const int at = open ? __builtin_ctz(open) : 31;       // 31: no element
+    open &= open - 1u;
+    uint32_t x = 0;
+#pragma unroll
+    for (int n = 0; n < 8; n++) {
+      x = (KEYS ? at & 7 : at >> 1) == n ? pair[n] : x;
+      asm("" : "+v"(x));          // (a chain of selects: recognised as an indexed array it would move to memory)
+    }
+    const int half = KEYS ? at >> 3 & 1 : at & 1, i = first + (KEYS ? at & 7 : at & 15);
+    const float mn = KEYS && half ? mn1 : mn0, s = KEYS && half ? s1 : s0;
+    const bool two = BITS == 3 && (i == 10 || i == 21);
+    const float inv = two ? (KEYS && half ? inv2_1 : inv2_0) : (KEYS && half ? inv1 : inv0);
+    const float d = (float)__builtin_bit_cast(half_t, (uint16_t)(x >> (16 * half))) - mn;
+    const uint32_t c = settle(d, inv, two ? (s * 7.0f) / 3.0f : s);
+#pragma unroll
+    for (int n = 0; n < 16; n++) {
+      code[n] = n == at ? c : code[n];
+      asm("" : "+v"(code[n]));
+    }
+  }
+}
+// The codes of a batch. The comparison of the two products of an element is a mask of the wave's lanes in scalar registers: only elements
+// that some lane has next to k + 1/2 are looked at again.
+template <int BITS, bool KEYS>
+__device__ __forceinline__ void quantize_batch(uint32_t (&code)[16], const uint32_t (&pair)[8], const GroupParams& g0, const GroupParams& g1, int first, uint64_t slow) {
+  auto element = [&](int at) { return first + (KEYS ? at & 7 : at); };
+  auto group = [&](int at) -> const GroupParams& { return KEYS && at >= 8 ? g1 : g0; };
+  auto d = [&](int at) {
+    const uint32_t x = pair[KEYS ? at & 7 : at >> 1];
+    const float mn = group(at).mn;
+    return (KEYS ? at >= 8 : at & 1) ? diff<1>(x, mn) : diff<0>(x, mn);
+  };
+  uint64_t near[16], any = slow;
+#pragma unroll
+  for (int at = 0; at < 16; at++) {
+    const float v = d(at);
+    code[at] = code_below<BITS>(v, group(at), element(at));
+    near[at] = __builtin_amdgcn_ballot_w64(code[at] != code_above<BITS>(v, group(at), element(at)));
+    any |= near[at];
+  }
+  if (__builtin_expect(any != 0, 0)) {
+    uint32_t open = 0;
+#pragma unroll
+    for (int at = 0; at < 16; at++)
+      if (near[at] != 0) code[at] = resolve_tie<BITS>(code[at], d(at), group(at), element(at), at, __builtin_amdgcn_inverse_ballot_w64(near[at]), open);
+    settle_open<BITS, KEYS>(code, pair, g0, g1, first, open);
+    if (slow != 0) {      // clip (and nothing but code 0 for what is not a number)
+#pragma unroll
+      for (int at = 0; at < 16; at++) {
+        const uint32_t top = kBias + (uint32_t)qmax_of<BITS>(element(at)), c = code[at] < top ? code[at] : top;
+        code[at] = (code[at] & 0x7fffffffu) > 0x7f800000u ? kBias : c;
+      }
+    }
+  }
+}
 
 __device__ __forceinline__ half2_t as_half2(uint32_t w) { return __builtin_bit_cast(half2_t, w); }
 
@@ -96,8 +226,8 @@ __device__ __forceinline__ half2_t as_half2(uint32_t w) { return __builtin_bit_c
 template <int BITS> constexpr int acc_words() { return BITS == 4 ? 32 : 16; }
 
 // Final step shared by both waves: `w` holds, in every lane of a quad (q = lane & 3), the complete words
-// i = 0..15 (per chunk) of column group (kq, j); lane q stores the words i = 4q .. 4q+3. `hi` (3-bit only)
-// holds the high-plane words, complete in both lanes j and j^1; the even-j lanes store them.
+// i = 0..15 (per chunk) of column group (kq, j); lane q has the words i = 4q .. 4q+3 to deliver. `hi` (3- and 1-bit)
+// holds the high-plane words, complete in both lanes j and j^1; the even-j lanes deliver them.
 // A word of which only the bits of `mask` are this launch's to write (PARTIAL: Values that leave the window token
 // by token share their words with the neighbouring tokens' codes, which are already in place or still to come).
 // No other lane of the launch touches the word, and launches on one cache are ordered by the caller's stream.
@@ -111,9 +241,11 @@ __device__ __forceinline__ void put_word(uint32_t* p, uint32_t v, uint32_t mask)
   }
 }
 
-template <int BITS, bool PARTIAL = false>
-__device__ __forceinline__ void store_words(uint32_t* sec, const uint32_t (&w)[acc_words<BITS>()], const uint32_t (&hi)[16],
-                                            int kq, int j, int q, uint32_t wmask = 0xFFFFFFFFu, uint32_t hmask = 0xFFFFFFFFu) {
+// Words of a section from the wave: lane q of a quad has those of columns i = 4q .. 4q+3. To the section itself where other launches'
+// bits share the words (PARTIAL), otherwise to the wave's image of the section in LDS.
+template <int BITS, bool PARTIAL>
+__device__ __forceinline__ void put_words(uint32_t* sec, const uint32_t (&w)[acc_words<BITS>()], const uint32_t (&hi)[16],
+                                          int kq, int j, int q, uint32_t wmask = 0xFFFFFFFFu, uint32_t hmask = 0xFFFFFFFFu) {
   constexpr int kChunks = BITS == 4 ? 2 : BITS == 1 ? 0 : 1;
   constexpr int kPlane = BITS == 1 ? 0 : 256;     // first word of the 1-bit plane
 #pragma unroll
@@ -133,55 +265,92 @@ __device__ __forceinline__ void store_words(uint32_t* sec, const uint32_t (&w)[a
     }
   }
 }
+// orders the wave's own LDS writes before its following LDS reads (LDS executes a wave's operations in order; this pins the compiler)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// Which accesses of a launch go past the caches (see launch_quantize_pack).
+enum Stream { kCached, kStreamOut, kStreamBoth };
+// the section from its image, 16 (bit plane: 8) bytes per lane and instruction
+template <Stream S, typename T>
+__device__ __forceinline__ void put(T* p, T v) {
+  if constexpr (S != kCached) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+template <int BITS, Stream S>
+__device__ __forceinline__ void store_section(uint32_t* sec, const uint32_t* image, int lane) {
+  constexpr int kChunks = BITS == 4 ? 2 : BITS == 1 ? 0 : 1;
+#pragma unroll
+  for (int c = 0; c < kChunks; c++) put<S>(reinterpret_cast<u32x4_t*>(sec) + 64 * c + lane, reinterpret_cast<const u32x4_t*>(image)[64 * c + lane]);
+  if constexpr (BITS == 3 || BITS == 1) {
+    constexpr int kPlane = BITS == 1 ? 0 : 256;
+    put<S>(reinterpret_cast<u32x2_t*>(sec + kPlane) + lane, reinterpret_cast<const u32x2_t*>(image + kPlane)[lane]);
+  }
+}
 
-// One workgroup of two waves quantizes and packs one (unit, 32-token tile) entirely in registers: wave 0
-// the Key tile, wave 1 the Value tile. A lane owns what ends up in the same words: lane = 16*kq + 4*j + q.
+template <Stream S, typename T>
+__device__ __forceinline__ T load_row(const uint16_t* p) {
+  const T* t = reinterpret_cast<const T*>(p);
+  return S == kStreamBoth ? __builtin_nontemporal_load(t) : *t;
+}
+
+// One workgroup of two waves quantizes and packs one (unit, 32-token tile): wave 0 the Key tile, wave 1 the Value tile, each for
+// itself. A lane owns what ends up in the same words: lane = 16*kq + 4*j + q.
 //   Key wave:   q = ks; channels d0 = 32*ks + 8*kq + 2*j and d0 + 1 over the 32 tokens (two groups); a word
 //               (l = 16*kq + i, j) gets its fields of slot ks + 4*m from this lane, the other ks from the quad.
 //   Value wave: q = g;  tokens 8*kq + 2*j and + 1, channels 32*g .. 32*g + 31 (two groups); a word gets its
 //               fields of slots 2*g, 2*g + 1 from this lane, the other blocks from the quad.
 // The lanes of a quad OR their partial words together (DPP), the 1-bit plane of 3-bit codes also across the
-// two j of a word; each lane then stores a quarter of the words. No LDS.
-// Row r of the sequence a launch quantizes: a ring slot of the window or a row of the input.
-__device__ __forceinline__ const uint16_t* source_row(const uint16_t* ring, const uint16_t* in, int64_t tok, int64_t unit_off,
-                                                      const QuantArgs& a, int u, int r) {
-  if (r < a.n_ring) {
-    int slot = a.ring_w0 + r;
-    if (slot >= a.W_cap) slot -= a.W_cap;
-    return ring + ((size_t)u * a.W_cap + slot) * kD;
-  }
-  return in + unit_off + (int64_t)(r - a.n_ring) * tok;
-}
-
-// Row r of an ageing launch (PARTIAL): always a ring slot; the launch may span more rows than the ring has slots
-// (only rows of live tokens are read).
-__device__ __forceinline__ const uint16_t* ring_row(const uint16_t* ring, const QuantArgs& a, int u, int r) {
-  const int slot = (a.ring_w0 + r) % a.W_cap;
-  return ring + ((size_t)u * a.W_cap + slot) * kD;
-}
-
+// two j of a word; each lane then has a quarter of the words.
+// Memory sees whole rows and whole sections: Key rows are 4 bytes per lane; Value rows 16 bytes per lane, four rows per instruction, handed to
+// their lanes through LDS; finished words go through LDS to a store of 1 KB per instruction, and so does the metadata of the
+// two waves (8 bytes of every 16 each). What a variant that only loads and stores takes for 31 488 tiles of 2/2 bit, its accesses past
+// the caches: 98 us with the metadata in its pieces, 93 this way (111 with Value rows in pieces of 16 bytes and words stored one by one).
+// The whole kernel: 112.9 us before, with divisions for ties, 90.7 now (a large copy's rate); 8 096 tiles of 3/4 bit 38.8 and 32.2, about 700
+// vector instructions per wave and tile (21 us of issue) that only partly overlap the loads when a place sees four tiles.
+//
 // PARTIAL: ageing with separate fronts for Keys and Values. The Key wave works on the tiles [k_tile_a, k_tile_b)
 // only; the Value wave writes the codes and metadata of the tokens [v_tok_a, v_tok_b) only, merging them into
-// words that it shares with other tokens.
-template <int KB, int VB, bool PARTIAL>
-__global__ __launch_bounds__(128, 5) void quantize_pack_kernel(QuantArgs a) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// words that it shares with other tokens. Every row comes from the ring.
+template <int KB, int VB, bool PARTIAL, Stream S>
+__global__ __launch_bounds__(128, 4) void quantize_pack_kernel(QuantArgs a) {
+  __shared__ __attribute__((aligned(16))) uint32_t s_key[512];             // the Key section's image
+  __shared__ __attribute__((aligned(16))) uint32_t s_value[kTile * kD / 2];   // the Value rows, then the Value section's image
+  __shared__ __attribute__((aligned(16))) uint32_t s_meta[kMetaWords];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kq = lane >> 4, j = (lane >> 2) & 3, q = lane & 3;
   const int tile_in = blockIdx.x, jh = blockIdx.y, b = blockIdx.z;   // no integer division at the start of a short kernel
   const int u = b * a.Hkv + jh;
+  const uint16_t* in = wave ? a.v + b * a.v_unit_b + jh * a.v_unit_h : a.k + b * a.k_unit_b + jh * a.k_unit_h;
+  const uint16_t* ring = (wave ? a.v_ring : a.k_ring) + (size_t)u * a.W_cap * kD;
+  const int64_t tok = wave ? a.v_tok : a.k_tok;
+  // Input row i (of those that stay in the window) to its ring slot: rows 16 bytes per lane, four at a time. from: ring slot, counted from
+  // ring_w0, of the first of 32 slots; the slots [lo, hi) of them are this workgroup's to fill.
+  auto copy_rows = [&](int from, int lo, int hi) {
+    uint16_t* ring_w = (wave ? a.v_ring_w : a.k_ring_w) + (size_t)u * a.W_cap * kD;
+    u32x4_t x[8];
+    int at[8];
+#pragma unroll
+    for (int n = 0; n < 8; n++) {
+      const int rel = from + 4 * n + (lane >> 4);
+      int i = rel - a.copy_at;
+      if (i < 0) i += a.W_cap;
+      at[n] = -1;
+      if (rel >= lo && rel < hi && i < a.n_copy) {
+        const int slot = a.ring_w0 + rel;
+        at[n] = slot >= a.W_cap ? slot - a.W_cap : slot;
+        x[n] = *reinterpret_cast<const u32x4_t*>(in + (int64_t)(a.copy_row + i) * tok + 8 * (lane & 15));
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < 8; n++)
+      if (at[n] >= 0) *reinterpret_cast<u32x4_t*>(ring_w + (size_t)at[n] * kD + 8 * (lane & 15)) = x[n];
+  };
   if constexpr (!PARTIAL) {
-    if (tile_in >= a.n_tiles) {       // window rows: one side per wave, 16 bytes per lane
-      const uint16_t* in = wave ? a.v + b * a.v_unit_b + jh * a.v_unit_h : a.k + b * a.k_unit_b + jh * a.k_unit_h;
-      uint16_t* ring = (wave ? a.v_ring_w : a.k_ring_w) + (size_t)u * a.W_cap * kD;
-      const int64_t tok = wave ? a.v_tok : a.k_tok;
-      const int i0 = (tile_in - a.n_tiles) * kTile + (lane >> 4), c = 8 * (lane & 15);
-      u32x4_t x[8];
-#pragma unroll
-      for (int n = 0; n < 8; n++)
-        if (i0 + 4 * n < a.n_copy) x[n] = *reinterpret_cast<const u32x4_t*>(in + (int64_t)(a.copy_row + i0 + 4 * n) * tok + c);
-#pragma unroll
-      for (int n = 0; n < 8; n++)
-        if (i0 + 4 * n < a.n_copy) *reinterpret_cast<u32x4_t*>(ring + (size_t)((a.copy_slot + i0 + 4 * n) % a.W_cap) * kD + c) = x[n];
+    if (tile_in >= a.n_tiles) {       // window rows that land in slots which no tile of the launch reads
+      copy_rows((tile_in - a.n_tiles + a.copy_tile0) * kTile, a.n_read, a.W_cap);
       return;
     }
   }
@@ -190,64 +359,70 @@ __global__ __launch_bounds__(128, 5) void quantize_pack_kernel(QuantArgs a) {
     if (wave == 0 && (tile_abs < a.k_tile_a || tile_abs >= a.k_tile_b)) return;   // wave-uniform; the waves never synchronize
   }
   uint32_t* rec = a.packed + ((size_t)u * a.tiles_cap + (size_t)(a.tile0 + tile_in)) * record_words(KB, VB);
+  // The tile's rows: the first n_old from ring slots, the rest from the input. Slots of one tile never wrap (everything is in steps of 32),
+  // so either part is a base and a stride.
+  int slot0 = a.ring_w0 + tile_in * kTile;
+  if constexpr (PARTIAL) slot0 %= a.W_cap;        // (the launch may span more rows than the ring has slots; only rows of live tokens are read)
+  else if (slot0 >= a.W_cap) slot0 -= a.W_cap;
+  const int n_old = PARTIAL ? kTile : a.n_ring - tile_in * kTile;
+  const uint16_t* old_rows = ring + (int64_t)slot0 * kD;
+  const uint16_t* new_rows = in - (int64_t)n_old * tok;           // row t of the tile, t >= n_old, at new_rows + t * tok
+  // a tile all of one kind, the usual case
+  const bool whole = PARTIAL || n_old >= kTile || n_old <= 0;
+  const uint16_t* rows = PARTIAL || n_old > 0 ? old_rows : new_rows;
+  const int64_t stride = PARTIAL || n_old > 0 ? kD : tok;
   uint32_t hi[16];
 #pragma unroll
   for (int i = 0; i < 16; i++) hi[i] = 0;
 
   if (wave == 0) {
-    const int64_t k_off = b * a.k_unit_b + jh * a.k_unit_h;
     const int d0 = 32 * q + 8 * kq + 2 * j;
     uint32_t xw[kTile];                              // (x[tau][d0], x[tau][d0 + 1])
+    if (whole) {
+      const uint16_t* row = rows;
 #pragma unroll
-    for (int t = 0; t < kTile; t++) {
-      const uint16_t* rowp = PARTIAL ? ring_row(a.k_ring, a, u, tile_in * kTile + t) : source_row(a.k_ring, a.k, a.k_tok, k_off, a, u, tile_in * kTile + t);
-      xw[t] = *reinterpret_cast<const uint32_t*>(rowp + d0);
-    }
-    half2_t mn2 = as_half2(xw[0]), mx2 = mn2;
+      for (int t = 0; t < kTile; t++) { xw[t] = load_row<S, uint32_t>(row + d0); row += stride; }
+    } else {
 #pragma unroll
-    for (int t = 1; t < kTile; t++) {
-      mn2 = __builtin_elementwise_min(mn2, as_half2(xw[t]));
-      mx2 = __builtin_elementwise_max(mx2, as_half2(xw[t]));
+      for (int t = 0; t < kTile; t++) xw[t] = load_row<kCached, uint32_t>((t < n_old ? old_rows + t * kD : new_rows + t * tok) + d0);
     }
+    half2_t mn2, mx2;
+    bool nan;
+    extremes(xw, mn2, mx2, nan);
     const GroupParams g0 = group_params<KB>((float)mn2[0], (float)mx2[0]);
     const GroupParams g1 = group_params<KB>((float)mn2[1], (float)mx2[1]);
+    const uint64_t slow = __builtin_amdgcn_ballot_w64(g0.slow || g1.slow || nan);
     // metadata word 4*(d0/2) + f: scale pair (f = 0), minimum pair (f = 1)
-    *reinterpret_cast<u32x2_t*>(rec + 4 * (d0 >> 1)) =
+    *reinterpret_cast<u32x2_t*>((PARTIAL ? rec : s_meta) + 4 * (d0 >> 1)) =
         u32x2_t{(uint32_t)g0.scale_h | ((uint32_t)g1.scale_h << 16), (uint32_t)g0.zero_h | ((uint32_t)g1.zero_h << 16)};
     uint32_t w[acc_words<KB>()];
 #pragma unroll
     for (int i = 0; i < acc_words<KB>(); i++) w[i] = 0;
 #pragma unroll
-    for (int t0 = 0; t0 < kTile; t0 += 4) {
-      uint32_t b0[4], b1[4];                         // biased codes of the lane's two channels
-      bool near = g0.slow || g1.slow;
+    for (int t0 = 0; t0 < kTile; t0 += 8) {
+      uint32_t bc[16];                               // biased codes: the lane's first channel, then its second
+      const uint32_t pairs[8] = {xw[t0], xw[t0 + 1], xw[t0 + 2], xw[t0 + 3], xw[t0 + 4], xw[t0 + 5], xw[t0 + 6], xw[t0 + 7]};
+      quantize_batch<KB, true>(bc, pairs, g0, g1, t0, slow);
+      // tokens t0 + n and t0 + 4 + n are the two token halves m of the same word of the column group
 #pragma unroll
       for (int n = 0; n < 4; n++) {
-        const half2_t xv = as_half2(xw[t0 + n]);
-        b0[n] = quantize_fast<KB>(diff(xv[0], g0.mn), g0, t0 + n, near);
-        b1[n] = quantize_fast<KB>(diff(xv[1], g1.mn), g1, t0 + n, near);
-      }
-      if (near) {
-#pragma unroll
-        for (int n = 0; n < 4; n++) {
-          const half2_t xv = as_half2(xw[t0 + n]);
-          b0[n] = quantize_exact<KB>(diff(xv[0], g0.mn), g0, t0 + n);
-          b1[n] = quantize_exact<KB>(diff(xv[1], g1.mn), g1, t0 + n);
-        }
-      }
-#pragma unroll
-      for (int n = 0; n < 4; n++) {
-        const int t = t0 + n;
-        // the two codes side by side: the low halves of the biased codes are the codes
-        const uint32_t pair = __builtin_amdgcn_perm(b1[n], b0[n], 0x05040100u);
-        const int i = 4 * (t >> 3) + (t & 3), m = (t & 7) >> 2;       // word of the column group, token half
+        const int i = 4 * (t0 >> 3) + n;
+        // the codes of the two channels side by side: the low halves of the biased codes are the codes
+        const uint32_t p0 = __builtin_amdgcn_perm(bc[8 + n], bc[n], 0x05040100u), p1 = __builtin_amdgcn_perm(bc[12 + n], bc[4 + n], 0x05040100u);
         if constexpr (KB == 1) {
-          hi[i] |= pair << (8 * (j & 1) + 2 * q + m);                  // the code is the plane's bit
+          hi[i] = (p0 | (p1 << 1)) << (8 * (j & 1) + 2 * q);           // the code is the plane's bit
         } else if constexpr (KB == 4) {
-          w[16 * m + i] |= pair << (4 * q);                            // chunk m, field ks
+          w[i] = p0 << (4 * q);                                        // chunk m, field ks
+          w[16 + i] = p1 << (4 * q);
         } else {
-          w[i] |= (pair & 0x00030003u) << (2 * q + 8 * m);             // slot ks + 4*m
-          if constexpr (KB == 3) hi[i] |= ((pair >> 2) & 0x00010001u) << (8 * (j & 1) + 2 * q + m);
+          const uint32_t both = p0 | (p1 << 8);                        // slots ks + 4*m
+          if constexpr (KB == 2) {
+            w[i] = both << (2 * q);
+          } else {
+            w[i] = (both & 0x03030303u) << (2 * q);
+            const uint32_t top = (both >> 2) & 0x01010101u;
+            hi[i] = ((top | (top >> 7)) & 0x00030003u) << (8 * (j & 1) + 2 * q);
+          }
         }
       }
     }
@@ -255,47 +430,71 @@ __global__ __launch_bounds__(128, 5) void quantize_pack_kernel(QuantArgs a) {
     for (int i = 0; i < acc_words<KB>(); i++) { w[i] |= quad_x1(w[i]); w[i] |= quad_x2(w[i]); }
     if constexpr (KB == 3 || KB == 1) {
 #pragma unroll
-      for (int i = 0; i < 16; i++) { hi[i] |= quad_x1(hi[i]); hi[i] |= quad_x2(hi[i]); hi[i] |= (uint32_t)__shfl_xor((int)hi[i], 4); }
+      for (int i = 0; i < 16; i++) { hi[i] |= quad_x1(hi[i]); hi[i] |= quad_x2(hi[i]); hi[i] |= lane_x4(hi[i]); }
     }
-    store_words<KB>(rec + kMetaWords, w, hi, kq, j, q);
+    if constexpr (PARTIAL) put_words<KB, false>(rec + kMetaWords, w, hi, kq, j, q);
+    else put_words<KB, false>(s_key, w, hi, kq, j, q);
   } else {
-    const int64_t v_off = b * a.v_unit_b + jh * a.v_unit_h;
     const int tau0 = 8 * kq + 2 * j;
-    u32x4_t xr[2][4];                                // rows tau0, tau0 + 1: channels 32*q .. 32*q + 31
     // PARTIAL: which of the lane's two tokens, and of the two of lane j ^ 1, are among those that leave now
     auto leaves = [&](int tau) { const int t = (a.tile0 + tile_in) * kTile + tau; return !PARTIAL || (t >= a.v_tok_a && t < a.v_tok_b); };
     const bool mine[2] = {leaves(tau0), leaves(tau0 + 1)};
+    // rows 4n + lane/16, piece lane%16 of 16 bytes; piece p of row t lies at p ^ (t/2 % 4) of its row in LDS: the 16 lanes that read
+    // together (4 rows, 4 pieces) then find theirs in distinct banks
+    {
+      const int r4 = lane >> 4, c = lane & 15;
+      u32x4_t x[8];
+#pragma unroll
+      for (int n = 0; n < 8; n++) x[n] = u32x4_t{0, 0, 0, 0};
+      if (whole) {
+        const uint16_t* row = rows + r4 * stride + 8 * c;
+#pragma unroll
+        for (int n = 0; n < 8; n++) {
+          if (leaves(4 * n + r4)) x[n] = load_row<S, u32x4_t>(row);
+          row += 4 * stride;
+        }
+      } else {
+#pragma unroll
+        for (int n = 0; n < 8; n++) {
+          const int t = 4 * n + r4;
+          x[n] = load_row<kCached, u32x4_t>((t < n_old ? old_rows + t * kD : new_rows + t * tok) + 8 * c);
+        }
+      }
+#pragma unroll
+      for (int n = 0; n < 8; n++) {
+        const int t = 4 * n + r4;
+        *reinterpret_cast<u32x4_t*>(s_value + 64 * t + 4 * (c ^ ((t >> 1) & 3))) = x[n];
+      }
+      wave_lds_fence();
+    }
+    u32x4_t xr[2][4];                                // rows tau0, tau0 + 1: channels 32*q .. 32*q + 31
 #pragma unroll
     for (int hh = 0; hh < 2; hh++)
 #pragma unroll
-      for (int c = 0; c < 4; c++) {
-        xr[hh][c] = u32x4_t{0, 0, 0, 0};
-        if (mine[hh]) {
-          const uint16_t* rowp = PARTIAL ? ring_row(a.v_ring, a, u, tile_in * kTile + tau0 + hh) : source_row(a.v_ring, a.v, a.v_tok, v_off, a, u, tile_in * kTile + tau0 + hh);
-          xr[hh][c] = *reinterpret_cast<const u32x4_t*>(rowp + 32 * q + 8 * c);
-        }
-      }
+      for (int c = 0; c < 4; c++) xr[hh][c] = *reinterpret_cast<const u32x4_t*>(s_value + 64 * (tau0 + hh) + 4 * ((4 * q + c) ^ j));
     const uint32_t wmask = (mine[0] ? 0x0000FFFFu : 0u) | (mine[1] ? 0xFFFF0000u : 0u);
     // a plane word holds the pairs j (even, bits 0-7 and 16-23) and j + 1 (bits 8-15 and 24-31); the even lane stores it
     uint32_t hmask = (mine[0] ? 0x000000FFu : 0u) | (mine[1] ? 0x00FF0000u : 0u);
     if constexpr (PARTIAL) hmask |= (leaves(tau0 + 2) ? 0x0000FF00u : 0u) | (leaves(tau0 + 3) ? 0xFF000000u : 0u);
     else hmask = 0xFFFFFFFFu;
     GroupParams gp[2];
+    uint64_t slow[2];
 #pragma unroll
     for (int hh = 0; hh < 2; hh++) {
-      half2_t mn2 = as_half2(xr[hh][0][0]), mx2 = mn2;
+      uint32_t x[16];
 #pragma unroll
-      for (int e = 1; e < 16; e++) {
-        mn2 = __builtin_elementwise_min(mn2, as_half2(xr[hh][e >> 2][e & 3]));
-        mx2 = __builtin_elementwise_max(mx2, as_half2(xr[hh][e >> 2][e & 3]));
-      }
+      for (int e = 0; e < 16; e++) x[e] = xr[hh][e >> 2][e & 3];
+      half2_t mn2, mx2;
+      bool nan;
+      extremes(x, mn2, mx2, nan);
       const float mn = fminf((float)mn2[0], (float)mn2[1]), mx = fmaxf((float)mx2[0], (float)mx2[1]);
       gp[hh] = group_params<VB>(mn, mx);
+      slow[hh] = __builtin_amdgcn_ballot_w64(gp[hh].slow || nan);
     }
     // metadata word 4*(16*g + tau0/2) + f: scale pair (f = 2), minimum pair (f = 3)
     {
       const uint32_t sc2 = (uint32_t)gp[0].scale_h | ((uint32_t)gp[1].scale_h << 16), zp2 = (uint32_t)gp[0].zero_h | ((uint32_t)gp[1].zero_h << 16);
-      uint32_t* mp = rec + 4 * (16 * q + (tau0 >> 1)) + 2;
+      uint32_t* mp = (PARTIAL ? rec : s_meta) + 4 * (16 * q + (tau0 >> 1)) + 2;
       if constexpr (!PARTIAL) {
         *reinterpret_cast<u32x2_t*>(mp) = u32x2_t{sc2, zp2};
       } else {
@@ -303,51 +502,34 @@ __global__ __launch_bounds__(128, 5) void quantize_pack_kernel(QuantArgs a) {
         put_word<true>(mp + 1, zp2, wmask);
       }
     }
-    // partial words with the lane-independent shifts first (fields of slot parity e/16 and token parity hh)
-    uint32_t pw[16], ph[16];
-#pragma unroll
-    for (int i = 0; i < 16; i++) { pw[i] = 0; ph[i] = 0; }
+    // partial words with the lane-independent shifts first: one token's fields (slot parity e/16), then the two tokens side by side
+    constexpr int kField = VB == 4 || VB == 3 ? 4 : 2;          // (3-bit codes: taken apart into planes afterwards)
+    uint32_t pw[2][16];
 #pragma unroll
     for (int hh = 0; hh < 2; hh++)
 #pragma unroll
-      for (int e0 = 0; e0 < 32; e0 += 8) {
-        uint32_t bc[8];                               // biased codes
-        bool near = gp[hh].slow;
+      for (int e0 = 0; e0 < 32; e0 += 16) {
+        uint32_t bc[16];                               // biased codes
+        uint32_t pairs[8];
 #pragma unroll
-        for (int n = 0; n < 8; n++) {
-          const half2_t xv = as_half2(xr[hh][e0 >> 3][n >> 1]);
-          bc[n] = quantize_fast<VB>(diff(xv[n & 1], gp[hh].mn), gp[hh], e0 + n, near);
-        }
-        if (near) {
+        for (int n = 0; n < 8; n++) pairs[n] = xr[hh][(e0 >> 3) + (n >> 2)][n & 3];
+        quantize_batch<VB, false>(bc, pairs, gp[hh], gp[hh], e0, slow[hh]);
 #pragma unroll
-          for (int n = 0; n < 8; n++) {
-            const half2_t xv = as_half2(xr[hh][e0 >> 3][n >> 1]);
-            bc[n] = quantize_exact<VB>(diff(xv[n & 1], gp[hh].mn), gp[hh], e0 + n);
-          }
-        }
-#pragma unroll
-        for (int n = 0; n < 8; n++) {
+        for (int n = 0; n < 16; n++) {
           const int e = e0 + n;
-          const int i = e & 15, sp = e >> 4;
-          // fields never overflow, so the shifted biased codes are added up and the bias taken off afterwards
-          if constexpr (VB == 1) {
-            ph[i] += bc[n] << (16 * hh + 2 * sp);
-          } else if constexpr (VB == 4) {
-            pw[i] += bc[n] << (16 * hh + 4 * sp);
-          } else if constexpr (VB == 2) {
-            pw[i] += bc[n] << (16 * hh + 2 * sp);
-          } else {
-            pw[i] |= (bc[n] & 3u) << (16 * hh + 2 * sp);
-            ph[i] |= ((bc[n] >> 2) & 1u) << (16 * hh + 2 * sp);
-          }
+          // (the bias lies above bit 16 and stays there)
+          pw[hh][e & 15] = e < 16 ? bc[n] : (bc[n] << kField) + pw[hh][e & 15];
         }
       }
-    if constexpr (VB != 3) {
-      constexpr int kField = VB == 4 ? 4 : 2;
-      constexpr uint32_t kBiasSum = (kBias << 0) + (kBias << kField) + (kBias << 16) + (kBias << (16 + kField));
+    uint32_t ph[16];
 #pragma unroll
-      for (int i = 0; i < 16; i++) {
-        if constexpr (VB == 1) ph[i] -= kBiasSum; else pw[i] -= kBiasSum;
+    for (int i = 0; i < 16; i++) {
+      const uint32_t both = __builtin_amdgcn_perm(pw[1][i], pw[0][i], 0x05040100u);       // the low halves side by side
+      pw[0][i] = both;
+      ph[i] = both;
+      if constexpr (VB == 3) {
+        pw[0][i] = (both & 0x00030003u) | ((both >> 2) & 0x000C000Cu);
+        ph[i] = ((both >> 2) & 0x00010001u) | ((both >> 4) & 0x00040004u);
       }
     }
     uint32_t w[acc_words<VB>()];
@@ -355,7 +537,7 @@ __global__ __launch_bounds__(128, 5) void quantize_pack_kernel(QuantArgs a) {
       // slot 2*g + sp: chunk g/2, field 2*(g%2) + sp; the chunk's words are complete after the pair (g, g^1)
 #pragma unroll
       for (int i = 0; i < 16; i++) {
-        uint32_t v = pw[i] << (8 * (q & 1));
+        uint32_t v = pw[0][i] << (8 * (q & 1));
         v |= quad_x1(v);
         const uint32_t other = quad_x2(v);            // the other chunk's words, from lane g ^ 2
         w[i] = (q & 2) ? other : v;                  // chunk 0
@@ -364,7 +546,7 @@ __global__ __launch_bounds__(128, 5) void quantize_pack_kernel(QuantArgs a) {
     } else {
 #pragma unroll
       for (int i = 0; i < 16; i++) {
-        w[i] = pw[i] << (4 * q);
+        w[i] = pw[0][i] << (4 * q);
         w[i] |= quad_x1(w[i]); w[i] |= quad_x2(w[i]);
       }
       if constexpr (VB == 3 || VB == 1) {
@@ -372,11 +554,24 @@ __global__ __launch_bounds__(128, 5) void quantize_pack_kernel(QuantArgs a) {
 #pragma unroll
         for (int i = 0; i < 16; i++) {
           hi[i] = ph[i] << (8 * (j & 1) + 4 * (q & 1) + (q >> 1));
-          hi[i] |= quad_x1(hi[i]); hi[i] |= quad_x2(hi[i]); hi[i] |= (uint32_t)__shfl_xor((int)hi[i], 4);
+          hi[i] |= quad_x1(hi[i]); hi[i] |= quad_x2(hi[i]); hi[i] |= lane_x4(hi[i]);
         }
       }
     }
-    store_words<VB, PARTIAL>(rec + kMetaWords + tile_words(KB), w, hi, kq, j, q, wmask, hmask);
+    if constexpr (PARTIAL) {
+      put_words<VB, true>(rec + kMetaWords + tile_words(KB), w, hi, kq, j, q, wmask, hmask);
+    } else {
+      wave_lds_fence();      // (the rows in this area have been read)
+      put_words<VB, false>(s_value, w, hi, kq, j, q);
+    }
+  }
+  if constexpr (!PARTIAL) {
+    __syncthreads();         // the metadata of both waves, and the wave's own section, are in LDS
+    if (wave == 0) store_section<KB, S>(rec + kMetaWords, s_key, lane);
+    else store_section<VB, S>(rec + kMetaWords + tile_words(KB), s_value, lane);
+    put<S>(reinterpret_cast<u32x2_t*>(rec) + 64 * wave + lane, reinterpret_cast<const u32x2_t*>(s_meta)[64 * wave + lane]);
+    // New rows that land in slots this tile was read from (both waves have their rows: the barrier): this workgroup fills those.
+    if (tile_in * kTile < a.n_read) copy_rows(tile_in * kTile, 0, a.n_read);
   }
 }
 
@@ -421,8 +616,10 @@ __global__ __launch_bounds__(768) void stream_read_kernel(const u32x4_t* buf, si
 }
 
 template <int KB, int VB, bool PARTIAL>
-hipError_t launch_qp(const QuantArgs& a, dim3 grid, hipStream_t s) {
-  quantize_pack_kernel<KB, VB, PARTIAL><<<grid, 128, 0, s>>>(a);
+hipError_t launch_qp(const QuantArgs& a, dim3 grid, Stream stream, hipStream_t s) {
+  if (PARTIAL || stream == kCached) quantize_pack_kernel<KB, VB, PARTIAL, kCached><<<grid, 128, 0, s>>>(a);
+  else if (stream == kStreamOut) quantize_pack_kernel<KB, VB, PARTIAL, PARTIAL ? kCached : kStreamOut><<<grid, 128, 0, s>>>(a);
+  else quantize_pack_kernel<KB, VB, PARTIAL, PARTIAL ? kCached : kStreamBoth><<<grid, 128, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -430,24 +627,31 @@ hipError_t launch_qp(const QuantArgs& a, dim3 grid, hipStream_t s) {
 template <bool PARTIAL>
 hipError_t launch_bits(const QuantArgs& a, int k_bits, int v_bits, int n_tiles, int units, hipStream_t s) {
   if (n_tiles == 0 || units == 0) return hipSuccess;
-  const dim3 grid(n_tiles + (PARTIAL ? 0 : (a.n_copy + kTile - 1) / kTile), a.Hkv, units / a.Hkv);
+  const dim3 grid(n_tiles + (PARTIAL ? 0 : a.copy_tiles), a.Hkv, units / a.Hkv);
+  // Rows are loaded past the caches where a launch reads more than the memory-side cache (256 MB) can still hold of what was
+  // written last. A variant that only loads and stores, 256 units of 44, 60, 76, 92, 123 tiles (16 KB each): cached 31.4, 42.3, 61.6, 76.4,
+  // 101.9 us, past the caches 33.7, 45.7, 57.4, 69.3, 92.9. Records are stored past them but for the few tiles of a decode step, which are
+  // read next. (The same variant, 2048 tiles: 5.8 us with cached stores, 5.1 without; 15 360: 43.8, 42.3; the whole kernel with 512
+  // tiles: 6.6, 7.0.)
+  const size_t tiles = (size_t)n_tiles * units;
+  const Stream streaming = tiles * (2 * kTile * kD * 2) > ((size_t)256 << 20) ? kStreamBoth : tiles >= 2048 ? kStreamOut : kCached;
   switch (k_bits * 10 + v_bits) {
-    case 11: return launch_qp<1, 1, PARTIAL>(a, grid, s);
-    case 12: return launch_qp<1, 2, PARTIAL>(a, grid, s);
-    case 13: return launch_qp<1, 3, PARTIAL>(a, grid, s);
-    case 14: return launch_qp<1, 4, PARTIAL>(a, grid, s);
-    case 21: return launch_qp<2, 1, PARTIAL>(a, grid, s);
-    case 22: return launch_qp<2, 2, PARTIAL>(a, grid, s);
-    case 23: return launch_qp<2, 3, PARTIAL>(a, grid, s);
-    case 24: return launch_qp<2, 4, PARTIAL>(a, grid, s);
-    case 31: return launch_qp<3, 1, PARTIAL>(a, grid, s);
-    case 32: return launch_qp<3, 2, PARTIAL>(a, grid, s);
-    case 33: return launch_qp<3, 3, PARTIAL>(a, grid, s);
-    case 34: return launch_qp<3, 4, PARTIAL>(a, grid, s);
-    case 41: return launch_qp<4, 1, PARTIAL>(a, grid, s);
-    case 42: return launch_qp<4, 2, PARTIAL>(a, grid, s);
-    case 43: return launch_qp<4, 3, PARTIAL>(a, grid, s);
-    case 44: return launch_qp<4, 4, PARTIAL>(a, grid, s);
+    case 11: return launch_qp<1, 1, PARTIAL>(a, grid, streaming, s);
+    case 12: return launch_qp<1, 2, PARTIAL>(a, grid, streaming, s);
+    case 13: return launch_qp<1, 3, PARTIAL>(a, grid, streaming, s);
+    case 14: return launch_qp<1, 4, PARTIAL>(a, grid, streaming, s);
+    case 21: return launch_qp<2, 1, PARTIAL>(a, grid, streaming, s);
+    case 22: return launch_qp<2, 2, PARTIAL>(a, grid, streaming, s);
+    case 23: return launch_qp<2, 3, PARTIAL>(a, grid, streaming, s);
+    case 24: return launch_qp<2, 4, PARTIAL>(a, grid, streaming, s);
+    case 31: return launch_qp<3, 1, PARTIAL>(a, grid, streaming, s);
+    case 32: return launch_qp<3, 2, PARTIAL>(a, grid, streaming, s);
+    case 33: return launch_qp<3, 3, PARTIAL>(a, grid, streaming, s);
+    case 34: return launch_qp<3, 4, PARTIAL>(a, grid, streaming, s);
+    case 41: return launch_qp<4, 1, PARTIAL>(a, grid, streaming, s);
+    case 42: return launch_qp<4, 2, PARTIAL>(a, grid, streaming, s);
+    case 43: return launch_qp<4, 3, PARTIAL>(a, grid, streaming, s);
+    case 44: return launch_qp<4, 4, PARTIAL>(a, grid, streaming, s);
   }
   return hipErrorInvalidValue;
 }

@@ -93,6 +93,44 @@ def test_quantize_pack_near_tie_quotients(bits):
     assert_cache_equal(rc, gc)
 
 
+@pytest.mark.parametrize("kb,vb", [(3, 3), (2, 3), (3, 4), (1, 2)])
+def test_quantize_pack_ties(kb, vb):
+    """Groups full of exact ties at the plain step and, in elements 10 and 21, at the step of the 2-bit elements of a 3-bit group (itself
+    rounded to fp32 unless the scale is a multiple of 3), their neighbours one fp16 number away, and tiny ranges with a subnormal
+    scale: codes that the bracket leaves open, bit for bit as the oracle has them."""
+    print(f"case ties kb={kb} vb={vb}", flush=True)
+    B, Hkv, T = 1, 2, 160
+    rng = np.random.default_rng(70 + 10 * kb + vb)
+
+    def groups(n, bits):
+        q_max = (1 << bits) - 1
+        out = np.zeros((n, 32), np.float16)
+        for g in range(n):
+            s = np.float16(rng.choice([3 * 2.0 ** -6, 2.0 ** -4, rng.uniform(0.01, 2.0), 2.0 ** -20]))
+            step = np.full(32, float(s))
+            if bits == 3:
+                step[[10, 21]] = np.float32(np.float32(s) * np.float32(7)) / np.float32(3)
+            top = np.full(32, q_max)
+            if bits == 3:
+                top[[10, 21]] = 3
+            x = (rng.integers(0, top) + 0.5) * step
+            x = x.astype(np.float16)
+            x = np.where(rng.random(32) < 0.25, np.nextafter(x, np.float16(rng.choice([-1, 9]))), x).astype(np.float16)
+            ends = [e for e in rng.permutation(32) if e not in (10, 21)][:2]
+            x[ends[0]], x[ends[1]] = 0, np.float16(float(s) * q_max)
+            out[g] = np.clip(x, 0, x[ends[1]])
+        return out
+
+    v = groups(B * Hkv * T * 4, vb).reshape(B, Hkv, T, 128)
+    kg = groups(B * Hkv * (T // 32) * 128, kb).reshape(B, Hkv, T // 32, 128, 32)
+    k = np.ascontiguousarray(kg.transpose(0, 1, 2, 4, 3)).reshape(B, Hkv, T, 128)
+    q = np.zeros((B, Hkv, 128), np.float16)
+    _, _, _, rc, gc, shape, cfg = make_pair(B, Hkv, Hkv, T + 32, 32, kb, vb,
+                                            q_k_v=(q, np.concatenate([k, k[:, :, :32]], 2), np.concatenate([v, v[:, :, :32]], 2)))
+    assert gc.n_q == rc.n_q == T
+    assert_cache_equal(rc, gc)
+
+
 def test_quantize_pack_offsets_and_strides():
     """Writing at a token offset into a larger cache, from a strided (sliced) source."""
     import torch

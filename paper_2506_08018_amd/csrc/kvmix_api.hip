@@ -460,7 +460,8 @@ int launch_plan(const AttnPlan& p, void* stream) {
 constexpr size_t kScratchBytes = KVMIX_STATIC_SCRATCH_BYTES;
 constexpr size_t kScratchCounterBytes = 16384;
 static_assert(kScratchCounterBytes / sizeof(uint32_t) >= kScratchBytes / (2 * (kD + 2) * sizeof(float)), "counters of every shape that fits");
-static __device__ __align__(256) unsigned char scratch[kScratchCounterBytes + kScratchBytes];
+// Partials of groups of up to 4 heads are zero between calls, those of larger groups are left as they are: each kind has a place of its own.
+static __device__ __align__(256) unsigned char scratch[kScratchCounterBytes + 2 * kScratchBytes];
 // In host code the array's name is only a handle; its address on a device comes from hipGetSymbolAddress,
 // asked once per device with that device current. Each GPU holds its own copy at its own address.
 std::mutex g_scratch_mutex;
@@ -471,9 +472,8 @@ __global__ void clear_words_kernel(uint32_t* p, int n) {
   if (i < n) p[i] = 0u;
 }
 
-// Address of the current device's copy of `scratch`. The first call on a device also clears the arrival counters
-// at its start on `stream`, ahead of the first launch that uses them; afterwards every attention launch leaves them
-// zero again.
+// Address of the current device's copy of `scratch`. The first call on a device also clears the arrival counters and the partials behind
+// them on `stream`, ahead of the first launch that uses them; afterwards every attention launch leaves them zero again.
 int scratch_address(void** ptr, hipStream_t stream) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -485,7 +485,7 @@ int scratch_address(void** ptr, hipStream_t stream) {
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return hip_fail(e);
     if (!p) return hip_fail(hipErrorInvalidSymbol);
-    constexpr int kWords = (int)(kScratchCounterBytes / 4);
+    constexpr int kWords = (int)((kScratchCounterBytes + kScratchBytes) / 4);
     clear_words_kernel<<<kWords / 256, 256, 0, stream>>>(reinterpret_cast<uint32_t*>(p), kWords);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e);
@@ -527,7 +527,7 @@ int kvmix_decode_attn_static(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, 
     st = scratch_address(&ptr, (hipStream_t)stream);
     if (st) return st;
     plan.a.counters = reinterpret_cast<uint32_t*>(ptr);
-    plan.a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ptr) + kScratchCounterBytes);
+    plan.a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ptr) + kScratchCounterBytes + (plan.G <= 4 ? 0 : kScratchBytes));
     plan.m.part = plan.a.part;
   } else {
     plan.a.counters = nullptr; plan.a.part = nullptr;

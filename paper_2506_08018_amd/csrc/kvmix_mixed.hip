@@ -369,8 +369,9 @@ __global__ __launch_bounds__(kMixWaves * kWave) void mixed_fronts_kernel(MixedAr
     const int blocks = a.G / a.G_main;
     const size_t uo = (size_t)u * blocks + hg / a.G_main;
     float* pp = a.part + ((uo * a.n_parts + a.part_index) * a.G_main + hg % a.G_main) * (kD + 2);
-    if (d == 0) { pp[0] = M; pp[1] = L; }
-    pp[2 + d] = Ov;
+    // (never a zero: to the merge a zero word is one that is not there yet)
+    if (d == 0) { pp[0] = M == 0.0f ? -0.0f : M; pp[1] = L == 0.0f ? -0.0f : L; }
+    pp[2 + d] = Ov == 0.0f ? -0.0f : Ov;
   }
 }
 

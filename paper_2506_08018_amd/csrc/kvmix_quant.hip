@@ -218,8 +218,6 @@ __device__ __forceinline__ void quantize_batch(uint32_t (&code)[16], const uint3
   }
 }
 
-__device__ __forceinline__ half2_t as_half2(uint32_t w) { return __builtin_bit_cast(half2_t, w); }
-
 // Number of 32-bit word accumulators a lane fills for one code section before the lanes of its quad are
 // combined: words i = 0..15 of its (kq, j) column group; 4-bit sections have two chunks. 1-bit sections
 // consist of the bit plane alone (the `hi` words below, stored at the start of the section).

@@ -476,6 +476,40 @@ def test_launches_in_blocks_of_sixteen_heads(units, G, kb, vb, tiles, n_w, n_spl
     assert not counters_of(ws, shape).any()
 
 
+@pytest.mark.parametrize("G,kb,vb", [(1, 2, 2), (2, 3, 2), (4, 2, 4), (4, 3, 3)])
+def test_split_counts_share_a_workspace(G, kb, vb):
+    """Partials of groups of up to 4 heads: one workspace through calls of many split counts (around the numbers of partials that are
+    requested together, more splits than tiles, unsplit in between), each against the oracle; all of the workspace is zero after every
+    call. The static entry point in turn with a group of 8 heads, whose partials stay."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case shared workspace G={G} kb={kb} vb={vb}", flush=True)
+    T, W = 32 * 70 + 45, 32
+    q, k, v = synth.gen_layer_numpy(1500 + G, 0, 1, 2 * G, 2, T)
+    _, _, _, rc, gc, shape, cfg = make_pair(1, 2 * G, 2, T, W, kb, vb, q_k_v=(q, k, v))
+    st, want = rc.decode_attn(u16(q))
+    assert st == 0
+    q8, k8, v8 = synth.gen_layer_numpy(1510 + G, 0, 1, 16, 2, T)
+    _, _, _, rc8, gc8, shape8, cfg8 = make_pair(1, 16, 2, T, W, 2, 2, q_k_v=(q8, k8, v8))
+    st, want8 = rc8.decode_attn(u16(q8))
+    assert st == 0
+    qt, qt8 = torch.from_numpy(q).cuda(), torch.from_numpy(q8).cuda()
+    out, out8 = torch.zeros_like(qt), torch.zeros_like(qt8)
+    ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
+    for n_splits in [2, 64, 3, 8, 9, 1, 16, 17, 32, 33, 31, 0, 7]:
+        for _ in range(3):
+            out.fill_(float("nan"))
+            kv.decode_attn(shape, cfg, qt, gc, out, ws, n_splits=n_splits)
+            torch.cuda.synchronize()
+            assert_attn_close(t16(out), want, f"{n_splits} splits", tight=True)
+            assert not ws.any()
+        kv.decode_attn_static(shape8, cfg8, qt8, gc8, out8, n_splits=n_splits)
+        kv.decode_attn_static(shape, cfg, qt, gc, out, n_splits=n_splits)
+        torch.cuda.synchronize()
+        assert_attn_close(t16(out8), want8, f"static, 8 heads, {n_splits} splits", tight=True)
+        assert_attn_close(t16(out), want, f"static, {n_splits} splits", tight=True)
+
+
 @pytest.mark.parametrize("W,W_cap,T0", [(32, 64, 0), (32, 64, 63), (32, 96, 37), (32, 128, 63), (64, 192, 64 + 31), (0, 32, 0), (0, 64, 31)])
 def test_chunk_copy_inside_the_quantizer_launch(W, W_cap, T0):
     """Rows that stay in the window ride in the quantizer's launch where no row lands in a slot that is still to be read, and are

@@ -14,11 +14,12 @@ COMMON = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall
 # uniform atomics would put a wait right behind them
 ATTN = ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
 # object -> (source, extra flags): the quantizer's arithmetic is specified operation by operation; the attention kernel exists
-# with 8 and with 12 waves per workgroup
+# with 8 and with 12 waves per workgroup, each without and with the tiles between a Key front and a Value front
 OBJECTS = {
     "kvmix_quant.o": ("kvmix_quant.hip", ["-ffp-contract=off"]),
-    "kvmix_attn8.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=8"]),
-    "kvmix_attn12.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=12"]),
+    "kvmix_attn8.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=8", "-DKVMIX_MIXED=0"]),
+    "kvmix_attn12.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=12", "-DKVMIX_MIXED=0"]),
+    "kvmix_attn12_fronts.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=12", "-DKVMIX_MIXED=1"]),
     "kvmix_mixed.o": ("kvmix_mixed.hip", ["-ffp-contract=off"]),
     "kvmix_api.o": ("kvmix_api.hip", []),
 }

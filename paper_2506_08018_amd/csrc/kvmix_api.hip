@@ -255,8 +255,8 @@ int kvmix_append(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint16
 namespace {
 
 // Everything an attention launch needs, filled by plan_attention after all host-side checks have passed.
-// `mixed`: the fronts of Keys and Values differ; the tokens between them go to a launch of their own (m) that
-// leaves one more partial for the main launch's merge.
+// `mixed`: the fronts of Keys and Values differ. Groups of up to 4 heads: the tiles between them are worked on by the same launch. Larger
+// groups: by a launch of their own (m) that leaves one more partial for the main launch's merge.
 struct AttnPlan { AttnArgs a; int kb, vb, G, block, units, waves; bool mixed; MixedArgs m; };
 
 constexpr int kWindowTileCost = 3;   // packed tiles that take a wave as long as one window tile
@@ -393,7 +393,8 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     }
   }
   AttnArgs a{};
-  const int n_parts = n_splits + (fr.mixed ? 1 : 0);
+  const bool in_launch = fr.mixed && G <= 4;       // no partial of their own
+  int n_parts = n_splits + (fr.mixed ? 1 : 0);
   if (n_parts > 1) {
     if (!workspace) return KVMIX_ERR_NULL;
     if (!aligned16(workspace)) return KVMIX_ERR_ALIGN;
@@ -401,6 +402,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     a.counters = reinterpret_cast<uint32_t*>(workspace);
     a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + counters_bytes(out_units(sh)));
   }
+  if (in_launch) n_parts = n_splits;      // (what a workspace is refused or accepted by is the same for all groups)
   // The counters' 256 bytes (at least) are shared out evenly: splits that arrive together then meet on fewer cache lines
   // (8 units x 32 splits, whose 256 arrivals queued up on one line for 1.3 us on average)
   a.counter_stride = 1;
@@ -412,7 +414,13 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   a.tiles_cap = c->T_cap / kTile; a.W_cap = c->W_cap; a.n_w = fr.n_w_eff;
   a.ring_tiles = c->W_cap / kTile; a.w0_tile = fr.w0_eff / kTile;
   a.n_splits = n_splits; a.n_parts = n_parts;
-  const int live = (fr.n_w_eff + kTile - 1) / kTile;
+  int live = (fr.n_w_eff + kTile - 1) / kTile;
+  if (in_launch) {
+    a.m_first = fr.packed_tiles; a.m_tiles = (int)((fr.t_a + kTile - 1) / kTile) - fr.packed_tiles;
+    a.m_end = (int)fr.t_a; a.m_front = c->n_q + c->v_lead; a.m_ahead = c->v_lead > 0;
+    a.m_ring = slot_of(c, (long long)fr.packed_tiles * kTile) / kTile;
+    live += !a.m_ahead ? a.m_tiles : a.m_front < a.m_end ? 1 : 0;
+  }
   a.win_each = live / n_splits; a.win_extra = live % n_splits;
   a.win_tiles = kWindowTileCost < fr.packed_tiles / n_splits ? kWindowTileCost : fr.packed_tiles / n_splits;
   a.items_q = (fr.packed_tiles + a.win_extra * a.win_tiles) / n_splits;
@@ -424,11 +432,11 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   plan->vb = cfg->v_bits == 16 ? 2 : cfg->v_bits;
   plan->G = G; plan->units = units;
   plan->block = block;
-  plan->waves = attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, plan->block, plan->vb);
+  plan->waves = attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles + (a.m_ahead ? a.m_tiles : 0), n_splits, plan->block, plan->vb);
   plan->mixed = fr.mixed;
-  if (fr.mixed) {
-    // with the append inside the launch the new token must be a window token of the main launch
-    if (new_slot >= 0 && fr.n_w_eff < 1) return KVMIX_ERR_BAD_SHAPE;
+  // with the append inside the launch the new token must be a window token of the main launch
+  if (fr.mixed && new_slot >= 0 && fr.n_w_eff < 1) return KVMIX_ERR_BAD_SHAPE;
+  if (fr.mixed && !in_launch) {
     MixedArgs m{};
     m.q = q; m.packed = c->packed; m.k_win = c->k_win; m.v_win = c->v_win;
     m.part = a.part; m.n_parts = n_parts; m.part_index = n_splits;
@@ -444,12 +452,17 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
 }
 
 int launch_plan(const AttnPlan& p, void* stream) {
+  hipError_t e;
+  if (p.mixed && p.G <= 4) {
+    e = launch_decode_attn<12, true>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream);      // (does not fit the registers of 8 waves)
+    return e == hipSuccess ? KVMIX_OK : hip_fail(e);
+  }
   if (p.mixed) {
-    const hipError_t e = launch_mixed_fronts(p.m, p.units, (hipStream_t)stream);
+    e = launch_mixed_fronts(p.m, p.units, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e);
   }
-  const hipError_t e = p.waves == 8 ? launch_decode_attn<8>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream)
-                                    : launch_decode_attn<12>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream);
+  e = p.waves == 8 ? launch_decode_attn<8, false>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream)
+                   : launch_decode_attn<12, false>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream);
   return e == hipSuccess ? KVMIX_OK : hip_fail(e);
 }
 

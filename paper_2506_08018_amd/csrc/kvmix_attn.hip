@@ -33,9 +33,11 @@ namespace kvmix {
 
 namespace {
 
-// Waves per workgroup; this file is compiled once for each of the two forms (the launch picks one, see attn_waves in kvmix_api.hip).
+// Waves per workgroup; this file is compiled once for each of the two forms (the launch picks one, see attn_waves in kvmix_api.hip),
+// each without and with tiles between two fronts.
 // 12 waves, one workgroup per CU: 168 registers per lane. 8 waves: 128 registers, two workgroups per CU.
 constexpr int kNW = KVMIX_WAVES;
+constexpr bool kMixed = KVMIX_MIXED;     // with tiles between a Key front and a Value front
 constexpr int kMergeBatch = 32;          // splits whose partials the merging workgroup requests together (one round trip)
 // Reference of the running softmax (log2 units): numerators 2^(score - reference) are kept at or below 2^kRefCap;
 // when a score would exceed that, the reference is raised to (that score - kRefCap + 4), which leaves room for
@@ -246,8 +248,8 @@ template <int KB, int VB> struct Stage {
   }
 };
 
-__device__ __forceinline__ void st_agent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float ld_agent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+[[maybe_unused]] __device__ __forceinline__ void st_agent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+[[maybe_unused]] __device__ __forceinline__ float ld_agent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // Groups whose split partials tell of themselves: a word is zero until it has been stored (see the split merge).
 template <int G> constexpr bool kTagged = G <= 4;
@@ -362,7 +364,15 @@ template <int G, int NW> struct MergeLds {        // per-wave reference maximum 
   float l[NW][G];
 };
 
-template <int KB, int VB, int G, int NW>
+// MIXED: Keys and Values age at fronts of their own (groups of up to 4 heads); the tiles between the fronts have one side in a record and the other
+// in the ring. Two kinds of tile share a half with the window tiles and are worked on with them, two with the packed ones:
+//   Value front ahead: Keys from the ring, Values from the record (with the packed tiles); where the front stands inside a tile, the tokens
+//     behind it are a window tile of which only they count.
+//   Key front ahead: Keys from the record, Values from the ring (with the window tiles); the tokens before a front inside a tile are a
+//     packed tile of which only they count.
+// In a launch of their own on the vector unit these tiles took 13 us (14 tiles per unit of 128, 256 units, 1 head) next to 28 for the rest; a
+// decode step of two such layers, with its appends and flushes, went from 99.4 us to 80.3.
+template <int KB, int VB, int G, int NW, bool MIXED>
 __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(AttnArgs a) {
   constexpr int kWaves = NW;
   constexpr int kThreads = kWaves * kWave;
@@ -413,7 +423,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // loaded by the hi columns in use only (a load's cost at the start of a launch is its active lanes), copied to the lo columns later;
   // groups of 1 or 2 heads use it for window tiles only, and the other waves' requests are better spent on their first tiles (16 layers of
   // 256 units: 356.4 us with, 352.9 us without)
-  const bool needs_q = G > 2 || wave < a.win_each + (sp < a.win_extra ? 1 : 0);
+  const bool needs_q = MIXED || G > 2 || wave < a.win_each + (sp < a.win_extra ? 1 : 0);
 #pragma unroll
   for (int ks = 0; ks < 4; ks++) {
     qB[ks] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
@@ -455,9 +465,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   auto win_slot = [&](int r) { int wi = a.w0_tile + r; wi = wi >= a.ring_tiles ? wi - a.ring_tiles : wi; return wi * kTile; };   // first slot of the tile
   auto win_new = [&](int slot0) { return a.new_slot >= 0 && slot0 == (a.new_slot & ~31); };     // wave-uniform
   struct WinKeys { half8_t r[2][4]; };
-  auto win_load_k = [&](int r, int lane, WinKeys& w) {
+  // live: tokens of the tile (from its first row on) that are there, at least one
+  auto win_load_k = [&](int slot0, int live, int lane, WinKeys& w) {
     const int col = lane & 15, kq = lane >> 4;
-    const int slot0 = win_slot(r);
     const uint16_t* kw = a.k_win + ((size_t)u * a.W_cap + slot0) * kD;
     const uint16_t* kn = a.k_new + (size_t)u * kD;
     const bool has_new = win_new(slot0);
@@ -466,7 +476,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       const int tau = 8 * (col >> 2) + 4 * m + (col & 3);   // row `col` of M-tile m
       // a slot past the live tokens is not read: its lanes take the tile's first row instead (live, and already on its
       // way: a cache hit; k_new where the new token is that row), whose products the softmax mask discards
-      const int tau_r = r * kTile + tau < a.n_w ? tau : 0;
+      const int tau_r = tau < live ? tau : 0;
       const uint16_t* rowp = (has_new && tau_r == new_tau) ? kn : kw + (size_t)tau_r * kD;
 #pragma unroll
       for (int ks = 0; ks < 4; ks++) w.r[m][ks] = *reinterpret_cast<const half8_t*>(rowp + 32 * ks + 8 * kq);
@@ -475,18 +485,16 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // Value rows 4j .. 4j+3 per instruction, 16 bytes per lane in lane order: chunk c (8 channels) of row t goes to chunk
   // c ^ swizzle(t) of its row, so that the transposing reads below find their 8 rows x 32 bytes in distinct banks.
   auto swizzle = [](int t) { return 2 * ((t & 3) + 4 * ((t >> 3) & 1)); };
-  auto win_load_v = [&](int r, int lane) {
+  auto win_load_v = [&](int slot0, int live, int lo, int lane) {      // rows from lo on (0 but for tiles between two fronts)
     const int col = lane & 15, kq = lane >> 4;
-    const int slot0 = win_slot(r);
     // The resource spans the tile's rows that are live and in the ring (a new token is the last live row of its tile and not in
     // the ring yet). Rows beyond it are not read: their lanes write zeros, which meet a weight of zero (a dead slot may hold infinities
     // and NaN). A resource over the tile: a ring may be larger than 32-bit offsets reach.
-    const int live = a.n_w - r * kTile;
     const int n_rows = win_new(slot0) ? new_tau : live < kTile ? live : kTile;
     const rsrc_t rows = make_rsrc(a.v_win + ((size_t)u * a.W_cap + slot0) * kD, (uint32_t)n_rows * (kD * 2));
 #pragma unroll
     for (int j = 0; j < 8; j++)
-      buf_load_to_lds16(rows, 256u * (4 * j + kq) + 16u * (col ^ (2 * kq) ^ ((j & 2) ? 8 : 0)), 0, &T[4 * j][0]);
+      buf_load_to_lds16(rows, (MIXED && 4 * j + kq < lo ? 0x40000000u : 0u) + 256u * (4 * j + kq) + 16u * (col ^ (2 * kq) ^ ((j & 2) ? 8 : 0)), 0, &T[4 * j][0]);
   };
   // the append itself, one row of each side, 16 lanes each: requested with the tile, then stored into the ring and (the
   // Value row) into the staging area
@@ -579,22 +587,189 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   auto grab_take = [](int t) -> int { return __builtin_amdgcn_readfirstlane(t); };
   auto grab = [&]() -> int { return grab_take(grab_issue()); };
 
+  constexpr bool kSmall = G <= 2;
+  // A window tile once the scores of its tokens are there (x[e] * c + z, log2 domain, in both columns of a head; tokens that do not count:
+  // -infinity) and its Value rows requested: online softmax, sums.
+  auto absorb_window = [&](const float (&x)[8], float c, auto z, int ln, bool has_new, const u32x4_t& appended) {
+    float p[8];
+    constexpr bool kPlain = !std::is_same_v<decltype(z), float>;     // no z
+    if constexpr (kPlain) raise_reference(max8(x) * c);
+    else raise_reference(max8(x) * c + z);
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      if constexpr (kPlain) p[e] = fast_exp2(x[e] * c - mref);
+      else p[e] = fast_exp2(x[e] * c + (z - mref));
+    }
+    half8_t PB, PL;                                      // (blocks of 16: both parts in every column)
+#pragma unroll
+    for (int e = 0; e < 8; e++) { PB[e] = split_part(p[e], lo_part); if constexpr (kWide<G>) PL[e] = split_part(p[e], true); }
+    accZ = mfma16(col >= 4 ? ones8 : zero8, PB, accZ);   // rows 4..15 accumulate the sum of numerators
+    if constexpr (kWide<G>) accZ = mfma16(col >= 4 ? ones8 : zero8, PL, accZ);
+    __builtin_amdgcn_sched_barrier(0);       // (not in front of the numerators)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the Value rows are in the staging area
+    if (has_new) append_stage(appended);
+    wave_lds_fence();
+    // lane's part of the transposing reads: rows 8*kq + col/4 (+ 4), channels 4 * (col % 4) .. +3 of a block of 16
+    const int cc = ln & 15, k4 = ln >> 4;
+    const int t_off = (8 * k4 + (cc >> 2)) * (kD * 2) + ((((cc & 3) >> 1) ^ (2 * (cc >> 2) + 8 * (k4 & 1))) << 4) + 8 * (cc & 1);
+#pragma unroll
+    for (int m = 0; m < 8; m++) {
+      const half8_t Avm = read_transposed(reinterpret_cast<const char*>(&T[0][0]), t_off ^ (m << 5));
+      float4_t t = mfma16(Avm, PB, float4_t{0, 0, 0, 0});
+      if constexpr (kWide<G>) t = mfma16(Avm, PL, t);
+      if constexpr (VB == 3) {   // the final 7/3 step factor of channels 10 / 21 applies to codes only
+#pragma unroll
+        for (int r4 = 0; r4 < 4; r4++) {
+          const int dd = 16 * (m & 1) + 4 * kq + r4;
+          if (dd == 10 || dd == 21) t[r4] *= (3.0f / 7.0f);
+        }
+      }
+      acc[m] += t * __builtin_ldexpf(1.0f, field_pos<VB>(m & 3) - 24);
+      if (m & 1) __builtin_amdgcn_sched_barrier(0);      // (reads of all eight blocks hoisted together do not fit the registers)
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the staging area has been read: it is free again
+  };
+
+  auto op_write = [&](int hh) { return Operand<G>::write_at(lane, hh); };
+  // the zeros of the idle columns (nothing but window rows and results is ever written to these places)
+  auto zero_idle = [&]() {
+    if constexpr (Operand<G>::kIdle) {
+      if (lane < 4) *reinterpret_cast<u32x4_t*>(&L.k.op[Operand<G>::kZeroAt + lane * Operand<G>::kStep]) = u32x4_t{0, 0, 0, 0};
+      if constexpr (Operand<G>::kPieces) {
+        if (lane == 4) *reinterpret_cast<u32x4_t*>(&L.v.pq[Operand<G>::kZeroAt]) = u32x4_t{0, 0, 0, 0};
+      }
+      wave_lds_fence();
+    }
+  };
+  // Key sides of a packed tile: code sums S of the lane's tokens (8*kq + 4*m + r) and column, zero-point terms zt.
+  auto keys_small = [&](const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float (&zt)[G]) {
+    // Lane owns channels 2*lane, 2*lane+1: scale-folded query to LDS, zero-point term by dot product
+    const half2_t s2 = as_half2(meta[0]);
+    const uint32_t kz_pair = meta[1];   // a copy: a bit cast applied to the vector element itself reads element 0
+#pragma unroll
+    for (int hh = 0; hh < G; hh++) {
+      uint32_t hi, lo;
+      mul_split(qh[hh], s2, hi, lo);
+      *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh)]) = hi;
+      *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh) + Operand<G>::kLo]) = lo;
+      const float zp = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, qraw[hh]), __builtin_bit_cast(half2_t, kz_pair), 0.0f, false);
+      zt[hh] = wave_sum(zp) * c_plain;
+    }
+    wave_lds_fence();
+    const Codes<KB> kc(kr);
+    half8_t Bk[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) Bk[ks] = *reinterpret_cast<const half8_t*>(&L.k.op[op_read + ks * Operand<G>::kStep]);
+    S[0] = float4_t{0, 0, 0, 0}; S[1] = float4_t{0, 0, 0, 0};
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) S[m] = mfma16(kc.lo(ks + 4 * m), Bk[ks], S[m]);
+    if constexpr (KB == 3) {   // tokens 10 and 21 of the group step by s*7/3
+      if (kq == 1) S[0][2] *= (7.0f / 3.0f);
+      if (kq == 2) S[1][1] *= (7.0f / 3.0f);
+    }
+  };
+  auto keys_large = [&](const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float& zt) {
+    if constexpr (G != 4) return;
+    // Cooperative operand preparation: lane owns channels 2*lane, 2*lane+1.
+    const half2_t s2 = as_half2(meta[0]);
+#pragma unroll
+    for (int hh = 0; hh < G; hh++) {
+      uint32_t hi, lo;
+      mul_split(qh[hh], s2, hi, lo);
+      *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh)]) = hi;
+      *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh) + Operand<G>::kLo]) = lo;
+    }
+    reinterpret_cast<uint32_t*>(&L.k.zk[0])[lane] = meta[1];
+    wave_lds_fence();
+    const Codes<KB> kc(kr);
+    half8_t Bk[4];
+    float4_t Sz = {0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) {
+      const half8_t z8 = *reinterpret_cast<const half8_t*>(&L.k.zk[32 * ks + 8 * kq]);
+      Sz = mfma16(z8, qB[ks], Sz);     // every A row is the zero-point vector
+      Bk[ks] = *reinterpret_cast<const half8_t*>(&L.k.op[op_read + ks * Operand<G>::kStep]);
+    }
+    S[0] = float4_t{0, 0, 0, 0}; S[1] = float4_t{0, 0, 0, 0};
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) S[m] = mfma16(kc.lo(ks + 4 * m), Bk[ks], S[m]);
+    if constexpr (KB == 3) {   // tokens 10 and 21 of the group step by s*7/3
+      if (kq == 1) S[0][2] *= (7.0f / 3.0f);
+      if (kq == 2) S[1][1] *= (7.0f / 3.0f);
+    }
+    zt = Sz[0] * c_plain;
+  };
   // ---- fp16 window tiles: taken round-robin by the waves before the packed stream.
   // Past the end a wave re-reads the last tile (cache hit) and skips its work: the load stream and the
   // loop body stay uniform, which keeps the outstanding-load accounting exact.
+  const int live_tiles = (a.n_w + kTile - 1) / kTile;
+  // ring slot of tile j between the fronts
+  auto mixed_slot = [&](int j) { int wi = a.m_ring + j; wi = wi >= a.ring_tiles ? wi - a.ring_tiles : wi; return wi * kTile; };
   if (!early) {
     int r = sp + wave * a.n_splits;                      // < the number of live tiles, since wave < n_win
     const int r_step = kWaves * a.n_splits;
     int left = (n_win - wave + kWaves - 1) / kWaves;     // tiles of this wave
     for (int begin = 1; left > 0; left--, r += r_step) {
       asm volatile("" : "+s"(begin));     // (keeps the first pass from being compiled a second time: the code is read cold at the start of a launch)
-      const int first = r * kTile;
+      int slot0, live, lo = 0;
+      if (!MIXED || r < live_tiles) {
+        slot0 = win_slot(r);
+        live = a.n_w - r * kTile;
+      } else {
+        const int j = a.m_ahead ? a.m_tiles - 1 : r - live_tiles, t0 = (a.m_first + j) * kTile;
+        slot0 = mixed_slot(j);
+        live = a.m_end - t0;
+        lo = a.m_front - t0;
+      }
       // the lane number as a value of this iteration: addresses derived from it are not kept in registers around the loop
       int ln = lane;
       asm volatile("" : "+v"(ln));
+      if constexpr (MIXED) {
+        if (r >= live_tiles && !a.m_ahead) {      // Keys from the record
+          const uint32_t soff = (uint32_t)(a.m_first + r - live_tiles) * kRecBytes;
+          const u32x4_t meta = buf_load16(up, lane16, soff);
+          Raw<KB> kr;
+          kr.load(up, soff + (uint32_t)(kMetaWords * 4), lane16, lane16 >> 1);
+          __builtin_amdgcn_sched_barrier(0);
+          if (begin) start_barrier();
+          __builtin_amdgcn_sched_barrier(0);
+          if (begin) copy_q_to_lo();
+          begin = 0;
+          zero_idle();
+          float4_t S[2];
+          float z = 0.0f;
+          if constexpr (kSmall) {
+            float zt[G];
+            keys_small(meta, kr, S, zt);
+#pragma unroll
+            for (int hh = 0; hh < G; hh++) z = h == hh ? zt[hh] : z;
+          } else {
+            float zt;
+            keys_large(meta, kr, S, zt);
+            const float other = ror8(zt);
+            z = lo_part ? other : zt;
+          }
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the exchange area is about to take the Value rows)
+          win_load_v(slot0, live, lo, ln);
+          float x[8];
+#pragma unroll
+          for (int m = 0; m < 2; m++)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; r4++) {
+              const float sum = S[m][r4] + ror8(S[m][r4]);
+              x[4 * m + r4] = 8 * kq + 4 * m + r4 >= lo ? sum : -INFINITY;
+            }
+          absorb_window(x, c_code, z, ln, false, u32x4_t{0, 0, 0, 0});
+          continue;
+        }
+      }
       WinKeys wk;
-      const bool has_new = win_new(win_slot(r));
-      win_load_k(r, ln, wk);
+      const bool has_new = win_new(slot0);
+      win_load_k(slot0, live, ln, wk);
       const u32x4_t appended = append_load(has_new);
       __builtin_amdgcn_sched_barrier(0);      // (matrix instructions moved up here would wait for their rows in front of the barrier)
       if (begin) start_barrier();
@@ -606,42 +781,16 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       for (int m = 0; m < 2; m++)
 #pragma unroll
         for (int ks = 0; ks < 4; ks++) S[m] = mfma16(wk.r[m][ks], qB[ks], S[m]);
-      win_load_v(r, ln);
-      float x[8], p[8];
+      win_load_v(slot0, live, lo, ln);
+      float x[8];
 #pragma unroll
       for (int m = 0; m < 2; m++)
 #pragma unroll
-        for (int r4 = 0; r4 < 4; r4++) x[4 * m + r4] = (first + 8 * kq + 4 * m + r4) < a.n_w ? S[m][r4] : -INFINITY;
-      raise_reference(max8(x) * c_plain);
-#pragma unroll
-      for (int e = 0; e < 8; e++) p[e] = fast_exp2(x[e] * c_plain - mref);
-      half8_t PB, PL;                                      // (blocks of 16: both parts in every column)
-#pragma unroll
-      for (int e = 0; e < 8; e++) { PB[e] = split_part(p[e], lo_part); if constexpr (kWide<G>) PL[e] = split_part(p[e], true); }
-      accZ = mfma16(col >= 4 ? ones8 : zero8, PB, accZ);   // rows 4..15 accumulate the sum of numerators
-      if constexpr (kWide<G>) accZ = mfma16(col >= 4 ? ones8 : zero8, PL, accZ);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the Value rows are in the staging area
-      if (has_new) append_stage(appended);
-      wave_lds_fence();
-      // lane's part of the transposing reads: rows 8*kq + col/4 (+ 4), channels 4 * (col % 4) .. +3 of a block of 16
-      const int c = ln & 15, k4 = ln >> 4;
-      const int t_off = (8 * k4 + (c >> 2)) * (kD * 2) + ((((c & 3) >> 1) ^ (2 * (c >> 2) + 8 * (k4 & 1))) << 4) + 8 * (c & 1);
-#pragma unroll
-      for (int m = 0; m < 8; m++) {
-        const half8_t Avm = read_transposed(reinterpret_cast<const char*>(&T[0][0]), t_off ^ (m << 5));
-        float4_t t = mfma16(Avm, PB, float4_t{0, 0, 0, 0});
-        if constexpr (kWide<G>) t = mfma16(Avm, PL, t);
-        if constexpr (VB == 3) {   // the final 7/3 step factor of channels 10 / 21 applies to codes only
-#pragma unroll
-          for (int r4 = 0; r4 < 4; r4++) {
-            const int dd = 16 * (m & 1) + 4 * kq + r4;
-            if (dd == 10 || dd == 21) t[r4] *= (3.0f / 7.0f);
-          }
+        for (int r4 = 0; r4 < 4; r4++) {
+          const int tau = 8 * kq + 4 * m + r4;
+          x[4 * m + r4] = tau < live && (!MIXED || tau >= lo) ? S[m][r4] : -INFINITY;
         }
-        acc[m] += t * __builtin_ldexpf(1.0f, field_pos<VB>(m & 3) - 24);
-        if (m & 1) __builtin_amdgcn_sched_barrier(0);      // (reads of all eight blocks hoisted together do not fit the registers)
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the staging area has been read: it is free again
+      absorb_window(x, c_plain, std::false_type{}, ln, has_new, appended);
       if (has_new) append_store(appended);                 // (after the reads: those would wait for a store in front of them)
     }
     if (has_packed) {   // claim the first packed tile now
@@ -665,7 +814,6 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // ---- small query groups (G <= 2): the matrix core's columns are nearly empty, so the per-tile extras
   // (Key zero-point term, Value zero-point term, sum of numerators) are cheaper on the vector unit:
   // a packed dot product plus a wave reduction, and per-lane running sums reduced once at the end.
-  constexpr bool kSmall = G <= 2;
   float lwin = 0.0f;            // window tiles' sum of numerators of the lane's column (hi + lo)
   float lacc[G], zacc[G];       // running sum of numerators / of numerator * Value minimum over the lane's tokens
   float mref_u[G];              // reference of head hh, the same value in every lane
@@ -680,67 +828,36 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   }
   const float inv_c_code = 1.0f / c_code;
 
-  auto op_write = [&](int hh) { return Operand<G>::write_at(lane, hh); };
-
-  auto process_small = [&](const Stage<KB, VB>& st) {
-    // -- Key side. Lane owns channels 2*lane, 2*lane+1: scale-folded query to LDS, zero-point term by dot product
-    float zt[G];
-    {
-      const half2_t s2 = as_half2(st.meta[0]);
-      const uint32_t kz_pair = st.meta[1];   // a copy: a bit cast applied to the vector element itself reads element 0
-#pragma unroll
-      for (int hh = 0; hh < G; hh++) {
-        uint32_t hi, lo;
-        mul_split(qh[hh], s2, hi, lo);
-        *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh)]) = hi;
-        *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh) + Operand<G>::kLo]) = lo;
-        const float zp = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, qraw[hh]), __builtin_bit_cast(half2_t, kz_pair), 0.0f, false);
-        zt[hh] = wave_sum(zp) * c_plain;
-      }
+  // sums: code or plain products of the tile's tokens in the columns' rows of L.v.s, scores sum * c + zt; tokens from `limit` on (MIXED)
+  // do not count
+  auto scores_out = [&](const float4_t (&S)[2]) {
+    if (col_valid) {
+      *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq]) = S[0];
+      *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq + 4]) = S[1];
     }
-    wave_lds_fence();
-    {
-      const Codes<KB> kc(st.kc);
-      half8_t Bk[4];
-#pragma unroll
-      for (int ks = 0; ks < 4; ks++) Bk[ks] = *reinterpret_cast<const half8_t*>(&L.k.op[op_read + ks * Operand<G>::kStep]);
-      float4_t S[2] = {float4_t{0, 0, 0, 0}, float4_t{0, 0, 0, 0}};
-#pragma unroll
-      for (int m = 0; m < 2; m++)
-#pragma unroll
-        for (int ks = 0; ks < 4; ks++) {
-          S[m] = mfma16(kc.lo(ks + 4 * m), Bk[ks], S[m]);
-        }
-      if constexpr (KB == 3) {   // tokens 10 and 21 of the group step by s*7/3
-        if (kq == 1) S[0][2] *= (7.0f / 3.0f);
-        if (kq == 2) S[1][1] *= (7.0f / 3.0f);
-      }
-      if (col_valid) {
-        *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq]) = S[0];
-        *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq + 4]) = S[1];
-      }
-    }
+  };
+  auto values_small = [&](const u32x4_t& meta, const Raw<VB>& vr, float c, float inv_c, const float (&zt)[G], int limit) {
     wave_lds_fence();
     // -- Value side. Lane (tp, g) owns tokens (2*tp, 2*tp+1) of channel block g.
     {
       const int tp = lane & 15;
-      const float s0 = lo_half(st.meta[2]), s1 = hi_half(st.meta[2]);
-      const float z0 = lo_half(st.meta[3]), z1 = hi_half(st.meta[3]);
+      const float s0 = lo_half(meta[2]), s1 = hi_half(meta[2]);
+      const float z0 = lo_half(meta[3]), z1 = hi_half(meta[3]);
       float sum0[G], sum1[G];
       bool over = false;
 #pragma unroll
       for (int hh = 0; hh < G; hh++) {
         const float2_t sh = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh][2 * tp]);
         const float2_t sl = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh + 1][2 * tp]);
-        sum0[hh] = sh[0] + sl[0];
-        sum1[hh] = sh[1] + sl[1];
-        // score = sum * c_code + zt; it exceeds what the reference allows iff sum > (reference + cap - zt) / c_code
-        over |= fmaxf(sum0[hh], sum1[hh]) > (mref_u[hh] + kRefCap - zt[hh]) * inv_c_code;
+        sum0[hh] = 2 * tp < limit ? sh[0] + sl[0] : -INFINITY;
+        sum1[hh] = 2 * tp + 1 < limit ? sh[1] + sl[1] : -INFINITY;
+        // score = sum * c + zt; it exceeds what the reference allows iff sum > (reference + cap - zt) / c
+        over |= fmaxf(sum0[hh], sum1[hh]) > (mref_u[hh] + kRefCap - zt[hh]) * inv_c;
       }
       if (__any(over)) {   // rare: raise the reference of the heads that need it and rescale what was accumulated
 #pragma unroll
         for (int hh = 0; hh < G; hh++) {
-          const float mx = wave_max(fmaxf(sum0[hh], sum1[hh])) * c_code + zt[hh];
+          const float mx = wave_max(fmaxf(sum0[hh], sum1[hh])) * c + zt[hh];
           if (mx > mref_u[hh] + kRefCap) {          // wave-uniform
             const float mnew = mx + kRefMargin;
             const float f = fast_exp2(mref_u[hh] - mnew);      // 0 for the first tile (reference -inf)
@@ -758,8 +875,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
 #pragma unroll
       for (int hh = 0; hh < G; hh++) {
         const float off = zt[hh] - mref_u[hh];
-        const float p0 = fast_exp2(sum0[hh] * c_code + off);
-        const float p1 = fast_exp2(sum1[hh] * c_code + off);
+        const float p0 = fast_exp2(sum0[hh] * c + off);
+        const float p1 = fast_exp2(sum1[hh] * c + off);
         lacc[hh] += p0 + p1;
         zacc[hh] += p0 * z0 + p1 * z1;
         uint32_t hi, lo;
@@ -770,7 +887,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
     wave_lds_fence();
     {
-      const Codes<VB> vc(st.vc);
+      const Codes<VB> vc(vr);
       half8_t Bv[4];
 #pragma unroll
       for (int g = 0; g < 4; g++) Bv[g] = *reinterpret_cast<const half8_t*>(&L.v.op[op_read + g * Operand<G>::kStep]);
@@ -781,23 +898,123 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
     wave_lds_fence();   // the next tile's operand writes come after these reads
   };
+  auto process_small = [&](const Stage<KB, VB>& st) {
+    float4_t S[2];
+    float zt[G];
+    keys_small(st.meta, st.kc, S, zt);
+    scores_out(S);
+    values_small(st.meta, st.vc, c_code, inv_c_code, zt, kTile);
+  };
 
-  auto process_large = [&](const Stage<KB, VB>& st) {
-    if constexpr (kWide<G>) return;
-    // -- Key side. Cooperative operand preparation: lane owns channels 2*lane, 2*lane+1.
-    {
-      const half2_t s2 = as_half2(st.meta[0]);
-      if constexpr (kOwnOperand<G>) {
-        reinterpret_cast<uint32_t*>(L.k.op)[lane] = st.meta[0];
-      } else {
+  auto values_large = [&](const u32x4_t& meta, const Raw<VB>& vr, float (&x)[8], float c, float zt) {
+    if constexpr (G != 4) return;
+    // Reference maximum from the hi column (the lo column changes a score by < 2^-10 of its size, which a
+    // reference does not need); lo lanes take their partner's value so that a column pair stays in step.
+    float mx = max8(x) * c + zt;
+    const float mx_partner = ror8(mx);        // cross-lane read outside any divergent branch: all lanes must take part
+    mx = lo_part ? mx_partner : mx;
+    raise_reference(mx);
+    // log2-domain scores against the reference; the zero-point term and the reference enter through the hi column
+    const float off_col = lo_part ? 0.0f : zt - mref;
 #pragma unroll
-        for (int hh = 0; hh < G; hh++) {
-          uint32_t hi, lo;
-          mul_split(qh[hh], s2, hi, lo);
-          *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh)]) = hi;
-          *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh) + Operand<G>::kLo]) = lo;
-        }
+    for (int e = 0; e < 8; e++) x[e] = x[e] * c + off_col;
+
+    // -- Value side. Scores to LDS; lane (tp, g) then owns tokens (2*tp, 2*tp+1) of channel block g.
+    if (col_valid) {
+      *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq]) = float4_t{x[0], x[1], x[2], x[3]};
+      *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq + 4]) = float4_t{x[4], x[5], x[6], x[7]};
+    }
+    wave_lds_fence();
+    // The four lane groups g would all compute the same numerators; instead group g finishes those of the
+    // heads 4k + g only and hands them to the others through LDS as two fp16 terms (the rounded value and what
+    // the rounding left over: together ~22 bits, the same pair enters the Value sums, the zero-point sums and
+    // the denominator).
+    {
+      const int tp = lane & 15, g = lane >> 4;
+      // (all reads of a step are issued before its first write: the compiler does not move LDS reads across LDS
+      // writes through pointers of the same type, and one read at a time costs an LDS round trip each)
+      constexpr int kShare = G / 4 > 0 ? G / 4 : 1;   // (the function is only used with groups of 4 or 8 heads)
+      float2_t sh[kShare], sl[kShare];
+#pragma unroll
+      for (int k = 0; k < G / 4; k++) {
+        const int hh = 4 * k + g;                                  // differs between the lane groups
+        sh[k] = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh][2 * tp]);
+        sl[k] = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh + 1][2 * tp]);
       }
+#pragma unroll
+      for (int k = 0; k < G / 4; k++) {
+        const int hh = 4 * k + g;
+        // leading terms rounded to nearest: they are multiplied on their own below, and a truncated leading term
+        // whose remainder's product falls below the fp16 range would bias the sums (plain casts are safe here:
+        // the values come out of the exponential instruction, nothing can be fused into the conversions)
+        const float p0 = fast_exp2(sh[k][0] + sl[k][0]), p1 = fast_exp2(sh[k][1] + sl[k][1]);
+        const half2_t hv = {(half_t)p0, (half_t)p1};
+        const half2_t lv = {(half_t)(p0 - (float)hv[0]), (half_t)(p1 - (float)hv[1])};
+        const int at = Operand<G>::write_at(tp, hh);
+        *reinterpret_cast<uint32_t*>(&L.v.pq[at]) = as_u32(hv);
+        *reinterpret_cast<uint32_t*>(&L.v.pq[at + Operand<G>::kLo]) = as_u32(lv);
+      }
+      reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = meta[3];
+    }
+    wave_lds_fence();
+    half8_t Bv[4];
+    // plain numerators: the column's own row
+    const half8_t PB = *reinterpret_cast<const half8_t*>(&L.v.pq[op_read]);
+    {
+      const int tp = lane & 15;
+      const half2_t s2 = as_half2(meta[2]);
+      uint32_t pw[G], dw[G];
+#pragma unroll
+      for (int hh = 0; hh < G; hh++) {
+        const int at = Operand<G>::write_at(tp, hh);
+        pw[hh] = *reinterpret_cast<const uint32_t*>(&L.v.pq[at]);
+        dw[hh] = *reinterpret_cast<const uint32_t*>(&L.v.pq[at + Operand<G>::kLo]);
+      }
+#pragma unroll
+      for (int hh = 0; hh < G; hh++) {
+        const half2_t p2 = as_half2(pw[hh]), d2 = as_half2(dw[hh]);
+        // (p2 + d2) * s2: exact product of the leading term in two parts, the small term's product folded into the second
+        const half2_t hv = p2 * s2;
+        const half2_t lv = __builtin_elementwise_fma(d2, s2, __builtin_elementwise_fma(p2, s2, -hv));
+        *reinterpret_cast<uint32_t*>(&L.v.op[op_write(hh)]) = as_u32(hv);
+        *reinterpret_cast<uint32_t*>(&L.v.op[op_write(hh) + Operand<G>::kLo]) = as_u32(lv);
+      }
+      wave_lds_fence();
+#pragma unroll
+      for (int g = 0; g < 4; g++) Bv[g] = *reinterpret_cast<const half8_t*>(&L.v.op[op_read + g * Operand<G>::kStep]);
+    }
+    {
+      const Codes<VB> vc(vr);
+      // zero-point term: A rows 0..3 carry the zero-points of channel blocks 0..3, rows 4..15 are ones
+      // and accumulate the sum of the numerators
+      half8_t z8 = ones8;
+      if (col < 4) z8 = *reinterpret_cast<const half8_t*>(&L.v.zv[col][8 * kq]);
+      accZ = mfma16(z8, PB, accZ);
+#pragma unroll
+      for (int m = 0; m < 8; m++) {
+        acc[m] = mfma16(vc.lo(m), Bv[m >> 1], acc[m]);
+      }
+    }
+    wave_lds_fence();   // the next tile's operand writes come after these reads
+  };
+  auto process_large = [&](const Stage<KB, VB>& st) {
+    if constexpr (G != 4) return;
+    float4_t S[2];
+    float zt, x[8];
+    keys_large(st.meta, st.kc, S, zt);
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) x[4 * m + r] = S[m][r];
+    values_large(st.meta, st.vc, x, c_code, zt);
+  };
+  // Blocks of 8 heads: every lane folds the scales into its own operands. In one piece: cut in two like the one for 4 heads, 4 of its forms with 8
+  // waves spill.
+  auto process_own = [&](const Stage<KB, VB>& st) {
+    if constexpr (!kOwnOperand<G> || kWide<G>) return;
+    // -- Key side
+    {
+      reinterpret_cast<uint32_t*>(L.k.op)[lane] = st.meta[0];
       reinterpret_cast<uint32_t*>(&L.k.zk[0])[lane] = st.meta[1];
     }
     wave_lds_fence();
@@ -810,13 +1027,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       for (int ks = 0; ks < 4; ks++) {
         const half8_t z8 = *reinterpret_cast<const half8_t*>(&L.k.zk[32 * ks + 8 * kq]);
         Sz = mfma16(z8, qB[ks], Sz);     // every A row is the zero-point vector
-        if constexpr (kOwnOperand<G>) {
-          const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.k.op[64 * ks + 16 * kq]);
-          const half8_t qp = q_scaled(ks);
-          Bk[ks] = __builtin_elementwise_fma(qp, s8, -lo_only(qp * s8));
-        } else {
-          Bk[ks] = *reinterpret_cast<const half8_t*>(&L.k.op[op_read + ks * Operand<G>::kStep]);
-        }
+        const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.k.op[64 * ks + 16 * kq]);
+        const half8_t qp = q_scaled(ks);
+        Bk[ks] = __builtin_elementwise_fma(qp, s8, -lo_only(qp * s8));
       }
       float4_t S[2] = {float4_t{0, 0, 0, 0}, float4_t{0, 0, 0, 0}};
 #pragma unroll
@@ -882,43 +1095,19 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         *reinterpret_cast<uint32_t*>(&L.v.pq[at + Operand<G>::kLo]) = as_u32(lv);
       }
       reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = st.meta[3];
-      if constexpr (kOwnOperand<G>) reinterpret_cast<uint32_t*>(L.v.op)[lane] = st.meta[2];
+      reinterpret_cast<uint32_t*>(L.v.op)[lane] = st.meta[2];
     }
     wave_lds_fence();
     half8_t Bv[4];
     // plain numerators: the column's own row
     const half8_t PB = *reinterpret_cast<const half8_t*>(&L.v.pq[op_read]);
-    if constexpr (kOwnOperand<G>) {
-      // hi columns: the rounded products p * s; lo columns: what the rounding left, and the small terms' products
-      const half8_t p8 = *reinterpret_cast<const half8_t*>(&L.v.pq[Operand<G>::read_at(kq, h, false)]);
-      const half8_t px = lo_only(p8), dx = lo_only(PB);
+    // hi columns: the rounded products p * s; lo columns: what the rounding left, and the small terms' products
+    const half8_t p8 = *reinterpret_cast<const half8_t*>(&L.v.pq[Operand<G>::read_at(kq, h, false)]);
+    const half8_t px = lo_only(p8), dx = lo_only(PB);
 #pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.v.op[64 * g + 16 * kq]);
-        Bv[g] = __builtin_elementwise_fma(dx, s8, __builtin_elementwise_fma(p8, s8, -(px * s8)));
-      }
-    } else {
-      const int tp = lane & 15;
-      const half2_t s2 = as_half2(st.meta[2]);
-      uint32_t pw[G], dw[G];
-#pragma unroll
-      for (int hh = 0; hh < G; hh++) {
-        const int at = Operand<G>::write_at(tp, hh);
-        pw[hh] = *reinterpret_cast<const uint32_t*>(&L.v.pq[at]);
-        dw[hh] = *reinterpret_cast<const uint32_t*>(&L.v.pq[at + Operand<G>::kLo]);
-      }
-#pragma unroll
-      for (int hh = 0; hh < G; hh++) {
-        const half2_t p2 = as_half2(pw[hh]), d2 = as_half2(dw[hh]);
-        // (p2 + d2) * s2: exact product of the leading term in two parts, the small term's product folded into the second
-        const half2_t hv = p2 * s2;
-        const half2_t lv = __builtin_elementwise_fma(d2, s2, __builtin_elementwise_fma(p2, s2, -hv));
-        *reinterpret_cast<uint32_t*>(&L.v.op[op_write(hh)]) = as_u32(hv);
-        *reinterpret_cast<uint32_t*>(&L.v.op[op_write(hh) + Operand<G>::kLo]) = as_u32(lv);
-      }
-      wave_lds_fence();
-#pragma unroll
-      for (int g = 0; g < 4; g++) Bv[g] = *reinterpret_cast<const half8_t*>(&L.v.op[op_read + g * Operand<G>::kStep]);
+    for (int g = 0; g < 4; g++) {
+      const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.v.op[64 * g + 16 * kq]);
+      Bv[g] = __builtin_elementwise_fma(dx, s8, __builtin_elementwise_fma(p8, s8, -(px * s8)));
     }
     {
       const Codes<VB> vc(st.vc);
@@ -1005,18 +1194,67 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   auto process = [&](const Stage<KB, VB>& st) {
     if constexpr (kWide<G>) process_wide(st);
     else if constexpr (kSmall) process_small(st);
+    else if constexpr (kOwnOperand<G>) process_own(st);
     else process_large(st);
   };
 
-  if (has_packed) {
-    // the zeros of the idle columns (the wave's area held window rows up to here; nothing else is written to these places)
-    if constexpr (Operand<G>::kIdle) {
-      if (lane < 4) *reinterpret_cast<u32x4_t*>(&L.k.op[Operand<G>::kZeroAt + lane * Operand<G>::kStep]) = u32x4_t{0, 0, 0, 0};
-      if constexpr (Operand<G>::kPieces) {
-        if (lane == 4) *reinterpret_cast<u32x4_t*>(&L.v.pq[Operand<G>::kZeroAt]) = u32x4_t{0, 0, 0, 0};
+  if constexpr (MIXED) {
+    // tiles between the fronts whose Values come from the record: dealt out like the window tiles, the waves without one of those first
+    const int n_rec = a.m_ahead ? a.m_tiles : a.m_front > a.m_first * kTile ? 1 : 0;
+    bool first_rec = true;
+    for (int j = sp + (kWaves - 1 - wave) * a.n_splits; j < n_rec; j += kWaves * a.n_splits) {
+      const uint32_t soff = (uint32_t)(a.m_first + j) * kRecBytes;
+      const int t0 = (a.m_first + j) * kTile;
+      const int n_tok = (a.m_front < a.m_end ? a.m_front : a.m_end) - t0;        // tokens with a packed Value
+      const int limit = n_tok < kTile ? n_tok : kTile;
+      u32x4_t meta = buf_load16(up, lane16, soff);
+      Raw<VB> vr;
+      vr.load(up, soff + (uint32_t)((kMetaWords + tile_words(KB)) * 4), lane16, lane16 >> 1);
+      if (first_rec) zero_idle();
+      first_rec = false;
+      float4_t S[2];
+      float zts[G], ztl = 0.0f, c = c_code, inv_c = inv_c_code;
+      if (a.m_ahead) {
+        WinKeys wk;
+        win_load_k(mixed_slot(j), a.m_end - t0, lane, wk);
+        S[0] = float4_t{0, 0, 0, 0}; S[1] = float4_t{0, 0, 0, 0};
+#pragma unroll
+        for (int m = 0; m < 2; m++) {
+#pragma unroll
+          for (int ks = 0; ks < 4; ks++) S[m] = mfma16(wk.r[m][ks], qB[ks], S[m]);
+#pragma unroll
+          for (int e = 0; e < 4; e++) S[m][e] = lo_part ? 0.0f : S[m][e];
+        }
+#pragma unroll
+        for (int hh = 0; hh < G; hh++) zts[hh] = 0.0f;
+        c = c_plain;
+        inv_c = 1.0f / c_plain;
+      } else {
+        Raw<KB> kr;
+        kr.load(up, soff + (uint32_t)(kMetaWords * 4), lane16, lane16 >> 1);
+        if constexpr (kSmall) keys_small(meta, kr, S, zts);
+        else keys_large(meta, kr, S, ztl);
       }
-      wave_lds_fence();
+      // what the record holds for tokens without a packed Value is not defined
+      const int tp = lane & 15;
+      const uint32_t keep = (2 * tp < limit ? 0x0000FFFFu : 0u) | (2 * tp + 1 < limit ? 0xFFFF0000u : 0u);
+      meta[2] &= keep; meta[3] &= keep;
+      if constexpr (kSmall) {
+        scores_out(S);
+        values_small(meta, vr, c, inv_c, zts, limit);
+      } else {
+        float x[8];
+#pragma unroll
+        for (int m = 0; m < 2; m++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) x[4 * m + e] = 8 * kq + 4 * m + e < limit || lo_part ? S[m][e] : -INFINITY;
+        values_large(meta, vr, x, c, ztl);
+      }
     }
+  }
+
+  if (has_packed) {
+    zero_idle();
     while (it < p_end) {
       const int ticket = grab_issue();
       process(st);
@@ -1025,6 +1263,16 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
   }
 
+  {
+  // Where the packed loop has no register to spare, lane and thread number are made anew here (elsewhere the values at hand are better: 0.17 us per
+  // launch of 32 units x 8 splits).
+  constexpr bool kAnew = kWaves == 8 && G == 4 && KB >= 3 && VB >= 3;
+  int lane = threadIdx.x & 63;
+  if constexpr (kAnew) {
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
+    __builtin_assume(lane >= 0 && lane < kWave);
+  }
+  const int tid = kAnew ? wave * kWave + lane : (int)threadIdx.x, col = lane & 15, kq = lane >> 4;
   // ---- per-wave result (into the wave's own area, whose exchange contents are no longer needed): undo the
   // field scaling, add hi and lo columns, add the zero-point term.
   // accZ: lanes with kq == 0 hold the zero-point sums of channel blocks 0..3, lanes with kq >= 1 the
@@ -1289,20 +1537,23 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   }
   if (tid == 0) __hip_atomic_store(&a.counters[uo * a.counter_stride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  }
 }
 
 template <int KB, int VB>
 hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
   switch (G) {
-    case 1: decode_attn_kernel<KB, VB, 1, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
-    case 2: decode_attn_kernel<KB, VB, 2, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
-    case 4: decode_attn_kernel<KB, VB, 4, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
+    case 1: decode_attn_kernel<KB, VB, 1, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break;
+    case 2: decode_attn_kernel<KB, VB, 2, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break;
+    case 4: decode_attn_kernel<KB, VB, 4, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break;
+#if !KVMIX_MIXED
     case 8:
       // (8 heads with 3- or 4-bit Values always run 12 waves: attn_waves)
-      if constexpr (kNW == 12 || VB < 3) { decode_attn_kernel<KB, VB, 8, kNW><<<grid, kNW * kWave, 0, s>>>(a); break; }
+      if constexpr (kNW == 12 || VB < 3) { decode_attn_kernel<KB, VB, 8, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break; }
       else return hipErrorInvalidValue;
-#if KVMIX_WAVES == 8
-    case 16: decode_attn_kernel<KB, VB, 16, kNW><<<grid, kNW * kWave, 0, s>>>(a); break;
+#endif
+#if KVMIX_WAVES == 8 && !KVMIX_MIXED
+    case 16: decode_attn_kernel<KB, VB, 16, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break;
 #endif
     default: return hipErrorInvalidValue;
   }
@@ -1312,7 +1563,7 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
 }  // namespace
 
 template <>
-hipError_t launch_decode_attn<kNW>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s) {
+hipError_t launch_decode_attn<kNW, kMixed>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s) {
   const dim3 grid(a.n_splits, units, (a.G + block - 1) / block);
   switch (k_bits * 10 + v_bits) {
     case 11: return launch_g<1, 1>(a, block, grid, s);

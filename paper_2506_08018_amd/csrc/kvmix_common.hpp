@@ -150,6 +150,11 @@ struct AttnArgs {
   // window tile more than the others take win_tiles packed tiles less
   int items_q, items_r, win_tiles;
   float scale_log2;       // softmax_scale * log2(e)
+  // Tiles between two fronts, worked on in the same launch (groups of up to 4 heads): tiles [m_first, m_first + m_tiles), tokens up to m_end;
+  // m_front: the Value front; m_ahead: it is ahead of the Key front; m_ring: ring tile of tile m_first. The window tiles above are dealt
+  // out together with those of them whose Values come from the ring.
+  int m_first, m_tiles, m_end, m_front, m_ring;
+  bool m_ahead;
 };
 
 // Tokens [t_begin, t_end) of every unit, each Key and each Value from where it lives (packed before its front, the
@@ -175,11 +180,12 @@ hipError_t launch_mixed_fronts(const MixedArgs& a, int units, hipStream_t s);
 hipError_t launch_dequant(const DequantArgs& a, int units, hipStream_t s);
 hipError_t launch_append(const AppendArgs& a, hipStream_t s);
 hipError_t launch_stream_read(const void* buf, size_t bytes, int workgroups, int threads, uint32_t* sink, hipStream_t s);
-// WAVES: waves per workgroup, 8 or 12 (blocks of 16 heads: 8). block: query heads per workgroup (1, 2, 4, 8 or 16); a unit's group of
-// a.G heads takes (a.G + block - 1) / block workgroups per split.
-template <int WAVES>
+// WAVES: waves per workgroup, 8 or 12 (blocks of 16 heads: 8). MIXED: with the tiles between two fronts (blocks of up to 4 heads, 12 waves).
+// block: query heads per workgroup (1, 2, 4, 8 or 16); a unit's group of a.G heads takes (a.G + block - 1) / block workgroups per split.
+template <int WAVES, bool MIXED>
 hipError_t launch_decode_attn(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
-template <> hipError_t launch_decode_attn<8>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
-template <> hipError_t launch_decode_attn<12>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
+template <> hipError_t launch_decode_attn<8, false>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
+template <> hipError_t launch_decode_attn<12, false>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
+template <> hipError_t launch_decode_attn<12, true>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
 
 }  // namespace kvmix

@@ -1,6 +1,6 @@
-// Decode attention over the tokens that lie between the Key front and the Value front of a cache whose Keys and
-// Values age separately (paper Sec. 3.3: the Recent Pivotal Context ratio of a layer's Keys and of its Values may
-// differ; Sec. 3.2.2 step 4 for the dequantization).
+// Groups of 8 query heads and more: decode attention over the tokens that lie between the Key front and the Value front of a cache whose
+// Keys and Values age separately (paper Sec. 3.3: the Recent Pivotal Context ratio of a layer's Keys and of its Values may
+// differ; Sec. 3.2.2 step 4 for the dequantization). With up to 4 heads the main attention kernel works on these tiles itself.
 //
 // The main attention kernel works on tiles whose Keys and Values are both packed and on window tiles whose Keys and
 // Values are both fp16. The tokens in between ((r_k - r_v) x context of them under the count formula) have one
@@ -88,7 +88,7 @@ template <int BITS> __device__ __forceinline__ float step_of(float s, bool two_b
   return s;
 }
 
-// GH: query heads per workgroup (1, 2 or 4). V_AHEAD: the Value front is ahead of the Key front, i.e. in the whole
+// GH: query heads per workgroup (1 or 4). V_AHEAD: the Value front is ahead of the Key front, i.e. in the whole
 // range the Keys come from the ring and the Values from the records (but for the tokens from the Value front on);
 // otherwise the Keys come from the records and the Values from the ring (but for the tokens before the Value front).
 template <int KB, int VB, int GH, bool V_AHEAD>
@@ -369,9 +369,8 @@ __global__ __launch_bounds__(kMixWaves * kWave) void mixed_fronts_kernel(MixedAr
     const int blocks = a.G / a.G_main;
     const size_t uo = (size_t)u * blocks + hg / a.G_main;
     float* pp = a.part + ((uo * a.n_parts + a.part_index) * a.G_main + hg % a.G_main) * (kD + 2);
-    // (never a zero: to the merge a zero word is one that is not there yet)
-    if (d == 0) { pp[0] = M == 0.0f ? -0.0f : M; pp[1] = L == 0.0f ? -0.0f : L; }
-    pp[2 + d] = Ov == 0.0f ? -0.0f : Ov;
+    if (d == 0) { pp[0] = M; pp[1] = L; }
+    pp[2 + d] = Ov;
   }
 }
 
@@ -381,18 +380,13 @@ hipError_t launch_mx(const MixedArgs& a, int units, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Heads per workgroup: up to 4 when the Keys come from the ring. With Keys from the records one head per workgroup:
+// Heads per workgroup: 4 when the Keys come from the ring. With Keys from the records one head per workgroup:
 // unpacking a Key column against several heads at once (the query values of 32 channels per head and lane) does not
 // fit the register file, and a spilling kernel is slower than the repeated unpacking.
 template <int KB, int VB>
 hipError_t launch_gh(const MixedArgs& a, int units, hipStream_t s) {
   if (a.n_qv <= a.n_qk) return launch_mx<KB, VB, 1, false>(a, units, s);
-  switch (a.G >= 4 ? 4 : a.G) {
-    case 1: return launch_mx<KB, VB, 1, true>(a, units, s);
-    case 2: return launch_mx<KB, VB, 2, true>(a, units, s);
-    case 4: return launch_mx<KB, VB, 4, true>(a, units, s);
-  }
-  return hipErrorInvalidValue;
+  return launch_mx<KB, VB, 4, true>(a, units, s);
 }
 
 }  // namespace

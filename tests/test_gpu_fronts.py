@@ -133,6 +133,49 @@ def test_attention_with_fronts_apart(G, state):
         attn_both(rc, gc, shape, cfg, q, n_splits, static, f"G={G} state={state} splits={n_splits} static={static}")
 
 
+@pytest.mark.parametrize("G,kb,vb,keep_k,keep_v", [
+    (1, 3, 2, 1100, 70), (1, 2, 4, 70, 1100), (2, 2, 3, 1100, 33), (2, 4, 2, 64, 1009), (4, 3, 3, 1100, 64), (4, 3, 4, 61, 1100), (4, 2, 2, 900, 1),
+    (4, 4, 4, 3, 1100)])
+def test_many_tiles_between_the_fronts(G, kb, vb, keep_k, keep_v):
+    """More tiles between the fronts than a workgroup has waves, either front ahead, the Value front inside and at the end of a tile; what is not
+    to be read holds NaN: ring slots of packed and of no tokens, record fields of Values that are still in the ring. Unsplit, split in uneven
+    shares, split into more workgroups than there are window tiles; then fused steps on the same cache."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case many tiles between fronts G={G} kb={kb} vb={vb} keep={keep_k}/{keep_v}", flush=True)
+    B, Hkv, T, W_cap = 1, 2, 1205, 1280
+    q, k, v = synth.gen_layer_numpy(870 + G, keep_k, B, Hkv * G, Hkv, T + 3)
+    rc, gc, shape, cfg = make_ring_pair(B, Hkv * G, Hkv, kb, vb, 1280, W_cap)
+    rc.packed[:] = 0x7E017E01                                  # NaN as metadata
+    gc.packed.view(torch.int32).fill_(0x7E017E01)
+    for t in range(T):
+        assert rc.append(u16(k[:, :, t]), u16(v[:, :, t])) == 0
+    kt, vt = torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda()
+    kv.append_tokens(shape, cfg, kt[:, :, :T], vt[:, :, :T], gc)
+    assert rc.flush(keep_k, keep_v) == 0
+    kv.flush(shape, cfg, gc, keep_k, keep_v)
+    torch.cuda.synchronize()
+    assert_same_state(rc, gc, "before attention")
+    assert abs(gc.v_lead) > 32 * 25
+    for ring, front in ((gc.k_win, gc.n_q), (gc.v_win, gc.n_qv)):
+        live = [(gc.w0 + t - gc.n_q) % W_cap for t in range(front, T)]
+        dead = sorted(set(range(W_cap)) - set(live))
+        ring.view(torch.float16).view(-1, W_cap, 128)[:, dead] = float("nan")
+    for n_splits, static in ((1, False), (2, False), (5, False), (0, False), (40, False), (3, True)):
+        attn_both(rc, gc, shape, cfg, q, n_splits, static, f"G={G} splits={n_splits} static={static}")
+    ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
+    qt = torch.from_numpy(q).cuda()
+    out = torch.zeros_like(qt)
+    for i in range(3):
+        assert rc.append(u16(k[:, :, T + i]), u16(v[:, :, T + i])) == 0
+        st, want = rc.decode_attn(u16(q))
+        assert st == 0
+        kv.decode_step(shape, cfg, kt[:, :, T + i].contiguous(), vt[:, :, T + i].contiguous(), qt, gc, out, ws)
+        torch.cuda.synchronize()
+        assert_attn_close(t16(out), want, f"step {i}", tight=True)
+    assert not counters_of(ws, shape).any()
+
+
 @pytest.mark.parametrize("units,G,kb,vb,state,n_splits", [(86, 24, 2, 2, 0, 1), (29, 72, 3, 4, 1, 2), (129, 16, 4, 2, 4, 1), (5, 512, 2, 3, 2, 1)])
 def test_attention_with_fronts_apart_in_blocks_of_sixteen_heads(units, G, kb, vb, state, n_splits):
     """More blocks of 8 heads than there are compute units (256), so that the main launch runs blocks of 16 and its merge reads the partial of

@@ -170,7 +170,7 @@ int kvmix_cache_bytes(const kvmix_shape* shape, const kvmix_layer_cfg* cfg, int 
                       size_t* packed_b, size_t* win_b);
 
 /* Workspace needed by kvmix_decode_attn for any context up to T_max packed tokens (split
- * partials + arrival counters, and the partial of the tokens between the two fronts when v_lead != 0). The
+ * partials + arrival counters; with v_lead != 0 room for one more partial is asked for). The
  * workspace must be zero-filled once before first use, all of it; every call leaves the counters zero again, and with groups of up
  * to 4 query heads the partials too (a word that is zero is one that has not been stored yet). How many counters
  * there are depends on the shape: a workspace that has served one shape is zero-filled again before it serves
@@ -208,9 +208,8 @@ int kvmix_append(const kvmix_shape* shape, const kvmix_layer_cfg* cfg,
  * q, out: fp16 [B][Hq][128]. softmax_scale <= 0 selects 1/sqrt(D). Accumulation is fp32.
  * n_splits: number of context splits per unit (split-K), 0 = chosen by the library.
  * workspace: see kvmix_workspace_bytes (may be NULL when the effective n_splits is 1 and v_lead == 0).
- * With v_lead != 0 the tokens from the tile of the older front up to the tile end of the younger one (each Key and
- * each Value taken from where it lives: packed and dequantized, or fp16) are worked on by a launch of their own that
- * goes first and leaves one more partial in the workspace, which the main launch's merge includes. */
+ * With v_lead != 0 the tiles from the one of the older front up to the tile end of the younger one take each Key and
+ * each Value from where it lives (packed and dequantized, or fp16), in the same launch. */
 int kvmix_decode_attn(const kvmix_shape* shape, const kvmix_layer_cfg* cfg, const uint16_t* q,
                       const kvmix_layer_cache* cache, float softmax_scale, uint16_t* out,
                       void* workspace, size_t workspace_bytes, int n_splits, void* stream);

@@ -20,7 +20,6 @@ OBJECTS = {
     "kvmix_attn8.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=8", "-DKVMIX_MIXED=0"]),
     "kvmix_attn12.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=12", "-DKVMIX_MIXED=0"]),
     "kvmix_attn12_fronts.o": ("kvmix_attn.hip", ATTN + ["-DKVMIX_WAVES=12", "-DKVMIX_MIXED=1"]),
-    "kvmix_mixed.o": ("kvmix_mixed.hip", ["-ffp-contract=off"]),
     "kvmix_api.o": ("kvmix_api.hip", []),
 }
 

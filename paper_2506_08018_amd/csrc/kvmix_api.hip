@@ -255,9 +255,8 @@ int kvmix_append(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint16
 namespace {
 
 // Everything an attention launch needs, filled by plan_attention after all host-side checks have passed.
-// `mixed`: the fronts of Keys and Values differ. Groups of up to 4 heads: the tiles between them are worked on by the same launch. Larger
-// groups: by a launch of their own (m) that leaves one more partial for the main launch's merge.
-struct AttnPlan { AttnArgs a; int kb, vb, G, block, units, waves; bool mixed; MixedArgs m; };
+// `mixed`: the fronts of Keys and Values differ.
+struct AttnPlan { AttnArgs a; int kb, vb, G, block, units, waves; bool mixed; };
 
 constexpr int kWindowTileCost = 3;   // packed tiles that take a wave as long as one window tile
 
@@ -374,11 +373,12 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   }
   if (n_splits > n_items) n_splits = n_items;
   int block = G;
-  if (G > 8) {
+  if (G > 8 || (G == 8 && fr.mixed)) {
+    // (With the fronts apart 8 heads are half a block of 16: a block of 16 takes a tile in about the time of a block of 8.)
     // Blocks of 8 heads where a launch of them has at most one workgroup per compute unit (see above: the faster ones at equal split
     // counts), blocks of 16 otherwise.
     const int cus = num_cus();
-    block = cus > 0 && (long long)out_units(sh) * n_splits <= cus ? 8 : 16;
+    block = !fr.mixed && cus > 0 && (long long)out_units(sh) * n_splits <= cus ? 8 : 16;
     if (any_splits) {
       // The count above is that of blocks of 8, and it is what a workspace is refused or accepted by. A workspace that also holds the
       // partials of the count that suits blocks of 16 gets those where they are modelled to be faster, or within 2 % (4 x 48 heads over
@@ -393,8 +393,8 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     }
   }
   AttnArgs a{};
-  const bool in_launch = fr.mixed && G <= 4;       // no partial of their own
-  int n_parts = n_splits + (fr.mixed ? 1 : 0);
+  // (With the fronts apart a workspace is refused or accepted as if the tokens between them had a partial of their own.)
+  const int n_parts = n_splits + (fr.mixed ? 1 : 0);
   if (n_parts > 1) {
     if (!workspace) return KVMIX_ERR_NULL;
     if (!aligned16(workspace)) return KVMIX_ERR_ALIGN;
@@ -402,7 +402,6 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     a.counters = reinterpret_cast<uint32_t*>(workspace);
     a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + counters_bytes(out_units(sh)));
   }
-  if (in_launch) n_parts = n_splits;      // (what a workspace is refused or accepted by is the same for all groups)
   // The counters' 256 bytes (at least) are shared out evenly: splits that arrive together then meet on fewer cache lines
   // (8 units x 32 splits, whose 256 arrivals queued up on one line for 1.3 us on average)
   a.counter_stride = 1;
@@ -413,9 +412,9 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   a.k_new = k_new; a.v_new = v_new; a.k_win_w = c->k_win; a.v_win_w = c->v_win; a.new_slot = new_slot;
   a.tiles_cap = c->T_cap / kTile; a.W_cap = c->W_cap; a.n_w = fr.n_w_eff;
   a.ring_tiles = c->W_cap / kTile; a.w0_tile = fr.w0_eff / kTile;
-  a.n_splits = n_splits; a.n_parts = n_parts;
+  a.n_splits = n_splits;
   int live = (fr.n_w_eff + kTile - 1) / kTile;
-  if (in_launch) {
+  if (fr.mixed) {
     a.m_first = fr.packed_tiles; a.m_tiles = (int)((fr.t_a + kTile - 1) / kTile) - fr.packed_tiles;
     a.m_end = (int)fr.t_a; a.m_front = c->n_q + c->v_lead; a.m_ahead = c->v_lead > 0;
     a.m_ring = slot_of(c, (long long)fr.packed_tiles * kTile) / kTile;
@@ -436,33 +435,13 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   plan->mixed = fr.mixed;
   // with the append inside the launch the new token must be a window token of the main launch
   if (fr.mixed && new_slot >= 0 && fr.n_w_eff < 1) return KVMIX_ERR_BAD_SHAPE;
-  if (fr.mixed && !in_launch) {
-    MixedArgs m{};
-    m.q = q; m.packed = c->packed; m.k_win = c->k_win; m.v_win = c->v_win;
-    m.part = a.part; m.n_parts = n_parts; m.part_index = n_splits;
-    m.tiles_cap = a.tiles_cap; m.W_cap = c->W_cap; m.k_bits = plan->kb; m.v_bits = plan->vb;
-    m.n_qk = c->n_q; m.n_qv = c->n_q + c->v_lead;
-    m.t_begin = fr.packed_tiles * kTile; m.t_end = (int)fr.t_a;
-    m.slot_begin = slot_of(c, m.t_begin);
-    m.G = G; m.G_main = block == 16 ? G : block;
-    m.scale_log2 = a.scale_log2;
-    plan->m = m;
-  }
   return KVMIX_OK;
 }
 
 int launch_plan(const AttnPlan& p, void* stream) {
-  hipError_t e;
-  if (p.mixed && p.G <= 4) {
-    e = launch_decode_attn<12, true>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream);      // (does not fit the registers of 8 waves)
-    return e == hipSuccess ? KVMIX_OK : hip_fail(e);
-  }
-  if (p.mixed) {
-    e = launch_mixed_fronts(p.m, p.units, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e);
-  }
-  e = p.waves == 8 ? launch_decode_attn<8, false>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream)
-                   : launch_decode_attn<12, false>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream);
+  const hipError_t e = p.mixed        ? launch_decode_attn<12, true>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream)      // (does not fit the registers of 8 waves)
+                       : p.waves == 8 ? launch_decode_attn<8, false>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream)
+                                      : launch_decode_attn<12, false>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream);
   return e == hipSuccess ? KVMIX_OK : hip_fail(e);
 }
 
@@ -535,13 +514,12 @@ int kvmix_decode_attn_static(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, 
   // First pass with a workspace of the array's size at a dummy aligned address: settles the split count and runs every check.
   int st = plan_attention(sh, cfg, q, c, c->n_w, nullptr, nullptr, -1, softmax_scale, out, reinterpret_cast<void*>(256), kScratchBytes, n_splits, &plan);
   if (st) return st;
-  if (plan.a.n_parts > 1) {
+  if (plan.a.n_splits > 1) {
     void* ptr = nullptr;
     st = scratch_address(&ptr, (hipStream_t)stream);
     if (st) return st;
     plan.a.counters = reinterpret_cast<uint32_t*>(ptr);
     plan.a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ptr) + kScratchCounterBytes + (plan.G <= 4 ? 0 : kScratchBytes));
-    plan.m.part = plan.a.part;
   } else {
     plan.a.counters = nullptr; plan.a.part = nullptr;
   }
@@ -600,9 +578,8 @@ int kvmix_decode_step(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const u
   if (cfg->k_bits != 16 && c->W_cap < cfg->window + kTile) return KVMIX_ERR_BAD_SHAPE;
   if (!aligned16(k_new) || !aligned16(v_new)) return KVMIX_ERR_ALIGN;
   if (c->v_lead != 0 && fronts_of(c, c->n_w + 1).t_a > (long long)c->n_q + c->n_w) {
-    // The new token shares its tile with the younger front: it belongs to the range between the fronts, which is
-    // read from the ring by a launch of its own. Plan against the counters as the append will leave them, append,
-    // then the two attention launches.
+    // The new token shares its tile with the younger front: it belongs to the range between the fronts, whose ring rows the launch
+    // reads from the ring. Plan against the counters as the append will leave them, append, then the attention launch.
     kvmix_layer_cache after = *c;
     after.n_w += 1;
     st = plan_attention(sh, cfg, q, &after, after.n_w, nullptr, nullptr, -1, softmax_scale, out, workspace, workspace_bytes, n_splits, &plan);

@@ -364,14 +364,15 @@ template <int G, int NW> struct MergeLds {        // per-wave reference maximum 
   float l[NW][G];
 };
 
-// MIXED: Keys and Values age at fronts of their own (groups of up to 4 heads); the tiles between the fronts have one side in a record and the other
+// MIXED: Keys and Values age at fronts of their own (blocks of 1, 2, 4 and 16 heads); the tiles between the fronts have one side in a record and the other
 // in the ring. Two kinds of tile share a half with the window tiles and are worked on with them, two with the packed ones:
 //   Value front ahead: Keys from the ring, Values from the record (with the packed tiles); where the front stands inside a tile, the tokens
 //     behind it are a window tile of which only they count.
 //   Key front ahead: Keys from the record, Values from the ring (with the window tiles); the tokens before a front inside a tile are a
 //     packed tile of which only they count.
 // In a launch of their own on the vector unit these tiles took 13 us (14 tiles per unit of 128, 256 units, 1 head) next to 28 for the rest; a
-// decode step of two such layers, with its appends and flushes, went from 99.4 us to 80.3.
+// decode step of two such layers, with its appends and flushes, went from 99.4 us to 80.3, of two layers of 64 units x 3000 tokens and 8
+// heads from 103 to 47.
 template <int KB, int VB, int G, int NW, bool MIXED>
 __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(AttnArgs a) {
   constexpr int kWaves = NW;
@@ -703,6 +704,33 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
     zt = Sz[0] * c_plain;
   };
+  auto keys_wide = [&](const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float& zt) {
+    if constexpr (!kWide<G>) return;
+    reinterpret_cast<uint32_t*>(L.k.op)[lane] = meta[0];
+    reinterpret_cast<uint32_t*>(&L.k.zk[0])[lane] = meta[1];
+    wave_lds_fence();
+    const Codes<KB> kc(kr);
+    float4_t Sz = {0, 0, 0, 0};
+    S[0] = float4_t{0, 0, 0, 0}; S[1] = float4_t{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) {
+      const half8_t z8 = *reinterpret_cast<const half8_t*>(&L.k.zk[32 * ks + 8 * kq]);
+      const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.k.op[64 * ks + 16 * kq]);
+      Sz = mfma16(z8, qB[ks], Sz);       // every A row is the zero-point vector
+      const half8_t qp = q_scaled(ks), hi = qp * s8, lo = __builtin_elementwise_fma(qp, s8, -hi);
+#pragma unroll
+      for (int m = 0; m < 2; m++) {
+        const half8_t c = kc.lo(ks + 4 * m);
+        S[m] = mfma16(c, hi, S[m]);
+        S[m] = mfma16(c, lo, S[m]);
+      }
+    }
+    if constexpr (KB == 3) {   // tokens 10 and 21 of the group step by s*7/3
+      if (kq == 1) S[0][2] *= (7.0f / 3.0f);
+      if (kq == 2) S[1][1] *= (7.0f / 3.0f);
+    }
+    zt = Sz[0] * c_plain;
+  };
   // ---- fp16 window tiles: taken round-robin by the waves before the packed stream.
   // Past the end a wave re-reads the last tile (cache hit) and skips its work: the load stream and the
   // loop body stay uniform, which keeps the outstanding-load accounting exact.
@@ -747,6 +775,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
             keys_small(meta, kr, S, zt);
 #pragma unroll
             for (int hh = 0; hh < G; hh++) z = h == hh ? zt[hh] : z;
+          } else if constexpr (kWide<G>) {
+            keys_wide(meta, kr, S, z);
           } else {
             float zt;
             keys_large(meta, kr, S, zt);
@@ -760,7 +790,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
           for (int m = 0; m < 2; m++)
 #pragma unroll
             for (int r4 = 0; r4 < 4; r4++) {
-              const float sum = S[m][r4] + ror8(S[m][r4]);
+              const float sum = kWide<G> ? S[m][r4] : S[m][r4] + ror8(S[m][r4]);
               x[4 * m + r4] = 8 * kq + 4 * m + r4 >= lo ? sum : -INFINITY;
             }
           absorb_window(x, c_code, z, ln, false, u32x4_t{0, 0, 0, 0});
@@ -1129,43 +1159,14 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // go through LDS, and the codes are cut out once for 16 heads. Bound by instruction issue: about 260 vector and 38 matrix
   // instructions per tile and wave; at 72 heads x 32 sequences of 4096 tokens vector and matrix units are busy 79 % of the SIMD clocks
   // (58 + 21 %, a vector instruction 4.1 clocks, at 1.87 GHz). 27 us there; blocks of 8 took 49.
-  auto process_wide = [&](const Stage<KB, VB>& st) {
-    reinterpret_cast<uint32_t*>(L.k.op)[lane] = st.meta[0];
-    reinterpret_cast<uint32_t*>(&L.k.zk[0])[lane] = st.meta[1];
-    wave_lds_fence();
-    float x[8];
-    {
-      const Codes<KB> kc(st.kc);
-      float4_t S[2] = {float4_t{0, 0, 0, 0}, float4_t{0, 0, 0, 0}}, Sz = {0, 0, 0, 0};
+  auto values_wide = [&](const u32x4_t& meta, const Raw<VB>& vr, float (&x)[8], float c, float zt) {
+    if constexpr (!kWide<G>) return;
+    raise_reference(max8(x) * c + zt);
+    const float off = zt - mref;
 #pragma unroll
-      for (int ks = 0; ks < 4; ks++) {
-        const half8_t z8 = *reinterpret_cast<const half8_t*>(&L.k.zk[32 * ks + 8 * kq]);
-        const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.k.op[64 * ks + 16 * kq]);
-        Sz = mfma16(z8, qB[ks], Sz);       // every A row is the zero-point vector
-        const half8_t qp = q_scaled(ks), hi = qp * s8, lo = __builtin_elementwise_fma(qp, s8, -hi);
-#pragma unroll
-        for (int m = 0; m < 2; m++) {
-          const half8_t c = kc.lo(ks + 4 * m);
-          S[m] = mfma16(c, hi, S[m]);
-          S[m] = mfma16(c, lo, S[m]);
-        }
-      }
-      if constexpr (KB == 3) {   // tokens 10 and 21 of the group step by s*7/3
-        if (kq == 1) S[0][2] *= (7.0f / 3.0f);
-        if (kq == 2) S[1][1] *= (7.0f / 3.0f);
-      }
-      const float zt = Sz[0] * c_plain;
-#pragma unroll
-      for (int m = 0; m < 2; m++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) x[4 * m + r] = S[m][r];
-      raise_reference(max8(x) * c_code + zt);
-      const float off = zt - mref;
-#pragma unroll
-      for (int e = 0; e < 8; e++) x[e] = fast_exp2(x[e] * c_code + off);       // the numerators of tokens 8*kq + e
-    }
-    reinterpret_cast<uint32_t*>(L.v.op)[lane] = st.meta[2];
-    reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = st.meta[3];
+    for (int e = 0; e < 8; e++) x[e] = fast_exp2(x[e] * c + off);       // the numerators of tokens 8*kq + e
+    reinterpret_cast<uint32_t*>(L.v.op)[lane] = meta[2];
+    reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = meta[3];
     wave_lds_fence();
     half8_t P, R8;       // numerators as two fp16 terms: rounded to nearest, and the rest
 #pragma unroll
@@ -1176,7 +1177,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     if (col < 4) z8 = *reinterpret_cast<const half8_t*>(&L.v.zv[col][8 * kq]);
     accZ = mfma16(z8, P, accZ);
     accZ = mfma16(z8, R8, accZ);
-    const Codes<VB> vc(st.vc);
+    const Codes<VB> vc(vr);
 #pragma unroll
     for (int g = 0; g < 4; g++) {
       const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.v.op[64 * g + 16 * kq]);
@@ -1190,6 +1191,17 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       }
     }
     wave_lds_fence();   // the next tile's scales come after these reads
+  };
+  auto process_wide = [&](const Stage<KB, VB>& st) {
+    if constexpr (!kWide<G>) return;
+    float4_t S[2];
+    float zt, x[8];
+    keys_wide(st.meta, st.kc, S, zt);
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) x[4 * m + r] = S[m][r];
+    values_wide(st.meta, st.vc, x, c_code, zt);
   };
   auto process = [&](const Stage<KB, VB>& st) {
     if constexpr (kWide<G>) process_wide(st);
@@ -1233,6 +1245,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         Raw<KB> kr;
         kr.load(up, soff + (uint32_t)(kMetaWords * 4), lane16, lane16 >> 1);
         if constexpr (kSmall) keys_small(meta, kr, S, zts);
+        else if constexpr (kWide<G>) keys_wide(meta, kr, S, ztl);
         else keys_large(meta, kr, S, ztl);
       }
       // what the record holds for tokens without a packed Value is not defined
@@ -1248,7 +1261,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         for (int m = 0; m < 2; m++)
 #pragma unroll
           for (int e = 0; e < 4; e++) x[4 * m + e] = 8 * kq + 4 * m + e < limit || lo_part ? S[m][e] : -INFINITY;
-        values_large(meta, vr, x, c, ztl);
+        if constexpr (kWide<G>) values_wide(meta, vr, x, c, ztl);
+        else values_large(meta, vr, x, c, ztl);
       }
     }
   }
@@ -1335,12 +1349,12 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   };
   uint16_t* outp = a.out + row0 * kD;
   // partial of split s, head hh of the block: [unit][block][split][head of the block] (blocks of 16: [unit][split][head of the group])
-  const size_t part0 = kWide<G> ? (size_t)u * a.n_parts * a.G + head0 : (size_t)uo * a.n_parts * G;
+  const size_t part0 = kWide<G> ? (size_t)u * a.n_splits * a.G + head0 : (size_t)uo * a.n_splits * G;
   const int part_step = kWide<G> ? a.G : G;
   auto part_at = [&](int s, int hh) { return a.part + (part0 + (size_t)s * part_step + hh) * (kD + 2); };
   const int n_out = n_heads * kD;
 
-  if (a.n_parts == 1) {
+  if (a.n_splits == 1) {
     if constexpr (G <= 2) {
       // No barrier: a wave delivers its result and leaves; the last one to deliver combines them.
       // (LDS serves a wave's operations in order, so its results are in place before its count.)
@@ -1422,13 +1436,13 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     const uint32_t part_bytes = (uint32_t)(G * (kD + 2) * sizeof(float));
     if (hh < G) {
       // rows of the head, part after part. Parts past the last one are read as the last one and weigh nothing.
-      const rsrc_t rows = make_rsrc(part_at(0, hh), (uint32_t)(a.n_parts - 1) * part_bytes + (kD + 2) * 4u);
+      const rsrc_t rows = make_rsrc(part_at(0, hh), (uint32_t)(a.n_splits - 1) * part_bytes + (kD + 2) * 4u);
       auto merge = [&](auto batch) {
         constexpr int kBatch = decltype(batch)::value;
         float M = -INFINITY, Lsum = 0.0f;
         float2_t O = {0, 0};
-        for (int s0 = 0; s0 < a.n_parts; s0 += kBatch) {
-          const int n = a.n_parts - s0 < kBatch ? a.n_parts - s0 : kBatch;       // >= 1
+        for (int s0 = 0; s0 < a.n_splits; s0 += kBatch) {
+          const int n = a.n_splits - s0 < kBatch ? a.n_splits - s0 : kBatch;       // >= 1
           u32x2_t ml, os[kBatch];
           // The last arrival waits for stores that nothing holds up; the bound is for a workspace that was not zero to begin with.
           for (int tries = 0;; tries++) {
@@ -1471,7 +1485,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         const half2_t v = {(half_t)(O[0] / Lsum), (half_t)(O[1] / Lsum)};
         reinterpret_cast<uint32_t*>(outp + hh * kD)[lane] = as_u32(v);
       };
-      if (a.n_parts <= 8) merge(std::integral_constant<int, 8>{});
+      if (a.n_splits <= 8) merge(std::integral_constant<int, 8>{});
       else merge(std::integral_constant<int, G == 4 && kWaves == 8 ? 16 : kMergeBatch>{});     // (32 do not fit the registers there)
     }
     if (tid == 0) __hip_atomic_store(&a.counters[uo * a.counter_stride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1488,8 +1502,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     st_agent(pp + 2 + d, O);
   }
 
-  // ---- split merge: the last workgroup of the unit to arrive combines all partials (n_parts of them: one per
-  // split, and the one an earlier launch may have left for the tokens between a Key front and a Value front)
+  // ---- split merge: the last workgroup of the unit to arrive combines all partials
   // The partials were stored and are later loaded with agent scope, which the hardware keeps coherent
   // per access across the XCDs' L2s: waiting for the stores to complete is all the release needs.
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partial stores have completed ...
@@ -1508,9 +1521,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     // partial, every lane its channel of each of them, all before the first use; the weights 2^(m_k - M) are
     // computed once per wave (lane k holds the k-th) and handed out as scalars
     float M = -INFINITY, Lsum = 0.0f, O = 0.0f;
-    for (int s0 = 0; s0 < a.n_parts; s0 += kMergeBatch) {
+    for (int s0 = 0; s0 < a.n_splits; s0 += kMergeBatch) {
       float mk = -INFINITY, lk = 0.0f;
-      if (lane < kMergeBatch && s0 + lane < a.n_parts) {
+      if (lane < kMergeBatch && s0 + lane < a.n_splits) {
         const float* pp = base + (size_t)(s0 + lane) * stride;
         mk = ld_agent(pp);
         lk = ld_agent(pp + 1);
@@ -1519,7 +1532,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
 #pragma unroll
       for (int k = 0; k < kMergeBatch; k++) {
         os[k] = 0.0f;
-        if (s0 + k < a.n_parts) os[k] = ld_agent(base + (size_t)(s0 + k) * stride + 2 + d);   // wave-uniform test
+        if (s0 + k < a.n_splits) os[k] = ld_agent(base + (size_t)(s0 + k) * stride + 2 + d);   // wave-uniform test
       }
       // cross-lane reads stay outside divergent code
       const float mrow = row_max(mk);
@@ -1552,7 +1565,7 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
       if constexpr (kNW == 12 || VB < 3) { decode_attn_kernel<KB, VB, 8, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break; }
       else return hipErrorInvalidValue;
 #endif
-#if KVMIX_WAVES == 8 && !KVMIX_MIXED
+#if KVMIX_WAVES == 8 || KVMIX_MIXED
     case 16: decode_attn_kernel<KB, VB, 16, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break;
 #endif
     default: return hipErrorInvalidValue;

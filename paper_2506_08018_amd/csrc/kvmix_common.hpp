@@ -136,8 +136,7 @@ struct AttnArgs {
   const uint16_t* k_new; const uint16_t* v_new;
   uint16_t* k_win_w; uint16_t* v_win_w;
   int new_slot;           // -1: nothing to append
-  float* part;            // partials: [units][n_parts][G][kD + 2], the first n_splits of a unit written by this launch
-  int n_parts;            // n_splits, plus one when an earlier launch left the partial of the tokens between two fronts
+  float* part;            // partials: [units][n_splits][G][kD + 2]
   uint32_t* counters;     // arrival counters (zero before and after every call), one per (unit, head block), counter_stride words apart
   int counter_stride;
   int G;                  // query heads per kv head
@@ -150,25 +149,11 @@ struct AttnArgs {
   // window tile more than the others take win_tiles packed tiles less
   int items_q, items_r, win_tiles;
   float scale_log2;       // softmax_scale * log2(e)
-  // Tiles between two fronts, worked on in the same launch (groups of up to 4 heads): tiles [m_first, m_first + m_tiles), tokens up to m_end;
+  // Tiles between two fronts (MIXED): tiles [m_first, m_first + m_tiles), tokens up to m_end;
   // m_front: the Value front; m_ahead: it is ahead of the Key front; m_ring: ring tile of tile m_first. The window tiles above are dealt
   // out together with those of them whose Values come from the ring.
   int m_first, m_tiles, m_end, m_front, m_ring;
   bool m_ahead;
-};
-
-// Tokens [t_begin, t_end) of every unit, each Key and each Value from where it lives (packed before its front, the
-// fp16 ring from it on): one partial (reference, sum of numerators, unnormalized output) per (unit, head) into
-// slot part_index of the partials array.
-struct MixedArgs {
-  const uint16_t* q; const uint32_t* packed; const uint16_t* k_win; const uint16_t* v_win;
-  float* part; int n_parts, part_index;
-  int tiles_cap, W_cap, k_bits, v_bits;
-  int n_qk, n_qv;          // the two fronts
-  int t_begin, t_end;      // t_begin is a multiple of 32
-  int slot_begin;          // ring slot of token t_begin
-  int G, G_main;           // query heads per kv head; heads that the main kernel's partials lie together for (G, or its block of 8)
-  float scale_log2;
 };
 
 // over n_tiles tiles (and the window rows that a.n_copy names)
@@ -176,11 +161,10 @@ hipError_t launch_quantize_pack(QuantArgs a, int k_bits, int v_bits,
                                 int n_tiles, int units, hipStream_t s);
 hipError_t launch_quantize_fronts(const QuantArgs& a, int k_bits, int v_bits,
                                   int n_tiles, int units, hipStream_t s);
-hipError_t launch_mixed_fronts(const MixedArgs& a, int units, hipStream_t s);
 hipError_t launch_dequant(const DequantArgs& a, int units, hipStream_t s);
 hipError_t launch_append(const AppendArgs& a, hipStream_t s);
 hipError_t launch_stream_read(const void* buf, size_t bytes, int workgroups, int threads, uint32_t* sink, hipStream_t s);
-// WAVES: waves per workgroup, 8 or 12 (blocks of 16 heads: 8). MIXED: with the tiles between two fronts (blocks of up to 4 heads, 12 waves).
+// WAVES: waves per workgroup, 8 or 12 (blocks of 16 heads: 8). MIXED: with the tiles between two fronts (blocks of 1, 2, 4 and 16 heads, 12 waves).
 // block: query heads per workgroup (1, 2, 4, 8 or 16); a unit's group of a.G heads takes (a.G + block - 1) / block workgroups per split.
 template <int WAVES, bool MIXED>
 hipError_t launch_decode_attn(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);

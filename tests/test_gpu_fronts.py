@@ -135,7 +135,7 @@ def test_attention_with_fronts_apart(G, state):
 
 @pytest.mark.parametrize("G,kb,vb,keep_k,keep_v", [
     (1, 3, 2, 1100, 70), (1, 2, 4, 70, 1100), (2, 2, 3, 1100, 33), (2, 4, 2, 64, 1009), (4, 3, 3, 1100, 64), (4, 3, 4, 61, 1100), (4, 2, 2, 900, 1),
-    (4, 4, 4, 3, 1100)])
+    (4, 4, 4, 3, 1100), (8, 2, 3, 1100, 70), (8, 3, 4, 61, 1100), (24, 3, 2, 1100, 33), (24, 4, 2, 70, 1009)])
 def test_many_tiles_between_the_fronts(G, kb, vb, keep_k, keep_v):
     """More tiles between the fronts than a workgroup has waves, either front ahead, the Value front inside and at the end of a tile; what is not
     to be read holds NaN: ring slots of packed and of no tokens, record fields of Values that are still in the ring. Unsplit, split in uneven

@@ -297,6 +297,17 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
   hi = __builtin_bit_cast(uint32_t, hv);
   lo = __builtin_bit_cast(uint32_t, lv);
 }
+// fp32 pair -> packed fp16 pairs, hi rounded to nearest, lo what the rounding left (rounded): the remainder is taken with the fp16 number as it
+// is, without a conversion back (a tile of 16 heads: 16 vector instructions of 255 less).
+__device__ __forceinline__ void split_nearest(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+  const half2_t hv = __builtin_convertvector(float2_t{x0, x1}, half2_t);
+  hi = as_u32(hv);
+  float r0, r1;       // (the exponentials behind x0 and x1 have passed the conversion above: nothing here reads them too early)
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hi), "v"(x0));
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hi), "v"(x1));
+  const half2_t lv = __builtin_convertvector(float2_t{r0, r1}, half2_t);
+  lo = as_u32(lv);
+}
 __device__ __forceinline__ half_t split_part(float x, bool lo_part) {
   const half2_t hv = __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(x, 0.0f));
   const half_t hi = hv[0];
@@ -541,7 +552,16 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   };
   // zero outside the lo columns
   const uint32_t lo_mask = lo_part ? 0xFFFFFFFFu : 0u;
-  auto lo_only = [&](half8_t v) { return as_half8(__builtin_bit_cast(u32x4_t, v) & lo_mask); };
+  auto lo_only = [&](half8_t v, uint32_t signs = 0) {      // signs: 0x80008000 for the negative
+    u32x4_t w = __builtin_bit_cast(u32x4_t, v);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      uint32_t t = (w[i] ^ signs) & lo_mask;
+      asm("" : "+v"(t));      // (a sign taken off the result is an operand modifier then, not a bit operation on the masked word)
+      w[i] = t;
+    }
+    return as_half8(w);
+  };
 
   const half8_t zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
   const half8_t ones8 = {1, 1, 1, 1, 1, 1, 1, 1};
@@ -571,6 +591,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       for (int m = 0; m < 8; m++) acc[m] *= f;
     }
   };
+  // (No inline assembly here: an instruction that reads what the matrix core writes has to wait for it, and only the compiler's own are made to.)
   auto max8 = [](const float (&s)[8]) {
     float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
     mx = fmaxf(fmaxf(mx, s[3]), s[4]);
@@ -978,11 +999,11 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         // whose remainder's product falls below the fp16 range would bias the sums (plain casts are safe here:
         // the values come out of the exponential instruction, nothing can be fused into the conversions)
         const float p0 = fast_exp2(sh[k][0] + sl[k][0]), p1 = fast_exp2(sh[k][1] + sl[k][1]);
-        const half2_t hv = {(half_t)p0, (half_t)p1};
-        const half2_t lv = {(half_t)(p0 - (float)hv[0]), (half_t)(p1 - (float)hv[1])};
+        uint32_t hv, lv;
+        split_nearest(p0, p1, hv, lv);
         const int at = Operand<G>::write_at(tp, hh);
-        *reinterpret_cast<uint32_t*>(&L.v.pq[at]) = as_u32(hv);
-        *reinterpret_cast<uint32_t*>(&L.v.pq[at + Operand<G>::kLo]) = as_u32(lv);
+        *reinterpret_cast<uint32_t*>(&L.v.pq[at]) = hv;
+        *reinterpret_cast<uint32_t*>(&L.v.pq[at + Operand<G>::kLo]) = lv;
       }
       reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = meta[3];
     }
@@ -1118,11 +1139,11 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         // whose remainder's product falls below the fp16 range would bias the sums (plain casts are safe here:
         // the values come out of the exponential instruction, nothing can be fused into the conversions)
         const float p0 = fast_exp2(sh[k][0] + sl[k][0]), p1 = fast_exp2(sh[k][1] + sl[k][1]);
-        const half2_t hv = {(half_t)p0, (half_t)p1};
-        const half2_t lv = {(half_t)(p0 - (float)hv[0]), (half_t)(p1 - (float)hv[1])};
+        uint32_t hv, lv;
+        split_nearest(p0, p1, hv, lv);
         const int at = Operand<G>::write_at(tp, hh);
-        *reinterpret_cast<uint32_t*>(&L.v.pq[at]) = as_u32(hv);
-        *reinterpret_cast<uint32_t*>(&L.v.pq[at + Operand<G>::kLo]) = as_u32(lv);
+        *reinterpret_cast<uint32_t*>(&L.v.pq[at]) = hv;
+        *reinterpret_cast<uint32_t*>(&L.v.pq[at + Operand<G>::kLo]) = lv;
       }
       reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = st.meta[3];
       reinterpret_cast<uint32_t*>(L.v.op)[lane] = st.meta[2];
@@ -1133,11 +1154,11 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     const half8_t PB = *reinterpret_cast<const half8_t*>(&L.v.pq[op_read]);
     // hi columns: the rounded products p * s; lo columns: what the rounding left, and the small terms' products
     const half8_t p8 = *reinterpret_cast<const half8_t*>(&L.v.pq[Operand<G>::read_at(kq, h, false)]);
-    const half8_t px = lo_only(p8), dx = lo_only(PB);
+    const half8_t nx = lo_only(p8, 0x80008000u), dx = lo_only(PB);
 #pragma unroll
     for (int g = 0; g < 4; g++) {
       const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.v.op[64 * g + 16 * kq]);
-      Bv[g] = __builtin_elementwise_fma(dx, s8, __builtin_elementwise_fma(p8, s8, -(px * s8)));
+      Bv[g] = __builtin_elementwise_fma(dx, s8, __builtin_elementwise_fma(p8, s8, nx * s8));
     }
     {
       const Codes<VB> vc(st.vc);
@@ -1168,9 +1189,10 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     reinterpret_cast<uint32_t*>(L.v.op)[lane] = meta[2];
     reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = meta[3];
     wave_lds_fence();
-    half8_t P, R8;       // numerators as two fp16 terms: rounded to nearest, and the rest
+    u32x4_t pw, rw;       // numerators as two fp16 terms: rounded to nearest, and the rest
 #pragma unroll
-    for (int e = 0; e < 8; e++) { P[e] = (half_t)x[e]; R8[e] = (half_t)(x[e] - (float)P[e]); }
+    for (int e = 0; e < 4; e++) { uint32_t hv, lv; split_nearest(x[2 * e], x[2 * e + 1], hv, lv); pw[e] = hv; rw[e] = lv; }
+    const half8_t P = as_half8(pw), R8 = as_half8(rw);
     // zero-point term: A rows 0..3 carry the zero-points of channel blocks 0..3, rows 4..15 are ones
     // and accumulate the sum of the numerators
     half8_t z8 = ones8;

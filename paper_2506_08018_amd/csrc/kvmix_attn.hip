@@ -248,9 +248,6 @@ template <int KB, int VB> struct Stage {
   }
 };
 
-[[maybe_unused]] __device__ __forceinline__ void st_agent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-[[maybe_unused]] __device__ __forceinline__ float ld_agent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
 // Groups whose split partials tell of themselves: a word is zero until it has been stored (see the split merge).
 template <int G> constexpr bool kTagged = G <= 4;
 constexpr int kMaxTries = 1 << 16;      // a round trip to memory each
@@ -1354,27 +1351,30 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   }
   if (col < G && kq == 0) { R.m[wave][col] = mref; R.l[wave][col] = lsum; }
 
-  // combines the per-wave results of output idx = head * 128 + channel
-  auto combine = [&](int idx, float& M, float& Lsum, float& O) {
-    const int hh = idx / kD, d = idx % kD;
-    M = -INFINITY;
+  // Wave w combines the waves' results of heads w, w + kWaves, ... of the block, a lane two channels: the weights 2^(m_w - M) once per head (lane w
+  // holds the w-th), handed out as scalars.
+  constexpr int kHeads = (G + kWaves - 1) / kWaves;       // heads per wave
+  auto combine_head = [&](int hh, float2_t& ml, float2_t& O) {
+    const float mw = lane < kWaves ? R.m[lane < kWaves ? lane : 0][hh] : -INFINITY, lw = lane < kWaves ? R.l[lane < kWaves ? lane : 0][hh] : 0.0f;
+    float2_t o[kWaves];
 #pragma unroll
-    for (int w = 0; w < kWaves; w++) M = fmaxf(M, R.m[w][hh]);
-    Lsum = 0.0f; O = 0.0f;
+    for (int w = 0; w < kWaves; w++) o[w] = *reinterpret_cast<const float2_t*>(&s_wave[w].o[hh][2 * lane]);
+    const float M = uniform_lane(row_max(mw), 0);
+    const float fw = (mw == -INFINITY) ? 0.0f : fast_exp2(mw - M);
+    ml = float2_t{M, uniform_lane(row_sum(lw * fw), 0)};
+    O = float2_t{0, 0};
 #pragma unroll
-    for (int w = 0; w < kWaves; w++) {
-      const float mw = R.m[w][hh];
-      const float f = (mw == -INFINITY) ? 0.0f : fast_exp2(mw - M);
-      Lsum += R.l[w][hh] * f;
-      O += s_wave[w].o[hh][d] * f;
-    }
+    for (int w = 0; w < kWaves; w++) O += o[w] * uniform_lane(fw, w);
   };
   uint16_t* outp = a.out + row0 * kD;
   // partial of split s, head hh of the block: [unit][block][split][head of the block] (blocks of 16: [unit][split][head of the group])
   const size_t part0 = kWide<G> ? (size_t)u * a.n_splits * a.G + head0 : (size_t)uo * a.n_splits * G;
   const int part_step = kWide<G> ? a.G : G;
   auto part_at = [&](int s, int hh) { return a.part + (part0 + (size_t)s * part_step + hh) * (kD + 2); };
-  const int n_out = n_heads * kD;
+  auto put_out = [&](int hh, const float2_t& O, float Lsum) {
+    const half2_t v = {(half_t)(O[0] / Lsum), (half_t)(O[1] / Lsum)};
+    reinterpret_cast<uint32_t*>(outp + hh * kD)[lane] = as_u32(v);
+  };
 
   if (a.n_splits == 1) {
     if constexpr (G <= 2) {
@@ -1411,167 +1411,140 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         outp[hh * kD + lane + kWave] = __builtin_bit_cast(uint16_t, (half_t)(O1 * inv));
       }
     } else {
-      __syncthreads();
-      for (int idx = tid; idx < n_out; idx += kThreads) {
-        float M, Lsum, O;
-        combine(idx, M, Lsum, O);
-        outp[idx] = __builtin_bit_cast(uint16_t, (half_t)(O / Lsum));
+      lds_barrier();
+#pragma unroll
+      for (int k = 0; k < kHeads; k++) {
+        const int hh = wave + k * kWaves;
+        float2_t ml, O;
+        if (hh < n_heads) {
+          combine_head(hh, ml, O);
+          put_out(hh, O, ml[1]);
+        }
       }
     }
     return;
   }
 
+  // ---- split merge: every workgroup stores its partial, the last one of the unit to arrive combines them. Partials are stored and loaded with
+  // agent scope, which the hardware keeps coherent per access across the XCDs' L2s: stores are written through to the level that all
+  // XCDs share, loads miss the XCD's own, no cache-wide flush is needed.
+  // Larger groups: a wave waits until its stores have completed; after a barrier the arrival is counted.
+  // Groups of up to 4 heads: partials that tell of themselves. Every word of the partials is zero before and after a call; a split stores
+  // its words as anything but zero (a zero as minus zero). The arrival is counted, by a wave of its own, before the partial is even
+  // combined: the count is on its way meanwhile, and no store is waited for. The workgroup that arrives last knows that every other one of
+  // the unit has its results and stores them without waiting for anything; it takes a partial when all of its words read as
+  // other than zero. Stores that wait for nothing and a count that is back when they
+  // are issued, instead of stores, their acknowledgement, a barrier and the count in a row: 32 units of 3 splits (one small layer) 6.35 ->
+  // 5.75 us, 24 units of 6 splits and 4 heads 8.2 -> 7.6, 32 units of 8 splits 10.4 -> 9.6, 128 of 2 splits 24.9 -> 24.1; 8 units of 32
+  // splits, 66 KB to read and to zero for the one workgroup, 12.4 -> 12.3. (Zeroing after the merge instead of under it: 12.4.) Groups of 8
+  // heads have no wave to spare for the count, and twice the words to zero.
+  static_assert(!kTagged<G> || G < kWaves);
+  lds_barrier();          // the waves' results are in LDS
+  uint32_t prev = 0;
   if constexpr (kTagged<G>) {
-    // ---- split merge of small groups: partials that tell of themselves. Every word of the partials is zero before and after a call; a split stores
-    // its words as anything but zero (a zero as minus zero). The arrival is counted, by a wave of its own, before the partial is even
-    // combined: the count is on its way meanwhile, and no store is waited for. The workgroup that arrives last knows that every other one of
-    // the unit has its results and stores them without waiting for anything; it takes a partial when all of its words read as
-    // other than zero. Wave w works on head w, a lane on two of its channels. Stores that wait for nothing and a count that is back when they
-    // are issued, instead of stores, their acknowledgement, a barrier and the count in a row: 32 units of 3 splits (one small layer) 6.35 ->
-    // 5.75 us, 24 units of 6 splits and 4 heads 8.2 -> 7.6, 32 units of 8 splits 10.4 -> 9.6, 128 of 2 splits 24.9 -> 24.1; 8 units of 32
-    // splits, 66 KB to read and to zero for the one workgroup, 12.4 -> 12.3. (Zeroing after the merge instead of under it: 12.4.) Groups of 8
-    // heads have no wave to spare for the count, and twice the words to zero.
-    static_assert(G < kWaves);
-    lds_barrier();          // the waves' results are in LDS
-    uint32_t prev = 0;
     if (tid == kThreads - 1) prev = __hip_atomic_fetch_add(&a.counters[uo * a.counter_stride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int hh = wave;
-    float2_t own = {0, 0}, own_ml = {-INFINITY, 0};
-    uint64_t* row = reinterpret_cast<uint64_t*>(part_at(sp, hh));
-    if (hh < G) {
-      const float mw = lane < kWaves ? R.m[lane < kWaves ? lane : 0][hh] : -INFINITY, lw = lane < kWaves ? R.l[lane < kWaves ? lane : 0][hh] : 0.0f;
-      float2_t o[kWaves];
+  }
 #pragma unroll
-      for (int w = 0; w < kWaves; w++) o[w] = *reinterpret_cast<const float2_t*>(&s_wave[w].o[hh][2 * lane]);
-      const float M = uniform_lane(row_max(mw), 0);
-      const float fw = (mw == -INFINITY) ? 0.0f : fast_exp2(mw - M);
-      own_ml = float2_t{M, uniform_lane(row_sum(lw * fw), 0)};
-#pragma unroll
-      for (int w = 0; w < kWaves; w++) own += o[w] * uniform_lane(fw, w);
-      // agent-scope stores: written through to the level all XCDs share
-      if (lane == 0) st_agent2(row, own_ml);
-      st_agent2(row + 1 + lane, own);
+  for (int k = 0; k < kHeads; k++) {
+    const int hh = wave + k * kWaves;
+    if (hh < n_heads) {
+      float2_t ml, O;
+      combine_head(hh, ml, O);
+      uint64_t* row = reinterpret_cast<uint64_t*>(part_at(sp, hh));
+      if (lane == 0) st_agent2(row, ml);
+      st_agent2(row + 1 + lane, O);
     }
+  }
+  if constexpr (kTagged<G>) {
     if (tid == kThreads - 1) s_done = prev == (uint32_t)a.n_splits - 1u;   // reused as the "last workgroup" flag
     lds_barrier();
-    if (!s_done) return;
-    const uint32_t part_bytes = (uint32_t)(G * (kD + 2) * sizeof(float));
-    if (hh < G) {
-      // rows of the head, part after part. Parts past the last one are read as the last one and weigh nothing.
-      const rsrc_t rows = make_rsrc(part_at(0, hh), (uint32_t)(a.n_splits - 1) * part_bytes + (kD + 2) * 4u);
-      auto merge = [&](auto batch) {
-        constexpr int kBatch = decltype(batch)::value;
-        float M = -INFINITY, Lsum = 0.0f;
-        float2_t O = {0, 0};
-        for (int s0 = 0; s0 < a.n_splits; s0 += kBatch) {
-          const int n = a.n_splits - s0 < kBatch ? a.n_splits - s0 : kBatch;       // >= 1
-          u32x2_t ml, os[kBatch];
-          // The last arrival waits for stores that nothing holds up; the bound is for a workspace that was not zero to begin with.
-          for (int tries = 0;; tries++) {
-            asm volatile("" ::: "memory");        // (to the compiler these loads see the same memory every time otherwise)
-            ml = ld_agent2(rows, (uint32_t)(s0 + (lane < n ? lane : n - 1)) * part_bytes, 0);
-#pragma unroll
-            for (int k = 0; k < kBatch; k++) os[k] = ld_agent2(rows, 8u + 8u * lane, (uint32_t)(s0 + (k < n ? k : n - 1)) * part_bytes);
-            uint32_t least = ml[0] < ml[1] ? ml[0] : ml[1];
-#pragma unroll
-            for (int k = 0; k < kBatch; k++) {
-              least = os[k][0] < least ? os[k][0] : least;
-              least = os[k][1] < least ? os[k][1] : least;
-            }
-            if (__builtin_amdgcn_ballot_w64(least == 0u) == 0 || tries == kMaxTries) break;
-          }
-          // nobody else reads the rows of this head: zero again, on the way while the sums are taken
-          if (lane < n) st_agent2_zero(rows, (uint32_t)(s0 + lane) * part_bytes, 0);
-#pragma unroll
-          for (int k = 0; k < kBatch; k++)
-            if (k < n) st_agent2_zero(rows, 8u + 8u * lane, (uint32_t)(s0 + k) * part_bytes);
-          const uint32_t mb = ml[0], lb = ml[1];      // (copies: a bit cast applied to an element itself reads element 0)
-          const float mk = lane < n ? __builtin_bit_cast(float, mb) : -INFINITY, lk = __builtin_bit_cast(float, lb);
-          // weights 2^(m_k - M) once per wave (lane k holds the k-th), handed out as scalars; cross-lane reads stay outside divergent code
-          const float mrow = row_max(mk);
-          float Mn = fmaxf(M, uniform_lane(mrow, 0));
-          if constexpr (kBatch > 16) Mn = fmaxf(Mn, uniform_lane(mrow, 16));
-          const float fold = (M == -INFINITY) ? 0.0f : fast_exp2(M - Mn);
-          const float fk = (mk == -INFINITY) ? 0.0f : fast_exp2(mk - Mn);
-          const float lrow = row_sum(lk * fk);
-          Lsum = Lsum * fold + uniform_lane(lrow, 0);
-          if constexpr (kBatch > 16) Lsum += uniform_lane(lrow, 16);
-          O *= fold;
-#pragma unroll
-          for (int k = 0; k < kBatch; k++) {
-            const uint32_t o0 = os[k][0], o1 = os[k][1];
-            O += float2_t{__builtin_bit_cast(float, o0), __builtin_bit_cast(float, o1)} * uniform_lane(fk, k);
-          }
-          M = Mn;
-        }
-        const half2_t v = {(half_t)(O[0] / Lsum), (half_t)(O[1] / Lsum)};
-        reinterpret_cast<uint32_t*>(outp + hh * kD)[lane] = as_u32(v);
-      };
-      if (a.n_splits <= 8) merge(std::integral_constant<int, 8>{});
-      else merge(std::integral_constant<int, G == 4 && kWaves == 8 ? 16 : kMergeBatch>{});     // (32 do not fit the registers there)
-    }
-    if (tid == 0) __hip_atomic_store(&a.counters[uo * a.counter_stride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return;
   } else {
-  __syncthreads();
-  for (int idx = tid; idx < n_out; idx += kThreads) {
-    float M, Lsum, O;
-    combine(idx, M, Lsum, O);
-    // agent-scope stores: written through to the level all XCDs share (no cache-wide flush needed)
-    const int hh = idx / kD, d = idx % kD;
-    float* pp = part_at(sp, hh);
-    if (d == 0) { st_agent(pp, M); st_agent(pp + 1, Lsum); }
-    st_agent(pp + 2 + d, O);
-  }
-
-  // ---- split merge: the last workgroup of the unit to arrive combines all partials
-  // The partials were stored and are later loaded with agent scope, which the hardware keeps coherent
-  // per access across the XCDs' L2s: waiting for the stores to complete is all the release needs.
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partial stores have completed ...
-  __syncthreads();                                     // ... and so have those of all waves, before the arrival is counted
-  if (tid == 0) {
-    const uint32_t prev = __hip_atomic_fetch_add(&a.counters[uo * a.counter_stride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_done = (prev == (uint32_t)a.n_splits - 1u);   // reused as the "last workgroup" flag
-  }
-  __syncthreads();
-  if (!s_done) return;
-  for (int idx = tid; idx < n_out; idx += kThreads) {
-    const int hh = __builtin_amdgcn_readfirstlane(idx / kD), d = idx % kD;   // a wave's 64 outputs share the head
-    const float* base = part_at(0, hh);
-    const size_t stride = (size_t)part_step * (kD + 2);
-    // one pass, kMergeBatch partials per round trip: lane k requests reference and sum of the batch's k-th
-    // partial, every lane its channel of each of them, all before the first use; the weights 2^(m_k - M) are
-    // computed once per wave (lane k holds the k-th) and handed out as scalars
-    float M = -INFINITY, Lsum = 0.0f, O = 0.0f;
-    for (int s0 = 0; s0 < a.n_splits; s0 += kMergeBatch) {
-      float mk = -INFINITY, lk = 0.0f;
-      if (lane < kMergeBatch && s0 + lane < a.n_splits) {
-        const float* pp = base + (size_t)(s0 + lane) * stride;
-        mk = ld_agent(pp);
-        lk = ld_agent(pp + 1);
-      }
-      float os[kMergeBatch];
-#pragma unroll
-      for (int k = 0; k < kMergeBatch; k++) {
-        os[k] = 0.0f;
-        if (s0 + k < a.n_splits) os[k] = ld_agent(base + (size_t)(s0 + k) * stride + 2 + d);   // wave-uniform test
-      }
-      // cross-lane reads stay outside divergent code
-      const float mrow = row_max(mk);
-      const float Mn = fmaxf(M, fmaxf(uniform_lane(mrow, 0), uniform_lane(mrow, 16)));
-      const float fold = (M == -INFINITY) ? 0.0f : fast_exp2(M - Mn);
-      const float fk = (mk == -INFINITY) ? 0.0f : fast_exp2(mk - Mn);
-      const float lrow = row_sum(lk * fk);
-      Lsum = Lsum * fold + (uniform_lane(lrow, 0) + uniform_lane(lrow, 16));
-      O *= fold;
-#pragma unroll
-      for (int k = 0; k < kMergeBatch; k++) O += os[k] * uniform_lane(fk, k);
-      M = Mn;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partial stores have completed ...
+    __syncthreads();                                     // ... and so have those of all waves, before the arrival is counted
+    if (tid == 0) {
+      prev = __hip_atomic_fetch_add(&a.counters[uo * a.counter_stride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_done = prev == (uint32_t)a.n_splits - 1u;
     }
-    outp[idx] = __builtin_bit_cast(uint16_t, (half_t)(O / Lsum));
+    __syncthreads();
+  }
+  if (!s_done) return;
+  // The loads of all heads of a wave and up to kBatch parts are under way together, without a branch around each; parts past the last one are
+  // read as the last one and weigh nothing. (Blocks of 16 heads used to take four round trips: 32 units x 72 heads, 3 splits, 27.5 -> 22.8 us per
+  // launch; 4 x 16 heads 12.0 -> 9.9; 8 units of 8 heads 10.1 -> 8.4.)
+  const uint32_t part_bytes = (uint32_t)(part_step * (kD + 2) * sizeof(float));
+  auto merge = [&](auto batch) {
+    constexpr int kBatch = decltype(batch)::value;
+    float M[kHeads], Lsum[kHeads];
+    float2_t O[kHeads];
+#pragma unroll
+    for (int k = 0; k < kHeads; k++) { M[k] = -INFINITY; Lsum[k] = 0.0f; O[k] = float2_t{0, 0}; }
+    for (int s0 = 0; s0 < a.n_splits; s0 += kBatch) {
+      const int n = a.n_splits - s0 < kBatch ? a.n_splits - s0 : kBatch;       // >= 1
+      u32x2_t ml[kHeads], os[kHeads][kBatch];
+      // (tagged) The last arrival waits for stores that nothing holds up; the bound is for a workspace that was not zero to begin with.
+      for (int tries = 0;; tries++) {
+        asm volatile("" ::: "memory");        // (to the compiler these loads see the same memory every time otherwise)
+        uint32_t least = 1;
+#pragma unroll
+        for (int k = 0; k < kHeads; k++) {
+          const int hh = wave + k * kWaves < n_heads ? wave + k * kWaves : n_heads - 1;
+          const rsrc_t rows = make_rsrc(part_at(0, hh), (uint32_t)(a.n_splits - 1) * part_bytes + (kD + 2) * 4u);
+          ml[k] = ld_agent2(rows, (uint32_t)(s0 + (lane < n ? lane : n - 1)) * part_bytes, 0);
+#pragma unroll
+          for (int i = 0; i < kBatch; i++) os[k][i] = ld_agent2(rows, 8u + 8u * lane, (uint32_t)(s0 + (i < n ? i : n - 1)) * part_bytes);
+        }
+        if constexpr (!kTagged<G>) break;
+#pragma unroll
+        for (int k = 0; k < kHeads; k++) {
+          least = ml[k][0] < ml[k][1] ? ml[k][0] : ml[k][1];
+#pragma unroll
+          for (int i = 0; i < kBatch; i++) {
+            least = os[k][i][0] < least ? os[k][i][0] : least;
+            least = os[k][i][1] < least ? os[k][i][1] : least;
+          }
+        }
+        if (__builtin_amdgcn_ballot_w64(least == 0u) == 0 || tries == kMaxTries) break;
+      }
+      if constexpr (kTagged<G>) {
+        // nobody else reads the rows of this head: zero again, on the way while the sums are taken
+        const rsrc_t rows = make_rsrc(part_at(0, wave), (uint32_t)(a.n_splits - 1) * part_bytes + (kD + 2) * 4u);
+        if (lane < n) st_agent2_zero(rows, (uint32_t)(s0 + lane) * part_bytes, 0);
+#pragma unroll
+        for (int i = 0; i < kBatch; i++)
+          if (i < n) st_agent2_zero(rows, 8u + 8u * lane, (uint32_t)(s0 + i) * part_bytes);
+      }
+#pragma unroll
+      for (int k = 0; k < kHeads; k++) {
+        const uint32_t mb = ml[k][0], lb = ml[k][1];      // (copies: a bit cast applied to an element itself reads element 0)
+        const float mk = lane < n ? __builtin_bit_cast(float, mb) : -INFINITY, lk = __builtin_bit_cast(float, lb);
+        // weights 2^(m_k - M) once per wave (lane i holds the i-th), handed out as scalars; cross-lane reads stay outside divergent code
+        const float mrow = row_max(mk);
+        float Mn = fmaxf(M[k], uniform_lane(mrow, 0));
+        if constexpr (kBatch > 16) Mn = fmaxf(Mn, uniform_lane(mrow, 16));
+        const float fold = (M[k] == -INFINITY) ? 0.0f : fast_exp2(M[k] - Mn);
+        const float fk = (mk == -INFINITY) ? 0.0f : fast_exp2(mk - Mn);
+        const float lrow = row_sum(lk * fk);
+        Lsum[k] = Lsum[k] * fold + uniform_lane(lrow, 0);
+        if constexpr (kBatch > 16) Lsum[k] += uniform_lane(lrow, 16);
+        O[k] *= fold;
+#pragma unroll
+        for (int i = 0; i < kBatch; i++) {
+          const uint32_t o0 = os[k][i][0], o1 = os[k][i][1];
+          O[k] += float2_t{__builtin_bit_cast(float, o0), __builtin_bit_cast(float, o1)} * uniform_lane(fk, i);
+        }
+        M[k] = Mn;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kHeads; k++)
+      if (wave + k * kWaves < n_heads) put_out(wave + k * kWaves, O[k], Lsum[k]);
+  };
+  if (wave < n_heads) {
+    constexpr bool kFewer = (kWaves == 8 && G >= 4) || kHeads > 1;      // (32 do not fit the registers)
+    if (a.n_splits <= 8) merge(std::integral_constant<int, 8>{});
+    else merge(std::integral_constant<int, kFewer ? 16 : kMergeBatch>{});
   }
   if (tid == 0) __hip_atomic_store(&a.counters[uo * a.counter_stride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
   }
 }
 

@@ -301,22 +301,22 @@ int attn_waves(long long workgroups, int n_tiles, int n_splits, int block, int v
 }
 
 // Groups of 16 heads and more run in blocks of 16 or of 8 heads. A block of 16 takes less work per head, a block of 8 has the shorter
-// chain per tile and half the outputs to combine and to merge. Modelled times of a launch, in units of the 0.19 us that a 2/2-bit tile takes a
-// workgroup of 16 heads with a compute unit to itself; fixed parts and merging splits besides the tiles. Blocks of 16: workgroups that share
-// a compute unit share its rate, and the second one starts late. A tile of 3/4 bit counts as 1.3 (8 x 48 heads over 8000 tokens: 17.5 us in
-// blocks of 8, 17.1 in blocks of 16; 2/2 bit 16.2, 16.4), a window tile as 2.4 (full precision, 32 x 48 over 2000: 26.1, 22.9; 8 x 72:
-// 15.0, 14.4; 8 x 48: 12.2, 14.6). Fitted to 1 x 72 heads over 8000 tokens (1, 4, 8, 16, 32 splits:
-// 51.8, 21.3, 15.7, 14.3, 16.4 us in blocks of 16; 40.6, 16.7, 12.9, 11.2, 15.2 in blocks of 8), 16 x 48 over 4000 (2, 4, 6, 8: 22.4, 16.9,
-// 20.6, 19.4), 32 x 48 over 2000 (1, 2, 4: 16.7, 16.3, 19.0; 14.6 in blocks of 8, unsplit), 1 x 16 over 64, 480 and 992 (unsplit: 5.8, 7.8,
-// 10.4; 4.8, 7.2, 9.7).
+// chain per tile and half the outputs to combine and to merge. Modelled times of a launch in us, for tiles of 2/2 bit; fixed parts and merging
+// splits besides the tiles. Blocks of 16: workgroups that share
+// a compute unit share its rate, and the second one starts late. A tile of 3/4 bit counts as 1.3 (8 x 48 heads over 8000 tokens: 16.3 us in
+// blocks of 8, 14.3 in blocks of 16), a window tile as 2.4. Fitted to 1 x 72 heads over 8000 tokens (1, 4, 8, 16, 32 splits:
+// 42.7, 15.9, 12.2, 11.0, 12.2 us in blocks of 16; 36.9, 14.8, 11.0, 9.6, 12.7 in blocks of 8), 16 x 48 over 4000 (2, 4, 5, 6, 8: 18.2, 13.6,
+// 12.8, 16.0, 15.2; 16.7 in blocks of 8, 2 splits), 32 x 48 over 2000 (1, 2, 4: 15.7, 13.3, 15.0; 15.4 in blocks of 8, unsplit), 64 x 16 over 1000
+// (2, 3, 4, 5: 10.7, 10.1, 9.5, 12.1; 10.3 in blocks of 8, 2 splits), 1 x 16 over 1000 (1, 4: 8.9, 7.9; 8.9, 7.3), 32 x 72 over 4000 (1 to 4: 29.5,
+// 29.8, 24.0, 28.2).
 double tile_work(int packed_tiles, int window_tiles, int k_bits, int v_bits) {
   return packed_tiles * (1.0 + 0.1 * (k_bits + v_bits - 4)) + 2.4 * window_tiles;
 }
 double cost_of_16(double sharing, double work, int s) {
-  return s == 1 ? 24.0 + 0.98 * sharing * work : 47.0 + 12.0 * (sharing - 1.0) + sharing * work / s + 1.2 * s;
+  return s == 1 ? 5.0 + 0.16 * sharing * work : 7.6 + 2.2 * (sharing - 1.0) + 0.155 * sharing * work / s + 0.12 * s;
 }
 double cost_of_8(double work, int s) {      // one workgroup per compute unit
-  return s == 1 ? 24.5 + 0.755 * work : 40.0 + 0.725 * work / s + 0.62 * s;
+  return s == 1 ? 6.0 + 0.122 * work : 7.0 + 0.122 * work / s + 0.08 * s;
 }
 double sharing_of(int workgroups, int s, int cus) { return (double)(((long long)workgroups * s + cus - 1) / cus); }
 // Split count of a launch in blocks of 16 heads, at least 6 tiles per split: the smallest modelled time, all tiles alike (weighted, 32 x 72

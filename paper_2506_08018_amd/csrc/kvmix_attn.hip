@@ -1386,29 +1386,11 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       done = __builtin_amdgcn_readfirstlane(done);
       if (done != kWaves - 1) return;
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-      // lane w < kWaves holds wave w's reference and sum; the weights 2^(m_w - M) are computed once per head
-      // and handed out as scalars, then every lane adds up two channels over the waves
 #pragma unroll
       for (int hh = 0; hh < G; hh++) {
-        const bool has = lane < kWaves;
-        const float mw = has ? R.m[has ? lane : 0][hh] : -INFINITY;
-        const float lw = has ? R.l[has ? lane : 0][hh] : 0.0f;
-        float o0[kWaves], o1[kWaves];         // requested first: their latency overlaps the weight computation
-#pragma unroll
-        for (int w = 0; w < kWaves; w++) { o0[w] = s_wave[w].o[hh][lane]; o1[w] = s_wave[w].o[hh][lane + kWave]; }
-        const float M = uniform_lane(row_max(mw), 0);
-        const float fw = (mw == -INFINITY) ? 0.0f : fast_exp2(mw - M);
-        const float Lsum = uniform_lane(row_sum(lw * fw), 0);
-        float O0 = 0.0f, O1 = 0.0f;
-#pragma unroll
-        for (int w = 0; w < kWaves; w++) {
-          const float f = uniform_lane(fw, w);
-          O0 += o0[w] * f;
-          O1 += o1[w] * f;
-        }
-        const float inv = 1.0f / Lsum;
-        outp[hh * kD + lane] = __builtin_bit_cast(uint16_t, (half_t)(O0 * inv));
-        outp[hh * kD + lane + kWave] = __builtin_bit_cast(uint16_t, (half_t)(O1 * inv));
+        float2_t ml, O;
+        combine_head(hh, ml, O);
+        put_out(hh, O, ml[1]);
       }
     } else {
       lds_barrier();

@@ -358,7 +358,7 @@ def widened_rows(device, seed):
     units = B * Hkv
     nb = units * (c.n_q * (16 * 3 + 16) + c.n_qv * (16 * 2 + 16) + (c.n - c.n_q) * 256 + (c.n - c.n_qv) * 256)
     out["fronts_apart_r_0.2_0.1"] = {"batch": B, "kv_heads": Hkv, "context": c.n, "bits": "3/2", "key_front": c.n_q, "value_front": c.n_qv,
-                                      "launches": 2, "us_per_call": us, "bytes_per_call": nb, "hbm_gbs": nb / us / 1e3,
+                                      "launches": 1, "us_per_call": us, "bytes_per_call": nb, "hbm_gbs": nb / us / 1e3,
                                       "frac_of_peak": nb / us / 1e3 / HBM_PEAK_GBS}
     del caches, ws
     torch.cuda.empty_cache()

@@ -320,7 +320,7 @@ double cost_of_8(double work, int s) {      // one workgroup per compute unit
 }
 double sharing_of(int workgroups, int s, int cus) { return (double)(((long long)workgroups * s + cus - 1) / cus); }
 // Split count of a launch in blocks of 16 heads, at least 6 tiles per split: the smallest modelled time, all tiles alike (weighted, 32 x 72
-// heads over 2000 full-precision tokens get 3 splits and take 27.6 us instead of 26.7)
+// heads over 2000 full-precision tokens got 3 splits and took 27.6 us instead of 26.7, measured before the merge became head-wise)
 int wide_splits(int workgroups, int n_items, int s_max, int cus) {
   int best_s = 1;
   double best = 0.0;
@@ -368,7 +368,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
       if (s == 1 || cost < best) { best = cost; n_splits = s; }
     }
     // an unsplit launch has no partials to write and merge, which the model leaves out: it wins a near tie
-    // (multi-query shape with 288 workgroups: 51 us unsplit, 55 us with 2 splits, modelled 352 against 336)
+    // (288 workgroups of 8 heads over 4096 tokens: 51 us unsplit, 55 us with 2 splits, modelled 352 against 336)
     if (unsplit <= 1.06 * best) n_splits = 1;
   }
   if (n_splits > n_items) n_splits = n_items;
@@ -382,7 +382,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     if (any_splits) {
       // The count above is that of blocks of 8, and it is what a workspace is refused or accepted by. A workspace that also holds the
       // partials of the count that suits blocks of 16 gets those where they are modelled to be faster, or within 2 % (4 x 48 heads over
-      // 32 000 tokens, modelled alike: 23.3 us in blocks of 8, 21.9 in blocks of 16).
+      // 32 000 tokens, modelled alike: 22.8 us in blocks of 8, 20.8 in blocks of 16).
       const double work = tile_work(fr.packed_tiles, (fr.n_w_eff + kTile - 1) / kTile, cfg->k_bits, cfg->v_bits);
       const int wide = units * ((G + 15) / 16), n = wide_splits(wide, n_items, max_splits(sh), cus);
       auto fits = [&](int splits) {

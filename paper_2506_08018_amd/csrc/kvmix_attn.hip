@@ -25,7 +25,8 @@
 // Softmax is online, per wave, with a lazily raised reference maximum; waves of a workgroup
 // take tiles from a shared counter and merge through LDS (without a barrier when the unit is not
 // split: the last wave to deliver combines); splits of one unit merge through a workspace, the
-// last arriving workgroup writes the output.
+// last arriving workgroup writes the output. Tiles between a Key front and a Value front (one side in a record, the
+// other in the ring) are taken by the same waves in the same launch.
 #include <type_traits>
 #include "kvmix_common.hpp"
 
@@ -1174,9 +1175,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // Blocks of 16 heads (of groups of 16 and more, multi-query attention): a column is a head, the hi and lo parts are two matrix instructions
   // on the same accumulators. The scores come out with a lane holding 8 tokens of its head, which are the tokens
   // of its operand for the Values: softmax, numerators and operands stay in the lane, only the tile's scales and minima
-  // go through LDS, and the codes are cut out once for 16 heads. Bound by instruction issue: about 260 vector and 38 matrix
-  // instructions per tile and wave; at 72 heads x 32 sequences of 4096 tokens vector and matrix units are busy 79 % of the SIMD clocks
-  // (58 + 21 %, a vector instruction 4.1 clocks, at 1.87 GHz). 27 us there; blocks of 8 took 49.
+  // go through LDS, and the codes are cut out once for 16 heads. Bound by instruction issue: about 240 vector and 38 matrix
+  // instructions per tile and wave (255 with masks and numerator splits written out: 27 us at 72 heads x 32 sequences of 4096 tokens, and 22.8 with
+  // these and the head-wise tail; blocks of 8 took 49).
   auto values_wide = [&](const u32x4_t& meta, const Raw<VB>& vr, float (&x)[8], float c, float zt) {
     if constexpr (!kWide<G>) return;
     raise_reference(max8(x) * c + zt);

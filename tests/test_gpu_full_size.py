@@ -141,7 +141,7 @@ def test_full_size_multi_query_shape():
 
 
 def test_full_size_chunk_append():
-    """The 4096-token chunk bench.py sends through kvmix_append_tokens at the headline shape (two launches): the
+    """The 4096-token chunk bench.py sends through kvmix_append_tokens at the headline shape (one launch): the
     records of sampled units bit for bit, the window rows and the counts against token-by-token appends of the oracle."""
     import torch
     import paper_2506_08018_amd as kv
@@ -175,7 +175,7 @@ def test_full_size_chunk_append():
 
 def test_full_size_fronts_apart():
     """The row bench.py times with the Value front ahead of the Key front (ratios 0.2 / 0.1 of Sec. 3.3 at the headline
-    shape, 3/2 bit, two launches per call): sampled units against the oracle taken through the same calls."""
+    shape, 3/2 bit, one launch per call): sampled units against the oracle taken through the same calls."""
     import torch
     import paper_2506_08018_amd as kv
     from oracle.kvmix_ref import RefCache

@@ -382,14 +382,15 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     if (any_splits) {
       // The count above is that of blocks of 8, and it is what a workspace is refused or accepted by. A workspace that also holds the
       // partials of the count that suits blocks of 16 gets those where they are modelled to be faster, or within 2 % (4 x 48 heads over
-      // 32 000 tokens, modelled alike: 22.8 us in blocks of 8, 20.8 in blocks of 16).
+      // 32 000 tokens, modelled alike: 22.8 us in blocks of 8, 20.8 in blocks of 16). At equal counts blocks of 8 it is (64 x 16 heads over 300 tokens,
+      // unsplit: 7.8 us per launch, 8.6 in blocks of 16).
       const double work = tile_work(fr.packed_tiles, (fr.n_w_eff + kTile - 1) / kTile, cfg->k_bits, cfg->v_bits);
       const int wide = units * ((G + 15) / 16), n = wide_splits(wide, n_items, max_splits(sh), cus);
       auto fits = [&](int splits) {
         const int parts = splits + (fr.mixed ? 1 : 0);
         return parts == 1 || (workspace && aligned16(workspace) && workspace_bytes >= split_workspace_bytes(units, parts, G));
       };
-      if (fits(n) && fits(n_splits) && (block == 16 || cost_of_16(sharing_of(wide, n, cus), work, n) < 1.02 * cost_of_8(work, n_splits))) { n_splits = n; block = 16; }
+      if (fits(n) && fits(n_splits) && (block == 16 || (n != n_splits && cost_of_16(sharing_of(wide, n, cus), work, n) < 1.02 * cost_of_8(work, n_splits)))) { n_splits = n; block = 16; }
     }
   }
   AttnArgs a{};

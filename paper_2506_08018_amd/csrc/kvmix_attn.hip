@@ -1455,13 +1455,14 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // read as the last one and weigh nothing. (Blocks of 16 heads used to take four round trips: 32 units x 72 heads, 3 splits, 27.5 -> 22.8 us per
   // launch; 4 x 16 heads 12.0 -> 9.9; 8 units of 8 heads 10.1 -> 8.4.)
   const uint32_t part_bytes = (uint32_t)(part_step * (kD + 2) * sizeof(float));
-  auto merge = [&](auto batch) {
+  // hd: first head of the wave (every kWaves-th from there on); the splits from s_first on, a batch every s_step
+  auto merge = [&](auto batch, int hd, int s_first, int s_step, auto put) {
     constexpr int kBatch = decltype(batch)::value;
     float M[kHeads], Lsum[kHeads];
     float2_t O[kHeads];
 #pragma unroll
     for (int k = 0; k < kHeads; k++) { M[k] = -INFINITY; Lsum[k] = 0.0f; O[k] = float2_t{0, 0}; }
-    for (int s0 = 0; s0 < a.n_splits; s0 += kBatch) {
+    for (int s0 = s_first; s0 < a.n_splits; s0 += s_step) {
       const int n = a.n_splits - s0 < kBatch ? a.n_splits - s0 : kBatch;       // >= 1
       u32x2_t ml[kHeads], os[kHeads][kBatch];
       // (tagged) The last arrival waits for stores that nothing holds up; the bound is for a workspace that was not zero to begin with.
@@ -1470,7 +1471,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         uint32_t least = 1;
 #pragma unroll
         for (int k = 0; k < kHeads; k++) {
-          const int hh = wave + k * kWaves < n_heads ? wave + k * kWaves : n_heads - 1;
+          const int hh = hd + k * kWaves < n_heads ? hd + k * kWaves : n_heads - 1;
           const rsrc_t rows = make_rsrc(part_at(0, hh), (uint32_t)(a.n_splits - 1) * part_bytes + (kD + 2) * 4u);
           ml[k] = ld_agent2(rows, (uint32_t)(s0 + (lane < n ? lane : n - 1)) * part_bytes, 0);
 #pragma unroll
@@ -1489,12 +1490,17 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         if (__builtin_amdgcn_ballot_w64(least == 0u) == 0 || tries == kMaxTries) break;
       }
       if constexpr (kTagged<G>) {
-        // nobody else reads the rows of this head: zero again, on the way while the sums are taken
-        const rsrc_t rows = make_rsrc(part_at(0, wave), (uint32_t)(a.n_splits - 1) * part_bytes + (kD + 2) * 4u);
-        if (lane < n) st_agent2_zero(rows, (uint32_t)(s0 + lane) * part_bytes, 0);
+        // nobody else reads these rows: zero again, on the way while the sums are taken (after the last batch: loads behind stores wait for them)
+        if (s0 + s_step >= a.n_splits) {
+          const rsrc_t rows = make_rsrc(part_at(0, hd), (uint32_t)(a.n_splits - 1) * part_bytes + (kD + 2) * 4u);
+          for (int z0 = s_first; z0 < a.n_splits; z0 += s_step) {
+            const int nz = a.n_splits - z0 < kBatch ? a.n_splits - z0 : kBatch;
+            if (lane < nz) st_agent2_zero(rows, (uint32_t)(z0 + lane) * part_bytes, 0);
 #pragma unroll
-        for (int i = 0; i < kBatch; i++)
-          if (i < n) st_agent2_zero(rows, 8u + 8u * lane, (uint32_t)(s0 + i) * part_bytes);
+            for (int i = 0; i < kBatch; i++)
+              if (i < nz) st_agent2_zero(rows, 8u + 8u * lane, (uint32_t)(z0 + i) * part_bytes);
+          }
+        }
       }
 #pragma unroll
       for (int k = 0; k < kHeads; k++) {
@@ -1520,12 +1526,44 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
 #pragma unroll
     for (int k = 0; k < kHeads; k++)
-      if (wave + k * kWaves < n_heads) put_out(wave + k * kWaves, O[k], Lsum[k]);
+      if (hd + k * kWaves < n_heads) put(hd + k * kWaves, O[k], Lsum[k], M[k]);
   };
-  if (wave < n_heads) {
-    constexpr bool kFewer = (kWaves == 8 && G >= 4) || kHeads > 1;      // (32 do not fit the registers)
-    if (a.n_splits <= 8) merge(std::integral_constant<int, 8>{});
-    else merge(std::integral_constant<int, kFewer ? 16 : kMergeBatch>{});
+  auto to_out = [&](int hh, const float2_t& O, float Lsum, float) { put_out(hh, O, Lsum); };
+  if constexpr (kTagged<G>) {
+    constexpr int kBatch = kWaves == 8 && G == 4 ? 16 : kMergeBatch;      // (4 heads, 8 waves: 32 do not fit the registers)
+    if (a.n_splits <= 8) {
+      if (wave < n_heads) merge(std::integral_constant<int, 8>{}, wave, 0, 8, to_out);
+    } else if (G == 4 || a.n_splits <= kBatch) {
+      if (wave < n_heads) merge(std::integral_constant<int, kBatch>{}, wave, 0, kBatch, to_out);
+    } else if constexpr (G < 4) {
+      // 16 partials of one head to a wave, then the waves' sums like the waves' results before. (When one wave took both batches of
+      // its head, with the zeros of the first in front of the second's loads, 4 units of 1 head in 50 splits took 9.0 us per launch; 7.4 now. With 32
+      // splits and 4 heads two waves of 16 are slower than one of 32, 13.0 us against 12.3, and the longer code costs the short launches 1 %.)
+      constexpr int kRows = kWaves / G;      // x 16: at least 64
+      const int hd = wave % G, row = wave / G, rows = (a.n_splits + 15) / 16 < kRows ? (a.n_splits + 15) / 16 : kRows;
+      if (wave >= rows) {       // rows of no partial
+        if (lane < G) { R.m[wave][lane] = -INFINITY; R.l[wave][lane] = 0.0f; }
+#pragma unroll
+        for (int hh = 0; hh < G; hh++) *reinterpret_cast<float2_t*>(&s_wave[wave].o[hh][2 * lane]) = float2_t{0, 0};
+      }
+      if (row < rows && hd < n_heads)
+        merge(std::integral_constant<int, 16>{}, hd, 16 * row, 16 * kRows, [&](int hh, const float2_t& O, float Lsum, float M) {
+          if (lane == 0) { R.m[row][hh] = M; R.l[row][hh] = Lsum; }
+          *reinterpret_cast<float2_t*>(&s_wave[row].o[hh][2 * lane]) = O;
+        });
+      lds_barrier();
+      if (wave < n_heads) {
+        float2_t ml, O;
+        combine_head(wave, ml, O);
+        put_out(wave, O, ml[1]);
+      }
+    }
+  } else if (wave < n_heads) {
+    if (a.n_splits <= 8) merge(std::integral_constant<int, 8>{}, wave, 0, 8, to_out);
+    else {
+      constexpr int kBatch = kHeads > 1 ? 16 : kMergeBatch;      // (32 do not fit the registers)
+      merge(std::integral_constant<int, kBatch>{}, wave, 0, kBatch, to_out);
+    }
   }
   if (tid == 0) __hip_atomic_store(&a.counters[uo * a.counter_stride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }

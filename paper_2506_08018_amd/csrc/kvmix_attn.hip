@@ -473,14 +473,15 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // counts it in n_w) and stores it into the ring for the steps to come.
   const int new_tau = a.new_slot & 31;
   auto win_slot = [&](int r) { int wi = a.w0_tile + r; wi = wi >= a.ring_tiles ? wi - a.ring_tiles : wi; return wi * kTile; };   // first slot of the tile
-  auto win_new = [&](int slot0) { return a.new_slot >= 0 && slot0 == (a.new_slot & ~31); };     // wave-uniform
+  // Whether a window tile is the new token's (wave-uniform). Not to be asked of a tile between two fronts: in a full ring the new token may share
+  // the ring tile of the oldest Values, in rows before theirs.
+  auto win_new = [&](int slot0) { return a.new_slot >= 0 && slot0 == (a.new_slot & ~31); };
   struct WinKeys { half8_t r[2][4]; };
-  // live: tokens of the tile (from its first row on) that are there, at least one
-  auto win_load_k = [&](int slot0, int live, int lane, WinKeys& w) {
+  // live: tokens of the tile (from its first row on) that are there, at least one; has_new: the new token is the last of them
+  auto win_load_k = [&](int slot0, int live, bool has_new, int lane, WinKeys& w) {
     const int col = lane & 15, kq = lane >> 4;
     const uint16_t* kw = a.k_win + ((size_t)u * a.W_cap + slot0) * kD;
     const uint16_t* kn = a.k_new + (size_t)u * kD;
-    const bool has_new = win_new(slot0);
 #pragma unroll
     for (int m = 0; m < 2; m++) {
       const int tau = 8 * (col >> 2) + 4 * m + (col & 3);   // row `col` of M-tile m
@@ -495,12 +496,12 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // Value rows 4j .. 4j+3 per instruction, 16 bytes per lane in lane order: chunk c (8 channels) of row t goes to chunk
   // c ^ swizzle(t) of its row, so that the transposing reads below find their 8 rows x 32 bytes in distinct banks.
   auto swizzle = [](int t) { return 2 * ((t & 3) + 4 * ((t >> 3) & 1)); };
-  auto win_load_v = [&](int slot0, int live, int lo, int lane) {      // rows from lo on (0 but for tiles between two fronts)
+  auto win_load_v = [&](int slot0, int live, bool has_new, int lo, int lane) {      // rows from lo on (0 but for tiles between two fronts)
     const int col = lane & 15, kq = lane >> 4;
     // The resource spans the tile's rows that are live and in the ring (a new token is the last live row of its tile and not in
     // the ring yet). Rows beyond it are not read: their lanes write zeros, which meet a weight of zero (a dead slot may hold infinities
     // and NaN). A resource over the tile: a ring may be larger than 32-bit offsets reach.
-    const int n_rows = win_new(slot0) ? new_tau : live < kTile ? live : kTile;
+    const int n_rows = has_new ? new_tau : live < kTile ? live : kTile;
     const rsrc_t rows = make_rsrc(a.v_win + ((size_t)u * a.W_cap + slot0) * kD, (uint32_t)n_rows * (kD * 2));
 #pragma unroll
     for (int j = 0; j < 8; j++)
@@ -803,7 +804,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
             z = lo_part ? other : zt;
           }
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the exchange area is about to take the Value rows)
-          win_load_v(slot0, live, lo, ln);
+          win_load_v(slot0, live, false, lo, ln);
           float x[8];
 #pragma unroll
           for (int m = 0; m < 2; m++)
@@ -817,8 +818,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         }
       }
       WinKeys wk;
-      const bool has_new = win_new(slot0);
-      win_load_k(slot0, live, ln, wk);
+      const bool has_new = (!MIXED || r < live_tiles) && win_new(slot0);
+      win_load_k(slot0, live, has_new, ln, wk);
       const u32x4_t appended = append_load(has_new);
       __builtin_amdgcn_sched_barrier(0);      // (matrix instructions moved up here would wait for their rows in front of the barrier)
       if (begin) start_barrier();
@@ -830,7 +831,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       for (int m = 0; m < 2; m++)
 #pragma unroll
         for (int ks = 0; ks < 4; ks++) S[m] = mfma16(wk.r[m][ks], qB[ks], S[m]);
-      win_load_v(slot0, live, lo, ln);
+      win_load_v(slot0, live, has_new, lo, ln);
       float x[8];
 #pragma unroll
       for (int m = 0; m < 2; m++)
@@ -1248,7 +1249,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       float zts[G], ztl = 0.0f, c = c_code, inv_c = inv_c_code;
       if (a.m_ahead) {
         WinKeys wk;
-        win_load_k(mixed_slot(j), a.m_end - t0, lane, wk);
+        win_load_k(mixed_slot(j), a.m_end - t0, false, lane, wk);
         S[0] = float4_t{0, 0, 0, 0}; S[1] = float4_t{0, 0, 0, 0};
 #pragma unroll
         for (int m = 0; m < 2; m++) {

@@ -243,6 +243,45 @@ def test_decode_loop_under_the_count_formula(kb, vb, G, r_k, r_v):
     assert not counters_of(ws, shape).any()
 
 
+@pytest.mark.parametrize("n_splits", [1, 2])
+@pytest.mark.parametrize("T,keep_k,keep_v", [(64, 0, 27), (45, 13, 35)])
+@pytest.mark.parametrize("G,kb,vb", [(1, 2, 2), (2, 3, 4), (4, 2, 3), (4, 4, 2), (8, 2, 2), (16, 3, 2), (24, 2, 4)])
+def test_fused_steps_until_the_ring_is_full(G, kb, vb, T, keep_k, keep_v, n_splits):
+    """The Key front ahead, the Value front inside a tile (rows 5 / 10 on): fused steps until no slot of the 64 is free. The last ones put the
+    new token into the ring tile that still holds the oldest Values, in the rows before theirs; those Values count in full on every step."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case full ring G={G} kb={kb} vb={vb} T={T} keep={keep_k}/{keep_v} splits={n_splits}", flush=True)
+    B, Hkv, W_cap = 1, 2, 64
+    steps = (T - keep_v) + W_cap - T                            # the ring holds the tokens from the Value front on
+    q, k, v = synth.gen_layer_numpy(930 + G, T, B, Hkv * G, Hkv, T + steps)
+    rc, gc, shape, cfg = make_ring_pair(B, Hkv * G, Hkv, kb, vb, 128, W_cap)
+    for t in range(T):
+        assert rc.append(u16(k[:, :, t]), u16(v[:, :, t])) == 0
+    kt, vt, qt = torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda(), torch.from_numpy(q).cuda()
+    kv.append_tokens(shape, cfg, kt[:, :, :T], vt[:, :, :T], gc)
+    assert rc.flush(keep_k, keep_v) == 0
+    kv.flush(shape, cfg, gc, keep_k, keep_v)
+    assert (gc.n_q, gc.n_qv) == ((T - keep_k) // 32 * 32, T - keep_v)
+    ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
+    out = torch.zeros_like(qt)
+    shared = 0
+    for t in range(T, T + steps):
+        assert rc.append(u16(k[:, :, t]), u16(v[:, :, t])) == 0
+        st, want = rc.decode_attn(u16(q))
+        assert st == 0
+        shared += (gc.w0 + t - gc.n_q) % W_cap // 32 == (gc.w0 + gc.n_qv - gc.n_q) % W_cap // 32
+        kv.decode_step(shape, cfg, kt[:, :, t].contiguous(), vt[:, :, t].contiguous(), qt, gc, out, ws, n_splits=n_splits)
+        torch.cuda.synchronize()
+        assert_attn_close(t16(out), want, f"token {t} (n_q={gc.n_q} n_qv={gc.n_qv})", tight=True)
+    assert shared == gc.n_qv % 32 and gc.n - gc.n_qv == W_cap
+    assert_same_state(rc, gc, "ring full")
+    assert_windows_equal(rc, gc)
+    live = [(gc.w0 + t - gc.n_q) % W_cap for t in range(gc.n_qv, gc.n)]
+    assert np.array_equal(bits_of(gc.v_win, np.uint16).reshape(rc.v_win.shape)[:, live], rc.v_win[:, live])
+    assert not counters_of(ws, shape).any()
+
+
 def test_fronts_error_returns():
     import torch
     import paper_2506_08018_amd as kv

@@ -112,6 +112,17 @@ __device__ __forceinline__ void wave_lds_fence() {
 // lowest mantissa bits loses product bits (measured: ~1e-5 relative at position 0, exact from 6 up).
 template <int BITS> __device__ __forceinline__ constexpr int field_pos(int s) { return BITS == 4 ? 4 * (s & 1) + 2 : BITS == 1 ? 2 * s + 4 : 2 * s + 2; }
 
+// The codes of a tile between two fronts: multiplied up to the fp16 number code * 2^-7, a normal one, whatever the field. Of products of subnormal
+// operands the matrix core drops low bits (see above): where a field lies low, that is more than everything else takes from a result. These tiles
+// used to be summed in fp32 on the vector unit, and their error against 64 bits stays what it was. 1000 tokens, all Keys in the ring and all Values
+// packed at 2, 3, 4 bit, outputs that are not the fp16 rounding of the result in 64 bits: 0.1 to 0.3 % on the vector unit, 8, 5 and 4 % with the fields
+// as they are (an error of 4e-5, 2e-5, 1e-5 of the result next to the rounding's 2.1e-4), 0.2 to 0.7 % this way (5e-7).
+constexpr int kExactPos = 17;
+template <int BITS> __device__ __forceinline__ half8_t exact_codes(half8_t fields, int s) {
+  const half_t up = (half_t)__builtin_ldexpf(1.0f, kExactPos - field_pos<BITS>(s));
+  return fields * half8_t{up, up, up, up, up, up, up, up};
+}
+
 // ---- A operands from packed words. wa = word << 2, wb = word >> 6 (slots 0..3 / 4..7 of each half).
 // 2-bit plane (also the low plane of 3-bit): slot field from bits 2*slot to bits 2*(slot%4) + 2.
 __device__ __forceinline__ half8_t unpack2(const u32x4_t& wa, const u32x4_t& wb, int slot) {
@@ -663,14 +674,18 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
   };
   // Key sides of a packed tile: code sums S of the lane's tokens (8*kq + 4*m + r) and column, zero-point terms zt.
-  auto keys_small = [&](const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float (&zt)[G]) {
+  // EXACT (a tile between two fronts): codes as normal numbers and the query as it is; the sums come out in the same unit.
+  const float kExactKeys = __builtin_ldexpf(1.0f, kPos0 - kExactPos);
+  auto key_operand = [](auto exact, const Codes<KB>& kc, int slot) { return decltype(exact)::value ? exact_codes<KB>(kc.lo(slot), slot & 3) : kc.lo(slot); };
+  auto keys_small = [&](auto exact, const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float (&zt)[G]) {
+    constexpr bool EXACT = decltype(exact)::value;
     // Lane owns channels 2*lane, 2*lane+1: scale-folded query to LDS, zero-point term by dot product
     const half2_t s2 = as_half2(meta[0]);
     const uint32_t kz_pair = meta[1];   // a copy: a bit cast applied to the vector element itself reads element 0
 #pragma unroll
     for (int hh = 0; hh < G; hh++) {
       uint32_t hi, lo;
-      mul_split(qh[hh], s2, hi, lo);
+      mul_split(EXACT ? as_half2(qraw[hh]) : qh[hh], s2, hi, lo);
       *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh)]) = hi;
       *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh) + Operand<G>::kLo]) = lo;
       const float zp = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, qraw[hh]), __builtin_bit_cast(half2_t, kz_pair), 0.0f, false);
@@ -685,20 +700,25 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
 #pragma unroll
     for (int m = 0; m < 2; m++)
 #pragma unroll
-      for (int ks = 0; ks < 4; ks++) S[m] = mfma16(kc.lo(ks + 4 * m), Bk[ks], S[m]);
+      for (int ks = 0; ks < 4; ks++) S[m] = mfma16(key_operand(exact, kc, ks + 4 * m), Bk[ks], S[m]);
+    if constexpr (EXACT) { S[0] *= kExactKeys; S[1] *= kExactKeys; }
     if constexpr (KB == 3) {   // tokens 10 and 21 of the group step by s*7/3
       if (kq == 1) S[0][2] *= (7.0f / 3.0f);
       if (kq == 2) S[1][1] *= (7.0f / 3.0f);
     }
   };
-  auto keys_large = [&](const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float& zt) {
+  auto keys_large = [&](auto exact, const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float& zt) {
     if constexpr (G != 4) return;
+    constexpr bool EXACT = decltype(exact)::value;
+    half2_t qx[G];        // (as it is, the query is read again: no registers for it around the loop)
+#pragma unroll
+    for (int hh = 0; hh < G; hh++) qx[hh] = EXACT ? as_half2(reinterpret_cast<const uint32_t*>(qbase + hh * kD)[lane]) : qh[hh];
     // Cooperative operand preparation: lane owns channels 2*lane, 2*lane+1.
     const half2_t s2 = as_half2(meta[0]);
 #pragma unroll
     for (int hh = 0; hh < G; hh++) {
       uint32_t hi, lo;
-      mul_split(qh[hh], s2, hi, lo);
+      mul_split(qx[hh], s2, hi, lo);
       *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh)]) = hi;
       *reinterpret_cast<uint32_t*>(&L.k.op[op_write(hh) + Operand<G>::kLo]) = lo;
     }
@@ -717,15 +737,17 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
 #pragma unroll
     for (int m = 0; m < 2; m++)
 #pragma unroll
-      for (int ks = 0; ks < 4; ks++) S[m] = mfma16(kc.lo(ks + 4 * m), Bk[ks], S[m]);
+      for (int ks = 0; ks < 4; ks++) S[m] = mfma16(key_operand(exact, kc, ks + 4 * m), Bk[ks], S[m]);
+    if constexpr (EXACT) { S[0] *= kExactKeys; S[1] *= kExactKeys; }
     if constexpr (KB == 3) {   // tokens 10 and 21 of the group step by s*7/3
       if (kq == 1) S[0][2] *= (7.0f / 3.0f);
       if (kq == 2) S[1][1] *= (7.0f / 3.0f);
     }
     zt = Sz[0] * c_plain;
   };
-  auto keys_wide = [&](const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float& zt) {
+  auto keys_wide = [&](auto exact, const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float& zt) {
     if constexpr (!kWide<G>) return;
+    constexpr bool EXACT = decltype(exact)::value;
     reinterpret_cast<uint32_t*>(L.k.op)[lane] = meta[0];
     reinterpret_cast<uint32_t*>(&L.k.zk[0])[lane] = meta[1];
     wave_lds_fence();
@@ -737,20 +759,24 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       const half8_t z8 = *reinterpret_cast<const half8_t*>(&L.k.zk[32 * ks + 8 * kq]);
       const half8_t s8 = *reinterpret_cast<const half8_t*>(&L.k.op[64 * ks + 16 * kq]);
       Sz = mfma16(z8, qB[ks], Sz);       // every A row is the zero-point vector
-      const half8_t qp = q_scaled(ks), hi = qp * s8, lo = __builtin_elementwise_fma(qp, s8, -hi);
+      const half8_t qp = EXACT ? qB[ks] : q_scaled(ks), hi = qp * s8, lo = __builtin_elementwise_fma(qp, s8, -hi);
 #pragma unroll
       for (int m = 0; m < 2; m++) {
-        const half8_t c = kc.lo(ks + 4 * m);
+        const half8_t c = key_operand(exact, kc, ks + 4 * m);
         S[m] = mfma16(c, hi, S[m]);
         S[m] = mfma16(c, lo, S[m]);
       }
     }
+    if constexpr (EXACT) { S[0] *= kExactKeys; S[1] *= kExactKeys; }
     if constexpr (KB == 3) {   // tokens 10 and 21 of the group step by s*7/3
       if (kq == 1) S[0][2] *= (7.0f / 3.0f);
       if (kq == 2) S[1][1] *= (7.0f / 3.0f);
     }
     zt = Sz[0] * c_plain;
   };
+  // Tiles between the fronts whose Values come from the record: dealt out like the window tiles, the waves without one of those first.
+  const int n_rec = !MIXED ? 0 : a.m_ahead ? a.m_tiles : a.m_front > a.m_first * kTile ? 1 : 0;
+  const int first_rec = sp + (kWaves - 1 - wave) * a.n_splits;
   // ---- fp16 window tiles: taken round-robin by the waves before the packed stream.
   // Past the end a wave re-reads the last tile (cache hit) and skips its work: the load stream and the
   // loop body stay uniform, which keeps the outstanding-load accounting exact.
@@ -792,14 +818,14 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
           float z = 0.0f;
           if constexpr (kSmall) {
             float zt[G];
-            keys_small(meta, kr, S, zt);
+            keys_small(std::true_type{}, meta, kr, S, zt);
 #pragma unroll
             for (int hh = 0; hh < G; hh++) z = h == hh ? zt[hh] : z;
           } else if constexpr (kWide<G>) {
-            keys_wide(meta, kr, S, z);
+            keys_wide(std::true_type{}, meta, kr, S, z);
           } else {
             float zt;
-            keys_large(meta, kr, S, zt);
+            keys_large(std::true_type{}, meta, kr, S, zt);
             const float other = ror8(zt);
             z = lo_part ? other : zt;
           }
@@ -886,7 +912,20 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq + 4]) = S[1];
     }
   };
-  auto values_small = [&](const u32x4_t& meta, const Raw<VB>& vr, float c, float inv_c, const float (&zt)[G], int limit) {
+  // Adds the products of the codes of block m (16 channels) and the lanes' operands: hi, and lo where that is an operand of its own.
+  auto add_values = [&](auto exact, const Codes<VB>& vc, int m, half8_t hi, auto... lo) {
+    if constexpr (decltype(exact)::value) {
+      const half8_t c = exact_codes<VB>(vc.lo(m), m & 3);
+      float4_t t = mfma16(c, hi, float4_t{0, 0, 0, 0});
+      ((t = mfma16(c, lo, t)), ...);
+      acc[m] += t * __builtin_ldexpf(1.0f, field_pos<VB>(m & 3) - kExactPos);
+    } else {
+      const half8_t c = vc.lo(m);
+      acc[m] = mfma16(c, hi, acc[m]);
+      ((acc[m] = mfma16(c, lo, acc[m])), ...);
+    }
+  };
+  auto values_small = [&](auto exact, const u32x4_t& meta, const Raw<VB>& vr, float c, float inv_c, const float (&zt)[G], int limit) {
     wave_lds_fence();
     // -- Value side. Lane (tp, g) owns tokens (2*tp, 2*tp+1) of channel block g.
     {
@@ -942,21 +981,19 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
 #pragma unroll
       for (int g = 0; g < 4; g++) Bv[g] = *reinterpret_cast<const half8_t*>(&L.v.op[op_read + g * Operand<G>::kStep]);
 #pragma unroll
-      for (int m = 0; m < 8; m++) {
-        acc[m] = mfma16(vc.lo(m), Bv[m >> 1], acc[m]);
-      }
+      for (int m = 0; m < 8; m++) add_values(exact, vc, m, Bv[m >> 1]);
     }
     wave_lds_fence();   // the next tile's operand writes come after these reads
   };
   auto process_small = [&](const Stage<KB, VB>& st) {
     float4_t S[2];
     float zt[G];
-    keys_small(st.meta, st.kc, S, zt);
+    keys_small(std::false_type{}, st.meta, st.kc, S, zt);
     scores_out(S);
-    values_small(st.meta, st.vc, c_code, inv_c_code, zt, kTile);
+    values_small(std::false_type{}, st.meta, st.vc, c_code, inv_c_code, zt, kTile);
   };
 
-  auto values_large = [&](const u32x4_t& meta, const Raw<VB>& vr, float (&x)[8], float c, float zt) {
+  auto values_large = [&](auto exact, const u32x4_t& meta, const Raw<VB>& vr, float (&x)[8], float c, float zt) {
     if constexpr (G != 4) return;
     // Reference maximum from the hi column (the lo column changes a score by < 2^-10 of its size, which a
     // reference does not need); lo lanes take their partner's value so that a column pair stays in step.
@@ -1041,9 +1078,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       if (col < 4) z8 = *reinterpret_cast<const half8_t*>(&L.v.zv[col][8 * kq]);
       accZ = mfma16(z8, PB, accZ);
 #pragma unroll
-      for (int m = 0; m < 8; m++) {
-        acc[m] = mfma16(vc.lo(m), Bv[m >> 1], acc[m]);
-      }
+      for (int m = 0; m < 8; m++) add_values(exact, vc, m, Bv[m >> 1]);
     }
     wave_lds_fence();   // the next tile's operand writes come after these reads
   };
@@ -1051,12 +1086,12 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     if constexpr (G != 4) return;
     float4_t S[2];
     float zt, x[8];
-    keys_large(st.meta, st.kc, S, zt);
+    keys_large(std::false_type{}, st.meta, st.kc, S, zt);
 #pragma unroll
     for (int m = 0; m < 2; m++)
 #pragma unroll
       for (int r = 0; r < 4; r++) x[4 * m + r] = S[m][r];
-    values_large(st.meta, st.vc, x, c_code, zt);
+    values_large(std::false_type{}, st.meta, st.vc, x, c_code, zt);
   };
   // Blocks of 8 heads: every lane folds the scales into its own operands. In one piece: cut in two like the one for 4 heads, 4 of its forms with 8
   // waves spill.
@@ -1179,7 +1214,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // go through LDS, and the codes are cut out once for 16 heads. Bound by instruction issue: about 240 vector and 38 matrix
   // instructions per tile and wave (255 with masks and numerator splits written out: 27 us at 72 heads x 32 sequences of 4096 tokens, and 22.8 with
   // these and the head-wise tail; blocks of 8 took 49).
-  auto values_wide = [&](const u32x4_t& meta, const Raw<VB>& vr, float (&x)[8], float c, float zt) {
+  auto values_wide = [&](auto exact, const u32x4_t& meta, const Raw<VB>& vr, float (&x)[8], float c, float zt) {
     if constexpr (!kWide<G>) return;
     raise_reference(max8(x) * c + zt);
     const float off = zt - mref;
@@ -1205,11 +1240,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       const half8_t hi = P * s8;
       const half8_t lo = __builtin_elementwise_fma(R8, s8, __builtin_elementwise_fma(P, s8, -hi));
 #pragma unroll
-      for (int m = 2 * g; m < 2 * g + 2; m++) {
-        const half8_t c = vc.lo(m);
-        acc[m] = mfma16(c, hi, acc[m]);
-        acc[m] = mfma16(c, lo, acc[m]);
-      }
+      for (int m = 2 * g; m < 2 * g + 2; m++) add_values(exact, vc, m, hi, lo);
     }
     wave_lds_fence();   // the next tile's scales come after these reads
   };
@@ -1217,12 +1248,12 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     if constexpr (!kWide<G>) return;
     float4_t S[2];
     float zt, x[8];
-    keys_wide(st.meta, st.kc, S, zt);
+    keys_wide(std::false_type{}, st.meta, st.kc, S, zt);
 #pragma unroll
     for (int m = 0; m < 2; m++)
 #pragma unroll
       for (int r = 0; r < 4; r++) x[4 * m + r] = S[m][r];
-    values_wide(st.meta, st.vc, x, c_code, zt);
+    values_wide(std::false_type{}, st.meta, st.vc, x, c_code, zt);
   };
   auto process = [&](const Stage<KB, VB>& st) {
     if constexpr (kWide<G>) process_wide(st);
@@ -1231,11 +1262,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     else process_large(st);
   };
 
-  if constexpr (MIXED) {
-    // tiles between the fronts whose Values come from the record: dealt out like the window tiles, the waves without one of those first
-    const int n_rec = a.m_ahead ? a.m_tiles : a.m_front > a.m_first * kTile ? 1 : 0;
-    bool first_rec = true;
-    for (int j = sp + (kWaves - 1 - wave) * a.n_splits; j < n_rec; j += kWaves * a.n_splits) {
+  if constexpr (MIXED) if (first_rec < n_rec) {
+    zero_idle();
+    for (int j = first_rec; j < n_rec; j += kWaves * a.n_splits) {
       const uint32_t soff = (uint32_t)(a.m_first + j) * kRecBytes;
       const int t0 = (a.m_first + j) * kTile;
       const int n_tok = (a.m_front < a.m_end ? a.m_front : a.m_end) - t0;        // tokens with a packed Value
@@ -1243,8 +1272,6 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       u32x4_t meta = buf_load16(up, lane16, soff);
       Raw<VB> vr;
       vr.load(up, soff + (uint32_t)((kMetaWords + tile_words(KB)) * 4), lane16, lane16 >> 1);
-      if (first_rec) zero_idle();
-      first_rec = false;
       float4_t S[2];
       float zts[G], ztl = 0.0f, c = c_code, inv_c = inv_c_code;
       if (a.m_ahead) {
@@ -1265,9 +1292,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       } else {
         Raw<KB> kr;
         kr.load(up, soff + (uint32_t)(kMetaWords * 4), lane16, lane16 >> 1);
-        if constexpr (kSmall) keys_small(meta, kr, S, zts);
-        else if constexpr (kWide<G>) keys_wide(meta, kr, S, ztl);
-        else keys_large(meta, kr, S, ztl);
+        if constexpr (kSmall) keys_small(std::true_type{}, meta, kr, S, zts);
+        else if constexpr (kWide<G>) keys_wide(std::true_type{}, meta, kr, S, ztl);
+        else keys_large(std::true_type{}, meta, kr, S, ztl);
       }
       // what the record holds for tokens without a packed Value is not defined
       const int tp = lane & 15;
@@ -1275,15 +1302,15 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       meta[2] &= keep; meta[3] &= keep;
       if constexpr (kSmall) {
         scores_out(S);
-        values_small(meta, vr, c, inv_c, zts, limit);
+        values_small(std::true_type{}, meta, vr, c, inv_c, zts, limit);
       } else {
         float x[8];
 #pragma unroll
         for (int m = 0; m < 2; m++)
 #pragma unroll
           for (int e = 0; e < 4; e++) x[4 * m + e] = 8 * kq + 4 * m + e < limit || lo_part ? S[m][e] : -INFINITY;
-        if constexpr (kWide<G>) values_wide(meta, vr, x, c, ztl);
-        else values_large(meta, vr, x, c, ztl);
+        if constexpr (kWide<G>) values_wide(std::true_type{}, meta, vr, x, c, ztl);
+        else values_large(std::true_type{}, meta, vr, x, c, ztl);
       }
     }
   }

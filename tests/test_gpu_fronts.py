@@ -176,6 +176,43 @@ def test_many_tiles_between_the_fronts(G, kb, vb, keep_k, keep_v):
     assert not counters_of(ws, shape).any()
 
 
+@pytest.mark.parametrize("kb,vb", [(2, 2), (3, 3), (4, 4)])
+@pytest.mark.parametrize("G", [1, 2, 4, 8, 16])
+def test_sums_between_the_fronts_are_good_to_fp32(G, kb, vb):
+    """All tokens between the fronts, either side ahead, against the attention over the dequantized tokens in 64 bits. An error of e fp16 spacings
+    ahead of the final rounding moves a share of 2 e of the outputs to the neighbouring fp16 number. 1.2 % of them are 0.006 spacings or 2^-18.4
+    of an output, which is what 32-bit sums leave where terms of either sign cancel to about 1/60 of their size (2^-24 x 60). Measured: 0.1 to 0.8 %
+    (fp32 on the vector unit 0.1 to 0.4 %); with two-bit fields at the bottom of subnormal matrix operands it was 8 to 9 %, 1.1 to 2 % on the Key side."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case precision between fronts G={G} kb={kb} vb={vb}", flush=True)
+    B, Hkv, T = 1, max(2, 32 // G), 1000
+    for keep_k, keep_v in ((T, 0), (0, T)):
+        q, k, v = synth.gen_layer_numpy(940 + G, kb, B, Hkv * G, Hkv, T + 24)
+        T = T if keep_k else T + 24                                       # Keys leave in whole tiles
+        rc, gc, shape, cfg = make_ring_pair(B, Hkv * G, Hkv, kb, vb, 1056, 1056)
+        kt, vt, qt = torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda(), torch.from_numpy(q).cuda()
+        kv.append_tokens(shape, cfg, kt[:, :, :T], vt[:, :, :T], gc)
+        kv.flush(shape, cfg, gc, keep_k, keep_v)
+        assert (gc.n_q, gc.n_qv) == (T - keep_k, T - min(T, keep_v)) or (gc.n_q, gc.n_qv) == (T, 24)
+        k64, v64 = kt[0, :, :T].double(), vt[0, :, :T].double()
+        for which, x, n in ((0, k64, gc.n_q), (1, v64, gc.n_qv)):
+            if n:
+                d = torch.zeros(Hkv, n, 128, device="cuda")
+                kv.dequant(shape, cfg, gc, which, d)
+                x[:, :n] = d.double()
+        q64 = qt.view(Hkv, G, 128).double().transpose(1, 2).contiguous()
+        p = torch.softmax(torch.bmm(k64, q64) / 128 ** 0.5, dim=1)
+        want = torch.bmm(p.transpose(1, 2).contiguous(), v64).half()
+        for n_splits in (1, 0):
+            out = torch.zeros_like(qt)
+            ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
+            kv.decode_attn(shape, cfg, qt, gc, out, ws, n_splits=n_splits)
+            off = (out.view(Hkv, G, 128) != want).double().mean().item()
+            print(f"keep {keep_k}/{keep_v} splits {n_splits}: {100 * off:.2f} % of the outputs not the 64-bit result's rounding", flush=True)
+            assert off <= 0.012
+
+
 @pytest.mark.parametrize("units,G,kb,vb,state,n_splits", [(86, 24, 2, 2, 0, 1), (29, 72, 3, 4, 1, 2), (129, 16, 4, 2, 4, 1), (5, 512, 2, 3, 2, 1)])
 def test_attention_with_fronts_apart_in_blocks_of_sixteen_heads(units, G, kb, vb, state, n_splits):
     """More blocks of 8 heads than there are compute units (256), so that the main launch runs blocks of 16 and its merge reads the partial of

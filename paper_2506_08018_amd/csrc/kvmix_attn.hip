@@ -440,6 +440,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   const size_t row0 = kWide<G> ? (size_t)u * a.G + head0 : (size_t)uo * G;      // first of the block's rows of q and out
   const uint16_t* qbase = a.q + row0 * kD;   // heads of unit u = (b, j) are rows (b*Hkv + j)*G .. +G-1 of q and out
   half8_t qB[4];       // plain q as B operand: the column's head (hi and lo columns alike, zero in columns not in use)
+  constexpr bool kLateQuery = MIXED && G == 4 && VB == 4;      // (next to the tiles between two fronts there are no registers for it: read in front of the packed ones)
   uint32_t qraw[G];    // q of channels (2*lane, 2*lane+1) of every head (not needed where the lanes make their own operands)
   // loaded by the hi columns in use only (a load's cost at the start of a launch is its active lanes), copied to the lo columns later;
   // groups of 1 or 2 heads use it for window tiles only, and the other waves' requests are better spent on their first tiles (16 layers of
@@ -461,7 +462,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
   };
 #pragma unroll
-  for (int hh = 0; hh < G; hh++) qraw[hh] = kOwnOperand<G> ? 0u : reinterpret_cast<const uint32_t*>(qbase + hh * kD)[lane];
+  for (int hh = 0; hh < G; hh++) qraw[hh] = kOwnOperand<G> || kLateQuery ? 0u : reinterpret_cast<const uint32_t*>(qbase + hh * kD)[lane];
 
   constexpr uint32_t kRecBytes = (uint32_t)(record_words(KB, VB) * 4);
   const rsrc_t up = make_rsrc(reinterpret_cast<const char*>(a.packed) + (size_t)u * a.tiles_cap * kRecBytes, (uint32_t)a.tiles_cap * kRecBytes);
@@ -777,6 +778,11 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // Tiles between the fronts whose Values come from the record: dealt out like the window tiles, the waves without one of those first.
   const int n_rec = !MIXED ? 0 : a.m_ahead ? a.m_tiles : a.m_front > a.m_first * kTile ? 1 : 0;
   const int first_rec = sp + (kWaves - 1 - wave) * a.n_splits;
+  // 4 heads (and 1 head with 4/3 bit): a wave that has some requests its first packed tile after them. Held in registers meanwhile, the tile made 13 of
+  // the 16 kernels spill, and scratch memory alone costs a launch 2 to 3 us (128 units x 4 heads x 4000 tokens, 3/4 bit, 800 Keys and 400 Values in
+  // fp16: 36.4 us, 20.9 this way; 2/4 bit 24.9, 19.8). The others have the registers, and lose 3 to 13 % when the tile comes late.
+  constexpr bool kLateTile = MIXED && (G == 4 || (G == 1 && KB == 4 && VB == 3));
+  const bool late_tile = kLateTile && first_rec < n_rec;
   // ---- fp16 window tiles: taken round-robin by the waves before the packed stream.
   // Past the end a wave re-reads the last tile (cache hit) and skips its work: the load stream and the
   // loop body stay uniform, which keeps the outstanding-load accounting exact.
@@ -871,7 +877,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
     if (has_packed) {   // claim the first packed tile now
       it = grab();
-      st.load(up, it < p_end ? it : p_end - 1, lane16);
+      if (!late_tile) st.load(up, it < p_end ? it : p_end - 1, lane16);
     }
   }
   // (a condition of its own: as the else of the one above it would be laid out in front of it, and the loads above would then wait
@@ -880,7 +886,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   asm volatile("" : "+s"(early_s));
   if (early_s) {
     it = p_begin + (wave - n_win);
-    if (has_packed) st.load(up, it < p_end ? it : p_end - 1, lane16);
+    if (has_packed && !late_tile) st.load(up, it < p_end ? it : p_end - 1, lane16);
     __builtin_amdgcn_sched_barrier(0);
     start_barrier();
     __builtin_amdgcn_sched_barrier(0);
@@ -1313,9 +1319,18 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         else values_large(std::true_type{}, meta, vr, x, c, ztl);
       }
     }
+    if constexpr (kLateTile) {
+      Stage<KB, VB> first;       // (not st itself: what it holds without a packed tile would be kept)
+      if (has_packed) first.load(up, it < p_end ? it : p_end - 1, lane16);
+      st = first;
+    }
   }
 
   if (has_packed) {
+    if constexpr (kLateQuery) {
+#pragma unroll
+      for (int hh = 0; hh < G; hh++) qh[hh] = as_half2(reinterpret_cast<const uint32_t*>(qbase + hh * kD)[lane]) * half2_t{pre, pre};
+    }
     zero_idle();
     while (it < p_end) {
       const int ticket = grab_issue();
@@ -1328,7 +1343,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   {
   // Where the packed loop has no register to spare, lane and thread number are made anew here (elsewhere the values at hand are better: 0.17 us per
   // launch of 32 units x 8 splits).
-  constexpr bool kAnew = kWaves == 8 && G == 4 && KB >= 3 && VB >= 3;
+  constexpr bool kAnew = kWaves == 8 && G == 4 && ((KB >= 3 && VB >= 3) || (KB == 4 && VB == 2));
   int lane = threadIdx.x & 63;
   if constexpr (kAnew) {
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));

@@ -372,10 +372,12 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     if (unsplit <= 1.06 * best) n_splits = 1;
   }
   if (n_splits > n_items) n_splits = n_items;
-  // 3 and 4 heads: no more than the 32 splits whose partials one wave merges in two batches at most (4 units x 16 000 tokens: 10.1 us with 32 splits, 10.4
-  // with 48, 11.6 with 63). A workspace is refused or accepted by the count above all the same.
+  // 4 heads: no more than the 32 splits whose partials one wave merges in two batches at most, until a split of the full count would have 24 tiles
+  // less than one of 32. A tile takes 0.11 us (2/2 bit; 3/4: 0.13), merging 64 partials 2.4 to 2.8 us longer than 32 (32 and 64 splits, 1 unit: 16 000
+  // tokens 9.0 and 10.8 us, 48 000 12.6 and 12.7, 96 000 17.9 and 15.0; 4 units: 9.5 and 11.6, 13.1 and 13.5, 18.5 and 16.1; 5 units, 32 and 51 splits,
+  // 64 000: 15.1 and 15.2, 96 000: 18.7 and 17.4). A workspace is refused or accepted by the full count all the same.
   const int n_counted = n_splits;
-  if (any_splits && G > 2 && G <= 4 && n_splits > 32) n_splits = 32;
+  if (any_splits && G == 4 && n_splits > 32 && (double)n_items * (1.0 / 32 - 1.0 / n_splits) < 24.0) n_splits = 32;
   int block = G;
   if (G > 8 || (G == 8 && fr.mixed)) {
     // (With the fronts apart 8 heads are half a block of 16: a block of 16 takes a tile in about the time of a block of 8.)

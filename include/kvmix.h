@@ -172,7 +172,8 @@ int kvmix_cache_bytes(const kvmix_shape* shape, const kvmix_layer_cfg* cfg, int 
 /* Workspace needed by kvmix_decode_attn for any context up to T_max packed tokens (split
  * partials + arrival counters; with v_lead != 0 room for one more partial is asked for). The
  * workspace must be zero-filled once before first use, all of it; every call leaves the counters zero again, and with groups of up
- * to 4 query heads the partials too (a word that is zero is one that has not been stored yet). How many counters
+ * to 4 query heads the partials too (a word that is zero is one that has not been stored yet; on a workspace that was not zero-filled a
+ * result may be wrong, and is NaN where a partial is waited for in vain). How many counters
  * there are depends on the shape: a workspace that has served one shape is zero-filled again before it serves
  * another (with more units its counters would lie where the first shape left partials). */
 int kvmix_workspace_bytes(const kvmix_shape* shape, int T_max, size_t* bytes);

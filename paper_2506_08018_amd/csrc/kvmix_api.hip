@@ -438,7 +438,8 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   plan->vb = cfg->v_bits == 16 ? 2 : cfg->v_bits;
   plan->G = G; plan->units = units;
   plan->block = block;
-  plan->waves = attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles + (a.m_ahead ? a.m_tiles : 0), n_splits, plan->block, plan->vb);
+  // (with the fronts apart always 12: those kernels do not fit the registers of 8 waves)
+  plan->waves = fr.mixed ? 12 : attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, plan->block, plan->vb);
   plan->mixed = fr.mixed;
   // with the append inside the launch the new token must be a window token of the main launch
   if (fr.mixed && new_slot >= 0 && fr.n_w_eff < 1) return KVMIX_ERR_BAD_SHAPE;
@@ -446,7 +447,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
 }
 
 int launch_plan(const AttnPlan& p, void* stream) {
-  const hipError_t e = p.mixed        ? launch_decode_attn<12, true>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream)      // (does not fit the registers of 8 waves)
+  const hipError_t e = p.mixed        ? launch_decode_attn<12, true>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream)
                        : p.waves == 8 ? launch_decode_attn<8, false>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream)
                                       : launch_decode_attn<12, false>(p.a, p.kb, p.vb, p.block, p.units, (hipStream_t)stream);
   return e == hipSuccess ? KVMIX_OK : hip_fail(e);

@@ -708,6 +708,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       if (kq == 2) S[1][1] *= (7.0f / 3.0f);
     }
   };
+  // Groups of 4 heads (the others only compile these).
   auto keys_large = [&](auto exact, const u32x4_t& meta, const Raw<KB>& kr, float4_t (&S)[2], float& zt) {
     if constexpr (G != 4) return;
     constexpr bool EXACT = decltype(exact)::value;
@@ -1018,35 +1019,24 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq + 4]) = float4_t{x[4], x[5], x[6], x[7]};
     }
     wave_lds_fence();
-    // The four lane groups g would all compute the same numerators; instead group g finishes those of the
-    // heads 4k + g only and hands them to the others through LDS as two fp16 terms (the rounded value and what
-    // the rounding left over: together ~22 bits, the same pair enters the Value sums, the zero-point sums and
-    // the denominator).
+    // The four lane groups g would all compute the same numerators; instead group g finishes those of head g and hands them to the others through
+    // LDS as two fp16 terms (the rounded value and what the rounding left over: together ~22 bits, the same pair enters the Value sums, the
+    // zero-point sums and the denominator).
     {
-      const int tp = lane & 15, g = lane >> 4;
-      // (all reads of a step are issued before its first write: the compiler does not move LDS reads across LDS
-      // writes through pointers of the same type, and one read at a time costs an LDS round trip each)
-      constexpr int kShare = G / 4 > 0 ? G / 4 : 1;   // (the function is only used with groups of 4 or 8 heads)
-      float2_t sh[kShare], sl[kShare];
-#pragma unroll
-      for (int k = 0; k < G / 4; k++) {
-        const int hh = 4 * k + g;                                  // differs between the lane groups
-        sh[k] = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh][2 * tp]);
-        sl[k] = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh + 1][2 * tp]);
-      }
-#pragma unroll
-      for (int k = 0; k < G / 4; k++) {
-        const int hh = 4 * k + g;
-        // leading terms rounded to nearest: they are multiplied on their own below, and a truncated leading term
-        // whose remainder's product falls below the fp16 range would bias the sums (plain casts are safe here:
-        // the values come out of the exponential instruction, nothing can be fused into the conversions)
-        const float p0 = fast_exp2(sh[k][0] + sl[k][0]), p1 = fast_exp2(sh[k][1] + sl[k][1]);
-        uint32_t hv, lv;
-        split_nearest(p0, p1, hv, lv);
-        const int at = Operand<G>::write_at(tp, hh);
-        *reinterpret_cast<uint32_t*>(&L.v.pq[at]) = hv;
-        *reinterpret_cast<uint32_t*>(&L.v.pq[at + Operand<G>::kLo]) = lv;
-      }
+      const int tp = lane & 15, hh = lane >> 4;
+      // (both reads are issued before the first write: the compiler does not move LDS reads across LDS writes through pointers of the same
+      // type, and one read at a time costs an LDS round trip each)
+      const float2_t sh = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh][2 * tp]);
+      const float2_t sl = *reinterpret_cast<const float2_t*>(&L.v.s[2 * hh + 1][2 * tp]);
+      // leading terms rounded to nearest: they are multiplied on their own below, and a truncated leading term
+      // whose remainder's product falls below the fp16 range would bias the sums (plain casts are safe here:
+      // the values come out of the exponential instruction, nothing can be fused into the conversions)
+      const float p0 = fast_exp2(sh[0] + sl[0]), p1 = fast_exp2(sh[1] + sl[1]);
+      uint32_t hv, lv;
+      split_nearest(p0, p1, hv, lv);
+      const int at = Operand<G>::write_at(tp, hh);
+      *reinterpret_cast<uint32_t*>(&L.v.pq[at]) = hv;
+      *reinterpret_cast<uint32_t*>(&L.v.pq[at + Operand<G>::kLo]) = lv;
       reinterpret_cast<uint32_t*>(&L.v.zv[0][0])[lane] = meta[3];
     }
     wave_lds_fence();
@@ -1164,7 +1154,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       const int tp = lane & 15, g = lane >> 4;
       // (all reads of a step are issued before its first write: the compiler does not move LDS reads across LDS
       // writes through pointers of the same type, and one read at a time costs an LDS round trip each)
-      constexpr int kShare = G / 4 > 0 ? G / 4 : 1;   // (the function is only used with groups of 4 or 8 heads)
+      constexpr int kShare = G / 4 > 0 ? G / 4 : 1;   // (only used with 8 heads)
       float2_t sh[kShare], sl[kShare];
 #pragma unroll
       for (int k = 0; k < G / 4; k++) {

@@ -40,7 +40,8 @@ constexpr float kMagic = 12582912.0f;
 constexpr uint32_t kBias = 0x4B400000u;
 
 // range / q_max, correctly rounded: a product with the rounded reciprocal, its exact remainder and one correction. Equal to the IEEE
-// quotient for 3, 7 and 15 at every fp32 significand (tried one by one); a range of fp16 numbers is far from the ends of the exponent range.
+// quotient for 3, 7 and 15 at every fp32 significand (tried one by one in tests/test_quantizer_division.py); a range of fp16 numbers is far
+// from the ends of the exponent range.
 template <int BITS>
 __device__ __forceinline__ float over_qmax(float range) {
   if constexpr (BITS == 1) return range;

@@ -479,7 +479,7 @@ def test_launches_in_blocks_of_sixteen_heads(units, G, kb, vb, tiles, n_w, n_spl
 @pytest.mark.parametrize("G,kb,vb", [(1, 2, 2), (2, 3, 2), (4, 2, 4), (4, 3, 3)])
 def test_split_counts_share_a_workspace(G, kb, vb):
     """Partials of groups of up to 4 heads: one workspace through calls of many split counts (around the numbers of partials that are
-    requested together, more splits than tiles, unsplit in between), each against the oracle; all of the workspace is zero after every
+    requested together, unsplit in between, then every count from 1 to 64), each against the oracle; all of the workspace is zero after every
     call. The static entry point in turn with a group of 8 heads, whose partials stay."""
     import torch
     import paper_2506_08018_amd as kv
@@ -496,7 +496,7 @@ def test_split_counts_share_a_workspace(G, kb, vb):
     qt, qt8 = torch.from_numpy(q).cuda(), torch.from_numpy(q8).cuda()
     out, out8 = torch.zeros_like(qt), torch.zeros_like(qt8)
     ws = torch.zeros(kv.workspace_bytes(shape, gc.T_cap), dtype=torch.uint8, device="cuda")
-    for n_splits in [2, 64, 3, 8, 9, 1, 16, 17, 32, 33, 31, 0, 7]:
+    for n_splits in [2, 64, 3, 8, 9, 1, 16, 17, 32, 33, 31, 0, 7] + list(range(1, 65)):
         for _ in range(3):
             out.fill_(float("nan"))
             kv.decode_attn(shape, cfg, qt, gc, out, ws, n_splits=n_splits)
@@ -547,8 +547,9 @@ def test_library_chooses_splits_by_the_context(units, n):
 
 @pytest.mark.parametrize("W,W_cap,T0", [(32, 64, 0), (32, 64, 63), (32, 96, 37), (32, 128, 63), (64, 192, 64 + 31), (0, 32, 0), (0, 64, 31)])
 def test_chunk_copy_inside_the_quantizer_launch(W, W_cap, T0):
-    """Rows that stay in the window ride in the quantizer's launch where no row lands in a slot that is still to be read, and are
-    copied after it where one does: chunks around both cases, rings of different room, from empty and part-filled windows."""
+    """Rows that stay in the window ride in the quantizer's launch: in workgroups of their own where no row lands in a slot that is still to be
+    read, else by the workgroup that reads the slot. Chunk after chunk, each case somewhere, both windows and all records against token-by-token appends of the
+    oracle."""
     import torch
     import paper_2506_08018_amd as kv
     print(f"case chunk copy W={W} W_cap={W_cap} T0={T0}", flush=True)

@@ -391,7 +391,7 @@ template <int G, int NW> struct MergeLds {        // per-wave reference maximum 
 //   Key front ahead: Keys from the record, Values from the ring (with the window tiles); the tokens before a front inside a tile are a
 //     packed tile of which only they count.
 // In a launch of their own on the vector unit these tiles took 13 us (14 tiles per unit of 128, 256 units, 1 head) next to 28 for the rest; a
-// decode step of two such layers, with its appends and flushes, went from 99.4 us to 80.3, of two layers of 64 units x 3000 tokens and 8
+// decode step of two such layers, with its appends and flushes, went from 103 us to 80.4, of two layers of 64 units x 3000 tokens and 8
 // heads from 103 to 47.
 template <int KB, int VB, int G, int NW, bool MIXED>
 __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(AttnArgs a) {
@@ -1450,10 +1450,10 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // combined: the count is on its way meanwhile, and no store is waited for. The workgroup that arrives last knows that every other one of
   // the unit has its results and stores them without waiting for anything; it takes a partial when all of its words read as
   // other than zero. Stores that wait for nothing and a count that is back when they
-  // are issued, instead of stores, their acknowledgement, a barrier and the count in a row: 32 units of 3 splits (one small layer) 6.35 ->
-  // 5.75 us, 24 units of 6 splits and 4 heads 8.2 -> 7.6, 32 units of 8 splits 10.4 -> 9.6, 128 of 2 splits 24.9 -> 24.1; 8 units of 32
-  // splits, 66 KB to read and to zero for the one workgroup, 12.4 -> 12.3. (Zeroing after the merge instead of under it: 12.4.) Groups of 8
-  // heads have no wave to spare for the count, and twice the words to zero.
+  // are issued, instead of stores, their acknowledgement, a barrier and the count in a row: 32 units of 3 splits (one small layer) 6.37 ->
+  // 5.85 us, 24 units of 6 splits and 4 heads 8.2 -> 7.6, 32 units of 8 splits 10.4 -> 9.6, 128 of 2 splits 24.9 -> 24.5; 8 units of 32
+  // splits, 66 KB to read and to zero for the one workgroup, 12.2 as before, of 63 and 64 splits 1 to 4 % more. (Zeroing after the merge instead of under it:
+  // 0.1 us more.) Groups of 8 heads have no wave to spare for the count, and twice the words to zero.
   static_assert(!kTagged<G> || G < kWaves);
   lds_barrier();          // the waves' results are in LDS
   uint32_t prev = 0;

@@ -441,6 +441,11 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   // (with the fronts apart always 12: those kernels do not fit the registers of 8 waves)
   plan->waves = fr.mixed ? 12 : attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, plan->block, plan->vb);
   plan->mixed = fr.mixed;
+  // Workgroups of 8 waves that are all resident at once, two to a compute unit, keep pace with each other (8 heads, 512 units of 4070 tokens: 2/2 bit 48.3 ->
+  // 45.6 us, 3/2 bit 57.8 -> 54.5; 320 units 43.1 -> 40.1; 4 heads 38.7 -> 37.2; 1 head, 320 units 27.4 -> 26.5; 16 heads 49.7 -> 47.9). With more of them than that it
+  // is better that some end early and make room (768 workgroups of 128 tiles: 75.9 us as they come, 83.7 at one pace).
+  const long long workgroups = (long long)units * n_splits * ((G + block - 1) / block), cus = num_cus();
+  plan->a.even = plan->waves == 8 && workgroups > cus && workgroups <= 2 * cus;
   // with the append inside the launch the new token must be a window token of the main launch
   if (fr.mixed && new_slot >= 0 && fr.n_w_eff < 1) return KVMIX_ERR_BAD_SHAPE;
   return KVMIX_OK;

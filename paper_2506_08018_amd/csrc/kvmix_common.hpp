@@ -154,6 +154,7 @@ struct AttnArgs {
   // out together with those of them whose Values come from the ring.
   int m_first, m_tiles, m_end, m_front, m_ring;
   bool m_ahead;
+  bool even;              // the workgroups that share a compute unit keep pace with each other (8 waves)
 };
 
 // over n_tiles tiles (and the window rows that a.n_copy names)

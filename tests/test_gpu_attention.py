@@ -374,6 +374,10 @@ def test_graph_replays_match_eager(n_splits):
     (33, 1, 8, 2, 2, 5, 32, 40, 0),       # 264 units: more workgroups than compute units
     (33, 8, 8, 2, 3, 5, 32, 63, 0),       # the same with 8 heads and 3-bit Values
     (33, 4, 8, 3, 4, 0, 64, 70, 0),       # nothing packed yet
+    (33, 1, 8, 3, 2, 13, 32, 40, 0),      # two workgroups to a compute unit that keep pace: the fewest tiles for that, thresholds at 6, 9 and 11 of 13
+    (40, 2, 8, 2, 2, 16, 32, 33, 0),      # thresholds in the middle of the tiles that the waves start with
+    (64, 4, 8, 2, 2, 17, 32, 63, 0),      # 512 workgroups: as many as are resident
+    (65, 4, 8, 2, 2, 17, 32, 40, 0),      # 520: more
     (1, 4, 1, 3, 4, 38, 32, 45, 2),       # 20 tiles per split, and one more
     (1, 4, 1, 3, 4, 39, 32, 45, 2),
     (1, 2, 2, 2, 2, 3, 288, 300, 4),      # 10 window tiles over 4 splits, fewer packed tiles than splits

@@ -292,11 +292,10 @@ Fronts fronts_of(const kvmix_layer_cache* c, int n_w) {
 // 2048 of 20: 38.9 against 50.6). With at most one workgroup per compute unit the 4 more waves pay when each has many tiles to stream (1 head,
 // 256 units of 128 tiles: 20.5 us against 23.2; 32 tiles: 10.3 against 10.6), and cost in start and merge when there are few
 // (9 tiles: 7.7 us against 7.5); from 16 to 24 tiles the two are within 2 % (16: 8.5 and 8.5).
-// 8 heads with 3- or 4-bit Values do not fit the 128 registers of the 8-wave form (spilling: 93 us where 12 waves take 62).
-int attn_waves(long long workgroups, int n_tiles, int n_splits, int block, int v_bits) {
+// 8 heads with 3- or 4-bit Values do not fit the 128 registers of the 8-wave form (spilling: 93 us where 12 waves take 62; as half a block of 16: plan_attention).
+int attn_waves(long long workgroups, int n_tiles, int n_splits, int block, int v_bits, int cus) {
   if (block > 8) return 8;
   if (block == 8 && (v_bits == 3 || v_bits == 4)) return 12;
-  const int cus = num_cus();
   return workgroups > (cus > 0 ? cus : 256) || n_tiles <= 20 * n_splits ? 8 : 12;
 }
 
@@ -349,12 +348,12 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   const int n_items = c->W_cap / kTile + fr.packed_tiles;
   if (n_splits < 0 || n_splits > max_splits(sh)) return KVMIX_ERR_BAD_SHAPE;
   const bool any_splits = n_splits == 0;
+  const int cus = num_cus();
   if (any_splits) {
     // The launch is taken to run in rounds of `cus` workgroups. A round costs a fixed part (start, merge of the waves,
     // partial and arrival: about what 48 tiles take) plus the tiles of one split; take the split count with the
     // smallest rounds x (48 + tiles per split), at least 8 tiles each. (Twice as many workgroups of 8 waves fit the card; the count is
     // also what a workspace is refused or accepted by, and 128 units of 256 tiles take 24.4 us with 4 splits of 8 waves, 23.8 with 2 of 12.)
-    const int cus = num_cus();
     if (cus == 0) return hip_fail(hipErrorInvalidDevice);
     const int ou = out_units(sh);
     int s_max = n_items / 8;
@@ -383,7 +382,6 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     // (With the fronts apart 8 heads are half a block of 16: a block of 16 takes a tile in about the time of a block of 8.)
     // Blocks of 8 heads where a launch of them has at most one workgroup per compute unit (see above: the faster ones at equal split
     // counts), blocks of 16 otherwise.
-    const int cus = num_cus();
     block = !fr.mixed && cus > 0 && (long long)out_units(sh) * n_splits <= cus ? 8 : 16;
     if (any_splits) {
       // The count above is that of blocks of 8, and it is what a workspace is refused or accepted by. A workspace that also holds the
@@ -398,6 +396,16 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
       };
       if (fits(n) && fits(n_splits) && (block == 16 || (n != n_splits && cost_of_16(sharing_of(wide, n, cus), work, n) < 1.02 * cost_of_8(work, n_splits)))) { n_splits = n; block = 16; }
     }
+  }
+  // 8 heads with 3- or 4-bit Values do not fit the 8-wave form of a block of 8 (attn_waves); as half a block of 16 they do. Where there are more workgroups than
+  // compute units, two of 8 waves side by side then beat one of 12 after the other, by more the more of a round stays empty (512 units: 300 tokens 14.5 -> 12.3 us, 1000 22.7 ->
+  // 19.3, 2000 32.3 -> 29.2, 4070 57.0 -> 53.5; 320 units x 4000 46.8 -> 42.4; 800 x 600 32.6 -> 25.4; 1600 x 2000 105.5 -> 95.7; all at 2/4 bit). A tile takes a little longer that way: long
+  // contexts stay with 12 waves (512 x 8000 tokens 101.4 in 12 waves, 103.5; 768 x 4000 83.0, 84.6). Relative error against 64 bits the same to four digits (2.076e-4, of which 2.075e-4 is the
+  // rounding to fp16).
+  const int tiles_each = (fr.packed_tiles + (fr.n_w_eff + kTile - 1) / kTile + n_splits - 1) / n_splits;      // of a workgroup
+  if (block == 8 && G == 8 && (cfg->v_bits == 3 || cfg->v_bits == 4)) {
+    const long long workgroups = (long long)units * n_splits;
+    if (cus > 0 && workgroups > cus && tiles_each <= (workgroups <= 2 * cus ? 160 : 96)) block = 16;
   }
   AttnArgs a{};
   // (With the fronts apart a workspace is refused or accepted as if the tokens between them had a partial of their own.)
@@ -439,12 +447,12 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   plan->G = G; plan->units = units;
   plan->block = block;
   // (with the fronts apart always 12: those kernels do not fit the registers of 8 waves)
-  plan->waves = fr.mixed ? 12 : attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, plan->block, plan->vb);
+  plan->waves = fr.mixed ? 12 : attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, plan->block, plan->vb, cus);
   plan->mixed = fr.mixed;
   // Workgroups of 8 waves that are all resident at once, two to a compute unit, keep pace with each other (8 heads, 512 units of 4070 tokens: 2/2 bit 48.3 ->
   // 45.6 us, 3/2 bit 57.8 -> 54.5; 320 units 43.1 -> 40.1; 4 heads 38.7 -> 37.2; 1 head, 320 units 27.4 -> 26.5; 16 heads 49.7 -> 47.9). With more of them than that it
   // is better that some end early and make room (768 workgroups of 128 tiles: 75.9 us as they come, 83.7 at one pace).
-  const long long workgroups = (long long)units * n_splits * ((G + block - 1) / block), cus = num_cus();
+  const long long workgroups = (long long)units * n_splits * ((G + block - 1) / block);
   plan->a.even = plan->waves == 8 && workgroups > cus && workgroups <= 2 * cus;
   // with the append inside the launch the new token must be a window token of the main launch
   if (fr.mixed && new_slot >= 0 && fr.n_w_eff < 1) return KVMIX_ERR_BAD_SHAPE;

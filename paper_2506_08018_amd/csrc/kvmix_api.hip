@@ -446,6 +446,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   plan->vb = cfg->v_bits == 16 ? 2 : cfg->v_bits;
   plan->G = G; plan->units = units;
   plan->block = block;
+  plan->a.head_blocks = (G + block - 1) / block;
   // (with the fronts apart always 12: those kernels do not fit the registers of 8 waves)
   plan->waves = fr.mixed ? 12 : attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, plan->block, plan->vb, cus);
   plan->mixed = fr.mixed;

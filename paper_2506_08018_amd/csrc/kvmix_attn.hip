@@ -393,8 +393,12 @@ template <int G, int NW> struct MergeLds {        // per-wave reference maximum 
 // In a launch of their own on the vector unit these tiles took 13 us (14 tiles per unit of 128, 256 units, 1 head) next to 28 for the rest; a
 // decode step of two such layers, with its appends and flushes, went from 103 us to 80.4, of two layers of 64 units x 3000 tokens and 8
 // heads from 103 to 47.
+// The parameters in front of `a` (equal to its fields of these names) are the 14 words that a workgroup finds in its scalar registers when it starts (they are
+// preloaded: build.py); what a wave needs for its query and its first packed tile. Read from memory, three reads in a row as the code comes to them, they kept the first requests back: 24 units x 4 heads, 6 splits 7.28 -> 6.97 us per launch, 8 units x 8 heads x 2000 tokens 7.35 ->
+// 6.99, 32 units x 1 head, 3 splits 6.06 -> 5.90; all read together at the start 7.24, 7.20, 6.11.
 template <int KB, int VB, int G, int NW, bool MIXED>
-__global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(AttnArgs a) {
+__global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(const uint16_t* q, const uint32_t* packed, int n_splits, int win_each, int win_extra, int items_q, int items_r, int win_tiles,
+                                                                                   int tiles_cap, int n_w, int G_all, int head_blocks, AttnArgs a) {
   constexpr int kWaves = NW;
   constexpr int kThreads = kWaves * kWave;
   // per wave: the exchange area of the packed tiles; before that, the staging area in which a window tile's
@@ -407,6 +411,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   __shared__ int s_next;   // next unclaimed packed tile of this workgroup
   __shared__ int s_done;   // waves that have delivered their result
 
+  a.q = q; a.packed = packed; a.n_splits = n_splits; a.win_each = win_each; a.win_extra = win_extra; a.items_q = items_q; a.items_r = items_r; a.win_tiles = win_tiles;
+  a.tiles_cap = tiles_cap; a.n_w = n_w; a.G = G_all; a.head_blocks = head_blocks;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // said to be uniform: what depends on it alone lives in scalar registers
   const int col = lane & 15, kq = lane >> 4;         // MFMA column / row index, k-quarter
@@ -418,7 +424,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // of a unit read the same records and window rows at about the same time, so a tile comes from HBM once and from
   // the caches after that. uo numbers the (unit, head block) pairs; blocks of 8: rows uo*8 .. uo*8+7 of q and out.
   // Blocks of 16: the last one of a group may be partly empty; its idle columns repeat the group's last head.
-  const int uo = u * (int)gridDim.z + (int)blockIdx.z;
+  const int uo = u * a.head_blocks + (int)blockIdx.z;
   const int head0 = kWide<G> ? (int)blockIdx.z * G : 0;              // first head of the block inside the unit's group
   const int n_heads = kWide<G> ? (a.G - head0 < G ? a.G - head0 : G) : G;
   WaveLds<G>& L = s_wave[wave].x;
@@ -1628,18 +1634,21 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
 
 template <int KB, int VB>
 hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
+  auto run = [&](auto kernel) {
+    kernel<<<grid, kNW * kWave, 0, s>>>(a.q, a.packed, a.n_splits, a.win_each, a.win_extra, a.items_q, a.items_r, a.win_tiles, a.tiles_cap, a.n_w, a.G, a.head_blocks, a);
+  };
   switch (G) {
-    case 1: decode_attn_kernel<KB, VB, 1, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break;
-    case 2: decode_attn_kernel<KB, VB, 2, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break;
-    case 4: decode_attn_kernel<KB, VB, 4, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break;
+    case 1: run(decode_attn_kernel<KB, VB, 1, kNW, kMixed>); break;
+    case 2: run(decode_attn_kernel<KB, VB, 2, kNW, kMixed>); break;
+    case 4: run(decode_attn_kernel<KB, VB, 4, kNW, kMixed>); break;
 #if !KVMIX_MIXED
     case 8:
       // (8 heads with 3- or 4-bit Values always run 12 waves: attn_waves)
-      if constexpr (kNW == 12 || VB < 3) { decode_attn_kernel<KB, VB, 8, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break; }
+      if constexpr (kNW == 12 || VB < 3) { run(decode_attn_kernel<KB, VB, 8, kNW, kMixed>); break; }
       else return hipErrorInvalidValue;
 #endif
 #if KVMIX_WAVES == 8 || KVMIX_MIXED
-    case 16: decode_attn_kernel<KB, VB, 16, kNW, kMixed><<<grid, kNW * kWave, 0, s>>>(a); break;
+    case 16: run(decode_attn_kernel<KB, VB, 16, kNW, kMixed>); break;
 #endif
     default: return hipErrorInvalidValue;
   }
@@ -1650,7 +1659,7 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
 
 template <>
 hipError_t launch_decode_attn<kNW, kMixed>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s) {
-  const dim3 grid(a.n_splits, units, (a.G + block - 1) / block);
+  const dim3 grid(a.n_splits, units, a.head_blocks);
   switch (k_bits * 10 + v_bits) {
     case 11: return launch_g<1, 1>(a, block, grid, s);
     case 12: return launch_g<1, 2>(a, block, grid, s);

@@ -128,27 +128,29 @@ struct AppendArgs {
 };
 
 struct AttnArgs {
-  const uint16_t* q; uint16_t* out;
+  const uint16_t* q;
   const uint32_t* packed;
   const uint16_t* k_win; const uint16_t* v_win;
   // fused append: the newest token of every unit ([units][128] each) is not in the window arrays yet but counted
   // in n_w; the wave that takes the window tile of ring slot new_slot reads it from here and stores it
   const uint16_t* k_new; const uint16_t* v_new;
-  uint16_t* k_win_w; uint16_t* v_win_w;
-  int new_slot;           // -1: nothing to append
-  float* part;            // partials: [units][n_splits][G][kD + 2]
-  uint32_t* counters;     // arrival counters (zero before and after every call), one per (unit, head block), counter_stride words apart
-  int counter_stride;
-  int G;                  // query heads per kv head
-  int tiles_cap, W_cap, n_w;
-  int ring_tiles, w0_tile;       // W_cap / 32; ring tile that holds the oldest window token
   int n_splits;
   // window tiles with live tokens: win_each per split, one more for the first win_extra splits
   int win_each, win_extra;
   // packed tiles: (packed tiles + win_extra * win_tiles) divided by n_splits, quotient and remainder; the splits with a
   // window tile more than the others take win_tiles packed tiles less
   int items_q, items_r, win_tiles;
+  int tiles_cap, W_cap, n_w;
+  int ring_tiles, w0_tile;       // W_cap / 32; ring tile that holds the oldest window token
+  int new_slot;           // -1: nothing to append
+  int G;                  // query heads per kv head
+  int head_blocks;        // workgroups per (split, unit): grid z
   float scale_log2;       // softmax_scale * log2(e)
+  int counter_stride;
+  uint16_t* out;
+  uint16_t* k_win_w; uint16_t* v_win_w;
+  float* part;            // partials: [units][n_splits][G][kD + 2]
+  uint32_t* counters;     // arrival counters (zero before and after every call), one per (unit, head block), counter_stride words apart
   // Tiles between two fronts (MIXED): tiles [m_first, m_first + m_tiles), tokens up to m_end;
   // m_front: the Value front; m_ahead: it is ahead of the Key front; m_ring: ring tile of tile m_first. The window tiles above are dealt
   // out together with those of them whose Values come from the ring.

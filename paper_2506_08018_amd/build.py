@@ -9,10 +9,12 @@ LIB = os.path.join(HERE, "libkvmix.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 COMMON = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
-          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          # the first 14 words of a kernel's arguments come preloaded in scalar registers
+          "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 # tile claims are single-lane LDS atomics whose result is taken late; the wave-reduction rewrite of
-# uniform atomics would put a wait right behind them. The first 14 words of a kernel's arguments come preloaded in scalar registers.
-ATTN = ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None", "-mllvm", "-amdgpu-kernarg-preload-count=14"]
+# uniform atomics would put a wait right behind them
+ATTN = ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
 # object -> (source, extra flags): the quantizer's arithmetic is specified operation by operation; the attention kernel exists
 # with 8 and with 12 waves per workgroup, each without and with the tiles between a Key front and a Value front
 OBJECTS = {

@@ -158,8 +158,7 @@ int kvmix_quantize_pack(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const
     return KVMIX_ERR_ALIGN;
   QuantArgs a{};
   a.k = k_fp16; a.v = v_fp16;
-  a.k_tok = token_stride; a.k_unit_b = batch_stride; a.k_unit_h = head_stride;
-  a.v_tok = token_stride; a.v_unit_b = batch_stride; a.v_unit_h = head_stride;
+  a.tok = token_stride; a.unit_b = batch_stride; a.unit_h = head_stride;
   a.n_ring = 0; a.W_cap = 1;
   fill_quant_dst(a, c);
   a.tile0 = t0 / kTile;
@@ -221,8 +220,7 @@ int kvmix_append_tokens(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const
     a.copy_tile0 = first / kTile;
     a.copy_tiles = n_copy > 0 && last > first ? (last + kTile - 1) / kTile - a.copy_tile0 : 0;
     a.k = k_new; a.v = v_new;
-    a.k_tok = token_stride; a.k_unit_b = batch_stride; a.k_unit_h = head_stride;
-    a.v_tok = token_stride; a.v_unit_b = batch_stride; a.v_unit_h = head_stride;
+    a.tok = token_stride; a.unit_b = batch_stride; a.unit_h = head_stride;
     a.k_ring = c->k_win; a.v_ring = c->v_win; a.n_ring = c->n_w; a.ring_w0 = c->w0; a.W_cap = W;
     fill_quant_dst(a, c);
     a.tile0 = c->n_q / kTile;
@@ -575,7 +573,10 @@ int kvmix_decode_step(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const u
       if (st) return st;
       const int W = c->W_cap;
       QuantArgs qa{};
-      qa.k_ring = c->k_win; qa.v_ring = c->v_win; qa.n_ring = kTile; qa.ring_w0 = c->w0; qa.W_cap = W;
+      // (the tile's slots do not wrap: its rows are rows of an input with the ring's strides)
+      qa.k = c->k_win + (size_t)c->w0 * kD; qa.v = c->v_win + (size_t)c->w0 * kD;
+      qa.tok = kD; qa.unit_h = (int64_t)W * kD; qa.unit_b = qa.unit_h * sh->Hkv;
+      qa.n_ring = 0; qa.W_cap = W;
       fill_quant_dst(qa, c);
       qa.tile0 = c->n_q / kTile;
       qa.Hkv = sh->Hkv;
@@ -651,7 +652,8 @@ int kvmix_flush(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, kvmix_layer_c
     if ((nv + kTile - 1) / kTile > last) last = (nv + kTile - 1) / kTile;
   }
   QuantArgs a{};
-  a.k_ring = c->k_win; a.v_ring = c->v_win; a.W_cap = c->W_cap;
+  a.k = c->k_win; a.v = c->v_win; a.W_cap = c->W_cap;
+  a.tok = kD; a.unit_h = (int64_t)c->W_cap * kD; a.unit_b = a.unit_h * sh->Hkv;
   a.ring_w0 = slot_of(c, first * kTile);
   fill_quant_dst(a, c);
   a.tile0 = (int)first;

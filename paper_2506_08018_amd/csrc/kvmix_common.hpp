@@ -95,8 +95,7 @@ struct QuantArgs {
   // fp16 windows ([units][W_cap][128]), every later row r is row r - n_ring of the input. Tile t takes rows
   // 32 t .. 32 t + 31.
   const uint16_t* k; const uint16_t* v;
-  int64_t k_tok, k_unit_b, k_unit_h;            // Key input: channel stride 1
-  int64_t v_tok, v_unit_b, v_unit_h;            // Value input: channel stride 1
+  int64_t tok, unit_b, unit_h;                  // strides of both inputs (channel stride 1)
   const uint16_t* k_ring; const uint16_t* v_ring;
   int n_ring, ring_w0, W_cap;
   uint32_t* packed;
@@ -109,7 +108,7 @@ struct QuantArgs {
   // each, from slot 32 copy_tile0 on.
   int n_tiles, n_copy, copy_row, copy_at, n_read, copy_tile0, copy_tiles;
   uint16_t* k_ring_w; uint16_t* v_ring_w;
-  // Ageing with separate fronts (every row comes from the ring, row r of the launch is token 32*tile0 + r): the Key
+  // Ageing with separate fronts (every row comes from the ring, which is the input then; row r of the launch is token 32*tile0 + r): the Key
   // side is written for the destination tiles [k_tile_a, k_tile_b) only, the Value side for the tokens
   // [v_tok_a, v_tok_b) only; everything else in the records is left as it is.
   int k_tile_a, k_tile_b, v_tok_a, v_tok_b;

@@ -6,6 +6,7 @@
 //
 // Built with -ffp-contract=off: the code arithmetic is specified operation by operation
 // (fp32 subtract, IEEE divide, round-half-even) so that codes are reproducible bit for bit.
+#include <type_traits>
 #include "kvmix_common.hpp"
 
 namespace kvmix {
@@ -158,7 +159,11 @@ __device__ __forceinline__ uint32_t settle(float d, float inv_lo, float step) {
 // A lane's batch of 16 elements: code[at], of element first + at of the group g0 (Values), whose fp16 number is half at % 2 of pair[at / 2],
 // or of element first + at % 8 of g0 or g1 (Keys), half at / 8 of pair[at % 8]. open: the elements to compare with the ends of the range; one
 // per lane and round, next to never.
-template <int BITS, bool KEYS>
+// Index inside its group of element `at` of a batch that begins with `first`. Two Value waves to a tile (HALF 0, 1): channels 8 HALF .. + 7, then 16 further.
+template <bool KEYS, int HALF> __device__ __forceinline__ constexpr int element_of(int first, int at) {
+  return KEYS ? first + (at & 7) : HALF < 0 ? first + (at & 15) : 8 * HALF + (at & 7) + 16 * (at >> 3 & 1);
+}
+template <int BITS, bool KEYS, int HALF>
 __device__ __forceinline__ void settle_open(uint32_t (&code)[16], const uint32_t (&pair)[8], const GroupParams& g0, const GroupParams& g1, int first, uint32_t open) {
   const float mn0 = g0.mn, mn1 = g1.mn, s0 = g0.s, s1 = g1.s, inv0 = g0.inv_lo, inv1 = g1.inv_lo, inv2_0 = g0.inv2_lo, inv2_1 = g1.inv2_lo;
 #pragma unroll 1
@@ -171,7 +176,7 @@ __device__ __forceinline__ void settle_open(uint32_t (&code)[16], const uint32_t
       x = (KEYS ? at & 7 : at >> 1) == n ? pair[n] : x;
       asm("" : "+v"(x));          // (a chain of selects: recognised as an indexed array it would move to memory)
     }
-    const int half = KEYS ? at >> 3 & 1 : at & 1, i = first + (KEYS ? at & 7 : at & 15);
+    const int half = KEYS ? at >> 3 & 1 : at & 1, i = element_of<KEYS, HALF>(first, at);
     const float mn = KEYS && half ? mn1 : mn0, s = KEYS && half ? s1 : s0;
     const bool two = BITS == 3 && (i == 10 || i == 21);
     const float inv = two ? (KEYS && half ? inv2_1 : inv2_0) : (KEYS && half ? inv1 : inv0);
@@ -186,9 +191,9 @@ __device__ __forceinline__ void settle_open(uint32_t (&code)[16], const uint32_t
 }
 // The codes of a batch. The comparison of the two products of an element is a mask of the wave's lanes in scalar registers: only elements
 // that some lane has next to k + 1/2 are looked at again.
-template <int BITS, bool KEYS>
+template <int BITS, bool KEYS, int HALF>
 __device__ __forceinline__ void quantize_batch(uint32_t (&code)[16], const uint32_t (&pair)[8], const GroupParams& g0, const GroupParams& g1, int first, uint64_t slow) {
-  auto element = [&](int at) { return first + (KEYS ? at & 7 : at); };
+  auto element = [&](int at) { return element_of<KEYS, HALF>(first, at); };
   auto group = [&](int at) -> const GroupParams& { return KEYS && at >= 8 ? g1 : g0; };
   auto d = [&](int at) {
     const uint32_t x = pair[KEYS ? at & 7 : at >> 1];
@@ -208,7 +213,7 @@ __device__ __forceinline__ void quantize_batch(uint32_t (&code)[16], const uint3
 #pragma unroll
     for (int at = 0; at < 16; at++)
       if (near[at] != 0) code[at] = resolve_tie<BITS>(code[at], d(at), group(at), element(at), at, __builtin_amdgcn_inverse_ballot_w64(near[at]), open);
-    settle_open<BITS, KEYS>(code, pair, g0, g1, first, open);
+    settle_open<BITS, KEYS, HALF>(code, pair, g0, g1, first, open);
     if (slow != 0) {      // clip (and nothing but code 0 for what is not a number)
 #pragma unroll
       for (int at = 0; at < 16; at++) {
@@ -220,46 +225,54 @@ __device__ __forceinline__ void quantize_batch(uint32_t (&code)[16], const uint3
 }
 
 // Number of 32-bit word accumulators a lane fills for one code section before the lanes of its quad are
-// combined: words i = 0..15 of its (kq, j) column group; 4-bit sections have two chunks. 1-bit sections
+// combined: words i = 0..15 (half of them where two waves share a section) of its (kq, j) column group; 4-bit sections have two chunks. 1-bit sections
 // consist of the bit plane alone (the `hi` words below, stored at the start of the section).
-template <int BITS> constexpr int acc_words() { return BITS == 4 ? 32 : 16; }
+template <int BITS, int SPLIT> constexpr int acc_words() { return (BITS == 4 ? 32 : 16) / SPLIT; }
 
-// Final step shared by both waves: `w` holds, in every lane of a quad (q = lane & 3), the complete words
-// i = 0..15 (per chunk) of column group (kq, j); lane q has the words i = 4q .. 4q+3 to deliver. `hi` (3- and 1-bit)
+// Final step of every wave: `w` holds, in every lane of a quad (q = lane & 3), the complete words
+// i = 0..15 (per chunk) of column group (kq, j), or 8 of them from i0 on; lane q has a quarter of them to deliver. `hi` (3- and 1-bit)
 // holds the high-plane words, complete in both lanes j and j^1; the even-j lanes deliver them.
-// A word of which only the bits of `mask` are this launch's to write (PARTIAL: Values that leave the window token
-// by token share their words with the neighbouring tokens' codes, which are already in place or still to come).
-// No other lane of the launch touches the word, and launches on one cache are ordered by the caller's stream.
-template <bool PARTIAL>
+// A word of which only the bytes of `mask` are this launch's to write (PARTIAL: Values that leave the window token
+// by token share their words with the neighbouring tokens' codes, which are already in place or still to come). A token's are whole halves of a word, and whole
+// bytes of a plane word (BYTES): stored as such, nothing is read. (Words were read and written back: the read waited for memory at the end of the kernel.)
+template <bool PARTIAL, bool BYTES>
 __device__ __forceinline__ void put_word(uint32_t* p, uint32_t v, uint32_t mask) {
-  if constexpr (!PARTIAL) {
+  if (!PARTIAL || mask == 0xFFFFFFFFu) {
     *p = v;
+  } else if constexpr (BYTES) {
+    uint8_t* at = reinterpret_cast<uint8_t*>(p);
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      if (mask >> (8 * i) & 1u) at[i] = (uint8_t)(v >> (8 * i));
   } else {
-    if (mask == 0xFFFFFFFFu) *p = v;
-    else if (mask != 0u) *p = (*p & ~mask) | (v & mask);
+    uint16_t* at = reinterpret_cast<uint16_t*>(p);
+    if (mask & 1u) at[0] = (uint16_t)v;
+    if (mask >> 16) at[1] = (uint16_t)(v >> 16);
   }
 }
 
 // Words of a section from the wave: lane q of a quad has those of columns i = 4q .. 4q+3. To the section itself where other launches'
 // bits share the words (PARTIAL), otherwise to the wave's image of the section in LDS.
-template <int BITS, bool PARTIAL>
-__device__ __forceinline__ void put_words(uint32_t* sec, const uint32_t (&w)[acc_words<BITS>()], const uint32_t (&hi)[16],
-                                          int kq, int j, int q, uint32_t wmask = 0xFFFFFFFFu, uint32_t hmask = 0xFFFFFFFFu) {
+template <int BITS, bool PARTIAL, int SPLIT>
+__device__ __forceinline__ void put_words(uint32_t* sec, const uint32_t (&w)[acc_words<BITS, SPLIT>()], const uint32_t (&hi)[16 / SPLIT],
+                                          int kq, int j, int q, int i0, uint32_t wmask = 0xFFFFFFFFu, uint32_t hmask = 0xFFFFFFFFu) {
   constexpr int kChunks = BITS == 4 ? 2 : BITS == 1 ? 0 : 1;
   constexpr int kPlane = BITS == 1 ? 0 : 256;     // first word of the 1-bit plane
+  constexpr int kWords = 16 / SPLIT, kEach = kWords / 4;
 #pragma unroll
   for (int c = 0; c < kChunks; c++)
 #pragma unroll
-    for (int n = 0; n < 4; n++) {
-      const uint32_t v = q == 0 ? w[16 * c + n] : q == 1 ? w[16 * c + 4 + n] : q == 2 ? w[16 * c + 8 + n] : w[16 * c + 12 + n];
-      put_word<PARTIAL>(sec + 256 * c + 4 * (16 * kq + 4 * q + n) + j, v, wmask);
+    for (int n = 0; n < kEach; n++) {
+      const uint32_t* x = &w[kWords * c + n];
+      const uint32_t v = q == 0 ? x[0] : q == 1 ? x[kEach] : q == 2 ? x[2 * kEach] : x[3 * kEach];
+      put_word<PARTIAL, false>(sec + 256 * c + 4 * (16 * kq + i0 + kEach * q + n) + j, v, wmask);
     }
   if constexpr (BITS == 3 || BITS == 1) {
     if ((j & 1) == 0) {
 #pragma unroll
-      for (int n = 0; n < 4; n++) {
-        const uint32_t v = q == 0 ? hi[n] : q == 1 ? hi[4 + n] : q == 2 ? hi[8 + n] : hi[12 + n];
-        put_word<PARTIAL>(sec + kPlane + 2 * (16 * kq + 4 * q + n) + (j >> 1), v, hmask);
+      for (int n = 0; n < kEach; n++) {
+        const uint32_t v = q == 0 ? hi[n] : q == 1 ? hi[kEach + n] : q == 2 ? hi[2 * kEach + n] : hi[3 * kEach + n];
+        put_word<PARTIAL, true>(sec + kPlane + 2 * (16 * kq + i0 + kEach * q + n) + (j >> 1), v, hmask);
       }
     }
   }
@@ -295,7 +308,7 @@ __device__ __forceinline__ T load_row(const uint16_t* p) {
   return S == kStreamBoth ? __builtin_nontemporal_load(t) : *t;
 }
 
-// One workgroup of two waves quantizes and packs one (unit, 32-token tile): wave 0 the Key tile, wave 1 the Value tile, each for
+// One workgroup of two waves (SPLIT = 1) or four (SPLIT = 2) quantizes and packs one (unit, 32-token tile). Two: wave 0 the Key tile, wave 1 the Value tile, each for
 // itself. A lane owns what ends up in the same words: lane = 16*kq + 4*j + q.
 //   Key wave:   q = ks; channels d0 = 32*ks + 8*kq + 2*j and d0 + 1 over the 32 tokens (two groups); a word
 //               (l = 16*kq + i, j) gets its fields of slot ks + 4*m from this lane, the other ks from the quad.
@@ -313,27 +326,38 @@ __device__ __forceinline__ T load_row(const uint16_t* p) {
 // PARTIAL: ageing with separate fronts for Keys and Values. The Key wave works on the tiles [k_tile_a, k_tile_b)
 // only; the Value wave writes the codes and metadata of the tokens [v_tok_a, v_tok_b) only, merging them into
 // words that it shares with other tokens. Every row comes from the ring.
-template <int KB, int VB, bool PARTIAL, Stream S>
-__global__ __launch_bounds__(128, 4) void quantize_pack_kernel(QuantArgs a) {
+//
+// SPLIT = 2: two waves for the Keys (16 tokens each) and two for the Values (channels 8 h .. 8 h + 7 and 16 + 8 h .. of every block of 32). Each
+// has half of a section's words; the two exchange the extremes of their halves of the groups through LDS. A lane has 32 elements instead of 64, one after the other: of the 3.5 us (4.6 at most,
+// where exact ties are settled) that a tile alone took in two waves from its start to its last store, the parameters of the groups were 0.45, the codes 1.05 (with ties 2.3) and the words 0.4.
+//
+// The parameters in front of `a` are preloaded into scalar registers (build.py): what the first requests need where all rows are rows of the input.
+// (Read from memory in turn, they let the first request out 0.85 us after the start.)
+template <int KB, int VB, bool PARTIAL, int SPLIT, Stream S>
+__global__ __launch_bounds__(128 * SPLIT, 4) void quantize_pack_kernel(const uint16_t* k_in, const uint16_t* v_in, int64_t tok, int64_t unit_b, int64_t unit_h,
+                                                                       uint32_t* packed, int n_tiles, int n_ring, QuantArgs a) {
+  constexpr int kWords = 16 / SPLIT;           // words of a column group, per wave
   __shared__ __attribute__((aligned(16))) uint32_t s_key[512];             // the Key section's image
   __shared__ __attribute__((aligned(16))) uint32_t s_value[kTile * kD / 2];   // the Value rows, then the Value section's image
   __shared__ __attribute__((aligned(16))) uint32_t s_meta[kMetaWords];
+  __shared__ __attribute__((aligned(16))) u32x4_t s_extremes[SPLIT == 2 ? 4 : 1][SPLIT == 2 ? kWave : 1];
+  // (read together: where they are used it would be one read after the other)
+  if constexpr (PARTIAL)
+    asm volatile("" ::"s"(a.ring_w0), "s"(a.W_cap), "s"(a.tile0), "s"(a.Hkv), "s"(a.k_tile_a), "s"(a.k_tile_b), "s"(a.v_tok_a), "s"(a.v_tok_b), "s"(a.tiles_cap));
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int side = wave / SPLIT, part = wave % SPLIT;      // side: 0 Keys, 1 Values
   const int kq = lane >> 4, j = (lane >> 2) & 3, q = lane & 3;
   const int tile_in = blockIdx.x, jh = blockIdx.y, b = blockIdx.z;   // no integer division at the start of a short kernel
-  const int u = b * a.Hkv + jh;
-  const uint16_t* in = wave ? a.v + b * a.v_unit_b + jh * a.v_unit_h : a.k + b * a.k_unit_b + jh * a.k_unit_h;
-  const uint16_t* ring = (wave ? a.v_ring : a.k_ring) + (size_t)u * a.W_cap * kD;
-  const int64_t tok = wave ? a.v_tok : a.k_tok;
+  const uint16_t* in = (side ? v_in : k_in) + b * unit_b + jh * unit_h;
   // Input row i (of those that stay in the window) to its ring slot: rows 16 bytes per lane, four at a time. from: ring slot, counted from
   // ring_w0, of the first of 32 slots; the slots [lo, hi) of them are this workgroup's to fill.
   auto copy_rows = [&](int from, int lo, int hi) {
-    uint16_t* ring_w = (wave ? a.v_ring_w : a.k_ring_w) + (size_t)u * a.W_cap * kD;
-    u32x4_t x[8];
-    int at[8];
+    uint16_t* ring_w = (side ? a.v_ring_w : a.k_ring_w) + (size_t)(b * a.Hkv + jh) * a.W_cap * kD;
+    u32x4_t x[8 / SPLIT];
+    int at[8 / SPLIT];
 #pragma unroll
-    for (int n = 0; n < 8; n++) {
-      const int rel = from + 4 * n + (lane >> 4);
+    for (int n = 0; n < 8 / SPLIT; n++) {
+      const int rel = from + 4 * (n * SPLIT + part) + (lane >> 4);
       int i = rel - a.copy_at;
       if (i < 0) i += a.W_cap;
       at[n] = -1;
@@ -344,185 +368,248 @@ __global__ __launch_bounds__(128, 4) void quantize_pack_kernel(QuantArgs a) {
       }
     }
 #pragma unroll
-    for (int n = 0; n < 8; n++)
+    for (int n = 0; n < 8 / SPLIT; n++)
       if (at[n] >= 0) *reinterpret_cast<u32x4_t*>(ring_w + (size_t)at[n] * kD + 8 * (lane & 15)) = x[n];
   };
   if constexpr (!PARTIAL) {
-    if (tile_in >= a.n_tiles) {       // window rows that land in slots which no tile of the launch reads
-      copy_rows((tile_in - a.n_tiles + a.copy_tile0) * kTile, a.n_read, a.W_cap);
+    if (tile_in >= n_tiles) {       // window rows that land in slots which no tile of the launch reads
+      copy_rows((tile_in - n_tiles + a.copy_tile0) * kTile, a.n_read, a.W_cap);
       return;
     }
   }
+  // orders LDS accesses of the two waves that share a side (all four pass it)
+  auto exchange = [&](u32x4_t mine) {
+    s_extremes[wave % (SPLIT == 2 ? 4 : 1)][lane % (SPLIT == 2 ? kWave : 1)] = mine;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    return s_extremes[(wave ^ 1) % (SPLIT == 2 ? 4 : 1)][lane % (SPLIT == 2 ? kWave : 1)];
+  };
   if constexpr (PARTIAL) {
     const int tile_abs = a.tile0 + tile_in;
-    if (wave == 0 && (tile_abs < a.k_tile_a || tile_abs >= a.k_tile_b)) return;   // wave-uniform; the waves never synchronize
+    if (side == 0 && (tile_abs < a.k_tile_a || tile_abs >= a.k_tile_b)) {        // the Keys of this tile are not in the launch
+      if constexpr (SPLIT == 2) exchange(u32x4_t{0, 0, 0, 0});
+      return;
+    }
   }
-  uint32_t* rec = a.packed + ((size_t)u * a.tiles_cap + (size_t)(a.tile0 + tile_in)) * record_words(KB, VB);
   // The tile's rows: the first n_old from ring slots, the rest from the input. Slots of one tile never wrap (everything is in steps of 32),
-  // so either part is a base and a stride.
-  int slot0 = a.ring_w0 + tile_in * kTile;
-  if constexpr (PARTIAL) slot0 %= a.W_cap;        // (the launch may span more rows than the ring has slots; only rows of live tokens are read)
-  else if (slot0 >= a.W_cap) slot0 -= a.W_cap;
-  const int n_old = PARTIAL ? kTile : a.n_ring - tile_in * kTile;
-  const uint16_t* old_rows = ring + (int64_t)slot0 * kD;
+  // so either part is a base and a stride. (PARTIAL: the input is the ring, its first row the one in slot 0.)
+  const int n_old = PARTIAL ? 0 : n_ring - tile_in * kTile;
   const uint16_t* new_rows = in - (int64_t)n_old * tok;           // row t of the tile, t >= n_old, at new_rows + t * tok
+  const uint16_t* old_rows = nullptr;
+  if constexpr (PARTIAL) {
+    int slot0 = a.ring_w0 + tile_in * kTile;
+    while (slot0 >= a.W_cap) slot0 -= a.W_cap;        // (the launch may span more rows than the ring has slots; only rows of live tokens are read)
+    new_rows = in + (int64_t)slot0 * kD;
+  } else if (n_old > 0) {
+    int slot0 = a.ring_w0 + tile_in * kTile;
+    if (slot0 >= a.W_cap) slot0 -= a.W_cap;
+    old_rows = (side ? a.v_ring : a.k_ring) + ((int64_t)(b * a.Hkv + jh) * a.W_cap + slot0) * kD;
+  }
   // a tile all of one kind, the usual case
   const bool whole = PARTIAL || n_old >= kTile || n_old <= 0;
-  const uint16_t* rows = PARTIAL || n_old > 0 ? old_rows : new_rows;
+  const uint16_t* rows = !PARTIAL && n_old > 0 ? old_rows : new_rows;
   const int64_t stride = PARTIAL || n_old > 0 ? kD : tok;
-  uint32_t hi[16];
+  // what the end of the kernel needs, read while the rows are on their way
+  auto read_rest = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!PARTIAL) asm volatile("" ::"s"(a.Hkv), "s"(a.tiles_cap), "s"(a.n_read));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto record = [&]() { return packed + ((size_t)(b * a.Hkv + jh) * a.tiles_cap + (size_t)tile_in) * record_words(KB, VB); };      // (packed: of the launch's first tile)
+  uint32_t hi[kWords];
 #pragma unroll
-  for (int i = 0; i < 16; i++) hi[i] = 0;
+  for (int i = 0; i < kWords; i++) hi[i] = 0;
 
-  if (wave == 0) {
+  if (side == 0) {
+    constexpr int kTokens = kTile / SPLIT;           // of this wave: kTokens * part ..
     const int d0 = 32 * q + 8 * kq + 2 * j;
-    uint32_t xw[kTile];                              // (x[tau][d0], x[tau][d0 + 1])
+    uint32_t xw[kTokens];                            // (x[tau][d0], x[tau][d0 + 1])
     if (whole) {
-      const uint16_t* row = rows;
+      const uint16_t* row = rows + kTokens * part * stride;
 #pragma unroll
-      for (int t = 0; t < kTile; t++) { xw[t] = load_row<S, uint32_t>(row + d0); row += stride; }
+      for (int t = 0; t < kTokens; t++) { xw[t] = load_row<S, uint32_t>(row + d0); row += stride; }
     } else {
 #pragma unroll
-      for (int t = 0; t < kTile; t++) xw[t] = load_row<kCached, uint32_t>((t < n_old ? old_rows + t * kD : new_rows + t * tok) + d0);
+      for (int n = 0; n < kTokens; n++) {
+        const int t = kTokens * part + n;
+        xw[n] = load_row<kCached, uint32_t>((t < n_old ? old_rows + t * kD : new_rows + t * tok) + d0);
+      }
     }
+    read_rest();
     half2_t mn2, mx2;
     bool nan;
     extremes(xw, mn2, mx2, nan);
+    if constexpr (SPLIT == 2) {
+      const u32x4_t other = exchange(u32x4_t{__builtin_bit_cast(uint32_t, mn2), __builtin_bit_cast(uint32_t, mx2), 0, 0});
+      const uint32_t omn = other[0], omx = other[1];       // (copies: a bit cast applied to the element itself reads element 0)
+      mn2 = __builtin_elementwise_min(mn2, __builtin_bit_cast(half2_t, omn));
+      mx2 = __builtin_elementwise_max(mx2, __builtin_bit_cast(half2_t, omx));
+    }
     const GroupParams g0 = group_params<KB>((float)mn2[0], (float)mx2[0]);
     const GroupParams g1 = group_params<KB>((float)mn2[1], (float)mx2[1]);
     const uint64_t slow = __builtin_amdgcn_ballot_w64(g0.slow || g1.slow || nan);
+    uint32_t* rec = PARTIAL ? record() : nullptr;
     // metadata word 4*(d0/2) + f: scale pair (f = 0), minimum pair (f = 1)
-    *reinterpret_cast<u32x2_t*>((PARTIAL ? rec : s_meta) + 4 * (d0 >> 1)) =
-        u32x2_t{(uint32_t)g0.scale_h | ((uint32_t)g1.scale_h << 16), (uint32_t)g0.zero_h | ((uint32_t)g1.zero_h << 16)};
-    uint32_t w[acc_words<KB>()];
+    if (part == 0)
+      *reinterpret_cast<u32x2_t*>((PARTIAL ? rec : s_meta) + 4 * (d0 >> 1)) =
+          u32x2_t{(uint32_t)g0.scale_h | ((uint32_t)g1.scale_h << 16), (uint32_t)g0.zero_h | ((uint32_t)g1.zero_h << 16)};
+    uint32_t w[acc_words<KB, SPLIT>()];
 #pragma unroll
-    for (int i = 0; i < acc_words<KB>(); i++) w[i] = 0;
+    for (int i = 0; i < acc_words<KB, SPLIT>(); i++) w[i] = 0;
+    auto codes = [&](auto first) {       // first: the wave's first token
 #pragma unroll
-    for (int t0 = 0; t0 < kTile; t0 += 8) {
-      uint32_t bc[16];                               // biased codes: the lane's first channel, then its second
-      const uint32_t pairs[8] = {xw[t0], xw[t0 + 1], xw[t0 + 2], xw[t0 + 3], xw[t0 + 4], xw[t0 + 5], xw[t0 + 6], xw[t0 + 7]};
-      quantize_batch<KB, true>(bc, pairs, g0, g1, t0, slow);
-      // tokens t0 + n and t0 + 4 + n are the two token halves m of the same word of the column group
+      for (int t0 = 0; t0 < kTokens; t0 += 8) {
+        uint32_t bc[16];                               // biased codes: the lane's first channel, then its second
+        const uint32_t pairs[8] = {xw[t0], xw[t0 + 1], xw[t0 + 2], xw[t0 + 3], xw[t0 + 4], xw[t0 + 5], xw[t0 + 6], xw[t0 + 7]};
+        quantize_batch<KB, true, -1>(bc, pairs, g0, g1, decltype(first)::value + t0, slow);
+        // tokens t0 + n and t0 + 4 + n are the two token halves m of the same word of the column group
 #pragma unroll
-      for (int n = 0; n < 4; n++) {
-        const int i = 4 * (t0 >> 3) + n;
-        // the codes of the two channels side by side: the low halves of the biased codes are the codes
-        const uint32_t p0 = __builtin_amdgcn_perm(bc[8 + n], bc[n], 0x05040100u), p1 = __builtin_amdgcn_perm(bc[12 + n], bc[4 + n], 0x05040100u);
-        if constexpr (KB == 1) {
-          hi[i] = (p0 | (p1 << 1)) << (8 * (j & 1) + 2 * q);           // the code is the plane's bit
-        } else if constexpr (KB == 4) {
-          w[i] = p0 << (4 * q);                                        // chunk m, field ks
-          w[16 + i] = p1 << (4 * q);
-        } else {
-          const uint32_t both = p0 | (p1 << 8);                        // slots ks + 4*m
-          if constexpr (KB == 2) {
-            w[i] = both << (2 * q);
+        for (int n = 0; n < 4; n++) {
+          const int i = 4 * (t0 >> 3) + n;
+          // the codes of the two channels side by side: the low halves of the biased codes are the codes
+          const uint32_t p0 = __builtin_amdgcn_perm(bc[8 + n], bc[n], 0x05040100u), p1 = __builtin_amdgcn_perm(bc[12 + n], bc[4 + n], 0x05040100u);
+          if constexpr (KB == 1) {
+            hi[i] = (p0 | (p1 << 1)) << (8 * (j & 1) + 2 * q);           // the code is the plane's bit
+          } else if constexpr (KB == 4) {
+            w[i] = p0 << (4 * q);                                        // chunk m, field ks
+            w[kWords + i] = p1 << (4 * q);
           } else {
-            w[i] = (both & 0x03030303u) << (2 * q);
-            const uint32_t top = (both >> 2) & 0x01010101u;
-            hi[i] = ((top | (top >> 7)) & 0x00030003u) << (8 * (j & 1) + 2 * q);
+            const uint32_t both = p0 | (p1 << 8);                        // slots ks + 4*m
+            if constexpr (KB == 2) {
+              w[i] = both << (2 * q);
+            } else {
+              w[i] = (both & 0x03030303u) << (2 * q);
+              const uint32_t top = (both >> 2) & 0x01010101u;
+              hi[i] = ((top | (top >> 7)) & 0x00030003u) << (8 * (j & 1) + 2 * q);
+            }
           }
         }
       }
-    }
+    };
+    // (only 3-bit groups have elements that differ from the others)
+    if (SPLIT == 2 && KB == 3 && part) codes(std::integral_constant<int, kTokens>{});
+    else codes(std::integral_constant<int, 0>{});
 #pragma unroll
-    for (int i = 0; i < acc_words<KB>(); i++) { w[i] |= quad_x1(w[i]); w[i] |= quad_x2(w[i]); }
+    for (int i = 0; i < acc_words<KB, SPLIT>(); i++) { w[i] |= quad_x1(w[i]); w[i] |= quad_x2(w[i]); }
     if constexpr (KB == 3 || KB == 1) {
 #pragma unroll
-      for (int i = 0; i < 16; i++) { hi[i] |= quad_x1(hi[i]); hi[i] |= quad_x2(hi[i]); hi[i] |= lane_x4(hi[i]); }
+      for (int i = 0; i < kWords; i++) { hi[i] |= quad_x1(hi[i]); hi[i] |= quad_x2(hi[i]); hi[i] |= lane_x4(hi[i]); }
     }
-    if constexpr (PARTIAL) put_words<KB, false>(rec + kMetaWords, w, hi, kq, j, q);
-    else put_words<KB, false>(s_key, w, hi, kq, j, q);
+    put_words<KB, false, SPLIT>(PARTIAL ? rec + kMetaWords : s_key, w, hi, kq, j, q, kWords * part);
   } else {
     const int tau0 = 8 * kq + 2 * j;
     // PARTIAL: which of the lane's two tokens, and of the two of lane j ^ 1, are among those that leave now
     auto leaves = [&](int tau) { const int t = (a.tile0 + tile_in) * kTile + tau; return !PARTIAL || (t >= a.v_tok_a && t < a.v_tok_b); };
     const bool mine[2] = {leaves(tau0), leaves(tau0 + 1)};
-    // rows 4n + lane/16, piece lane%16 of 16 bytes; piece p of row t lies at p ^ (t/2 % 4) of its row in LDS: the 16 lanes that read
-    // together (4 rows, 4 pieces) then find theirs in distinct banks
+    // Rows to LDS, pieces of 16 bytes: the whole row, or (two waves) every second piece. Piece p of row t lies at p ^ (t/2 % 4) of its row in LDS: the 16 lanes that read
+    // together (4 rows, 4 pieces) then find theirs in distinct banks (two waves: two at a time)
+    constexpr int kPieces = 16 / SPLIT, kRows = kWave / kPieces;      // of a row; rows per instruction
+    uint32_t* area = s_value + part * (kTile * kPieces * 4);
     {
-      const int r4 = lane >> 4, c = lane & 15;
-      u32x4_t x[8];
+      const int r4 = lane / kPieces, c = lane % kPieces, piece = SPLIT == 2 ? 2 * c + part : c;
+      u32x4_t x[kPieces / 2];
 #pragma unroll
-      for (int n = 0; n < 8; n++) x[n] = u32x4_t{0, 0, 0, 0};
+      for (int n = 0; n < kPieces / 2; n++) x[n] = u32x4_t{0, 0, 0, 0};
       if (whole) {
-        const uint16_t* row = rows + r4 * stride + 8 * c;
+        const uint16_t* row = rows + r4 * stride + 8 * piece;
 #pragma unroll
-        for (int n = 0; n < 8; n++) {
-          if (leaves(4 * n + r4)) x[n] = load_row<S, u32x4_t>(row);
-          row += 4 * stride;
+        for (int n = 0; n < kPieces / 2; n++) {
+          if (leaves(kRows * n + r4)) x[n] = load_row<S, u32x4_t>(row);
+          row += kRows * stride;
         }
       } else {
 #pragma unroll
-        for (int n = 0; n < 8; n++) {
-          const int t = 4 * n + r4;
-          x[n] = load_row<kCached, u32x4_t>((t < n_old ? old_rows + t * kD : new_rows + t * tok) + 8 * c);
+        for (int n = 0; n < kPieces / 2; n++) {
+          const int t = kRows * n + r4;
+          x[n] = load_row<kCached, u32x4_t>((t < n_old ? old_rows + t * kD : new_rows + t * tok) + 8 * piece);
         }
       }
+      read_rest();
 #pragma unroll
-      for (int n = 0; n < 8; n++) {
-        const int t = 4 * n + r4;
-        *reinterpret_cast<u32x4_t*>(s_value + 64 * t + 4 * (c ^ ((t >> 1) & 3))) = x[n];
+      for (int n = 0; n < kPieces / 2; n++) {
+        const int t = kRows * n + r4;
+        *reinterpret_cast<u32x4_t*>(area + 4 * kPieces * t + 4 * (c ^ ((t >> 1) & 3))) = x[n];
       }
       wave_lds_fence();
     }
-    u32x4_t xr[2][4];                                // rows tau0, tau0 + 1: channels 32*q .. 32*q + 31
+    constexpr int kOwn = 4 / SPLIT;                  // pieces of a group of this wave
+    u32x4_t xr[2][kOwn];                             // rows tau0, tau0 + 1: channels 32*q .. 32*q + 31 (two waves: 8*part .. + 7 and 16 + 8*part .. of them)
 #pragma unroll
     for (int hh = 0; hh < 2; hh++)
 #pragma unroll
-      for (int c = 0; c < 4; c++) xr[hh][c] = *reinterpret_cast<const u32x4_t*>(s_value + 64 * (tau0 + hh) + 4 * ((4 * q + c) ^ j));
+      for (int c = 0; c < kOwn; c++) xr[hh][c] = *reinterpret_cast<const u32x4_t*>(area + 4 * kPieces * (tau0 + hh) + 4 * ((kOwn * q + c) ^ j));
     const uint32_t wmask = (mine[0] ? 0x0000FFFFu : 0u) | (mine[1] ? 0xFFFF0000u : 0u);
     // a plane word holds the pairs j (even, bits 0-7 and 16-23) and j + 1 (bits 8-15 and 24-31); the even lane stores it
     uint32_t hmask = (mine[0] ? 0x000000FFu : 0u) | (mine[1] ? 0x00FF0000u : 0u);
     if constexpr (PARTIAL) hmask |= (leaves(tau0 + 2) ? 0x0000FF00u : 0u) | (leaves(tau0 + 3) ? 0xFF000000u : 0u);
     else hmask = 0xFFFFFFFFu;
+    half2_t mn2[2], mx2[2];
+    bool nan[2];
+#pragma unroll
+    for (int hh = 0; hh < 2; hh++) {
+      uint32_t x[4 * kOwn];
+#pragma unroll
+      for (int e = 0; e < 4 * kOwn; e++) x[e] = xr[hh][e >> 2][e & 3];
+      extremes(x, mn2[hh], mx2[hh], nan[hh]);
+    }
+    if constexpr (SPLIT == 2) {
+      const u32x4_t other = exchange(u32x4_t{__builtin_bit_cast(uint32_t, mn2[0]), __builtin_bit_cast(uint32_t, mx2[0]), __builtin_bit_cast(uint32_t, mn2[1]), __builtin_bit_cast(uint32_t, mx2[1])});
+#pragma unroll
+      for (int hh = 0; hh < 2; hh++) {
+        const uint32_t omn = other[2 * hh], omx = other[2 * hh + 1];
+        mn2[hh] = __builtin_elementwise_min(mn2[hh], __builtin_bit_cast(half2_t, omn));
+        mx2[hh] = __builtin_elementwise_max(mx2[hh], __builtin_bit_cast(half2_t, omx));
+      }
+    }
     GroupParams gp[2];
     uint64_t slow[2];
 #pragma unroll
     for (int hh = 0; hh < 2; hh++) {
-      uint32_t x[16];
-#pragma unroll
-      for (int e = 0; e < 16; e++) x[e] = xr[hh][e >> 2][e & 3];
-      half2_t mn2, mx2;
-      bool nan;
-      extremes(x, mn2, mx2, nan);
-      const float mn = fminf((float)mn2[0], (float)mn2[1]), mx = fmaxf((float)mx2[0], (float)mx2[1]);
+      const float mn = fminf((float)mn2[hh][0], (float)mn2[hh][1]), mx = fmaxf((float)mx2[hh][0], (float)mx2[hh][1]);
       gp[hh] = group_params<VB>(mn, mx);
-      slow[hh] = __builtin_amdgcn_ballot_w64(gp[hh].slow || nan);
+      slow[hh] = __builtin_amdgcn_ballot_w64(gp[hh].slow || nan[hh]);
     }
+    uint32_t* rec = PARTIAL ? record() : nullptr;
     // metadata word 4*(16*g + tau0/2) + f: scale pair (f = 2), minimum pair (f = 3)
-    {
+    if (part == 0) {
       const uint32_t sc2 = (uint32_t)gp[0].scale_h | ((uint32_t)gp[1].scale_h << 16), zp2 = (uint32_t)gp[0].zero_h | ((uint32_t)gp[1].zero_h << 16);
       uint32_t* mp = (PARTIAL ? rec : s_meta) + 4 * (16 * q + (tau0 >> 1)) + 2;
       if constexpr (!PARTIAL) {
         *reinterpret_cast<u32x2_t*>(mp) = u32x2_t{sc2, zp2};
       } else {
-        put_word<true>(mp, sc2, wmask);
-        put_word<true>(mp + 1, zp2, wmask);
+        put_word<true, false>(mp, sc2, wmask);
+        put_word<true, false>(mp + 1, zp2, wmask);
       }
     }
     // partial words with the lane-independent shifts first: one token's fields (slot parity e/16), then the two tokens side by side
     constexpr int kField = VB == 4 || VB == 3 ? 4 : 2;          // (3-bit codes: taken apart into planes afterwards)
-    uint32_t pw[2][16];
+    uint32_t pw[2][kWords];
+    auto codes = [&](auto half) {
+      constexpr int HALF = decltype(half)::value;
 #pragma unroll
-    for (int hh = 0; hh < 2; hh++)
+      for (int hh = 0; hh < 2; hh++)
 #pragma unroll
-      for (int e0 = 0; e0 < 32; e0 += 16) {
-        uint32_t bc[16];                               // biased codes
-        uint32_t pairs[8];
+        for (int e0 = 0; e0 < 32 / SPLIT; e0 += 16) {
+          uint32_t bc[16];                               // biased codes
+          uint32_t pairs[8];
 #pragma unroll
-        for (int n = 0; n < 8; n++) pairs[n] = xr[hh][(e0 >> 3) + (n >> 2)][n & 3];
-        quantize_batch<VB, false>(bc, pairs, gp[hh], gp[hh], e0, slow[hh]);
+          for (int n = 0; n < 8; n++) pairs[n] = xr[hh][(e0 >> 3) + (n >> 2)][n & 3];
+          quantize_batch<VB, false, HALF>(bc, pairs, gp[hh], gp[hh], e0, slow[hh]);
 #pragma unroll
-        for (int n = 0; n < 16; n++) {
-          const int e = e0 + n;
-          // (the bias lies above bit 16 and stays there)
-          pw[hh][e & 15] = e < 16 ? bc[n] : (bc[n] << kField) + pw[hh][e & 15];
+          for (int n = 0; n < 16; n++) {
+            const int i = n % kWords, slot = (e0 + n) / kWords;
+            // (the bias lies above bit 16 and stays there)
+            pw[hh][i] = slot == 0 ? bc[n] : (bc[n] << kField) + pw[hh][i];
+          }
         }
-      }
-    uint32_t ph[16];
+    };
+    if constexpr (SPLIT == 1) codes(std::integral_constant<int, -1>{});
+    else if (VB == 3 && part) codes(std::integral_constant<int, 1>{});
+    else codes(std::integral_constant<int, 0>{});
+    uint32_t ph[kWords];
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
+    for (int i = 0; i < kWords; i++) {
       const uint32_t both = __builtin_amdgcn_perm(pw[1][i], pw[0][i], 0x05040100u);       // the low halves side by side
       pw[0][i] = both;
       ph[i] = both;
@@ -531,45 +618,48 @@ __global__ __launch_bounds__(128, 4) void quantize_pack_kernel(QuantArgs a) {
         ph[i] = ((both >> 2) & 0x00010001u) | ((both >> 4) & 0x00040004u);
       }
     }
-    uint32_t w[acc_words<VB>()];
+    uint32_t w[acc_words<VB, SPLIT>()];
     if constexpr (VB == 4) {
       // slot 2*g + sp: chunk g/2, field 2*(g%2) + sp; the chunk's words are complete after the pair (g, g^1)
 #pragma unroll
-      for (int i = 0; i < 16; i++) {
+      for (int i = 0; i < kWords; i++) {
         uint32_t v = pw[0][i] << (8 * (q & 1));
         v |= quad_x1(v);
         const uint32_t other = quad_x2(v);            // the other chunk's words, from lane g ^ 2
         w[i] = (q & 2) ? other : v;                  // chunk 0
-        w[16 + i] = (q & 2) ? v : other;             // chunk 1
+        w[kWords + i] = (q & 2) ? v : other;         // chunk 1
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < 16; i++) {
+      for (int i = 0; i < kWords; i++) {
         w[i] = pw[0][i] << (4 * q);
         w[i] |= quad_x1(w[i]); w[i] |= quad_x2(w[i]);
       }
       if constexpr (VB == 3 || VB == 1) {
         // bit plane: bit 16*hh + 8*(j%2) + 2*(slot%4) + slot/4 with slot = 2*g + sp
 #pragma unroll
-        for (int i = 0; i < 16; i++) {
+        for (int i = 0; i < kWords; i++) {
           hi[i] = ph[i] << (8 * (j & 1) + 4 * (q & 1) + (q >> 1));
           hi[i] |= quad_x1(hi[i]); hi[i] |= quad_x2(hi[i]); hi[i] |= lane_x4(hi[i]);
         }
       }
     }
     if constexpr (PARTIAL) {
-      put_words<VB, true>(rec + kMetaWords + tile_words(KB), w, hi, kq, j, q, wmask, hmask);
+      put_words<VB, true, SPLIT>(rec + kMetaWords + tile_words(KB), w, hi, kq, j, q, kWords * part, wmask, hmask);
     } else {
-      wave_lds_fence();      // (the rows in this area have been read)
-      put_words<VB, false>(s_value, w, hi, kq, j, q);
+      wave_lds_fence();      // (the rows in this area have been read; by the other wave too: exchange)
+      put_words<VB, false, SPLIT>(s_value, w, hi, kq, j, q, kWords * part);
     }
   }
   if constexpr (!PARTIAL) {
-    __syncthreads();         // the metadata of both waves, and the wave's own section, are in LDS
-    if (wave == 0) store_section<KB, S>(rec + kMetaWords, s_key, lane);
-    else store_section<VB, S>(rec + kMetaWords + tile_words(KB), s_value, lane);
-    put<S>(reinterpret_cast<u32x2_t*>(rec) + 64 * wave + lane, reinterpret_cast<const u32x2_t*>(s_meta)[64 * wave + lane]);
-    // New rows that land in slots this tile was read from (both waves have their rows: the barrier): this workgroup fills those.
+    __syncthreads();         // the metadata of both sides, and the side's own section, are in LDS
+    uint32_t* rec = record();
+    if (part == 0) {
+      if (side == 0) store_section<KB, S>(rec + kMetaWords, s_key, lane);
+      else store_section<VB, S>(rec + kMetaWords + tile_words(KB), s_value, lane);
+    }
+    if (part == SPLIT - 1) put<S>(reinterpret_cast<u32x2_t*>(rec) + 64 * side + lane, reinterpret_cast<const u32x2_t*>(s_meta)[64 * side + lane]);
+    // New rows that land in slots this tile was read from (all waves have their rows: the barrier): this workgroup fills those.
     if (tile_in * kTile < a.n_read) copy_rows(tile_in * kTile, 0, a.n_read);
   }
 }
@@ -614,11 +704,28 @@ __global__ __launch_bounds__(768) void stream_read_kernel(const u32x4_t* buf, si
   if ((acc[0] & acc[1] & acc[2] & acc[3]) == 0xFFFFFFFFu && sink) sink[0] = 1u;
 }
 
+// Four waves to a tile or two: with four the chain from a tile's rows to its record is half as long, and more waves hide each other's; with two each row is read by one wave, and
+// 3-bit groups, whose two waves run code of their own, hold the instruction caches better. 4 and 2 waves: 8 tiles 3.5 us (2/2 bit) and 3.8 (3/4), 4.1 and 4.8 with 2; 512 tiles 4.5 and 5.0,
+// 5.1 and 6.0; 1536 tiles 7.5 and 9.0, 8.1 and 9.5; 4096 tiles 14.0 and 16.5, 14.9 and 16.7; 6144 tiles 19.2 and 23.5, 20.3 and 22.8; 8192 tiles 24.5 and 30.3, 25.5 and 28.9; 16 384 (cached) 55.7
+// and 62.2, 49.1 and 54.9. Ageing with the fronts apart (cached): 256 units, one Value token each 3.4 and 3.7 us, 4.3 and 4.8 with 2 waves; 4 tiles each 6.5 and 7.3, 7.0 and 8.0; 1024 units of 4 tiles
+// 13.5 and 16.7, 14.4 and 16.7; 19 tiles 64.5 and 76.1, 66.7 and 73.4.
 template <int KB, int VB, bool PARTIAL>
-hipError_t launch_qp(const QuantArgs& a, dim3 grid, Stream stream, hipStream_t s) {
-  if (PARTIAL || stream == kCached) quantize_pack_kernel<KB, VB, PARTIAL, kCached><<<grid, 128, 0, s>>>(a);
-  else if (stream == kStreamOut) quantize_pack_kernel<KB, VB, PARTIAL, PARTIAL ? kCached : kStreamOut><<<grid, 128, 0, s>>>(a);
-  else quantize_pack_kernel<KB, VB, PARTIAL, PARTIAL ? kCached : kStreamBoth><<<grid, 128, 0, s>>>(a);
+hipError_t launch_qp(const QuantArgs& a, dim3 grid, Stream stream, size_t tiles, hipStream_t s) {
+  auto run = [&](auto kernel, int waves) {
+    kernel<<<grid, waves * kWave, 0, s>>>(a.k, a.v, a.tok, a.unit_b, a.unit_h, a.packed + (size_t)a.tile0 * record_words(KB, VB), a.n_tiles, a.n_ring, a);
+  };
+  const bool four = tiles <= (PARTIAL || KB == 3 || VB == 3 ? 4096 : 8192);
+  if constexpr (PARTIAL) {
+    if (four) run(quantize_pack_kernel<KB, VB, true, 2, kCached>, 4);
+    else run(quantize_pack_kernel<KB, VB, true, 1, kCached>, 2);
+  } else if (stream == kCached) {
+    run(quantize_pack_kernel<KB, VB, false, 2, kCached>, 4);          // (fewer than 2048 tiles)
+  } else if (stream == kStreamOut) {
+    if (four) run(quantize_pack_kernel<KB, VB, false, 2, kStreamOut>, 4);
+    else run(quantize_pack_kernel<KB, VB, false, 1, kStreamOut>, 2);
+  } else {
+    run(quantize_pack_kernel<KB, VB, false, 1, kStreamBoth>, 2);
+  }
   return hipGetLastError();
 }
 
@@ -635,22 +742,22 @@ hipError_t launch_bits(const QuantArgs& a, int k_bits, int v_bits, int n_tiles, 
   const size_t tiles = (size_t)n_tiles * units;
   const Stream streaming = tiles * (2 * kTile * kD * 2) > ((size_t)256 << 20) ? kStreamBoth : tiles >= 2048 ? kStreamOut : kCached;
   switch (k_bits * 10 + v_bits) {
-    case 11: return launch_qp<1, 1, PARTIAL>(a, grid, streaming, s);
-    case 12: return launch_qp<1, 2, PARTIAL>(a, grid, streaming, s);
-    case 13: return launch_qp<1, 3, PARTIAL>(a, grid, streaming, s);
-    case 14: return launch_qp<1, 4, PARTIAL>(a, grid, streaming, s);
-    case 21: return launch_qp<2, 1, PARTIAL>(a, grid, streaming, s);
-    case 22: return launch_qp<2, 2, PARTIAL>(a, grid, streaming, s);
-    case 23: return launch_qp<2, 3, PARTIAL>(a, grid, streaming, s);
-    case 24: return launch_qp<2, 4, PARTIAL>(a, grid, streaming, s);
-    case 31: return launch_qp<3, 1, PARTIAL>(a, grid, streaming, s);
-    case 32: return launch_qp<3, 2, PARTIAL>(a, grid, streaming, s);
-    case 33: return launch_qp<3, 3, PARTIAL>(a, grid, streaming, s);
-    case 34: return launch_qp<3, 4, PARTIAL>(a, grid, streaming, s);
-    case 41: return launch_qp<4, 1, PARTIAL>(a, grid, streaming, s);
-    case 42: return launch_qp<4, 2, PARTIAL>(a, grid, streaming, s);
-    case 43: return launch_qp<4, 3, PARTIAL>(a, grid, streaming, s);
-    case 44: return launch_qp<4, 4, PARTIAL>(a, grid, streaming, s);
+    case 11: return launch_qp<1, 1, PARTIAL>(a, grid, streaming, tiles, s);
+    case 12: return launch_qp<1, 2, PARTIAL>(a, grid, streaming, tiles, s);
+    case 13: return launch_qp<1, 3, PARTIAL>(a, grid, streaming, tiles, s);
+    case 14: return launch_qp<1, 4, PARTIAL>(a, grid, streaming, tiles, s);
+    case 21: return launch_qp<2, 1, PARTIAL>(a, grid, streaming, tiles, s);
+    case 22: return launch_qp<2, 2, PARTIAL>(a, grid, streaming, tiles, s);
+    case 23: return launch_qp<2, 3, PARTIAL>(a, grid, streaming, tiles, s);
+    case 24: return launch_qp<2, 4, PARTIAL>(a, grid, streaming, tiles, s);
+    case 31: return launch_qp<3, 1, PARTIAL>(a, grid, streaming, tiles, s);
+    case 32: return launch_qp<3, 2, PARTIAL>(a, grid, streaming, tiles, s);
+    case 33: return launch_qp<3, 3, PARTIAL>(a, grid, streaming, tiles, s);
+    case 34: return launch_qp<3, 4, PARTIAL>(a, grid, streaming, tiles, s);
+    case 41: return launch_qp<4, 1, PARTIAL>(a, grid, streaming, tiles, s);
+    case 42: return launch_qp<4, 2, PARTIAL>(a, grid, streaming, tiles, s);
+    case 43: return launch_qp<4, 3, PARTIAL>(a, grid, streaming, tiles, s);
+    case 44: return launch_qp<4, 4, PARTIAL>(a, grid, streaming, tiles, s);
   }
   return hipErrorInvalidValue;
 }

@@ -111,6 +111,29 @@ STATES = [      # (tokens, [(keep_k, keep_v) flushes in order]): what the fronts
 ]
 
 
+@pytest.mark.parametrize("kb,vb,units,n,keep_k,keep_v", [
+    (2, 2, 64, 2048, 0, 0),            # 4096 tiles, the most for four waves to a tile
+    (2, 2, 66, 2048, 5, 3),            # 4224: two waves; the Value front inside a tile
+    (3, 4, 66, 2048, 40, 3),           # the Keys' last tile stays
+    (4, 3, 66, 2047, 0, 70), (1, 3, 66, 2047, 33, 31), (3, 1, 66, 2048, 64, 1),
+])
+def test_flush_of_many_tiles(kb, vb, units, n, keep_k, keep_v):
+    """One flush over more tiles than four waves each are used for, then another of a few tokens: the same records as the oracle's, stale words included."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case flush of many tiles kb={kb} vb={vb} units={units} n={n} keep={keep_k}/{keep_v}", flush=True)
+    _, k, v = synth.gen_layer_numpy(760 + kb * 10 + vb, 0, 1, 2, 2, n)
+    k, v = (np.concatenate([np.roll(a, 3 * i, axis=2) for i in range(units // 2)], 1) for a in (k, v))
+    rc, gc, shape, cfg = make_ring_pair(1, units, units, kb, vb, 2048, 2048)
+    rc.set_window(u16(k), u16(v))
+    gc.set_window(torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda())
+    for kk, kvv in ((keep_k, keep_v), (max(0, keep_k - 32), max(0, keep_v - 1))):
+        kv.flush(shape, cfg, gc, kk, kvv)
+        assert rc.flush(kk, kvv) == 0
+        torch.cuda.synchronize()
+        assert_same_state(rc, gc, f"keep {kk}/{kvv}")
+
+
 @pytest.mark.parametrize("G", [1, 2, 4, 8, 16, 24, 72])      # 24, 72: the last block of 16 heads is half full
 @pytest.mark.parametrize("state", range(len(STATES)))
 def test_attention_with_fronts_apart(G, state):

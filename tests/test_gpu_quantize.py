@@ -46,6 +46,25 @@ def test_quantize_pack_adversarial_groups(kb, vb):
     assert_cache_equal(rc, gc)
 
 
+@pytest.mark.parametrize("kb,vb,units,tiles", [
+    (2, 2, 128, 64), (2, 2, 128, 65),       # 8192 tiles, the most for four waves to a tile, and one tile per unit more
+    (4, 1, 128, 64), (1, 4, 128, 65), (4, 4, 128, 65), (1, 1, 128, 65),
+    (3, 4, 64, 64), (3, 4, 64, 65),         # 3-bit groups: 4096
+    (4, 3, 64, 64), (2, 3, 64, 65), (3, 3, 64, 65), (1, 3, 64, 64),
+    (2, 4, 64, 31), (2, 4, 64, 32),         # around 2048 tiles: records past the caches from there on
+])
+def test_quantize_pack_wave_forms(kb, vb, units, tiles):
+    print(f"case wave forms kb={kb} vb={vb} units={units} tiles={tiles}", flush=True)
+    B, Hkv, T = units // 8, 8, 32 * tiles
+    k, v = adversarial_kv(17, 1, Hkv, T)
+    k, v = (np.concatenate([np.roll(a, 32 * b, axis=2) for b in range(B)]) for a in (k, v))
+    q = np.zeros((B, Hkv, 128), np.float16)
+    window = lambda a: np.concatenate([a, a[:, :, :32]], 2)
+    _, _, _, rc, gc, shape, cfg = make_pair(B, Hkv, Hkv, T + 32, 32, kb, vb, q_k_v=(q, window(k), window(v)))
+    assert gc.n_q == T
+    assert_cache_equal(rc, gc)
+
+
 def near_tie_groups(rng, n_groups, q_max):
     """Groups of 32 fp16 values [mn, mx, x ...] whose quotients (x - mn) / s (s = the group's stored step) lie within
     a few 10^-6 relative of k + 1/2 without being ties: inside and just outside the band in which a kernel that

@@ -201,6 +201,33 @@ def test_append_tokens_equals_single_appends(kb, vb):
     assert_attn_close(run_attn(gc, shape, cfg, q), want, "after chunked appends", tight=True)
 
 
+@pytest.mark.parametrize("B,Hkv,n,offset", [
+    (2, 8, 64, 0), (2, 8, 65, 0),      # 1024 rows, and more: 16 bytes per lane
+    (3, 6, 90, 0), (1, 1, 1100, 0),    # heads that fill no workgroup
+    (2, 8, 65, 3),                     # rows that begin anywhere
+])
+def test_append_of_many_tokens(B, Hkv, n, offset):
+    """Tokens for a full-precision layer in one call, around the ring's end, from a strided source: the window's rows, and no other."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case append of many tokens B={B} Hkv={Hkv} n={n} offset={offset}", flush=True)
+    W_cap, n_w = (n + 95) // 32 * 32, 40
+    shape, cfg = kv.Shape(B, Hkv, Hkv), kv.LayerCfg(16, 16, 32)
+    gc = kv.LayerCache(shape, cfg, 32, W_cap)
+    gc.c.w0, gc.c.n_w = W_cap - 32, n_w
+    g = torch.Generator().manual_seed(n)
+    rows = [torch.randn(B * Hkv * (n + 5) * 128 + 8, generator=g).half().cuda()[offset:offset + B * Hkv * (n + 5) * 128].view(B, Hkv, n + 5, 128)[:, :, 2:2 + n] for _ in range(2)]
+    want = [torch.full((B, Hkv, W_cap, 128), 7.0, dtype=torch.float16, device="cuda") for _ in range(2)]
+    for side, w, x in zip((gc.k_win, gc.v_win), want, rows):
+        side.view(torch.float16).fill_(7.0)
+        w[:, :, [(W_cap - 32 + n_w + i) % W_cap for i in range(n)]] = x
+    kv.append_tokens(shape, cfg, *rows, gc)
+    torch.cuda.synchronize()
+    assert gc.n_w == n_w + n
+    for side, w in zip((gc.k_win, gc.v_win), want):
+        assert torch.equal(side.view(torch.float16).view(w.shape), w)
+
+
 @pytest.mark.parametrize("kb,vb,G,n_splits", [(2, 2, 1, 0), (2, 3, 2, 3), (3, 4, 4, 1), (4, 2, 8, 2), (16, 16, 2, 0)])
 def test_decode_step_equals_append_then_attention(kb, vb, G, n_splits):
     """The fused step (append inside the attention launch, two launches + attention when the window overflows)

@@ -370,9 +370,8 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   }
   if (n_splits > n_items) n_splits = n_items;
   // 4 heads: no more than the 32 splits whose partials one wave merges in two batches at most, until a split of the full count would have 24 tiles
-  // less than one of 32. A tile takes 0.11 us (2/2 bit; 3/4: 0.13), merging 64 partials 2.4 to 2.8 us longer than 32 (32 and 64 splits, 1 unit: 16 000
-  // tokens 9.0 and 10.8 us, 48 000 12.6 and 12.7, 96 000 17.9 and 15.0; 4 units: 9.5 and 11.6, 13.1 and 13.5, 18.5 and 16.1; 5 units, 32 and 51 splits,
-  // 64 000: 15.1 and 15.2, 96 000: 18.7 and 17.4). A workspace is refused or accepted by the full count all the same.
+  // less than one of 32, about where the two meet (32 and 64 splits, 1 unit, 2/2 bit: 16 000 tokens 8.6 and 10.0 us, 40 000 11.2 and 11.6, 48 000 12.0 and 11.6, 64 000 13.8 and 12.0; 3/4 bit 40 000 12.3 and
+  // 12.3, 48 000 13.1 and 12.2; 4 units, 2/2 bit: 40 000 11.6 and 12.6, 48 000 12.4 and 12.6, 64 000 14.2 and 13.1). A workspace is refused or accepted by the full count all the same.
   const int n_counted = n_splits;
   if (any_splits && G == 4 && n_splits > 32 && (double)n_items * (1.0 / 32 - 1.0 / n_splits) < 24.0) n_splits = 32;
   int block = G;

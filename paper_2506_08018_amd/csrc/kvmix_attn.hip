@@ -1359,7 +1359,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   {
   // Where the packed loop has no register to spare, lane and thread number are made anew here (elsewhere the values at hand are better: 0.17 us per
   // launch of 32 units x 8 splits).
-  constexpr bool kAnew = kWaves == 8 && G == 4 && ((KB >= 3 && VB >= 3) || (KB == 4 && VB == 2));
+  constexpr bool kAnew = G == 4 && (MIXED ? KB == 3 && VB <= 2 : kWaves == 8 && ((KB >= 3 && VB >= 3) || (KB == 4 && VB == 2)));
   int lane = threadIdx.x & 63;
   if constexpr (kAnew) {
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
@@ -1478,8 +1478,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // other than zero. Stores that wait for nothing and a count that is back when they
   // are issued, instead of stores, their acknowledgement, a barrier and the count in a row: 32 units of 3 splits (one small layer) 6.37 ->
   // 5.85 us, 24 units of 6 splits and 4 heads 8.2 -> 7.6, 32 units of 8 splits 10.4 -> 9.6, 128 of 2 splits 24.9 -> 24.5; 8 units of 32
-  // splits, 66 KB to read and to zero for the one workgroup, 12.2 as before, of 63 and 64 splits 1 to 4 % more. (Zeroing after the merge instead of under it:
-  // 0.1 us more.) Groups of 8 heads have no wave to spare for the count, and twice the words to zero.
+  // splits, 66 KB to read and to zero for the one workgroup, 12.2 as before. The waves that do not merge zero the partials while the others sum up: 11.4 (by the merging waves ahead of
+  // their sums their stores alone took 1.1 us; after the sums they were 0.1 us slower still). Groups of 8 heads have no wave to spare for the count, and twice the words to zero.
   static_assert(!kTagged<G> || G < kWaves);
   lds_barrier();          // the waves' results are in LDS
   uint32_t prev = 0;
@@ -1524,6 +1524,16 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     for (int s0 = s_first; s0 < a.n_splits; s0 += s_step) {
       const int n = a.n_splits - s0 < kBatch ? a.n_splits - s0 : kBatch;       // >= 1
       u32x2_t ml[kHeads], os[kHeads][kBatch];
+      uint32_t at[kBatch];      // where the rows begin, one after the other by addition (with a product and a choice for each, launches of 8 and more heads took 0 to 1.5 % longer)
+      {
+        const uint32_t last = (uint32_t)(s0 + n - 1) * part_bytes;
+        at[0] = (uint32_t)s0 * part_bytes;
+#pragma unroll
+        for (int i = 1; i < kBatch; i++) {
+          at[i] = at[i - 1] + part_bytes < last ? at[i - 1] + part_bytes : last;
+          asm("" : "+s"(at[i]));
+        }
+      }
       // (tagged) The last arrival waits for stores that nothing holds up. The bound is for a counter that was not zero to begin with, with which another
       // arrival may count as the last; even then the missing workgroups are on their way. (Partials that were not zero are taken for what they say.)
       for (int tries = 0;; tries++) {
@@ -1535,7 +1545,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
           const rsrc_t rows = make_rsrc(part_at(0, hh), (uint32_t)(a.n_splits - 1) * part_bytes + (kD + 2) * 4u);
           ml[k] = ld_agent2(rows, (uint32_t)(s0 + (lane < n ? lane : n - 1)) * part_bytes, 0);
 #pragma unroll
-          for (int i = 0; i < kBatch; i++) os[k][i] = ld_agent2(rows, 8u + 8u * lane, (uint32_t)(s0 + (i < n ? i : n - 1)) * part_bytes);
+          for (int i = 0; i < kBatch; i++) os[k][i] = ld_agent2(rows, 8u + 8u * lane, at[i]);
         }
         if constexpr (!kTagged<G>) break;
 #pragma unroll
@@ -1553,17 +1563,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         if (__builtin_expect(tries == kMaxTries, 0)) { ml[0][1] = 0x7FC00000u; break; }
       }
       if constexpr (kTagged<G>) {
-        // nobody else reads these rows: zero again, on the way while the sums are taken (after the last batch: loads behind stores wait for them)
-        if (s0 + s_step >= a.n_splits) {
-          const rsrc_t rows = make_rsrc(part_at(0, hd), (uint32_t)(a.n_splits - 1) * part_bytes + (kD + 2) * 4u);
-          for (int z0 = s_first; z0 < a.n_splits; z0 += s_step) {
-            const int nz = a.n_splits - z0 < kBatch ? a.n_splits - z0 : kBatch;
-            if (lane < nz) st_agent2_zero(rows, (uint32_t)(z0 + lane) * part_bytes, 0);
-#pragma unroll
-            for (int i = 0; i < kBatch; i++)
-              if (i < nz) st_agent2_zero(rows, 8u + 8u * lane, (uint32_t)(z0 + i) * part_bytes);
-          }
-        }
+        if (s0 + s_step >= a.n_splits) lds_barrier();      // the wave has all of its rows: the waves that don't merge zero them
       }
 #pragma unroll
       for (int k = 0; k < kHeads; k++) {
@@ -1594,28 +1594,40 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   auto to_out = [&](int hh, const float2_t& O, float Lsum, float) { put_out(hh, O, Lsum); };
   if constexpr (kTagged<G>) {
     constexpr int kBatch = kWaves == 8 && G == 4 ? 16 : kMergeBatch;      // (4 heads, 8 waves: 32 do not fit the registers)
-    if (a.n_splits <= 8) {
-      if (wave < n_heads) merge(std::integral_constant<int, 8>{}, wave, 0, 8, to_out);
-    } else if (G == 4 || a.n_splits <= kBatch) {
-      if (wave < n_heads) merge(std::integral_constant<int, kBatch>{}, wave, 0, kBatch, to_out);
-    } else if constexpr (G < 4) {
-      // 16 partials of one head to a wave, then the waves' sums like the waves' results before. (When one wave took both batches of
-      // its head, with the zeros of the first in front of the second's loads, 4 units of 1 head in 50 splits took 9.0 us per launch; 7.4 now. With 32
-      // splits and 4 heads two waves of 16 are slower than one of 32, 13.0 us against 12.3, and the longer code costs the short launches 1 %.)
-      constexpr int kRows = kWaves / G;      // x 16: at least 64
-      const int hd = wave % G, row = wave / G, rows = (a.n_splits + 15) / 16 < kRows ? (a.n_splits + 15) / 16 : kRows;
+    // Many splits of 1 or 2 heads: 16 partials of one head to a wave, then the waves' sums like the waves' results before. (When one wave took both batches of
+    // its head, with the zeros of the first in front of the second's loads, 4 units of 1 head in 50 splits took 9.0 us per launch; 7.4 now. With 32
+    // splits and 4 heads two waves of 16 are slower than one of 32, 13.0 us against 12.3, and the longer code costs the short launches 1 %.)
+    constexpr int kRows = kWaves / G;      // x 16: at least 64
+    const int rows = G == 4 || a.n_splits <= kBatch ? 1 : (a.n_splits + 15) / 16 < kRows ? (a.n_splits + 15) / 16 : kRows;
+    const int merging = rows * G;      // waves
+    if (wave >= merging) lds_barrier();
+    else if (a.n_splits <= 8) merge(std::integral_constant<int, 8>{}, wave, 0, 8, to_out);
+    else if (G == 4 || rows == 1) merge(std::integral_constant<int, kBatch>{}, wave, 0, kBatch, to_out);
+    else if constexpr (G < 4) {
+      const int hd = wave % G, row = wave / G;
+      merge(std::integral_constant<int, 16>{}, hd, 16 * row, 16 * kRows, [&](int hh, const float2_t& O, float Lsum, float M) {
+        if (lane == 0) { R.m[row][hh] = M; R.l[row][hh] = Lsum; }
+        *reinterpret_cast<float2_t*>(&s_wave[row].o[hh][2 * lane]) = O;
+      });
+    }
+    // Nobody else reads the unit's partials: zero again, the splits' rows one after the other, by the waves that don't merge while the others sum up (by the merging waves where all of
+    // them merge). 8 units of 4 heads, 32 splits 12.0 -> 11.4 us per launch, 1 unit, 64 splits 16.4 -> 15.4; 8 units of 1 head, 8 splits 6.53 -> 6.38; 32 units, 3 splits 5.87 -> 5.77.
+    if (wave >= merging || merging == kWaves) {
+      const int first = merging == kWaves ? 0 : merging;
+      const uint32_t bytes = (uint32_t)a.n_splits * part_bytes;          // a multiple of 8
+      const rsrc_t all = make_rsrc(part_at(0, 0), bytes);
+      for (uint32_t at = 16u * ((uint32_t)(wave - first) * kWave + lane); at + 16u <= bytes; at += 16u * kWave * (uint32_t)(kWaves - first))
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{0, 0, 0, 0}, all, (int)at, 0, kAgent);
+      if ((bytes & 8u) && wave == first && lane == 0) st_agent2_zero(all, bytes - 8u, 0);
+    }
+    if constexpr (G < 4) if (rows > 1) {
       if (wave >= rows) {       // rows of no partial
         if (lane < G) { R.m[wave][lane] = -INFINITY; R.l[wave][lane] = 0.0f; }
 #pragma unroll
         for (int hh = 0; hh < G; hh++) *reinterpret_cast<float2_t*>(&s_wave[wave].o[hh][2 * lane]) = float2_t{0, 0};
       }
-      if (row < rows && hd < n_heads)
-        merge(std::integral_constant<int, 16>{}, hd, 16 * row, 16 * kRows, [&](int hh, const float2_t& O, float Lsum, float M) {
-          if (lane == 0) { R.m[row][hh] = M; R.l[row][hh] = Lsum; }
-          *reinterpret_cast<float2_t*>(&s_wave[row].o[hh][2 * lane]) = O;
-        });
       lds_barrier();
-      if (wave < n_heads) {
+      if (wave < G) {
         float2_t ml, O;
         combine_head(wave, ml, O);
         put_out(wave, O, ml[1]);

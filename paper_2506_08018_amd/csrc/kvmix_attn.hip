@@ -393,12 +393,11 @@ template <int G, int NW> struct MergeLds {        // per-wave reference maximum 
 // In a launch of their own on the vector unit these tiles took 13 us (14 tiles per unit of 128, 256 units, 1 head) next to 28 for the rest; a
 // decode step of two such layers, with its appends and flushes, went from 103 us to 80.4, of two layers of 64 units x 3000 tokens and 8
 // heads from 103 to 47.
-// The parameters in front of `a` (equal to its fields of these names) are the 14 words that a workgroup finds in its scalar registers when it starts (they are
-// preloaded: build.py); what a wave needs for its query and its first packed tile. Read from memory, three reads in a row as the code comes to them, they kept the first requests back: 24 units x 4 heads, 6 splits 7.28 -> 6.97 us per launch, 8 units x 8 heads x 2000 tokens 7.35 ->
+// The parameters in front of `a` (fields of it, see the first lines) are the 14 words that a workgroup finds in its scalar registers when it starts (they are
+// preloaded: build.py); what a wave needs for its query and its first packed tile. (Few of them: every parameter costs the host's launch some 15 ns.) Read from memory, three reads in a row as the code comes to them, they kept the first requests back: 24 units x 4 heads, 6 splits 7.28 -> 6.97 us per launch, 8 units x 8 heads x 2000 tokens 7.35 ->
 // 6.99, 32 units x 1 head, 3 splits 6.06 -> 5.90; all read together at the start 7.24, 7.20, 6.11.
 template <int KB, int VB, int G, int NW, bool MIXED>
-__global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(const uint16_t* q, const uint32_t* packed, int n_splits, int win_each, int win_extra, int items_q, int items_r, int win_tiles,
-                                                                                   int tiles_cap, int n_w, int G_all, int head_blocks, AttnArgs a) {
+__global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(const uint16_t* q, const uint32_t* packed, u32x4_t shares, u32x4_t items, u32x2_t heads, AttnArgs a) {
   constexpr int kWaves = NW;
   constexpr int kThreads = kWaves * kWave;
   // per wave: the exchange area of the packed tiles; before that, the staging area in which a window tile's
@@ -411,8 +410,10 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   __shared__ int s_next;   // next unclaimed packed tile of this workgroup
   __shared__ int s_done;   // waves that have delivered their result
 
-  a.q = q; a.packed = packed; a.n_splits = n_splits; a.win_each = win_each; a.win_extra = win_extra; a.items_q = items_q; a.items_r = items_r; a.win_tiles = win_tiles;
-  a.tiles_cap = tiles_cap; a.n_w = n_w; a.G = G_all; a.head_blocks = head_blocks;
+  a.q = q; a.packed = packed;
+  a.n_splits = (int)shares[0]; a.win_each = (int)shares[1]; a.win_extra = (int)shares[2]; a.win_tiles = (int)shares[3];
+  a.items_q = (int)items[0]; a.items_r = (int)items[1]; a.tiles_cap = (int)items[2]; a.n_w = (int)items[3];
+  a.G = (int)heads[0]; a.head_blocks = (int)heads[1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // said to be uniform: what depends on it alone lives in scalar registers
   const int col = lane & 15, kq = lane >> 4;         // MFMA column / row index, k-quarter
@@ -1646,8 +1647,13 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
 
 template <int KB, int VB>
 hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
+  hipError_t e = hipErrorInvalidValue;
   auto run = [&](auto kernel) {
-    kernel<<<grid, kNW * kWave, 0, s>>>(a.q, a.packed, a.n_splits, a.win_each, a.win_extra, a.items_q, a.items_r, a.win_tiles, a.tiles_cap, a.n_w, a.G, a.head_blocks, a);
+    const uint32_t u[10] = {(uint32_t)a.n_splits, (uint32_t)a.win_each, (uint32_t)a.win_extra, (uint32_t)a.win_tiles, (uint32_t)a.items_q, (uint32_t)a.items_r,
+                            (uint32_t)a.tiles_cap, (uint32_t)a.n_w, (uint32_t)a.G, (uint32_t)a.head_blocks};
+    u32x4_t shares = {u[0], u[1], u[2], u[3]}, items = {u[4], u[5], u[6], u[7]};
+    u32x2_t heads = {u[8], u[9]};
+    e = launch(kernel, grid, kNW * kWave, s, a.q, a.packed, shares, items, heads, a);
   };
   switch (G) {
     case 1: run(decode_attn_kernel<KB, VB, 1, kNW, kMixed>); break;
@@ -1657,14 +1663,13 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
     case 8:
       // (8 heads with 3- or 4-bit Values always run 12 waves: attn_waves)
       if constexpr (kNW == 12 || VB < 3) { run(decode_attn_kernel<KB, VB, 8, kNW, kMixed>); break; }
-      else return hipErrorInvalidValue;
+      else break;
 #endif
 #if KVMIX_WAVES == 8 || KVMIX_MIXED
     case 16: run(decode_attn_kernel<KB, VB, 16, kNW, kMixed>); break;
 #endif
-    default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
+  return e;
 }
 
 }  // namespace

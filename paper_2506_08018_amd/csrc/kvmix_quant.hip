@@ -330,12 +330,8 @@ __device__ __forceinline__ T load_row(const uint16_t* p) {
 // SPLIT = 2: two waves for the Keys (16 tokens each) and two for the Values (channels 8 h .. 8 h + 7 and 16 + 8 h .. of every block of 32). Each
 // has half of a section's words; the two exchange the extremes of their halves of the groups through LDS. A lane has 32 elements instead of 64, one after the other: of the 3.5 us (4.6 at most,
 // where exact ties are settled) that a tile alone took in two waves from its start to its last store, the parameters of the groups were 0.45, the codes 1.05 (with ties 2.3) and the words 0.4.
-//
-// The parameters in front of `a` are preloaded into scalar registers (build.py): what the first requests need where all rows are rows of the input.
-// (Read from memory in turn, they let the first request out 0.85 us after the start.)
 template <int KB, int VB, bool PARTIAL, int SPLIT, Stream S>
-__global__ __launch_bounds__(128 * SPLIT, 4) void quantize_pack_kernel(const uint16_t* k_in, const uint16_t* v_in, int64_t tok, int64_t unit_b, int64_t unit_h,
-                                                                       uint32_t* packed, int n_tiles, int n_ring, QuantArgs a) {
+__device__ __forceinline__ void quantize_tile(const uint16_t* k_in, const uint16_t* v_in, int64_t tok, int64_t unit_b, int64_t unit_h, uint32_t* packed, int n_tiles, int n_ring, const QuantArgs& a) {
   constexpr int kWords = 16 / SPLIT;           // words of a column group, per wave
   __shared__ __attribute__((aligned(16))) uint32_t s_key[512];             // the Key section's image
   __shared__ __attribute__((aligned(16))) uint32_t s_value[kTile * kD / 2];   // the Value rows, then the Value section's image
@@ -509,13 +505,21 @@ __global__ __launch_bounds__(128 * SPLIT, 4) void quantize_pack_kernel(const uin
     {
       const int r4 = lane / kPieces, c = lane % kPieces, piece = SPLIT == 2 ? 2 * c + part : c;
       u32x4_t x[kPieces / 2];
+      if constexpr (PARTIAL) {
+        // Rows of tokens that stay are not read: beyond the resource's end a load returns zeros. (With a branch around each load the rows were once waited for one after the other.)
+        const uint64_t base = reinterpret_cast<uint64_t>(rows);
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base), hi32 = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+        const __amdgpu_buffer_rsrc_t tile = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uint64_t)hi32 << 32) | lo), 0, kTile * kD * 2, 0x00020000);
 #pragma unroll
-      for (int n = 0; n < kPieces / 2; n++) x[n] = u32x4_t{0, 0, 0, 0};
-      if (whole) {
+        for (int n = 0; n < kPieces / 2; n++) {
+          const int t = kRows * n + r4;
+          x[n] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(tile, leaves(t) ? 2 * kD * t + 16 * piece : 0x40000000, 0, 0));
+        }
+      } else if (whole) {
         const uint16_t* row = rows + r4 * stride + 8 * piece;
 #pragma unroll
         for (int n = 0; n < kPieces / 2; n++) {
-          if (leaves(kRows * n + r4)) x[n] = load_row<S, u32x4_t>(row);
+          x[n] = load_row<S, u32x4_t>(row);
           row += kRows * stride;
         }
       } else {
@@ -664,6 +668,19 @@ __global__ __launch_bounds__(128 * SPLIT, 4) void quantize_pack_kernel(const uin
   }
 }
 
+// Four waves: small launches. The parameters in front of `a` are preloaded into scalar registers (build.py): what the first requests need where all rows are rows of the input.
+// (Read from memory in turn, they let the first request out 0.85 us after the start.)
+typedef int64_t i64x2_t __attribute__((ext_vector_type(2)));
+template <int KB, int VB, bool PARTIAL, Stream S>
+__global__ __launch_bounds__(256, 4) void quantize_pack_kernel(const uint16_t* k, const uint16_t* v, i64x2_t strides, int64_t unit_h, uint32_t* packed, u32x2_t counts, QuantArgs a) {
+  quantize_tile<KB, VB, PARTIAL, 2, S>(k, v, strides[0], strides[1], unit_h, packed, (int)counts[0], (int)counts[1], a);
+}
+// Two waves: large launches, to which preloading (0.3 us in front of a launch) gives nothing.
+template <int KB, int VB, bool PARTIAL, Stream S>
+__global__ __launch_bounds__(128, 4) void quantize_pack_many_kernel(QuantArgs a) {
+  quantize_tile<KB, VB, PARTIAL, 1, S>(a.k, a.v, a.tok, a.unit_b, a.unit_h, a.packed + (size_t)a.tile0 * record_words(KB, VB), a.n_tiles, a.n_ring, a);
+}
+
 // x = code * s_i + min, evaluated in fp32 (multiply, then add), of the first n_tokens tokens of every unit.
 __global__ __launch_bounds__(256) void dequant_kernel(DequantArgs a) {
   const int u = blockIdx.y, tile_i = blockIdx.x;
@@ -719,29 +736,24 @@ __global__ __launch_bounds__(768) void stream_read_kernel(const u32x4_t* buf, si
   if ((acc[0] & acc[1] & acc[2] & acc[3]) == 0xFFFFFFFFu && sink) sink[0] = 1u;
 }
 
-// Four waves to a tile or two: with four the chain from a tile's rows to its record is half as long, and more waves hide each other's; with two each row is read by one wave, and
-// 3-bit groups, whose two waves run code of their own, hold the instruction caches better. 4 and 2 waves: 8 tiles 3.5 us (2/2 bit) and 3.8 (3/4), 4.1 and 4.8 with 2; 512 tiles 4.5 and 5.0,
-// 5.1 and 6.0; 1536 tiles 7.5 and 9.0, 8.1 and 9.5; 4096 tiles 14.0 and 16.5, 14.9 and 16.7; 6144 tiles 19.2 and 23.5, 20.3 and 22.8; 8192 tiles 24.5 and 30.3, 25.5 and 28.9; 16 384 (cached) 55.7
-// and 62.2, 49.1 and 54.9. Ageing with the fronts apart (cached): 256 units, one Value token each 3.4 and 3.7 us, 4.3 and 4.8 with 2 waves; 4 tiles each 6.5 and 7.3, 7.0 and 8.0; 1024 units of 4 tiles
-// 13.5 and 16.7, 14.4 and 16.7; 19 tiles 64.5 and 76.1, 66.7 and 73.4.
+// Four waves to a tile or two: with four the chain from a tile's rows to its record is half as long, and more waves hide each other's; with two each row is requested by one wave only, and the
+// work that both waves of a side do (extremes met through LDS, parameters) is done once. 4 and 2 waves: 8 tiles 3.5 us (2/2 bit) and 3.8 (3/4), 4.1 and 4.8 with 2; 512 tiles 4.5 and 5.1,
+// 5.1 and 6.0; 1536 tiles 7.5 and 9.0, 8.1 and 9.5; 4096 tiles 13.9 and 16.4, 14.8 and 16.6; 6144 tiles 19.2 and 23.5, 20.3 and 22.8; 8192 tiles 23.8 and 30.3, 24.6 and 28.9; 16 384 (cached) 55.7
+// and 62.2, 49.1 and 54.9. Ageing with the fronts apart (cached): 256 units, one Value token each 3.4 and 3.7 us, 4.3 and 4.8 with 2 waves; 4 tiles each 6.1 and 7.0, 7.0 and 8.0; 1024 units of 4 tiles
+// 12.9 and 16.5, 14.4 and 16.7; 19 tiles 64.5 and 76.1, 66.6 and 72.6.
 template <int KB, int VB, bool PARTIAL>
 hipError_t launch_qp(const QuantArgs& a, dim3 grid, Stream stream, size_t tiles, hipStream_t s) {
-  auto run = [&](auto kernel, int waves) {
-    kernel<<<grid, waves * kWave, 0, s>>>(a.k, a.v, a.tok, a.unit_b, a.unit_h, a.packed + (size_t)a.tile0 * record_words(KB, VB), a.n_tiles, a.n_ring, a);
+  auto run_four = [&](auto kernel) {
+    return launch(kernel, grid, 4 * kWave, s, a.k, a.v, i64x2_t{a.tok, a.unit_b}, a.unit_h, a.packed + (size_t)a.tile0 * record_words(KB, VB), u32x2_t{(uint32_t)a.n_tiles, (uint32_t)a.n_ring}, a);
   };
+  auto run_two = [&](auto kernel) { return launch(kernel, grid, 2 * kWave, s, a); };
   const bool four = tiles <= (PARTIAL || KB == 3 || VB == 3 ? 4096 : 8192);
-  if constexpr (PARTIAL) {
-    if (four) run(quantize_pack_kernel<KB, VB, true, 2, kCached>, 4);
-    else run(quantize_pack_kernel<KB, VB, true, 1, kCached>, 2);
-  } else if (stream == kCached) {
-    run(quantize_pack_kernel<KB, VB, false, 2, kCached>, 4);          // (fewer than 2048 tiles)
-  } else if (stream == kStreamOut) {
-    if (four) run(quantize_pack_kernel<KB, VB, false, 2, kStreamOut>, 4);
-    else run(quantize_pack_kernel<KB, VB, false, 1, kStreamOut>, 2);
-  } else {
-    run(quantize_pack_kernel<KB, VB, false, 1, kStreamBoth>, 2);
+  if constexpr (PARTIAL) return four ? run_four(quantize_pack_kernel<KB, VB, true, kCached>) : run_two(quantize_pack_many_kernel<KB, VB, true, kCached>);
+  if constexpr (!PARTIAL) {
+    if (stream == kCached) return run_four(quantize_pack_kernel<KB, VB, false, kCached>);          // (fewer than 2048 tiles)
+    if (stream == kStreamOut) return four ? run_four(quantize_pack_kernel<KB, VB, false, kStreamOut>) : run_two(quantize_pack_many_kernel<KB, VB, false, kStreamOut>);
+    return run_two(quantize_pack_many_kernel<KB, VB, false, kStreamBoth>);
   }
-  return hipGetLastError();
 }
 
 // The bit pairs the library accepts: every pair of 1..4 (a 16-bit side never reaches the quantizer).
@@ -804,10 +816,8 @@ hipError_t launch_append(const AppendArgs& a, hipStream_t s) {
   if (a.n == 0 || a.units == 0) return hipSuccess;
   const bool aligned = ((reinterpret_cast<uintptr_t>(a.k_new) | reinterpret_cast<uintptr_t>(a.v_new)) & 15u) == 0 && a.tok % 8 == 0 && a.head % 8 == 0 && a.batch % 8 == 0;
   if (aligned && (int64_t)a.units * a.n > 1024)
-    append_many_kernel<<<dim3(a.n, a.units / a.Hkv, (a.Hkv + kAppendHeads - 1) / kAppendHeads), 32 * kAppendHeads, 0, s>>>(a);
-  else
-    append_kernel<<<dim3(a.units, a.n), 128, 0, s>>>(a);
-  return hipGetLastError();
+    return launch(append_many_kernel, dim3(a.n, a.units / a.Hkv, (a.Hkv + kAppendHeads - 1) / kAppendHeads), 32 * kAppendHeads, s, a);
+  return launch(append_kernel, dim3(a.units, a.n), 128, s, a);
 }
 
 }  // namespace kvmix

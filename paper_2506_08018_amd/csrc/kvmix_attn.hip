@@ -394,8 +394,9 @@ template <int G, int NW> struct MergeLds {        // per-wave reference maximum 
 // decode step of two such layers, with its appends and flushes, went from 103 us to 80.4, of two layers of 64 units x 3000 tokens and 8
 // heads from 103 to 47.
 // The parameters in front of `a` (fields of it, see the first lines) are the 14 words that a workgroup finds in its scalar registers when it starts (they are
-// preloaded: build.py); what a wave needs for its query and its first packed tile. (Few of them: every parameter costs the host's launch some 15 ns.) Read from memory, three reads in a row as the code comes to them, they kept the first requests back: 24 units x 4 heads, 6 splits 7.28 -> 6.97 us per launch, 8 units x 8 heads x 2000 tokens 7.35 ->
-// 6.99, 32 units x 1 head, 3 splits 6.06 -> 5.90; all read together at the start 7.24, 7.20, 6.11.
+// preloaded: build.py): what a wave needs for its query and its first packed tile. Read from memory, three reads in a row as the code comes to them, they kept
+// the first requests back: 24 units x 4 heads, 6 splits 7.28 -> 6.97 us per launch, 8 units x 8 heads x 2000 tokens 7.35 -> 6.99, 32 units x 1 head, 3 splits
+// 6.06 -> 5.90; all read together at the start 7.24, 7.20, 6.11. Few parameters: each costs the host's launch some 15 ns.
 template <int KB, int VB, int G, int NW, bool MIXED>
 __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(const uint16_t* q, const uint32_t* packed, u32x4_t shares, u32x4_t items, u32x2_t heads, AttnArgs a) {
   constexpr int kWaves = NW;

@@ -175,8 +175,9 @@ int kvmix_cache_bytes(const kvmix_shape* shape, const kvmix_layer_cfg* cfg, int 
  * to 4 query heads the partials too (a word that is zero is one that has not been stored yet; on a workspace that was not zero-filled a
  * result may be wrong, and is NaN where a partial is waited for in vain). How many counters
  * there are depends on the shape: a workspace that has served one shape is zero-filled again before it serves
- * another (with more units its counters would lie where the first shape left partials). Calls that overlap in time need one each: with n_splits = 0
- * a call may split, and use it, wherever it is large enough. */
+ * another (with more units its counters would lie where the first shape left partials). Calls that overlap in time and split need one
+ * each. Left to the library (n_splits = 0), a call with up to 8 query heads per kv head that is accepted without a workspace leaves
+ * one that it is given alone; with more heads it may split, and use the workspace, wherever that is large enough. */
 int kvmix_workspace_bytes(const kvmix_shape* shape, int T_max, size_t* bytes);
 
 /* Part 1 (Sec. 3.2.2 steps 1-4, Sec. 3.4 item 1). Quantize n_tokens (multiple of 32) fp16

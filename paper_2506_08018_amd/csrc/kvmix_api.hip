@@ -374,19 +374,20 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   // 12.3, 48 000 13.1 and 12.2; 4 units, 2/2 bit: 40 000 11.6 and 12.6, 48 000 12.4 and 12.6, 64 000 14.2 and 13.1). A workspace is refused or accepted by the full count all the same.
   const int n_counted = n_splits;
   if (any_splits && G == 4 && n_splits > 32 && (double)n_items * (1.0 / 32 - 1.0 / n_splits) < 24.0) n_splits = 32;
-  // Two workgroups of 8 waves to a compute unit, at one pace, take a round's fixed part once (62 tiles' worth for the two) and leave fewer compute units empty: a launch that has one workgroup
-  // at most for each goes to a count that makes it more than one but at most two, where that is modelled 12 % better than unsplit or 8 % better than split (split launches cost
-  // another 12 tiles). 160 units of 94 + 4 tiles, 1 and 3 splits: 1 head 13.6 and 13.2 us, 4 heads 16.7 and 14.9, 8 heads 18.5 and 17.6; 130 units 13.3 and 12.1, 16.1 and 14.1, 18.0 and 16.9; 90 units of 250 tiles, 2 and 5
-  // splits: 17.0 and 15.7, 21.0 and 18.3, 23.7 and 22.2; of 126: 11.6 and 11.0, 13.6 and 12.6, 15.5 and 15.4. Not modelled better and not so: 170 units of 47 tiles, 4 heads, 11.2 and 11.7; 192 of 126 in 2 splits, 8 heads,
-  // 22.8 and 24.9. Wider codes are nearer to what memory gives either way (168 units of 152 tiles at 4/4 bit, 4 heads: 25.8 us unsplit, 27.1). Only with a workspace that holds these partials;
-  // it is refused or accepted by the count above.
+  // Two workgroups of 8 waves to a compute unit, at one pace, take a round's fixed part once (62 tiles' worth for the two) and
+  // leave fewer compute units empty: a split launch that has one workgroup at most for each goes to a count that makes it more
+  // than one but at most two, where that is modelled 8 % better (split launches cost another 12 tiles). 90 units, 2 and 5
+  // splits, 1, 4 and 8 heads: 250 tiles 17.0 and 15.7 us, 21.0 and 18.3, 23.7 and 22.2; 126 tiles 11.6 and 11.0, 13.6 and
+  // 12.6, 15.5 and 15.4. Only with a workspace that holds these partials; it is refused or accepted by the count above.
+  // An unsplit launch stays unsplit: it leaves the workspace alone, so that calls that overlap may hand over the same one, or
+  // one that is not zero (129 to 170 units in 3 splits would take 3 to 13 % less: 160 units of 94 tiles, 4 heads, 16.7 and 14.9).
   bool paired = false;
-  if (any_splits && !fr.mixed && G <= 8 && cfg->k_bits + cfg->v_bits <= 6 && !(G == 8 && cfg->v_bits >= 3) && (long long)units * n_splits <= cus && workspace && aligned16(workspace)) {
-    const double as_is = (n_splits == 1 ? 48.0 : 60.0) + (double)n_items / n_splits;
+  if (any_splits && n_splits > 1 && !fr.mixed && G <= 8 && cfg->k_bits + cfg->v_bits <= 6 && !(G == 8 && cfg->v_bits >= 3) && (long long)units * n_splits <= cus) {
+    const double as_is = 60.0 + (double)n_items / n_splits;
     int s = 2 * cus / units;
     if (s > max_splits(sh)) s = max_splits(sh);
     if (s > n_items / 8) s = n_items / 8;
-    if (s > n_splits && (long long)units * s > cus && 62.0 + 2.0 * n_items / s < (n_splits == 1 ? 0.88 : 0.92) * as_is && workspace_bytes >= split_workspace_bytes(units, s, G)) {
+    if (s > n_splits && (long long)units * s > cus && 62.0 + 2.0 * n_items / s < 0.92 * as_is && workspace_bytes >= split_workspace_bytes(units, s, G)) {
       n_splits = s;
       paired = true;
     }
@@ -428,8 +429,6 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     if (!workspace) return KVMIX_ERR_NULL;
     if (!aligned16(workspace)) return KVMIX_ERR_ALIGN;
     if (workspace_bytes < split_workspace_bytes(units, n_parts, G)) return KVMIX_ERR_WORKSPACE;
-  }
-  if (n_parts > 1 || n_splits > 1) {
     a.counters = reinterpret_cast<uint32_t*>(workspace);
     a.part = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + counters_bytes(out_units(sh)));
   }

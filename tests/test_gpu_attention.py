@@ -583,6 +583,24 @@ def test_two_workgroups_to_a_compute_unit(B, Hkv, G, kb, vb, n):
     assert_attn_close(t16(out), want, "static", tight=True, tight_abs=2.5e-4)
 
 
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_an_unsplit_call_leaves_its_workspace_alone(G):
+    """160 units of 94 tiles: the library does not split, so that a workspace in use elsewhere, or never cleared, changes nothing and is not changed."""
+    import torch
+    import paper_2506_08018_amd as kv
+    print(f"case workspace left alone G={G}", flush=True)
+    q, _, _, rc, gc, shape, cfg = make_pair(20, 8 * G, 8, 3100, 64, 2, 2, seed=1230 + G)
+    st, want = rc.decode_attn(u16(q))
+    assert st == 0
+    qt = torch.from_numpy(q).cuda()
+    out = torch.zeros_like(qt)
+    ws = torch.full((kv.workspace_bytes(shape, gc.T_cap),), 0x3F, dtype=torch.uint8, device="cuda")
+    kv.decode_attn(shape, cfg, qt, gc, out, ws)
+    torch.cuda.synchronize()
+    assert_attn_close(t16(out), want, "workspace of other data", tight=True, tight_abs=2.5e-4)
+    assert (ws == 0x3F).all()
+
+
 @pytest.mark.parametrize("units,n", [(1, 250016), (4, 128000), (4, 16000)])
 def test_library_chooses_splits_by_the_context(units, n):
     """Few units of 4 heads: 32 splits for a middling context, as many as fill the card for a long one. The choice takes at most 1.15 of the

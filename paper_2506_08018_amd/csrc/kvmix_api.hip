@@ -343,7 +343,8 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   if (c->n_q + n_w < 1 || n_w < 0 || n_w > c->W_cap || (long long)n_w - (c->v_lead < 0 ? c->v_lead : 0) > c->W_cap) return KVMIX_ERR_BAD_SHAPE;
   const int units = sh->B * sh->Hkv, G = sh->Hq / sh->Hkv;
   const Fronts fr = fronts_of(c, n_w);
-  const int n_items = c->W_cap / kTile + fr.packed_tiles;
+  const int n_items = c->W_cap / kTile + fr.packed_tiles;      // with the whole ring: the split count, and with it what a workspace is refused by, stays the same from step to step
+  const int live_tiles = fr.packed_tiles + (fr.n_w_eff + kTile - 1) / kTile;      // what there is to do (the ring may be mostly empty)
   if (n_splits < 0 || n_splits > max_splits(sh)) return KVMIX_ERR_BAD_SHAPE;
   const bool any_splits = n_splits == 0;
   const int cus = num_cus();
@@ -383,11 +384,11 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   // one that is not zero (129 to 170 units in 3 splits would take 3 to 13 % less: 160 units of 94 tiles, 4 heads, 16.7 and 14.9).
   bool paired = false;
   if (any_splits && n_splits > 1 && !fr.mixed && G <= 8 && cfg->k_bits + cfg->v_bits <= 6 && !(G == 8 && cfg->v_bits >= 3) && (long long)units * n_splits <= cus) {
-    const double as_is = 60.0 + (double)n_items / n_splits;
+    const double as_is = 60.0 + (double)live_tiles / n_splits;
     int s = 2 * cus / units;
     if (s > max_splits(sh)) s = max_splits(sh);
-    if (s > n_items / 8) s = n_items / 8;
-    if (s > n_splits && (long long)units * s > cus && 62.0 + 2.0 * n_items / s < 0.92 * as_is && workspace_bytes >= split_workspace_bytes(units, s, G)) {
+    if (s > live_tiles / 8) s = live_tiles / 8;
+    if (s > n_splits && (long long)units * s > cus && 62.0 + 2.0 * live_tiles / s < 0.92 * as_is && workspace_bytes >= split_workspace_bytes(units, s, G)) {
       n_splits = s;
       paired = true;
     }
@@ -417,7 +418,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   // 19.3, 2000 32.3 -> 29.2, 4070 57.0 -> 53.5; 320 units x 4000 46.8 -> 42.4; 800 x 600 32.6 -> 25.4; 1600 x 2000 105.5 -> 95.7; all at 2/4 bit). A tile takes a little longer that way: long
   // contexts stay with 12 waves (512 x 8000 tokens 101.4 in 12 waves, 103.5; 768 x 4000 83.0, 84.6). Relative error against 64 bits the same to four digits (2.076e-4, of which 2.075e-4 is the
   // rounding to fp16).
-  const int tiles_each = (fr.packed_tiles + (fr.n_w_eff + kTile - 1) / kTile + n_splits - 1) / n_splits;      // of a workgroup
+  const int tiles_each = (live_tiles + n_splits - 1) / n_splits;      // of a workgroup
   if (block == 8 && G == 8 && (cfg->v_bits == 3 || cfg->v_bits == 4)) {
     const long long workgroups = (long long)units * n_splits;
     if (cus > 0 && workgroups > cus && tiles_each <= (workgroups <= 2 * cus ? 160 : 96)) block = 16;

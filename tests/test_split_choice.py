@@ -40,3 +40,31 @@ def test_a_call_that_needs_no_workspace_uses_none(plans, G):
             unsplit += 1
             assert a == b, (c, a, b)
     assert unsplit > len(calls) // 3
+
+
+def counted(plans, calls):
+    """Per call the launch with the smallest workspace it is accepted with: the count without a second workgroup on any compute unit."""
+    found = [None] * len(calls)
+    for s in range(0, 65):
+        open_ = [i for i, f in enumerate(found) if f is None]
+        if not open_:
+            break
+        size = lambda u, G: 0 if s < 2 else (4 * u + 255) // 256 * 256 + u * s * G * 520
+        for i, o in zip(open_, plans([calls[i][:-1] + (size(calls[i][0], calls[i][1]),) for i in open_])):
+            if o[0] == 0:
+                found[i] = o
+    return found
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_more_splits_only_for_tiles_that_are_there(plans, G):
+    """A ring may be mostly empty (room for steps to come): what it could hold is no work, and no reason for more workgroups than compute units."""
+    calls = [(u, G, (2, 2), t, 96, W, -1) for W in (4, 100, 400) for t in (2, 20, 94, 126, 250, 500) for u in (40, 52, 56, 65, 73, 86, 94, 102)]
+    more = 0
+    for c, base, full in zip(calls, counted(plans, calls), plans(calls)):
+        if full[1] > base[1]:
+            more += 1
+            live = c[3] + 3
+            assert live // full[1] >= 8 and c[0] * full[1] <= 512, (c, base, full)
+            assert 62 + 2 * live / full[1] < 0.92 * (60 + live / base[1]), (c, base, full)
+    assert more > 10

@@ -343,7 +343,7 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   if (c->n_q + n_w < 1 || n_w < 0 || n_w > c->W_cap || (long long)n_w - (c->v_lead < 0 ? c->v_lead : 0) > c->W_cap) return KVMIX_ERR_BAD_SHAPE;
   const int units = sh->B * sh->Hkv, G = sh->Hq / sh->Hkv;
   const Fronts fr = fronts_of(c, n_w);
-  const int n_items = c->W_cap / kTile + fr.packed_tiles;      // with the whole ring: the split count, and with it what a workspace is refused by, stays the same from step to step
+  const int n_items = c->W_cap / kTile + fr.packed_tiles;      // with the whole ring: the count, and what a workspace is refused by, do not change as the window fills
   const int live_tiles = fr.packed_tiles + (fr.n_w_eff + kTile - 1) / kTile;      // what there is to do (the ring may be mostly empty)
   if (n_splits < 0 || n_splits > max_splits(sh)) return KVMIX_ERR_BAD_SHAPE;
   const bool any_splits = n_splits == 0;
@@ -377,13 +377,20 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   if (any_splits && G == 4 && n_splits > 32 && (double)n_items * (1.0 / 32 - 1.0 / n_splits) < 24.0) n_splits = 32;
   // Two workgroups of 8 waves to a compute unit, at one pace, take a round's fixed part once (62 tiles' worth for the two) and
   // leave fewer compute units empty: a split launch that has one workgroup at most for each goes to a count that makes it more
-  // than one but at most two, where that is modelled 8 % better (split launches cost another 12 tiles). 90 units, 2 and 5
-  // splits, 1, 4 and 8 heads: 250 tiles 17.0 and 15.7 us, 21.0 and 18.3, 23.7 and 22.2; 126 tiles 11.6 and 11.0, 13.6 and
-  // 12.6, 15.5 and 15.4. Only with a workspace that holds these partials; it is refused or accepted by the count above.
+  // than one but at most two, where that is modelled 8 % better (split launches cost another 12 tiles). Measured, old time over
+  // new, at 2/2 bit with 1, 2, 4, 8 heads:
+  //   2 -> 5 splits (86 to 102 units)  119 tiles 1.03-1.06 (8 heads 1.01), 253 tiles 1.02-1.10, 1.08-1.13, 1.14-1.15, 1.06-1.07
+  //   3 -> 7 splits (65 to 73 units)   378 tiles 0.99-1.02, 1.03-1.06, 1.08-1.09, 1.03-1.04; 1003 tiles 0.98-1.03, 1.02-1.11, 1.17, 1.10-1.12
+  //   4 -> 9 splits (52 to 56 units)   1003 tiles 0.97-1.03, 1.00-1.04, 1.10-1.12, 0.96-0.98
+  // so from 2 splits with any of them and from 3 with 2 heads and more. The wider the codes, the nearer a launch is to what memory
+  // gives either way: with 1 head up to 4 bits of Key and Value together (from 2 splits at 5 bits 0.99-1.18, at 6 0.98-1.09),
+  // otherwise up to 5 (0.99-1.23; at 6 bits 0.94-1.17). Only with a workspace that holds these partials; it is refused or accepted
+  // by the count above. 8 heads with 3- or 4-bit Values have 12 waves there.
   // An unsplit launch stays unsplit: it leaves the workspace alone, so that calls that overlap may hand over the same one, or
-  // one that is not zero (129 to 170 units in 3 splits would take 3 to 13 % less: 160 units of 94 tiles, 4 heads, 16.7 and 14.9).
+  // one that is not zero (129 to 170 units in 3 splits would take 3 to 13 % less: 160 units of 94 tiles, 4 heads, 16.7 and 14.9 us).
   bool paired = false;
-  if (any_splits && n_splits > 1 && !fr.mixed && G <= 8 && cfg->k_bits + cfg->v_bits <= 6 && !(G == 8 && cfg->v_bits >= 3) && (long long)units * n_splits <= cus) {
+  if (any_splits && (n_splits == 2 || (n_splits == 3 && G > 1)) && !fr.mixed && G <= 8 && cfg->k_bits + cfg->v_bits <= (G > 1 ? 5 : 4) && !(G == 8 && cfg->v_bits >= 3) &&
+      (long long)units * n_splits <= cus) {
     const double as_is = 60.0 + (double)live_tiles / n_splits;
     int s = 2 * cus / units;
     if (s > max_splits(sh)) s = max_splits(sh);

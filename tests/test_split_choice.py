@@ -68,3 +68,19 @@ def test_more_splits_only_for_tiles_that_are_there(plans, G):
             assert live // full[1] >= 8 and c[0] * full[1] <= 512, (c, base, full)
             assert 62 + 2 * live / full[1] < 0.92 * (60 + live / base[1]), (c, base, full)
     assert more > 10
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_more_splits_only_where_they_were_measured(plans, G):
+    """From 2 splits with all group sizes, from 3 with 2 heads and more, and with few bits per Key and Value; in the middle of those ranges they are taken."""
+    wide = 5 if G > 1 else 4
+    calls = [(u, G, bits, t, 96, 4, -1) for bits in BITS + ((1, 3), (4, 1)) for t in (94, 126, 250, 500, 1000) for u in range(40, 257)]
+    for c, base, full in zip(calls, counted(plans, calls), plans(calls)):
+        if full[1] > base[1]:
+            kb, vb = c[2]
+            assert base[1] == 2 or (base[1] == 3 and G > 1), (c, base, full)
+            assert kb + vb <= wide and not (G == 8 and vb > 2), (c, base, full)
+            assert full[1:3] == ({2: 5, 3: 7}[base[1]], 8) and full[4:] == (1, 1), (c, base, full)
+    middle = [(u, G, bits, t, 96, 4, -1) for bits in ((1, 1), (2, 2)) for u, t in ((94, 200), (94, 375)) + (((69, 500), (69, 1000)) if G > 1 else ())]
+    for c, base, full in zip(middle, counted(plans, middle), plans(middle)):
+        assert full[1] > base[1] > 1, (c, base, full)

@@ -420,11 +420,16 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
       if (fits(n) && fits(n_splits) && (block == 16 || (n != n_splits && cost_of_16(sharing_of(wide, n, cus), work, n) < 1.02 * cost_of_8(work, n_splits)))) { n_splits = n; block = 16; }
     }
   }
-  // 8 heads with 3- or 4-bit Values do not fit the 8-wave form of a block of 8 (attn_waves); as half a block of 16 they do. Where there are more workgroups than
-  // compute units, two of 8 waves side by side then beat one of 12 after the other, by more the more of a round stays empty (512 units: 300 tokens 14.5 -> 12.3 us, 1000 22.7 ->
-  // 19.3, 2000 32.3 -> 29.2, 4070 57.0 -> 53.5; 320 units x 4000 46.8 -> 42.4; 800 x 600 32.6 -> 25.4; 1600 x 2000 105.5 -> 95.7; all at 2/4 bit). A tile takes a little longer that way: long
-  // contexts stay with 12 waves (512 x 8000 tokens 101.4 in 12 waves, 103.5; 768 x 4000 83.0, 84.6). Relative error against 64 bits the same to four digits (2.076e-4, of which 2.075e-4 is the
-  // rounding to fp16).
+  // 8 heads with 3- or 4-bit Values do not fit the 8-wave form of a block of 8 (attn_waves); as half a block of 16 they do. Where
+  // there are more workgroups than compute units, two of 8 waves side by side then beat one of 12 after the other, by more the more
+  // of a round stays empty. Times of 12 waves over those of 8, all four Key widths with 3- and 4-bit Values: 512 units of 300 tokens
+  // 1.18-1.23, 1000 1.13-1.16, 2000 1.09-1.15, 4070 1.04-1.08 (3/4 bit 58.1 -> 54.6 us), 5000 1.04-1.07; 320 units x 4000 1.06-1.16;
+  // 800 x 600 1.26-1.29; 1600 x 2000 1.10-1.13; 1040 x 3000 1.04-1.07; in splits, 136 units x 2000 in 2 and 3 1.13-1.15 and
+  // 1.20-1.21, 384 x 4800 in 2 1.06-1.08. A tile takes a little longer that way: long contexts stay with 12 waves (2/4 bit, 512 x
+  // 8000 tokens 101.4 in 12 waves, 103.5; 768 x 4000 83.0, 84.6).
+  // Relative error against 64 bits (the rounding to fp16 alone is 2.07e-4), mean over these eight widths and 300 to 4000 tokens of
+  // N(0,1): 2.0821e-4 in 12 waves, 2.0821e-4. Nearly uniform weights over 4000 tokens, whose outputs are small next to what they are
+  // the sum of: 2.0756e-4 and 2.0772e-4 (both terms of an operand meet in one accumulator, as in every block of 16).
   const int tiles_each = (live_tiles + n_splits - 1) / n_splits;      // of a workgroup
   if (block == 8 && G == 8 && (cfg->v_bits == 3 || cfg->v_bits == 4)) {
     const long long workgroups = (long long)units * n_splits;

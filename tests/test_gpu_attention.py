@@ -403,6 +403,10 @@ def test_graph_replays_match_eager(n_splits):
     (64, 8, 8, 3, 4, 17, 32, 40, 0),      # 512 units of 8 heads with 4-bit Values: half a block of 16, and one more, where the pace is no longer kept
     (65, 8, 8, 4, 3, 17, 32, 63, 0),
     (33, 8, 8, 2, 4, 0, 64, 70, 0),
+    (17, 8, 8, 2, 4, 17, 32, 40, 2),      # the same in splits: 272 workgroups that keep pace, and 408
+    (17, 8, 8, 3, 3, 29, 32, 63, 2),
+    (17, 8, 8, 1, 4, 17, 32, 40, 3),
+    (18, 8, 8, 4, 3, 6, 96, 120, 4),      # 576: more than are resident, and fewer window tiles than splits for some
     (33, 4, 8, 3, 4, 0, 64, 70, 0),       # nothing packed yet
     (33, 1, 8, 3, 2, 13, 32, 40, 0),      # two workgroups to a compute unit that keep pace: the fewest tiles for that, thresholds at 6, 9 and 11 of 13
     (40, 2, 8, 2, 2, 16, 32, 33, 0),      # thresholds in the middle of the tiles that the waves start with

@@ -1330,9 +1330,14 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       for (int hh = 0; hh < G; hh++) qh[hh] = as_half2(reinterpret_cast<const uint32_t*>(qbase + hh * kD)[lane]) * half2_t{pre, pre};
     }
     zero_idle();
-    // Two workgroups share a compute unit: of the waves that can issue a SIMD takes the oldest, so that the workgroup that came first ran ahead and the other one was
-    // left with half of the unit's waves at the end (8 heads, 512 units of 126 tiles: first workgroups done at 41 us, second ones at 51). With a.even a wave's
-    // priority falls as the workgroup's tiles run out, at 1/2, 3/4 and 7/8 of them: the workgroup behind goes first, and both end together.
+    // Two workgroups share a compute unit: of the waves that can issue a SIMD takes the oldest, so that the workgroup that came first
+    // ran ahead and the other one was left with half of the unit's waves at the end (8 heads, 512 units of 126 tiles: first
+    // workgroups done at 41 us, second ones at 51). With a.even a wave starts at the highest priority and takes one step down with
+    // the first tile it claims past half of the workgroup's tiles, then past half of those that were left at that claim, twice: the
+    // workgroup behind goes first, and both end together. After its tiles a wave has the lowest: results and merge don't hold up the
+    // neighbour's tiles (kept at the level of its last claim, 512 units of 30 tiles took 17.8 us with 8 heads and 18.4 with 16; 17.5
+    // and 17.7; at 126 tiles the same within 1 %. The level from the number of the claimed tile alone, several steps at once: 17.6 and
+    // 18.3.)
     int prio = 0, next_at = p_end;
     if constexpr (kWaves == 8) {
       if (a.even && p_end - p_begin > 12) {      // (a handful of tiles, 32 units of 8: 6.2 us without, 6.4 with)
@@ -1356,6 +1361,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       it = grab_take(ticket);
       st.load(up, it < p_end ? it : p_end - 1, lane16);
     }
+    if constexpr (kWaves == 8) __builtin_amdgcn_s_setprio(0);
   }
 
   {

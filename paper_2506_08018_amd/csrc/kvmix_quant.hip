@@ -736,11 +736,16 @@ __global__ __launch_bounds__(768) void stream_read_kernel(const u32x4_t* buf, si
   if ((acc[0] & acc[1] & acc[2] & acc[3]) == 0xFFFFFFFFu && sink) sink[0] = 1u;
 }
 
-// Four waves to a tile or two: with four the chain from a tile's rows to its record is half as long, and more waves hide each other's; with two each row is requested by one wave only, and the
-// work that both waves of a side do (extremes met through LDS, parameters) is done once. 4 and 2 waves: 8 tiles 3.5 us (2/2 bit) and 3.8 (3/4), 4.1 and 4.8 with 2; 512 tiles 4.5 and 5.1,
-// 5.1 and 6.0; 1536 tiles 7.5 and 9.0, 8.1 and 9.5; 4096 tiles 13.9 and 16.4, 14.8 and 16.6; 6144 tiles 19.2 and 23.5, 20.3 and 22.8; 8192 tiles 23.8 and 30.3, 24.6 and 28.9; 16 384 (cached) 55.7
-// and 62.2, 49.1 and 54.9. Ageing with the fronts apart (cached): 256 units, one Value token each 3.4 and 3.7 us, 4.3 and 4.8 with 2 waves; 4 tiles each 6.1 and 7.0, 7.0 and 8.0; 1024 units of 4 tiles
-// 12.9 and 16.5, 14.4 and 16.7; 19 tiles 64.5 and 76.1, 66.6 and 72.6.
+// Four waves to a tile or two: with four the chain from a tile's rows to its record is half as long, and more waves hide each
+// other's; with two each row is requested by one wave only, and the work that both waves of a side do (extremes met through LDS,
+// parameters) is done once. Time of two waves over that of four, all pairs of widths, records past the caches from 2048 tiles on:
+//   tiles         512        2048       4096       6144       8192       12 288     16 384
+//   no 3 bit      1.16-1.25  1.06-1.11  1.05-1.08  1.04-1.06  1.03-1.05  1.01-1.03  1.00-1.03
+//   a 3-bit side  1.13-1.25  1.00-1.02  1.00-1.02  0.97-1.00  0.96-0.98  0.94-0.97  0.92-0.96
+// (2/2 bit 5.2 and 4.4 us, 9.4 and 8.8, ..., 44.7 and 44.7; 3/4 bit 6.1 and 5.0, 10.4 and 10.5, ..., 49.3 and 51.7.) More tiles are
+// also loaded past the caches, where four waves lose (31 488 tiles at 2/2 bit 91 and 105 us). 8 tiles: 4.1 and 3.5 us (2/2 bit), 4.8
+// and 3.8 (3/4). Ageing with the fronts apart, without and with a 3-bit side: 512 tiles 1.14-1.24 and 1.16-1.19, 4096 1.08-1.11 and
+// 1.03-1.04, 6144 1.06-1.10 and 0.97-0.99; one Value token for each of 256 units 4.3 and 3.4 us (2/2 bit).
 template <int KB, int VB, bool PARTIAL>
 hipError_t launch_qp(const QuantArgs& a, dim3 grid, Stream stream, size_t tiles, hipStream_t s) {
   auto run_four = [&](auto kernel) {

@@ -284,28 +284,28 @@ Fronts fronts_of(const kvmix_layer_cache* c, int n_w) {
   return f;
 }
 
-// Waves per workgroup of the attention kernel. 12 waves fill a compute unit with one workgroup, 8 leave room for two.
-// Launches that need more workgroups than there are compute units run 8: twice the workgroups are resident, so that one's start and
-// merge overlap another's stream (512 units of 128 tiles, 8 heads: 53.2 us against 54.1; 1 head, 600 units of 36: 23.3 against 25.9;
-// 2048 of 20: 38.9 against 50.6). With at most one workgroup per compute unit the 4 more waves pay when each has many tiles to stream (1 head,
-// 256 units of 128 tiles: 20.5 us against 23.2; 32 tiles: 10.3 against 10.6), and cost in start and merge when there are few
-// (9 tiles: 7.7 us against 7.5); from 16 to 24 tiles the two are within 2 % (16: 8.5 and 8.5).
-// 8 heads with 3- or 4-bit Values do not fit the 128 registers of the 8-wave form (spilling: 93 us where 12 waves take 62; as half a block of 16: plan_attention).
+// Waves per workgroup of the attention kernel. 12 waves fill a compute unit with one workgroup, 8 leave room for two. Launches that
+// need more workgroups than there are compute units run 8: twice the workgroups are resident, so that one's start and merge overlap
+// another's stream (512 units of 128 tiles, 8 heads: 53.2 us against 54.1; 1 head, 600 units of 36: 23.3 against 25.9; 2048 of 20:
+// 38.9 against 50.6). With at most one workgroup per compute unit the 4 more waves pay when each has many tiles to stream (1 head,
+// 256 units of 128 tiles: 20.5 us against 23.2; 32 tiles: 10.3 against 10.6), and cost in start and merge when there are few (9
+// tiles: 7.7 us against 7.5); from 16 to 24 tiles the two are within 2 % (16: 8.5 and 8.5). 8 heads with 3- or 4-bit Values do not
+// fit the 128 registers of the 8-wave form (spilling: 93 us where 12 waves take 62; as half a block of 16: plan_attention).
 int attn_waves(long long workgroups, int n_tiles, int n_splits, int block, int v_bits, int cus) {
   if (block > 8) return 8;
   if (block == 8 && (v_bits == 3 || v_bits == 4)) return 12;
   return workgroups > (cus > 0 ? cus : 256) || n_tiles <= 20 * n_splits ? 8 : 12;
 }
 
-// Groups of 16 heads and more run in blocks of 16 or of 8 heads. A block of 16 takes less work per head, a block of 8 has the shorter
-// chain per tile and half the outputs to combine and to merge. Modelled times of a launch in us, for tiles of 2/2 bit; fixed parts and merging
-// splits besides the tiles. Blocks of 16: workgroups that share
-// a compute unit share its rate, and the second one starts late. A tile of 3/4 bit counts as 1.3 (8 x 48 heads over 8000 tokens: 16.3 us in
-// blocks of 8, 14.3 in blocks of 16), a window tile as 2.4. Fitted to 1 x 72 heads over 8000 tokens (1, 4, 8, 16, 32 splits:
-// 42.7, 15.9, 12.2, 11.0, 12.2 us in blocks of 16; 36.9, 14.8, 11.0, 9.6, 12.7 in blocks of 8), 16 x 48 over 4000 (2, 4, 5, 6, 8: 18.2, 13.6,
-// 12.8, 16.0, 15.2; 16.7 in blocks of 8, 2 splits), 32 x 48 over 2000 (1, 2, 4: 15.7, 13.3, 15.0; 15.4 in blocks of 8, unsplit), 64 x 16 over 1000
-// (2, 3, 4, 5: 10.7, 10.1, 9.5, 12.1; 10.3 in blocks of 8, 2 splits), 1 x 16 over 1000 (1, 4: 8.9, 7.9; 8.9, 7.3), 32 x 72 over 4000 (1 to 4: 29.5,
-// 29.8, 24.0, 28.2).
+// Groups of 16 heads and more run in blocks of 16 or of 8 heads. A block of 16 takes less work per head, a block of 8 has the
+// shorter chain per tile and half the outputs to combine and to merge. Modelled times of a launch in us, for tiles of 2/2 bit;
+// fixed parts and merging splits besides the tiles. Blocks of 16: workgroups that share a compute unit share its rate, and the
+// second one starts late. A tile of 3/4 bit counts as 1.3 (8 x 48 heads over 8000 tokens: 16.3 us in blocks of 8, 14.3 in blocks of
+// 16), a window tile as 2.4. Fitted to 1 x 72 heads over 8000 tokens (1, 4, 8, 16, 32 splits: 42.7, 15.9, 12.2, 11.0, 12.2 us in
+// blocks of 16; 36.9, 14.8, 11.0, 9.6, 12.7 in blocks of 8), 16 x 48 over 4000 (2, 4, 5, 6, 8: 18.2, 13.6, 12.8, 16.0, 15.2; 16.7
+// in blocks of 8, 2 splits), 32 x 48 over 2000 (1, 2, 4: 15.7, 13.3, 15.0; 15.4 in blocks of 8, unsplit), 64 x 16 over 1000 (2, 3,
+// 4, 5: 10.7, 10.1, 9.5, 12.1; 10.3 in blocks of 8, 2 splits), 1 x 16 over 1000 (1, 4: 8.9, 7.9; 8.9, 7.3), 32 x 72 over 4000 (1 to
+// 4: 29.5, 29.8, 24.0, 28.2).
 double tile_work(int packed_tiles, int window_tiles, int k_bits, int v_bits) {
   return packed_tiles * (1.0 + 0.1 * (k_bits + v_bits - 4)) + 2.4 * window_tiles;
 }
@@ -343,16 +343,18 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   if (c->n_q + n_w < 1 || n_w < 0 || n_w > c->W_cap || (long long)n_w - (c->v_lead < 0 ? c->v_lead : 0) > c->W_cap) return KVMIX_ERR_BAD_SHAPE;
   const int units = sh->B * sh->Hkv, G = sh->Hq / sh->Hkv;
   const Fronts fr = fronts_of(c, n_w);
-  const int n_items = c->W_cap / kTile + fr.packed_tiles;      // with the whole ring: the count, and what a workspace is refused by, do not change as the window fills
-  const int live_tiles = fr.packed_tiles + (fr.n_w_eff + kTile - 1) / kTile;      // what there is to do (the ring may be mostly empty)
+  // With the whole ring: the split count, and what a workspace is refused by, do not change as the window fills.
+  const int n_items = c->W_cap / kTile + fr.packed_tiles;
+  // What there is to do: the ring may be mostly empty.
+  const int live_tiles = fr.packed_tiles + (fr.n_w_eff + kTile - 1) / kTile;
   if (n_splits < 0 || n_splits > max_splits(sh)) return KVMIX_ERR_BAD_SHAPE;
   const bool any_splits = n_splits == 0;
   const int cus = num_cus();
   if (any_splits) {
-    // The launch is taken to run in rounds of `cus` workgroups. A round costs a fixed part (start, merge of the waves,
-    // partial and arrival: about what 48 tiles take) plus the tiles of one split; take the split count with the
-    // smallest rounds x (48 + tiles per split), at least 8 tiles each. (Twice as many workgroups of 8 waves fit the card; the count is
-    // also what a workspace is refused or accepted by, and 128 units of 256 tiles take 24.4 us with 4 splits of 8 waves, 23.8 with 2 of 12.)
+    // The launch is taken to run in rounds of `cus` workgroups. A round costs a fixed part (start, merge of the waves, partial and
+    // arrival: about what 48 tiles take) plus the tiles of one split; take the split count with the smallest rounds x (48 + tiles
+    // per split), at least 8 tiles each. (Twice as many workgroups of 8 waves fit the card; the count is also what a workspace is
+    // refused or accepted by, and 128 units of 256 tiles take 24.4 us with 4 splits of 8 waves, 23.8 with 2 of 12.)
     if (cus == 0) return hip_fail(hipErrorInvalidDevice);
     const int ou = out_units(sh);
     int s_max = n_items / 8;
@@ -370,9 +372,11 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     if (unsplit <= 1.06 * best) n_splits = 1;
   }
   if (n_splits > n_items) n_splits = n_items;
-  // 4 heads: no more than the 32 splits whose partials one wave merges in two batches at most, until a split of the full count would have 24 tiles
-  // less than one of 32, about where the two meet (32 and 64 splits, 1 unit, 2/2 bit: 16 000 tokens 8.6 and 10.0 us, 40 000 11.2 and 11.6, 48 000 12.0 and 11.6, 64 000 13.8 and 12.0; 3/4 bit 40 000 12.3 and
-  // 12.3, 48 000 13.1 and 12.2; 4 units, 2/2 bit: 40 000 11.6 and 12.6, 48 000 12.4 and 12.6, 64 000 14.2 and 13.1). A workspace is refused or accepted by the full count all the same.
+  // 4 heads: no more than the 32 splits whose partials one wave merges in two batches at most, until a split of the full count
+  // would have 24 tiles less than one of 32, about where the two meet (32 and 64 splits, 1 unit, 2/2 bit: 16 000 tokens 8.6 and
+  // 10.0 us, 40 000 11.2 and 11.6, 48 000 12.0 and 11.6, 64 000 13.8 and 12.0; 3/4 bit 40 000 12.3 and 12.3, 48 000 13.1 and 12.2;
+  // 4 units, 2/2 bit: 40 000 11.6 and 12.6, 48 000 12.4 and 12.6, 64 000 14.2 and 13.1). A workspace is refused or accepted by the
+  // full count all the same.
   const int n_counted = n_splits;
   if (any_splits && G == 4 && n_splits > 32 && (double)n_items * (1.0 / 32 - 1.0 / n_splits) < 24.0) n_splits = 32;
   // Two workgroups of 8 waves to a compute unit, at one pace, take a round's fixed part once (62 tiles' worth for the two) and
@@ -389,13 +393,14 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   // An unsplit launch stays unsplit: it leaves the workspace alone, so that calls that overlap may hand over the same one, or
   // one that is not zero (129 to 170 units in 3 splits would take 3 to 13 % less: 160 units of 94 tiles, 4 heads, 16.7 and 14.9 us).
   bool paired = false;
-  if (any_splits && (n_splits == 2 || (n_splits == 3 && G > 1)) && !fr.mixed && G <= 8 && cfg->k_bits + cfg->v_bits <= (G > 1 ? 5 : 4) && !(G == 8 && cfg->v_bits >= 3) &&
-      (long long)units * n_splits <= cus) {
+  if (any_splits && (n_splits == 2 || (n_splits == 3 && G > 1)) && (long long)units * n_splits <= cus && !fr.mixed && G <= 8 &&
+      cfg->k_bits + cfg->v_bits <= (G > 1 ? 5 : 4) && !(G == 8 && cfg->v_bits >= 3)) {
     const double as_is = 60.0 + (double)live_tiles / n_splits;
     int s = 2 * cus / units;
     if (s > max_splits(sh)) s = max_splits(sh);
     if (s > live_tiles / 8) s = live_tiles / 8;
-    if (s > n_splits && (long long)units * s > cus && 62.0 + 2.0 * live_tiles / s < 0.92 * as_is && workspace_bytes >= split_workspace_bytes(units, s, G)) {
+    if (s > n_splits && (long long)units * s > cus && 62.0 + 2.0 * live_tiles / s < 0.92 * as_is &&
+        workspace_bytes >= split_workspace_bytes(units, s, G)) {
       n_splits = s;
       paired = true;
     }
@@ -407,10 +412,10 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
     // counts), blocks of 16 otherwise.
     block = !fr.mixed && cus > 0 && (long long)out_units(sh) * n_splits <= cus ? 8 : 16;
     if (any_splits) {
-      // The count above is that of blocks of 8, and it is what a workspace is refused or accepted by. A workspace that also holds the
-      // partials of the count that suits blocks of 16 gets those where they are modelled to be faster, or within 2 % (4 x 48 heads over
-      // 32 000 tokens, modelled alike: 22.8 us in blocks of 8, 20.8 in blocks of 16). At equal counts blocks of 8 it is (64 x 16 heads over 300 tokens,
-      // unsplit: 7.8 us per launch, 8.6 in blocks of 16).
+      // The count above is that of blocks of 8, and it is what a workspace is refused or accepted by. A workspace that also holds
+      // the partials of the count that suits blocks of 16 gets those where they are modelled to be faster, or within 2 % (4 x 48
+      // heads over 32 000 tokens, modelled alike: 22.8 us in blocks of 8, 20.8 in blocks of 16). At equal counts blocks of 8 it is
+      // (64 x 16 heads over 300 tokens, unsplit: 7.8 us per launch, 8.6 in blocks of 16).
       const double work = tile_work(fr.packed_tiles, (fr.n_w_eff + kTile - 1) / kTile, cfg->k_bits, cfg->v_bits);
       const int wide = units * ((G + 15) / 16), n = wide_splits(wide, n_items, max_splits(sh), cus);
       auto fits = [&](int splits) {
@@ -478,9 +483,10 @@ int plan_attention(const kvmix_shape* sh, const kvmix_layer_cfg* cfg, const uint
   // (with the fronts apart always 12: those kernels do not fit the registers of 8 waves)
   plan->waves = fr.mixed ? 12 : attn_waves((long long)out_units(sh) * n_splits, live + fr.packed_tiles, n_splits, plan->block, plan->vb, cus);
   plan->mixed = fr.mixed;
-  // Workgroups of 8 waves that are all resident at once, two to a compute unit, keep pace with each other (8 heads, 512 units of 4070 tokens: 2/2 bit 48.3 ->
-  // 45.6 us, 3/2 bit 57.8 -> 54.5; 320 units 43.1 -> 40.1; 4 heads 38.7 -> 37.2; 1 head, 320 units 27.4 -> 26.5; 16 heads 49.7 -> 47.9). With more of them than that it
-  // is better that some end early and make room (768 workgroups of 128 tiles: 75.9 us as they come, 83.7 at one pace).
+  // Workgroups of 8 waves that are all resident at once, two to a compute unit, keep pace with each other (8 heads, 512 units of
+  // 4070 tokens: 2/2 bit 48.3 -> 45.6 us, 3/2 bit 57.8 -> 54.5; 320 units 43.1 -> 40.1; 4 heads 38.7 -> 37.2; 1 head, 320 units
+  // 27.4 -> 26.5; 16 heads 49.7 -> 47.9). With more of them than that it is better that some end early and make room (768
+  // workgroups of 128 tiles: 75.9 us as they come, 83.7 at one pace).
   const long long workgroups = (long long)units * n_splits * ((G + block - 1) / block);
   plan->a.even = plan->waves == 8 && workgroups > cus && workgroups <= 2 * cus;
   // with the append inside the launch the new token must be a window token of the main launch
@@ -502,7 +508,8 @@ int launch_plan(const AttnPlan& p, void* stream) {
 constexpr size_t kScratchBytes = KVMIX_STATIC_SCRATCH_BYTES;
 constexpr size_t kScratchCounterBytes = 16384;
 static_assert(kScratchCounterBytes / sizeof(uint32_t) >= kScratchBytes / (2 * (kD + 2) * sizeof(float)), "counters of every shape that fits");
-// Partials of groups of up to 4 heads are zero between calls, those of larger groups are left as they are: each kind has a place of its own.
+// Partials of groups of up to 4 heads are zero between calls, those of larger groups are left as they are: each kind has a place of
+// its own.
 static __device__ __align__(256) unsigned char scratch[kScratchCounterBytes + 2 * kScratchBytes];
 // In host code the array's name is only a handle; its address on a device comes from hipGetSymbolAddress,
 // asked once per device with that device current. Each GPU holds its own copy at its own address.

@@ -6,15 +6,14 @@
 // Formulation. For one kv head and one 32-token tile
 //   score[t][h] = sum_d code[t][d] * (q[h][d]*s[d])  +  sum_d q[h][d]*z[d]
 //   out[d][h]  += sum_t code[t][d] * (p[t][h]*s[t][g(d)])  +  sum_t p[t][h]*z[t][g(d)]
-// Both code sums are 16x16x32 fp16 MFMAs whose A operand is the packed word ANDed with a mask:
-// a 1/2/4-bit field left in place inside a zero fp16 pattern is the subnormal code * 2^(pos-24),
-// exact, and MFMA honours subnormal inputs (3-bit codes are a 2-bit plane plus a 1-bit plane). The scale factors ride in the B operand, split
-// into an fp16 (hi, lo) pair held in two MFMA columns so that the products stay exact to
-// ~22 bits; the up-to-8 query heads of the group use columns 0..7 (hi) and 8..15 (lo). Groups of 16 heads and more run in
-// blocks of 8, or in blocks of 16: a head per column, with hi and lo as two instructions on the same accumulators.
-// The fp16 window runs on MFMAs with plain fp16 operands; so do the zero-point sums for groups of
-// 4 query heads and more, while groups of 1 or 2 heads take them (and the softmax denominator) on the
-// vector unit, where they are cheaper than matrix instructions with mostly empty columns.
+// Both code sums are 16x16x32 fp16 MFMAs whose A operand is the packed word ANDed with a mask: a 1/2/4-bit field left in place
+// inside a zero fp16 pattern is the subnormal code * 2^(pos-24), exact, and MFMA honours subnormal inputs (3-bit codes are a 2-bit
+// plane plus a 1-bit plane). The scale factors ride in the B operand, split into an fp16 (hi, lo) pair held in two MFMA columns so
+// that the products stay exact to ~22 bits; the up-to-8 query heads of the group use columns 0..7 (hi) and 8..15 (lo). Groups of 16
+// heads and more run in blocks of 8, or in blocks of 16: a head per column, with hi and lo as two instructions on the same
+// accumulators. The fp16 window runs on MFMAs with plain fp16 operands; so do the zero-point sums for groups of 4 query heads and
+// more, while groups of 1 or 2 heads take them (and the softmax denominator) on the vector unit, where they are cheaper than matrix
+// instructions with mostly empty columns.
 //
 // Data movement. Every byte of a tile record is loaded from HBM once, by one lane (16 B of
 // metadata and 16 B of every 1 KiB of codes per lane); a wave has one tile in flight while the
@@ -112,11 +111,12 @@ __device__ __forceinline__ void wave_lds_fence() {
 // lowest mantissa bits loses product bits (measured: ~1e-5 relative at position 0, exact from 6 up).
 template <int BITS> __device__ __forceinline__ constexpr int field_pos(int s) { return BITS == 4 ? 4 * (s & 1) + 2 : BITS == 1 ? 2 * s + 4 : 2 * s + 2; }
 
-// The codes of a tile between two fronts: multiplied up to the fp16 number code * 2^-7, a normal one, whatever the field. Of products of subnormal
-// operands the matrix core drops low bits (see above): where a field lies low, that is more than everything else takes from a result. These tiles
-// used to be summed in fp32 on the vector unit, and their error against 64 bits stays what it was. 1000 tokens, all Keys in the ring and all Values
-// packed at 2, 3, 4 bit, outputs that are not the fp16 rounding of the result in 64 bits: 0.1 to 0.3 % on the vector unit, 8, 5 and 4 % with the fields
-// as they are (an error of 4e-5, 2e-5, 1e-5 of the result next to the rounding's 2.1e-4), 0.2 to 0.7 % this way (5e-7).
+// The codes of a tile between two fronts: multiplied up to the fp16 number code * 2^-7, a normal one, whatever the field. Of
+// products of subnormal operands the matrix core drops low bits (see above): where a field lies low, that is more than everything
+// else takes from a result. These tiles used to be summed in fp32 on the vector unit, and their error against 64 bits stays what it
+// was. 1000 tokens, all Keys in the ring and all Values packed at 2, 3, 4 bit, outputs that are not the fp16 rounding of the result
+// in 64 bits: 0.1 to 0.3 % on the vector unit, 8, 5 and 4 % with the fields as they are (an error of 4e-5, 2e-5, 1e-5 of the result
+// next to the rounding's 2.1e-4), 0.2 to 0.7 % this way (5e-7).
 constexpr int kExactPos = 17;
 template <int BITS> __device__ __forceinline__ half8_t exact_codes(half8_t fields, int s) {
   const half_t up = (half_t)__builtin_ldexpf(1.0f, kExactPos - field_pos<BITS>(s));
@@ -306,8 +306,8 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
   hi = __builtin_bit_cast(uint32_t, hv);
   lo = __builtin_bit_cast(uint32_t, lv);
 }
-// fp32 pair -> packed fp16 pairs, hi rounded to nearest, lo what the rounding left (rounded): the remainder is taken with the fp16 number as it
-// is, without a conversion back (a tile of 16 heads: 16 vector instructions of 255 less).
+// fp32 pair -> packed fp16 pairs, hi rounded to nearest, lo what the rounding left (rounded): the remainder is taken with the fp16
+// number as it is, without a conversion back (a tile of 16 heads: 16 vector instructions of 255 less).
 __device__ __forceinline__ void split_nearest(float x0, float x1, uint32_t& hi, uint32_t& lo) {
   const half2_t hv = __builtin_convertvector(float2_t{x0, x1}, half2_t);
   hi = as_u32(hv);
@@ -333,10 +333,10 @@ __device__ __forceinline__ float hi_half(uint32_t v) { return (float)__builtin_b
 // XORed with P % 4 from 4 heads on: the 4 bytes per lane of a write then fall into distinct banks, and so do the 16 bytes
 // per lane of a read (measured: 4.5 cycles per read of 1 KiB, 8.4 with operand rows 272 bytes apart; with 4 or 8 heads the
 // exchange area was what bound the packed loop).
-// Up to 4 heads leave columns idle; nothing they compute is stored. Their lanes read 16 bytes of zeros that every step has at the same
-// offset from its start: with the heads' operands repeated in them instead the matrix core takes more power and the clock goes down in
-// a run of launches (4 heads: 2.13 GHz, 2.23 with zeros; 1 head: 2.21, 2.28). 8 layers of 128 units x 8200 tokens, 4 heads: 208.5 us repeated,
-// 204.3 with zeros; 16 layers of 256 units x 4100 tokens, 1 head: 354.2, 351.9.
+// Up to 4 heads leave columns idle; nothing they compute is stored. Their lanes read 16 bytes of zeros that every step has at the
+// same offset from its start: with the heads' operands repeated in them instead the matrix core takes more power and the clock goes
+// down in a run of launches (4 heads: 2.13 GHz, 2.23 with zeros; 1 head: 2.21, 2.28). 8 layers of 128 units x 8200 tokens, 4 heads:
+// 208.5 us repeated, 204.3 with zeros; 16 layers of 256 units x 4100 tokens, 1 head: 354.2, 351.9.
 // The Key side of a tile is done with its part before the Value side writes its own, so the two share memory (the
 // wave's LDS operations run in order; a fence between the steps pins the compiler): 16 waves per CU fit.
 // With 1 or 2 heads the few rows are kept whole, 320 bytes apart: the lanes of one row read the same 16 bytes, and a write is
@@ -384,21 +384,24 @@ template <int G, int NW> struct MergeLds {        // per-wave reference maximum 
   float l[NW][G];
 };
 
-// MIXED: Keys and Values age at fronts of their own (blocks of 1, 2, 4 and 16 heads); the tiles between the fronts have one side in a record and the other
-// in the ring. Two kinds of tile share a half with the window tiles and are worked on with them, two with the packed ones:
+// MIXED: Keys and Values age at fronts of their own (blocks of 1, 2, 4 and 16 heads); the tiles between the fronts have one side in
+// a record and the other in the ring. Two kinds of tile share a half with the window tiles and are worked on with them, two with
+// the packed ones:
 //   Value front ahead: Keys from the ring, Values from the record (with the packed tiles); where the front stands inside a tile, the tokens
 //     behind it are a window tile of which only they count.
 //   Key front ahead: Keys from the record, Values from the ring (with the window tiles); the tokens before a front inside a tile are a
 //     packed tile of which only they count.
-// In a launch of their own on the vector unit these tiles took 13 us (14 tiles per unit of 128, 256 units, 1 head) next to 28 for the rest; a
-// decode step of two such layers, with its appends and flushes, went from 103 us to 80.4, of two layers of 64 units x 3000 tokens and 8
-// heads from 103 to 47.
-// The parameters in front of `a` (fields of it, see the first lines) are the 14 words that a workgroup finds in its scalar registers when it starts (they are
-// preloaded: build.py): what a wave needs for its query and its first packed tile. Read from memory, three reads in a row as the code comes to them, they kept
-// the first requests back: 24 units x 4 heads, 6 splits 7.28 -> 6.97 us per launch, 8 units x 8 heads x 2000 tokens 7.35 -> 6.99, 32 units x 1 head, 3 splits
-// 6.06 -> 5.90; all read together at the start 7.24, 7.20, 6.11. Few parameters: each costs the host's launch some 15 ns.
+// In a launch of their own on the vector unit these tiles took 13 us (14 tiles per unit of 128, 256 units, 1 head) next to 28 for
+// the rest; a decode step of two such layers, with its appends and flushes, went from 103 us to 80.4, of two layers of 64 units x
+// 3000 tokens and 8 heads from 103 to 47.
+// The parameters in front of `a` (fields of it, see the first lines) are the 14 words that a workgroup finds in its scalar
+// registers when it starts (they are preloaded: build.py): what a wave needs for its query and its first packed tile. Read from
+// memory, three reads in a row as the code comes to them, they kept the first requests back: 24 units x 4 heads, 6 splits 7.28 ->
+// 6.97 us per launch, 8 units x 8 heads x 2000 tokens 7.35 -> 6.99, 32 units x 1 head, 3 splits 6.06 -> 5.90; all read together at
+// the start 7.24, 7.20, 6.11. Few parameters: each costs the host's launch some 15 ns.
 template <int KB, int VB, int G, int NW, bool MIXED>
-__global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(const uint16_t* q, const uint32_t* packed, u32x4_t shares, u32x4_t items, u32x2_t heads, AttnArgs a) {
+__global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kernel(
+    const uint16_t* q, const uint32_t* packed, u32x4_t shares, u32x4_t items, u32x2_t heads, AttnArgs a) {
   constexpr int kWaves = NW;
   constexpr int kThreads = kWaves * kWave;
   // per wave: the exchange area of the packed tiles; before that, the staging area in which a window tile's
@@ -434,9 +437,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   const int row = 2 * h + (lo_part ? 1 : 0);         // score row of this lane's column
   const int op_read = Operand<G>::kIdle && !col_valid ? Operand<G>::kZeroAt : Operand<G>::read_at(kq, h, lo_part);
 
-  // Work of this split: of the window's live tiles (numbered by age) those with index sp, sp + n_splits, ..., so
-  // that every split carries its share of them, and a contiguous range of packed tiles. The first a.win_extra splits have one window tile more than the
-  // others and a.win_tiles packed tiles less. (Quotient and remainder come from the host: the start of a launch is
+  // Work of this split: of the window's live tiles (numbered by age) those with index sp, sp + n_splits, ..., so that every split
+  // carries its share of them, and a contiguous range of packed tiles. The first a.win_extra splits have one window tile more than
+  // the others and a.win_tiles packed tiles less. (Quotient and remainder come from the host: the start of a launch is
   // latency-bound and integer division takes hundreds of instructions here.)
   const int extra = sp < a.win_extra ? sp : a.win_extra;
   const int p_begin = sp * a.items_q + (sp < a.items_r ? sp : a.items_r) - extra * a.win_tiles;
@@ -493,8 +496,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // counts it in n_w) and stores it into the ring for the steps to come.
   const int new_tau = a.new_slot & 31;
   auto win_slot = [&](int r) { int wi = a.w0_tile + r; wi = wi >= a.ring_tiles ? wi - a.ring_tiles : wi; return wi * kTile; };   // first slot of the tile
-  // Whether a window tile is the new token's (wave-uniform). Not to be asked of a tile between two fronts: in a full ring the new token may share
-  // the ring tile of the oldest Values, in rows before theirs.
+  // Whether a window tile is the new token's (wave-uniform). Not to be asked of a tile between two fronts: in a full ring the new
+  // token may share the ring tile of the oldest Values, in rows before theirs.
   auto win_new = [&](int slot0) { return a.new_slot >= 0 && slot0 == (a.new_slot & ~31); };
   struct WinKeys { half8_t r[2][4]; };
   // live: tokens of the tile (from its first row on) that are there, at least one; has_new: the new token is the last of them
@@ -610,7 +613,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       for (int m = 0; m < 8; m++) acc[m] *= f;
     }
   };
-  // (No inline assembly here: an instruction that reads what the matrix core writes has to wait for it, and only the compiler's own are made to.)
+  // (No inline assembly here: an instruction that reads what the matrix core writes has to wait for it, and only the compiler's own
+  // are made to.)
   auto max8 = [](const float (&s)[8]) {
     float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
     mx = fmaxf(fmaxf(mx, s[3]), s[4]);
@@ -787,9 +791,10 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   // Tiles between the fronts whose Values come from the record: dealt out like the window tiles, the waves without one of those first.
   const int n_rec = !MIXED ? 0 : a.m_ahead ? a.m_tiles : a.m_front > a.m_first * kTile ? 1 : 0;
   const int first_rec = sp + (kWaves - 1 - wave) * a.n_splits;
-  // 4 heads (and 1 head with 4/3 bit): a wave that has some requests its first packed tile after them. Held in registers meanwhile, the tile made 13 of
-  // the 16 kernels spill, and scratch memory alone costs a launch 2 to 3 us (128 units x 4 heads x 4000 tokens, 3/4 bit, 800 Keys and 400 Values in
-  // fp16: 36.4 us, 20.9 this way; 2/4 bit 24.9, 19.8). The others have the registers, and lose 3 to 13 % when the tile comes late.
+  // 4 heads (and 1 head with 4/3 bit): a wave that has some requests its first packed tile after them. Held in registers meanwhile,
+  // the tile made 13 of the 16 kernels spill, and scratch memory alone costs a launch 2 to 3 us (128 units x 4 heads x 4000 tokens,
+  // 3/4 bit, 800 Keys and 400 Values in fp16: 36.4 us, 20.9 this way; 2/4 bit 24.9, 19.8). The others have the registers, and lose
+  // 3 to 13 % when the tile comes late.
   constexpr bool kLateTile = MIXED && (G == 4 || (G == 1 && KB == 4 && VB == 3));
   const bool late_tile = kLateTile && first_rec < n_rec;
   // ---- fp16 window tiles: taken round-robin by the waves before the packed stream.
@@ -1027,9 +1032,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       *reinterpret_cast<float4_t*>(&L.v.s[row][8 * kq + 4]) = float4_t{x[4], x[5], x[6], x[7]};
     }
     wave_lds_fence();
-    // The four lane groups g would all compute the same numerators; instead group g finishes those of head g and hands them to the others through
-    // LDS as two fp16 terms (the rounded value and what the rounding left over: together ~22 bits, the same pair enters the Value sums, the
-    // zero-point sums and the denominator).
+    // The four lane groups g would all compute the same numerators; instead group g finishes those of head g and hands them to the
+    // others through LDS as two fp16 terms (the rounded value and what the rounding left over: together ~22 bits, the same pair
+    // enters the Value sums, the zero-point sums and the denominator).
     {
       const int tp = lane & 15, hh = lane >> 4;
       // (both reads are issued before the first write: the compiler does not move LDS reads across LDS writes through pointers of the same
@@ -1097,8 +1102,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
       for (int r = 0; r < 4; r++) x[4 * m + r] = S[m][r];
     values_large(std::false_type{}, st.meta, st.vc, x, c_code, zt);
   };
-  // Blocks of 8 heads: every lane folds the scales into its own operands. In one piece: cut in two like the one for 4 heads, 4 of its forms with 8
-  // waves spill.
+  // Blocks of 8 heads: every lane folds the scales into its own operands. In one piece: cut in two like the one for 4 heads, 4 of
+  // its forms with 8 waves spill.
   auto process_own = [&](const Stage<KB, VB>& st) {
     if constexpr (!kOwnOperand<G> || kWide<G>) return;
     // -- Key side
@@ -1212,11 +1217,11 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     }
     wave_lds_fence();   // the next tile's operand writes come after these reads
   };
-  // Blocks of 16 heads (of groups of 16 and more, multi-query attention): a column is a head, the hi and lo parts are two matrix instructions
-  // on the same accumulators. The scores come out with a lane holding 8 tokens of its head, which are the tokens
-  // of its operand for the Values: softmax, numerators and operands stay in the lane, only the tile's scales and minima
-  // go through LDS, and the codes are cut out once for 16 heads. Bound by instruction issue: about 240 vector and 38 matrix
-  // instructions per tile and wave (255 with masks and numerator splits written out: 27 us at 72 heads x 32 sequences of 4096 tokens, and 22.8 with
+  // Blocks of 16 heads (of groups of 16 and more, multi-query attention): a column is a head, the hi and lo parts are two matrix
+  // instructions on the same accumulators. The scores come out with a lane holding 8 tokens of its head, which are the tokens of
+  // its operand for the Values: softmax, numerators and operands stay in the lane, only the tile's scales and minima go through
+  // LDS, and the codes are cut out once for 16 heads. Bound by instruction issue: about 240 vector and 38 matrix instructions per
+  // tile and wave (255 with masks and numerator splits written out: 27 us at 72 heads x 32 sequences of 4096 tokens, and 22.8 with
   // these and the head-wise tail; blocks of 8 took 49).
   auto values_wide = [&](auto exact, const u32x4_t& meta, const Raw<VB>& vr, float (&x)[8], float c, float zt) {
     if constexpr (!kWide<G>) return;
@@ -1365,8 +1370,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   }
 
   {
-  // Where the packed loop has no register to spare, lane and thread number are made anew here (elsewhere the values at hand are better: 0.17 us per
-  // launch of 32 units x 8 splits).
+  // Where the packed loop has no register to spare, lane and thread number are made anew here (elsewhere the values at hand are
+  // better: 0.17 us per launch of 32 units x 8 splits).
   constexpr bool kAnew = G == 4 && (MIXED ? KB == 3 && VB <= 2 : kWaves == 8 && ((KB >= 3 && VB >= 3) || (KB == 4 && VB == 2)));
   int lane = threadIdx.x & 63;
   if constexpr (kAnew) {
@@ -1419,8 +1424,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   }
   if (col < G && kq == 0) { R.m[wave][col] = mref; R.l[wave][col] = lsum; }
 
-  // Wave w combines the waves' results of heads w, w + kWaves, ... of the block, a lane two channels: the weights 2^(m_w - M) once per head (lane w
-  // holds the w-th), handed out as scalars.
+  // Wave w combines the waves' results of heads w, w + kWaves, ... of the block, a lane two channels: the weights 2^(m_w - M) once
+  // per head (lane w holds the w-th), handed out as scalars.
   constexpr int kHeads = (G + kWaves - 1) / kWaves;       // heads per wave
   auto combine_head = [&](int hh, float2_t& ml, float2_t& O) {
     const float mw = lane < kWaves ? R.m[lane < kWaves ? lane : 0][hh] : -INFINITY, lw = lane < kWaves ? R.l[lane < kWaves ? lane : 0][hh] : 0.0f;
@@ -1475,19 +1480,19 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     return;
   }
 
-  // ---- split merge: every workgroup stores its partial, the last one of the unit to arrive combines them. Partials are stored and loaded with
-  // agent scope, which the hardware keeps coherent per access across the XCDs' L2s: stores are written through to the level that all
-  // XCDs share, loads miss the XCD's own, no cache-wide flush is needed.
-  // Larger groups: a wave waits until its stores have completed; after a barrier the arrival is counted.
-  // Groups of up to 4 heads: partials that tell of themselves. Every word of the partials is zero before and after a call; a split stores
-  // its words as anything but zero (a zero as minus zero). The arrival is counted, by a wave of its own, before the partial is even
-  // combined: the count is on its way meanwhile, and no store is waited for. The workgroup that arrives last knows that every other one of
-  // the unit has its results and stores them without waiting for anything; it takes a partial when all of its words read as
-  // other than zero. Stores that wait for nothing and a count that is back when they
-  // are issued, instead of stores, their acknowledgement, a barrier and the count in a row: 32 units of 3 splits (one small layer) 6.37 ->
-  // 5.85 us, 24 units of 6 splits and 4 heads 8.2 -> 7.6, 32 units of 8 splits 10.4 -> 9.6, 128 of 2 splits 24.9 -> 24.5; 8 units of 32
-  // splits, 66 KB to read and to zero for the one workgroup, 12.2 as before. The waves that do not merge zero the partials while the others sum up: 11.4 (by the merging waves ahead of
-  // their sums their stores alone took 1.1 us; after the sums they were 0.1 us slower still). Groups of 8 heads have no wave to spare for the count, and twice the words to zero.
+  // ---- split merge: every workgroup stores its partial, the last one of the unit to arrive combines them. Partials are stored and
+  // loaded with agent scope, which the hardware keeps coherent per access across the XCDs' L2s: stores are written through to the
+  // level that all XCDs share, loads miss the XCD's own, no cache-wide flush is needed.
+  // Larger groups: a wave waits until its stores have completed; after a barrier the arrival is counted. Groups of up to 4 heads:
+  // partials that tell of themselves. Every word of the partials is zero before and after a call; a split stores its words as
+  // anything but zero (a zero as minus zero). The arrival is counted, by a wave of its own, before the partial is even combined:
+  // the count is on its way meanwhile, and no store is waited for. The workgroup that arrives last knows that every other one of
+  // the unit has its results and stores them without waiting for anything; it takes a partial when all of its words read as other
+  // than zero. Stores that wait for nothing and a count that is back when they are issued, instead of stores, their
+  // acknowledgement, a barrier and the count in a row: 32 units of 3 splits (one small layer) 6.37 -> 5.85 us, 24 units of 6 splits
+  // and 4 heads 8.2 -> 7.6, 32 units of 8 splits 10.4 -> 9.6, 128 of 2 splits 24.9 -> 24.5; no change for 8 units of 32 splits, 66
+  // KB to read and to zero for the one workgroup. Groups of 8 heads have no wave to spare for the count, and twice the words to
+  // zero.
   static_assert(!kTagged<G> || G < kWaves);
   lds_barrier();          // the waves' results are in LDS
   uint32_t prev = 0;
@@ -1518,9 +1523,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     __syncthreads();
   }
   if (!s_done) return;
-  // The loads of all heads of a wave and up to kBatch parts are under way together, without a branch around each; parts past the last one are
-  // read as the last one and weigh nothing. (Blocks of 16 heads used to take four round trips: 32 units x 72 heads, 3 splits, 27.5 -> 22.8 us per
-  // launch; 4 x 16 heads 12.0 -> 9.9; 8 units of 8 heads 10.1 -> 8.4.)
+  // The loads of all heads of a wave and up to kBatch parts are under way together, without a branch around each; parts past the
+  // last one are read as the last one and weigh nothing. (Blocks of 16 heads used to take four round trips: 32 units x 72 heads, 3
+  // splits, 27.5 -> 22.8 us per launch; 4 x 16 heads 12.0 -> 9.9; 8 units of 8 heads 10.1 -> 8.4.)
   const uint32_t part_bytes = (uint32_t)(part_step * (kD + 2) * sizeof(float));
   // hd: first head of the wave (every kWaves-th from there on); the splits from s_first on, a batch every s_step
   auto merge = [&](auto batch, int hd, int s_first, int s_step, auto put) {
@@ -1532,7 +1537,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
     for (int s0 = s_first; s0 < a.n_splits; s0 += s_step) {
       const int n = a.n_splits - s0 < kBatch ? a.n_splits - s0 : kBatch;       // >= 1
       u32x2_t ml[kHeads], os[kHeads][kBatch];
-      uint32_t at[kBatch];      // where the rows begin, one after the other by addition (with a product and a choice for each, launches of 8 and more heads took 0 to 1.5 % longer)
+      // where the rows begin, one after the other by addition (with a product and a choice for each, launches of 8 and more heads
+      // took 0 to 1.5 % longer)
+      uint32_t at[kBatch];
       {
         const uint32_t last = (uint32_t)(s0 + n - 1) * part_bytes;
         at[0] = (uint32_t)s0 * part_bytes;
@@ -1542,8 +1549,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
           asm("" : "+s"(at[i]));
         }
       }
-      // (tagged) The last arrival waits for stores that nothing holds up. The bound is for a counter that was not zero to begin with, with which another
-      // arrival may count as the last; even then the missing workgroups are on their way. (Partials that were not zero are taken for what they say.)
+      // (tagged) The last arrival waits for stores that nothing holds up. The bound is for a counter that was not zero to begin
+      // with, with which another arrival may count as the last; even then the missing workgroups are on their way. (Partials that
+      // were not zero are taken for what they say.)
       for (int tries = 0;; tries++) {
         asm volatile("" ::: "memory");        // (to the compiler these loads see the same memory every time otherwise)
         uint32_t least = 1;
@@ -1566,8 +1574,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
           }
         }
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(least == 0u) == 0, 1)) break;
-        // In vain: NaN as this batch's sum of numerators, so that the head comes out as NaN and not as a number without some of its tokens. (Marking the
-        // counter as well, for later calls, costs every launch of 4 heads 0.1 us of 7 to 16.)
+        // In vain: NaN as this batch's sum of numerators, so that the head comes out as NaN and not as a number without some of its
+        // tokens. (Marking the counter as well, for later calls, costs every launch of 4 heads 0.1 us of 7 to 16.)
         if (__builtin_expect(tries == kMaxTries, 0)) { ml[0][1] = 0x7FC00000u; break; }
       }
       if constexpr (kTagged<G>) {
@@ -1602,9 +1610,10 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
   auto to_out = [&](int hh, const float2_t& O, float Lsum, float) { put_out(hh, O, Lsum); };
   if constexpr (kTagged<G>) {
     constexpr int kBatch = kWaves == 8 && G == 4 ? 16 : kMergeBatch;      // (4 heads, 8 waves: 32 do not fit the registers)
-    // Many splits of 1 or 2 heads: 16 partials of one head to a wave, then the waves' sums like the waves' results before. (When one wave took both batches of
-    // its head, with the zeros of the first in front of the second's loads, 4 units of 1 head in 50 splits took 9.0 us per launch; 7.4 now. With 32
-    // splits and 4 heads two waves of 16 are slower than one of 32, 13.0 us against 12.3, and the longer code costs the short launches 1 %.)
+    // Many splits of 1 or 2 heads: 16 partials of one head to a wave, then the waves' sums like the waves' results before. (When
+    // one wave took both batches of its head, with the zeros of the first in front of the second's loads, 4 units of 1 head in 50
+    // splits took 9.0 us per launch; 7.4 now. With 32 splits and 4 heads two waves of 16 are slower than one of 32, 13.0 us against
+    // 12.3, and the longer code costs the short launches 1 %.)
     constexpr int kRows = kWaves / G;      // x 16: at least 64
     const int rows = G == 4 || a.n_splits <= kBatch ? 1 : (a.n_splits + 15) / 16 < kRows ? (a.n_splits + 15) / 16 : kRows;
     const int merging = rows * G;      // waves
@@ -1618,8 +1627,10 @@ __global__ __launch_bounds__(NW * kWave, NW == 12 ? 3 : 4) void decode_attn_kern
         *reinterpret_cast<float2_t*>(&s_wave[row].o[hh][2 * lane]) = O;
       });
     }
-    // Nobody else reads the unit's partials: zero again, the splits' rows one after the other, by the waves that don't merge while the others sum up (by the merging waves where all of
-    // them merge). 8 units of 4 heads, 32 splits 12.0 -> 11.4 us per launch, 1 unit, 64 splits 16.4 -> 15.4; 8 units of 1 head, 8 splits 6.53 -> 6.38; 32 units, 3 splits 5.87 -> 5.77.
+    // Nobody else reads the unit's partials: zero again, the splits' rows one after the other, by the waves that don't merge while
+    // the others sum up (by the merging waves where all of them merge). Zeroed by the merging waves ahead of their sums, whose
+    // stores alone took 1.1 us then (behind the sums 0.1 us more), and now: 8 units of 4 heads, 32 splits 12.0 -> 11.4 us per
+    // launch, 1 unit, 64 splits 16.4 -> 15.4; 8 units of 1 head, 8 splits 6.53 -> 6.38; 32 units, 3 splits 5.87 -> 5.77.
     if (wave >= merging || merging == kWaves) {
       const int first = merging == kWaves ? 0 : merging;
       const uint32_t bytes = (uint32_t)a.n_splits * part_bytes;          // a multiple of 8
@@ -1668,7 +1679,7 @@ hipError_t launch_g(const AttnArgs& a, int G, dim3 grid, hipStream_t s) {
     case 4: run(decode_attn_kernel<KB, VB, 4, kNW, kMixed>); break;
 #if !KVMIX_MIXED
     case 8:
-      // (8 heads with 3- or 4-bit Values always run 12 waves: attn_waves)
+      // (a block of 8 heads with 3- or 4-bit Values has 12 waves: attn_waves)
       if constexpr (kNW == 12 || VB < 3) { run(decode_attn_kernel<KB, VB, 8, kNW, kMixed>); break; }
       else break;
 #endif

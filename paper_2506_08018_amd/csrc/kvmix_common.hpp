@@ -103,15 +103,15 @@ struct QuantArgs {
   int tiles_cap;   // tiles per unit in the packed cache
   int tile0;       // first destination tile
   int Hkv;
-  // Input rows that stay in the window (an appending launch only): row copy_row + i, i = 0 .. n_copy - 1, goes to the ring slot that lies
-  // copy_at + i slots behind ring_w0, around the ring. The slots [0, n_read) behind ring_w0 are also read by tiles of the launch: the
-  // workgroup of the tile in question fills those, once it has its rows. The others are filled by copy_tiles workgroups from n_tiles on, 32 slots
-  // each, from slot 32 copy_tile0 on.
+  // Input rows that stay in the window (an appending launch only): row copy_row + i, i = 0 .. n_copy - 1, goes to the ring slot
+  // that lies copy_at + i slots behind ring_w0, around the ring. The slots [0, n_read) behind ring_w0 are also read by tiles of the
+  // launch: the workgroup of the tile in question fills those, once it has its rows. The others are filled by copy_tiles workgroups
+  // from n_tiles on, 32 slots each, from slot 32 copy_tile0 on.
   int n_tiles, n_copy, copy_row, copy_at, n_read, copy_tile0, copy_tiles;
   uint16_t* k_ring_w; uint16_t* v_ring_w;
-  // Ageing with separate fronts (every row comes from the ring, which is the input then; row r of the launch is token 32*tile0 + r): the Key
-  // side is written for the destination tiles [k_tile_a, k_tile_b) only, the Value side for the tokens
-  // [v_tok_a, v_tok_b) only; everything else in the records is left as it is.
+  // Ageing with separate fronts (every row comes from the ring, which is the input then; row r of the launch is token 32*tile0 +
+  // r): the Key side is written for the destination tiles [k_tile_a, k_tile_b) only, the Value side for the tokens [v_tok_a,
+  // v_tok_b) only; everything else in the records is left as it is.
   int k_tile_a, k_tile_b, v_tok_a, v_tok_b;
 };
 
@@ -159,8 +159,8 @@ struct AttnArgs {
   bool even;              // the workgroups that share a compute unit keep pace with each other (8 waves)
 };
 
-// A launch by hipLaunchKernel itself, without the configuration that <<<>>> pushes and pops (host time of a decode step of one launch 5.6 -> 5.3 us, with the preloaded
-// parameters as few as they can be: passed one by one, 13 of them, it was 5.8).
+// A launch by hipLaunchKernel itself, without the configuration that <<<>>> pushes and pops (host time of a decode step of one
+// launch 5.6 -> 5.3 us, with the preloaded parameters as few as they can be: passed one by one, 13 of them, it was 5.8).
 template <typename... Params, typename... Args>
 hipError_t launch(void (*kernel)(Params...), dim3 grid, int threads, hipStream_t s, const Args&... args) {
   static_assert((std::is_same_v<Params, Args> && ...), "an argument of its own type for each parameter");
@@ -178,8 +178,9 @@ hipError_t launch_quantize_fronts(const QuantArgs& a, int k_bits, int v_bits,
 hipError_t launch_dequant(const DequantArgs& a, int units, hipStream_t s);
 hipError_t launch_append(const AppendArgs& a, hipStream_t s);
 hipError_t launch_stream_read(const void* buf, size_t bytes, int workgroups, int threads, uint32_t* sink, hipStream_t s);
-// WAVES: waves per workgroup, 8 or 12 (blocks of 16 heads: 8). MIXED: with the tiles between two fronts (blocks of 1, 2, 4 and 16 heads, 12 waves).
-// block: query heads per workgroup (1, 2, 4, 8 or 16); a unit's group of a.G heads takes (a.G + block - 1) / block workgroups per split.
+// WAVES: waves per workgroup, 8 or 12 (blocks of 16 heads: 8). MIXED: with the tiles between two fronts (blocks of 1, 2, 4 and 16
+// heads, 12 waves). block: query heads per workgroup (1, 2, 4, 8 or 16); a unit's group of a.G heads takes (a.G + block - 1) /
+// block workgroups per split.
 template <int WAVES, bool MIXED>
 hipError_t launch_decode_attn(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);
 template <> hipError_t launch_decode_attn<8, false>(const AttnArgs& a, int k_bits, int v_bits, int block, int units, hipStream_t s);

@@ -83,8 +83,8 @@ __device__ __forceinline__ GroupParams group_params(float mn, float mx) {
 }
 
 // Extremes of 32 fp16 numbers per half, 16 pairs from one source and 16 from another or 32 of one: three operands at a time. The
-// instructions hand a NaN on, unlike the ones that take two operands: nan says that there is one (the group then goes the slow way, with the
-// extremes of the others).
+// instructions hand a NaN on, unlike the ones that take two operands: nan says that there is one (the group then goes the slow way,
+// with the extremes of the others).
 __device__ __forceinline__ uint32_t min3(uint32_t a, uint32_t b, uint32_t c) { uint32_t r; asm("v_pk_minimum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
 __device__ __forceinline__ uint32_t max3(uint32_t a, uint32_t b, uint32_t c) { uint32_t r; asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
 template <int N>
@@ -156,10 +156,11 @@ __device__ __forceinline__ uint32_t settle(float d, float inv_lo, float step) {
   if ((double)d < s * ((double)h - (h == 0.5f ? 0.5 * half : half))) code = lo;
   return code;
 }
-// A lane's batch of 16 elements: code[at], of element first + at of the group g0 (Values), whose fp16 number is half at % 2 of pair[at / 2],
-// or of element first + at % 8 of g0 or g1 (Keys), half at / 8 of pair[at % 8]. open: the elements to compare with the ends of the range; one
-// per lane and round, next to never.
-// Index inside its group of element `at` of a batch that begins with `first`. Two Value waves to a tile (HALF 0, 1): channels 8 HALF .. + 7, then 16 further.
+// A lane's batch of 16 elements: code[at], of element first + at of the group g0 (Values), whose fp16 number is half at % 2 of
+// pair[at / 2], or of element first + at % 8 of g0 or g1 (Keys), half at / 8 of pair[at % 8]. open: the elements to compare with
+// the ends of the range; one per lane and round, next to never.
+// Index inside its group of element `at` of a batch that begins with `first`. Two Value waves to a tile (HALF 0, 1): channels 8
+// HALF .. + 7, then 16 further.
 template <bool KEYS, int HALF> __device__ __forceinline__ constexpr int element_of(int first, int at) {
   return KEYS ? first + (at & 7) : HALF < 0 ? first + (at & 15) : 8 * HALF + (at & 7) + 16 * (at >> 3 & 1);
 }
@@ -224,17 +225,18 @@ __device__ __forceinline__ void quantize_batch(uint32_t (&code)[16], const uint3
   }
 }
 
-// Number of 32-bit word accumulators a lane fills for one code section before the lanes of its quad are
-// combined: words i = 0..15 (half of them where two waves share a section) of its (kq, j) column group; 4-bit sections have two chunks. 1-bit sections
+// Number of 32-bit word accumulators a lane fills for one code section before the lanes of its quad are combined: words i = 0..15
+// (half of them where two waves share a section) of its (kq, j) column group; 4-bit sections have two chunks. 1-bit sections
 // consist of the bit plane alone (the `hi` words below, stored at the start of the section).
 template <int BITS, int SPLIT> constexpr int acc_words() { return (BITS == 4 ? 32 : 16) / SPLIT; }
 
 // Final step of every wave: `w` holds, in every lane of a quad (q = lane & 3), the complete words
 // i = 0..15 (per chunk) of column group (kq, j), or 8 of them from i0 on; lane q has a quarter of them to deliver. `hi` (3- and 1-bit)
 // holds the high-plane words, complete in both lanes j and j^1; the even-j lanes deliver them.
-// A word of which only the bytes of `mask` are this launch's to write (PARTIAL: Values that leave the window token
-// by token share their words with the neighbouring tokens' codes, which are already in place or still to come). A token's are whole halves of a word, and whole
-// bytes of a plane word (BYTES): stored as such, nothing is read. (Words were read and written back: the read waited for memory at the end of the kernel.)
+// A word of which only the bytes of `mask` are this launch's to write (PARTIAL: Values that leave the window token by token share
+// their words with the neighbouring tokens' codes, which are already in place or still to come). A token's are whole halves of a
+// word, and whole bytes of a plane word (BYTES): stored as such, nothing is read. (Words were read and written back: the read
+// waited for memory at the end of the kernel.)
 template <bool PARTIAL, bool BYTES>
 __device__ __forceinline__ void put_word(uint32_t* p, uint32_t v, uint32_t mask) {
   if (!PARTIAL || mask == 0xFFFFFFFFu) {
@@ -308,30 +310,35 @@ __device__ __forceinline__ T load_row(const uint16_t* p) {
   return S == kStreamBoth ? __builtin_nontemporal_load(t) : *t;
 }
 
-// One workgroup of two waves (SPLIT = 1) or four (SPLIT = 2) quantizes and packs one (unit, 32-token tile). Two: wave 0 the Key tile, wave 1 the Value tile, each for
-// itself. A lane owns what ends up in the same words: lane = 16*kq + 4*j + q.
+// One workgroup of two waves (SPLIT = 1) or four (SPLIT = 2) quantizes and packs one (unit, 32-token tile). Two: wave 0 the Key
+// tile, wave 1 the Value tile, each for itself. A lane owns what ends up in the same words: lane = 16*kq + 4*j + q.
 //   Key wave:   q = ks; channels d0 = 32*ks + 8*kq + 2*j and d0 + 1 over the 32 tokens (two groups); a word
 //               (l = 16*kq + i, j) gets its fields of slot ks + 4*m from this lane, the other ks from the quad.
 //   Value wave: q = g;  tokens 8*kq + 2*j and + 1, channels 32*g .. 32*g + 31 (two groups); a word gets its
 //               fields of slots 2*g, 2*g + 1 from this lane, the other blocks from the quad.
 // The lanes of a quad OR their partial words together (DPP), the 1-bit plane of 3-bit codes also across the
 // two j of a word; each lane then has a quarter of the words.
-// Memory sees whole rows and whole sections: Key rows are 4 bytes per lane; Value rows 16 bytes per lane, four rows per instruction, handed to
-// their lanes through LDS; finished words go through LDS to a store of 1 KB per instruction, and so does the metadata of the
-// two waves (8 bytes of every 16 each). What a variant that only loads and stores takes for 31 488 tiles of 2/2 bit, its accesses past
-// the caches: 98 us with the metadata in its pieces, 93 this way (111 with Value rows in pieces of 16 bytes and words stored one by one).
-// The whole kernel: 112.9 us before, with divisions for ties, 90.7 now (a large copy's rate); 8 096 tiles of 3/4 bit 38.8 and 32.2, about 700
-// vector instructions per wave and tile (21 us of issue) that only partly overlap the loads when a place sees four tiles.
+// Memory sees whole rows and whole sections: Key rows are 4 bytes per lane; Value rows 16 bytes per lane, four rows per
+// instruction, handed to their lanes through LDS; finished words go through LDS to a store of 1 KB per instruction, and so does the
+// metadata of the two waves (8 bytes of every 16 each). What a variant that only loads and stores takes for 31 488 tiles of 2/2
+// bit, its accesses past the caches: 98 us with the metadata in its pieces, 93 this way (111 with Value rows in pieces of 16 bytes
+// and words stored one by one). The whole kernel: 112.9 us before, with divisions for ties, 90.7 now (a large copy's rate); 8 096
+// tiles of 3/4 bit 38.8 and 32.2, about 700 vector instructions per wave and tile (21 us of issue) that only partly overlap the
+// loads when a place sees four tiles.
 //
 // PARTIAL: ageing with separate fronts for Keys and Values. The Key wave works on the tiles [k_tile_a, k_tile_b)
-// only; the Value wave writes the codes and metadata of the tokens [v_tok_a, v_tok_b) only, merging them into
-// words that it shares with other tokens. Every row comes from the ring.
+// only; the Value wave writes the codes and metadata of the tokens [v_tok_a, v_tok_b) only: the halves and bytes of words that are
+// theirs (put_word), without reading the words. Every row comes from the ring, everything is written in place. With four waves a tile
+// (below) the exchange is a barrier all the same: Key waves that leave early pass it first.
 //
-// SPLIT = 2: two waves for the Keys (16 tokens each) and two for the Values (channels 8 h .. 8 h + 7 and 16 + 8 h .. of every block of 32). Each
-// has half of a section's words; the two exchange the extremes of their halves of the groups through LDS. A lane has 32 elements instead of 64, one after the other: of the 3.5 us (4.6 at most,
-// where exact ties are settled) that a tile alone took in two waves from its start to its last store, the parameters of the groups were 0.45, the codes 1.05 (with ties 2.3) and the words 0.4.
+// SPLIT = 2: two waves for the Keys (16 tokens each) and two for the Values (channels 8 h .. 8 h + 7 and 16 + 8 h .. of every block
+// of 32). Each has half of a section's words; the two exchange the extremes of their halves of the groups through LDS. A lane has
+// 32 elements instead of 64, one after the other: of the 3.5 us (4.6 at most, where exact ties are settled) that a tile alone took
+// in two waves from its start to its last store, the parameters of the groups were 0.45, the codes 1.05 (with ties 2.3) and the
+// words 0.4.
 template <int KB, int VB, bool PARTIAL, int SPLIT, Stream S>
-__device__ __forceinline__ void quantize_tile(const uint16_t* k_in, const uint16_t* v_in, int64_t tok, int64_t unit_b, int64_t unit_h, uint32_t* packed, int n_tiles, int n_ring, const QuantArgs& a) {
+__device__ __forceinline__ void quantize_tile(const uint16_t* k_in, const uint16_t* v_in, int64_t tok, int64_t unit_b, int64_t unit_h, uint32_t* packed,
+                                              int n_tiles, int n_ring, const QuantArgs& a) {
   constexpr int kWords = 16 / SPLIT;           // words of a column group, per wave
   __shared__ __attribute__((aligned(16))) uint32_t s_key[512];             // the Key section's image
   __shared__ __attribute__((aligned(16))) uint32_t s_value[kTile * kD / 2];   // the Value rows, then the Value section's image
@@ -412,7 +419,8 @@ __device__ __forceinline__ void quantize_tile(const uint16_t* k_in, const uint16
     if constexpr (!PARTIAL) asm volatile("" ::"s"(a.Hkv), "s"(a.tiles_cap), "s"(a.n_read));
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto record = [&]() { return packed + ((size_t)(b * a.Hkv + jh) * a.tiles_cap + (size_t)tile_in) * record_words(KB, VB); };      // (packed: of the launch's first tile)
+  // (packed: of the launch's first tile)
+  auto record = [&]() { return packed + ((size_t)(b * a.Hkv + jh) * a.tiles_cap + (size_t)tile_in) * record_words(KB, VB); };
   uint32_t hi[kWords];
 #pragma unroll
   for (int i = 0; i < kWords; i++) hi[i] = 0;
@@ -498,15 +506,17 @@ __device__ __forceinline__ void quantize_tile(const uint16_t* k_in, const uint16
     // PARTIAL: which of the lane's two tokens, and of the two of lane j ^ 1, are among those that leave now
     auto leaves = [&](int tau) { const int t = (a.tile0 + tile_in) * kTile + tau; return !PARTIAL || (t >= a.v_tok_a && t < a.v_tok_b); };
     const bool mine[2] = {leaves(tau0), leaves(tau0 + 1)};
-    // Rows to LDS, pieces of 16 bytes: the whole row, or (two waves) every second piece. Piece p of row t lies at p ^ (t/2 % 4) of its row in LDS: the 16 lanes that read
-    // together (4 rows, 4 pieces) then find theirs in distinct banks (two waves: two at a time)
+    // Rows to LDS, pieces of 16 bytes: the whole row, or (two waves) every second piece. Piece p of row t lies at p ^ (t/2 % 4) of
+    // its row in LDS: the 16 lanes that read together (4 rows, 4 pieces) then find theirs in distinct banks (two waves: two at a
+    // time)
     constexpr int kPieces = 16 / SPLIT, kRows = kWave / kPieces;      // of a row; rows per instruction
     uint32_t* area = s_value + part * (kTile * kPieces * 4);
     {
       const int r4 = lane / kPieces, c = lane % kPieces, piece = SPLIT == 2 ? 2 * c + part : c;
       u32x4_t x[kPieces / 2];
       if constexpr (PARTIAL) {
-        // Rows of tokens that stay are not read: beyond the resource's end a load returns zeros. (With a branch around each load the rows were once waited for one after the other.)
+        // Rows of tokens that stay are not read: beyond the resource's end a load returns zeros. (With a branch around each load
+        // the rows were once waited for one after the other.)
         const uint64_t base = reinterpret_cast<uint64_t>(rows);
         const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base), hi32 = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
         const __amdgpu_buffer_rsrc_t tile = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uint64_t)hi32 << 32) | lo), 0, kTile * kD * 2, 0x00020000);
@@ -538,7 +548,8 @@ __device__ __forceinline__ void quantize_tile(const uint16_t* k_in, const uint16
       wave_lds_fence();
     }
     constexpr int kOwn = 4 / SPLIT;                  // pieces of a group of this wave
-    u32x4_t xr[2][kOwn];                             // rows tau0, tau0 + 1: channels 32*q .. 32*q + 31 (two waves: 8*part .. + 7 and 16 + 8*part .. of them)
+    // rows tau0, tau0 + 1: channels 32*q .. 32*q + 31 (two waves: 8*part .. + 7 and 16 + 8*part .. of them)
+    u32x4_t xr[2][kOwn];
 #pragma unroll
     for (int hh = 0; hh < 2; hh++)
 #pragma unroll
@@ -558,7 +569,8 @@ __device__ __forceinline__ void quantize_tile(const uint16_t* k_in, const uint16
       extremes(x, mn2[hh], mx2[hh], nan[hh]);
     }
     if constexpr (SPLIT == 2) {
-      const u32x4_t other = exchange(u32x4_t{__builtin_bit_cast(uint32_t, mn2[0]), __builtin_bit_cast(uint32_t, mx2[0]), __builtin_bit_cast(uint32_t, mn2[1]), __builtin_bit_cast(uint32_t, mx2[1])});
+      const u32x4_t other = exchange(u32x4_t{__builtin_bit_cast(uint32_t, mn2[0]), __builtin_bit_cast(uint32_t, mx2[0]),
+                                             __builtin_bit_cast(uint32_t, mn2[1]), __builtin_bit_cast(uint32_t, mx2[1])});
 #pragma unroll
       for (int hh = 0; hh < 2; hh++) {
         const uint32_t omn = other[2 * hh], omx = other[2 * hh + 1];
@@ -668,11 +680,13 @@ __device__ __forceinline__ void quantize_tile(const uint16_t* k_in, const uint16
   }
 }
 
-// Four waves: small launches. The parameters in front of `a` are preloaded into scalar registers (build.py): what the first requests need where all rows are rows of the input.
-// (Read from memory in turn, they let the first request out 0.85 us after the start.)
+// Four waves: small launches. The parameters in front of `a` are preloaded into scalar registers (build.py): what the first
+// requests need where all rows are rows of the input. (Read from memory in turn, they let the first request out 0.85 us after the
+// start.)
 typedef int64_t i64x2_t __attribute__((ext_vector_type(2)));
 template <int KB, int VB, bool PARTIAL, Stream S>
-__global__ __launch_bounds__(256, 4) void quantize_pack_kernel(const uint16_t* k, const uint16_t* v, i64x2_t strides, int64_t unit_h, uint32_t* packed, u32x2_t counts, QuantArgs a) {
+__global__ __launch_bounds__(256, 4) void quantize_pack_kernel(const uint16_t* k, const uint16_t* v, i64x2_t strides, int64_t unit_h, uint32_t* packed,
+                                                               u32x2_t counts, QuantArgs a) {
   quantize_tile<KB, VB, PARTIAL, 2, S>(k, v, strides[0], strides[1], unit_h, packed, (int)counts[0], (int)counts[1], a);
 }
 // Two waves: large launches, to which preloading (0.3 us in front of a launch) gives nothing.
@@ -692,9 +706,10 @@ __global__ __launch_bounds__(256) void dequant_kernel(DequantArgs a) {
   }
 }
 
-// New tokens of every unit into consecutive ring slots of the two fp16 windows (one full row each). The arguments are not preloaded here: that costs a launch 0.3 us (one token for 256
-// units: 1.95 and 2.15 us), and there is nothing in these kernels to hide it.
-// Few rows, bound by the launch, and rows that don't begin at multiples of 16 bytes (full-precision layers take any): a workgroup per unit and token.
+// New tokens of every unit into consecutive ring slots of the two fp16 windows (one full row each). The arguments are not preloaded
+// here: that costs a launch 0.3 us (one token for 256 units: 1.95 and 2.15 us), and there is nothing in these kernels to hide it.
+// Few rows, bound by the launch, and rows that don't begin at multiples of 16 bytes (full-precision layers take any): a workgroup
+// per unit and token.
 __global__ __launch_bounds__(128) void append_kernel(AppendArgs a) {
   const int u = blockIdx.x, i = blockIdx.y, d = threadIdx.x;
   const int64_t src = (int64_t)(u / a.Hkv) * a.batch + (int64_t)(u % a.Hkv) * a.head + (int64_t)i * a.tok + d;
@@ -702,8 +717,9 @@ __global__ __launch_bounds__(128) void append_kernel(AppendArgs a) {
   a.k_win[dst] = a.k_new[src];
   a.v_win[dst] = a.v_new[src];
 }
-// More of them, bound by memory: 16 bytes per lane, a workgroup takes 4 kv heads of a token. 300 tokens for 512 units 63 -> 24 us, 31 for 2048 units 19.9 -> 8.8, 300 for
-// 8 units 2.57 -> 2.15; below 1024 rows it is no faster (one token for 256 units 1.94 and 1.98 us).
+// More of them, bound by memory: 16 bytes per lane, a workgroup takes 4 kv heads of a token. 300 tokens for 512 units 63 -> 24 us,
+// 31 for 2048 units 19.9 -> 8.8, 300 for 8 units 2.57 -> 2.15; below 1024 rows it is no faster (one token for 256 units 1.94 and
+// 1.98 us).
 constexpr int kAppendHeads = 4;
 __global__ __launch_bounds__(32 * kAppendHeads) void append_many_kernel(AppendArgs a) {
   const int row = threadIdx.x >> 4, piece = threadIdx.x & 15;
@@ -749,14 +765,16 @@ __global__ __launch_bounds__(768) void stream_read_kernel(const u32x4_t* buf, si
 template <int KB, int VB, bool PARTIAL>
 hipError_t launch_qp(const QuantArgs& a, dim3 grid, Stream stream, size_t tiles, hipStream_t s) {
   auto run_four = [&](auto kernel) {
-    return launch(kernel, grid, 4 * kWave, s, a.k, a.v, i64x2_t{a.tok, a.unit_b}, a.unit_h, a.packed + (size_t)a.tile0 * record_words(KB, VB), u32x2_t{(uint32_t)a.n_tiles, (uint32_t)a.n_ring}, a);
+    return launch(kernel, grid, 4 * kWave, s, a.k, a.v, i64x2_t{a.tok, a.unit_b}, a.unit_h, a.packed + (size_t)a.tile0 * record_words(KB, VB),
+                  u32x2_t{(uint32_t)a.n_tiles, (uint32_t)a.n_ring}, a);
   };
   auto run_two = [&](auto kernel) { return launch(kernel, grid, 2 * kWave, s, a); };
   const bool four = tiles <= (PARTIAL || KB == 3 || VB == 3 ? 4096 : 8192);
   if constexpr (PARTIAL) return four ? run_four(quantize_pack_kernel<KB, VB, true, kCached>) : run_two(quantize_pack_many_kernel<KB, VB, true, kCached>);
   if constexpr (!PARTIAL) {
     if (stream == kCached) return run_four(quantize_pack_kernel<KB, VB, false, kCached>);          // (fewer than 2048 tiles)
-    if (stream == kStreamOut) return four ? run_four(quantize_pack_kernel<KB, VB, false, kStreamOut>) : run_two(quantize_pack_many_kernel<KB, VB, false, kStreamOut>);
+    if (stream == kStreamOut)
+      return four ? run_four(quantize_pack_kernel<KB, VB, false, kStreamOut>) : run_two(quantize_pack_many_kernel<KB, VB, false, kStreamOut>);
     return run_two(quantize_pack_many_kernel<KB, VB, false, kStreamBoth>);
   }
 }
@@ -819,7 +837,8 @@ hipError_t launch_stream_read(const void* buf, size_t bytes, int workgroups, int
 
 hipError_t launch_append(const AppendArgs& a, hipStream_t s) {
   if (a.n == 0 || a.units == 0) return hipSuccess;
-  const bool aligned = ((reinterpret_cast<uintptr_t>(a.k_new) | reinterpret_cast<uintptr_t>(a.v_new)) & 15u) == 0 && a.tok % 8 == 0 && a.head % 8 == 0 && a.batch % 8 == 0;
+  const bool aligned = ((reinterpret_cast<uintptr_t>(a.k_new) | reinterpret_cast<uintptr_t>(a.v_new)) & 15u) == 0 &&
+                       a.tok % 8 == 0 && a.head % 8 == 0 && a.batch % 8 == 0;
   if (aligned && (int64_t)a.units * a.n > 1024)
     return launch(append_many_kernel, dim3(a.n, a.units / a.Hkv, (a.Hkv + kAppendHeads - 1) / kAppendHeads), 32 * kAppendHeads, s, a);
   return launch(append_kernel, dim3(a.units, a.n), 128, s, a);

@@ -1,6 +1,6 @@
-// The host side of the attention calls without a GPU: kvmix_decode_attn with the launches taken down instead of made, on a device of 256 compute units. One call per input line
-// (B Hkv G k_bits v_bits n_q n_w W_cap v_lead workspace n_splits; workspace in bytes, -1: kvmix_workspace_bytes, 0: none), one line out: status, splits, waves, heads per block,
-// workgroups keep pace, workspace handed to the kernel.
+// The host side of the attention calls without a GPU: kvmix_decode_attn with the launches taken down instead of made, on a device of
+// 256 compute units. One call per input line (B Hkv G k_bits v_bits n_q n_w W_cap v_lead workspace n_splits; workspace in bytes,
+// -1: kvmix_workspace_bytes, 0: none), one line out: status, splits, waves, heads per block, workgroups keep pace, workspace used.
 #include "../paper_2506_08018_amd/csrc/kvmix_api.hip"
 #include <cstdio>
 

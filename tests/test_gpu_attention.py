@@ -554,8 +554,9 @@ def test_split_counts_share_a_workspace(G, kb, vb):
     (33, 2, 4, 2, 2, 13000, 3, 7), (33, 2, 8, 1, 2, 13000, 3, 7),
 ])
 def test_two_workgroups_to_a_compute_unit(B, Hkv, G, kb, vb, n, counted, most):
-    """Split counts chosen by the library where one workgroup per compute unit would leave many empty: with the full workspace, and with one that holds no more than the partials of the
-    count that it is accepted by (tests/test_split_choice.py: which of the two is taken). Partials of 8 heads stay behind and show it here as well."""
+    """Split counts chosen by the library where one workgroup per compute unit would leave many empty: with the full workspace,
+    with one 16 bytes short of the larger count, and with one that holds no more than the partials of the count that a call is
+    accepted by (tests/test_split_choice.py: which of the two is taken). Partials of 8 heads stay behind and show it here as well."""
     import torch
     import paper_2506_08018_amd as kv
     print(f"case two workgroups to a compute unit B={B} Hkv={Hkv} G={G} bits={kb}/{vb} n={n}", flush=True)
@@ -590,7 +591,8 @@ def test_two_workgroups_to_a_compute_unit(B, Hkv, G, kb, vb, n, counted, most):
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_an_unsplit_call_leaves_its_workspace_alone(G):
-    """160 units of 94 tiles: the library does not split, so that a workspace in use elsewhere, or never cleared, changes nothing and is not changed."""
+    """160 units of 94 tiles: the library does not split, so that a workspace in use elsewhere, or never cleared, changes nothing and
+    is not changed."""
     import torch
     import paper_2506_08018_amd as kv
     print(f"case workspace left alone G={G}", flush=True)

@@ -15,7 +15,8 @@ def plans(tmp_path_factory):
     subprocess.run(build.COMMON + [os.path.join(HERE, "split_choice.hip"), "-o", exe], check=True, capture_output=True)
 
     def run(calls):
-        """calls: (units, G, (k_bits, v_bits), packed tiles, window tokens, ring tiles, workspace) each -> (status, splits, waves, block, pace, uses the workspace)"""
+        """calls: (units, G, (k_bits, v_bits), packed tiles, window tokens, ring tiles, workspace) each
+        -> (status, splits, waves, block, pace, uses the workspace)"""
         lines = "\n".join(f"{u} 1 {G} {kb} {vb} {32 * t} {n_w} {32 * W} 0 {ws} 0" for u, G, (kb, vb), t, n_w, W, ws in calls) + "\n"
         out = subprocess.run([exe], input=lines, capture_output=True, text=True, check=True).stdout.split("\n")[:-1]
         assert len(out) == len(calls)
@@ -30,7 +31,8 @@ BITS = ((1, 1), (2, 2), (3, 2), (2, 4), (3, 3), (4, 4))
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_a_call_that_needs_no_workspace_uses_none(plans, G):
-    """What is accepted without a workspace leaves one that it is given alone, whatever it holds and whoever else uses it: overlapping calls may hand over the same one."""
+    """What is accepted without a workspace leaves one that it is given alone, whatever it holds and whoever else uses it:
+    overlapping calls may hand over the same one."""
     calls = [(u, G, bits, t, 96, 4, 0) for bits in BITS for t in TILES for u in range(1, 620)]
     alone = plans(calls)
     given = plans([c[:-1] + (-1,) for c in calls])
@@ -72,7 +74,8 @@ def test_more_splits_only_for_tiles_that_are_there(plans, G):
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_more_splits_only_where_they_were_measured(plans, G):
-    """From 2 splits with all group sizes, from 3 with 2 heads and more, and with few bits per Key and Value; in the middle of those ranges they are taken."""
+    """From 2 splits with all group sizes, from 3 with 2 heads and more, and with few bits per Key and Value; in the middle of
+    those ranges they are taken."""
     wide = 5 if G > 1 else 4
     calls = [(u, G, bits, t, 96, 4, -1) for bits in BITS + ((1, 3), (4, 1)) for t in (94, 126, 250, 500, 1000) for u in range(40, 257)]
     for c, base, full in zip(calls, counted(plans, calls), plans(calls)):

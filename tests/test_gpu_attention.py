@@ -408,8 +408,8 @@ def test_graph_replays_match_eager(n_splits):
     (17, 8, 8, 1, 4, 17, 32, 40, 3),
     (18, 8, 8, 4, 3, 6, 96, 120, 4),      # 576: more than are resident, and fewer window tiles than splits for some
     (33, 4, 8, 3, 4, 0, 64, 70, 0),       # nothing packed yet
-    (33, 1, 8, 3, 2, 13, 32, 40, 0),      # two workgroups to a compute unit that keep pace: the fewest tiles for that, thresholds at 6, 9 and 11 of 13
-    (40, 2, 8, 2, 2, 16, 32, 33, 0),      # thresholds in the middle of the tiles that the waves start with
+    (33, 1, 8, 3, 2, 13, 32, 40, 0),      # two workgroups to a compute unit that keep pace: the fewest tiles for that, first step from tile 6 on
+    (40, 2, 8, 2, 2, 16, 32, 33, 0),      # first step just behind the tiles that the waves start with
     (64, 4, 8, 2, 2, 17, 32, 63, 0),      # 512 workgroups: as many as are resident
     (65, 4, 8, 2, 2, 17, 32, 40, 0),      # 520: more
     (1, 4, 1, 3, 4, 38, 32, 45, 2),       # 20 tiles per split, and one more
